@@ -302,6 +302,13 @@ int launch_backward_data_wide_f32(const Geom &g, const float *dy, const float *w
 int launch_forward_bf16(const Geom &g, const void *x, const void *w, const float *bias, float alpha, float *y,
                         hipStream_t s);
 int launch_backward_data_bf16(const Geom &g, const void *dy, const void *w, float *dx, hipStream_t s);
+// any geometry (patch rows of at least four values): both operands straight from global memory, contraction split over
+// waves where the layer has few tiles
+bool forward_general_supported(const Geom &g, int es);   // es: bytes per operand element
+int launch_forward_general_f32(const Geom &g, const float *x, const float *w, const float *bias, float alpha,
+                               const float *alpha_dev, float *y, hipStream_t s);
+int launch_forward_general_bf16(const Geom &g, const void *x, const void *w, const float *bias, float alpha, float *y,
+                                hipStream_t s);
 // bf16 storage through the fp32 kernels' structure: the pipelined kernels for the aligned shapes (bf16 MFMAs in the
 // backward-data pass, operands widened on the way in elsewhere), the masked kernels for every other shape
 bool backward_data_bf16_pipelined_supported(const Geom &g);

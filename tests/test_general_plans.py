@@ -1,0 +1,87 @@
+"""The general kernels (any geometry, operands straight from global memory): their index arithmetic replayed on the CPU
+from the launch plans, against the contraction it stands for.  Every product of the definition is formed exactly once,
+every address is inside its tensor, every output is stored."""
+import random
+
+import numpy as np
+import pytest
+
+import paper_1502_03409_amd as lc
+from paper_1502_03409_amd import binding as B
+
+
+def cdiv(a, b):
+    return -(-a // b)
+
+
+def geometries(n, seed):
+    r = random.Random(seed)
+    out = []
+    while len(out) < n:
+        R, S, C = r.randint(1, 9), r.randint(1, 6), r.choice([1, 2, 3, 4, 5, 7, 16])
+        H, W = R + r.randint(0, 9), R + r.randint(0, 12)
+        F, Bn = r.choice([r.randint(1, 40), r.randint(1, 130), 16 * r.randint(1, 8)]), r.choice([1, 2, 5, 16, 17, 37, 64, 70, 130])
+        out.append((Bn, H, W, C, R, S, F))
+    return out
+
+
+def forward_vectors(R, RC, NV, nvt, per, ks):
+    """(slice, lane group kk, step) -> the vectors a wave loads: arrays of patch row, offset in the row, leading elements
+    that count as zero; walked the way the kernel does."""
+    back, dv, dr = 4 * NV - RC, 4 % NV, 4 // NV
+    out = []
+    for sl in range(ks):
+        vbeg, vend = sl * per, min((sl + 1) * per, nvt)
+        ng = cdiv(max(vend - vbeg, 0), 4)
+        for kk in range(4):
+            vi = vbeg + kk
+            row, v = vi // NV, vi % NV
+            for _ in range(ng):
+                if vi < vend:
+                    sh = back if v == NV - 1 else 0
+                    out.append((sl, kk, row, 4 * v - sh, sh))
+                else:
+                    out.append((sl, kk, 0, 0, 4))
+                vi, v, row = vi + 4, v + dv, row + dr
+                if v >= NV:
+                    v, row = v - NV, row + 1
+    return out
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_general_forward_covers_every_product_once(seed):
+    n_general = 0
+    for geo in geometries(150, 10 + seed):
+        G = lc.geom(*geo)
+        Bn, H, W, C, R, S, F = geo
+        LH, LW, K = lc.geom_derive(G)
+        RC = R * C
+        for dtype in (B.LC_F32, B.LC_BF16):
+            plans = lc.plan_query(G, B.LC_OP_FORWARD, dtype)
+            p = plans[0]
+            if p["kernel"] != "lc_forward_generic" or p["arg"][0] != cdiv(RC, 4) or p["tparam"][5] < 1:
+                assert p["kernel"] != "lc_forward_generic" or RC < 4, (geo, p)
+                continue
+            n_general += 1
+            MT, NT, _, ES, rag, ks, tasks = p["tparam"][:7]
+            NV, nvt, per, nbt, nfw, ntask = p["arg"][:6]
+            # patch elements: each exactly once over slices, lane groups and steps; four elements inside the patch row
+            seen = np.zeros(K, dtype=int)
+            for _, _, row, off, skip in forward_vectors(R, RC, NV, nvt, per, ks):
+                assert 0 <= row < R and 0 <= off and off + 4 <= RC
+                seen[row * RC + off + skip:row * RC + off + 4] += 1
+            assert (seen == 1).all(), (geo, p)
+            # filters: runs of NT inside the filters, all of them reached by a wave that stores
+            f = set()
+            for f0 in range(0, p["grid"][1] * nfw * NT * 16, NT * 16):
+                if f0 >= F:
+                    continue
+                for n in range(16):
+                    fl = min(f0 + NT * n, F - NT)
+                    assert 0 <= fl and fl + NT <= F
+                    f.update(range(fl, fl + NT))
+            assert f == set(range(F))
+            # tasks: every field with every batch tile, images clamped into the batch
+            assert ntask == LH * LW * nbt and nbt * 16 * MT >= Bn > (nbt - 1) * 16 * MT
+            assert p["grid"][0] * tasks >= ntask and p["block"] == 64 * ks * nfw * tasks
+    assert n_general > 100

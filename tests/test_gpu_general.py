@@ -1,0 +1,76 @@
+"""The general kernels on the GPU, at the sizes where their tiles, vectors and slices end, against the fp64 oracle.
+
+Tolerance: a sum of n products in fp32 (bf16 products are exact in fp32) is off by about sqrt(n) roundings of 2^-24
+relative to its terms' norm; four times that."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1502_03409_amd as lc
+import workloads as wl
+from conftest import rel_fro
+
+pytestmark = pytest.mark.gpu
+
+
+def bar(n):
+    return 4.0 * max(n, 16) ** 0.5 * 2.0 ** -24
+
+
+def operand(a, dtype):
+    """(device tensor in the operand type, the values it holds as fp32)."""
+    t = torch.from_numpy(np.ascontiguousarray(a)).cuda()
+    t = t.bfloat16() if dtype == lc.LC_BF16 else t
+    return t, t.float().cpu().numpy()
+
+
+def nan(*shape):
+    return torch.full(shape, float("nan"), device="cuda")
+
+
+# (B, H, W, C, R, S, F): patch rows of 4 to 7 values and of odd lengths, one vector per row, filters below a tile, at a
+# tile's edge and one past it, one image, one image past a tile, contractions cut into slices, one field, gaps
+SHAPES = [(1, 9, 11, 4, 1, 1, 3), (1, 7, 7, 5, 1, 2, 1), (17, 9, 14, 3, 2, 1, 17), (16, 12, 9, 7, 1, 1, 16), (33, 11, 13, 1, 5, 2, 33),
+          (5, 31, 29, 3, 11, 4, 50), (2, 24, 27, 16, 13, 5, 60), (65, 10, 12, 3, 5, 3, 49), (130, 13, 11, 5, 3, 2, 19),
+          (3, 20, 20, 8, 20, 1, 40), (7, 17, 23, 3, 3, 5, 11), (70, 19, 18, 5, 7, 2, 72), (48, 15, 17, 6, 4, 3, 65)]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+@pytest.mark.parametrize("dtype", [lc.LC_F32, lc.LC_BF16], ids=["f32", "bf16"])
+def test_forward(shape, dtype):
+    print(f"case general forward {shape} {dtype}", flush=True)
+    g = wl.LCGeom(*shape)
+    G = lc.geom(*shape)
+    x, w, _, bias = wl.lc_inputs(g, "gaussian", seed=1, with_bias=True)
+    (xd, xv), (wd, wv) = operand(x, dtype), operand(w, dtype)
+    y = nan(g.B, g.LH, g.LW, g.F)
+    lc.lc_forward(G, xd, wd, torch.from_numpy(bias).cuda(), 0.75, y, dtype)
+    ref = oracle.lc_forward(shape, xv, wv, bias, 0.75)
+    assert rel_fro(y.cpu().numpy(), ref) <= bar(g.K)
+    again = nan(g.B, g.LH, g.LW, g.F)
+    lc.lc_forward(G, xd, wd, torch.from_numpy(bias).cuda(), 0.75, again, dtype)
+    assert torch.equal(y, again)
+
+
+@pytest.mark.parametrize("dtype", [lc.LC_F32, lc.LC_BF16], ids=["f32", "bf16"])
+def test_forward_infinities_stay_in_their_fields(dtype):
+    """An infinite pixel makes the outputs of the fields that hold it infinite, NaN nowhere; a NaN between fields (stride
+    beyond the field) reaches nothing."""
+    print(f"case general forward infinities {dtype}", flush=True)
+    shape = (3, 18, 20, 3, 3, 5, 11)
+    g = wl.LCGeom(*shape)
+    x, w, _ = wl.lc_inputs(g, "gaussian", seed=2)
+    x[:, 3:5] = np.nan
+    x[:, :, 3:5] = np.nan
+    x[1, 6, 7, 2] = np.inf                       # last value of a patch row
+    x[2, 10, 10, 0] = -np.inf                    # first value of a field
+    (xd, xv), (wd, wv) = operand(x, dtype), operand(w, dtype)
+    y = nan(g.B, g.LH, g.LW, g.F)
+    lc.lc_forward(lc.geom(*shape), xd, wd, None, 1.0, y, dtype)
+    ref = oracle.lc_forward(shape, xv, wv)
+    y = y.cpu().numpy()
+    assert np.isinf(ref).sum() == 2 * g.F and not np.isnan(ref).any()
+    assert np.array_equal(np.isinf(y), np.isinf(ref)) and np.array_equal(y[np.isinf(ref)], ref[np.isinf(ref)])
+    m = np.isfinite(ref)
+    assert rel_fro(y[m], ref[m]) <= bar(g.K)
