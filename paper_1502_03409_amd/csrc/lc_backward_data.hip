@@ -1065,6 +1065,7 @@ int launch_backward_data_f32(const Geom &g, const float *dy, const float *w, flo
         const int rc = launch_backward_data_fast_path(g, dy, w, dx, s, &done);
         if (done) return rc;
     }
+    if (backward_data_general_supported(g, 4)) return launch_backward_data_general_f32(g, dy, w, dx, s);
     return launch_backward_data_generic(g, dy, w, dx, s);
 }
 
@@ -1079,6 +1080,7 @@ int launch_backward_data_bf16_storage(const Geom &g, const void *dy, const void 
     bool done = false;
     const int rc = launch_backward_data_fast_path(g, (const bf16_t *)dy, (const bf16_t *)w, dx, s, &done);
     if (done) return rc;
+    if (backward_data_general_supported(g, 2)) return launch_backward_data_general_bf16(g, dy, w, dx, s);
     return launch_backward_data_generic(g, (const bf16_t *)dy, (const bf16_t *)w, dx, s);
 }
 

@@ -309,6 +309,10 @@ int launch_forward_general_f32(const Geom &g, const float *x, const float *w, co
                                const float *alpha_dev, float *y, hipStream_t s);
 int launch_forward_general_bf16(const Geom &g, const void *x, const void *w, const float *bias, float alpha, float *y,
                                 hipStream_t s);
+// the same for backward data (at least four filters)
+bool backward_data_general_supported(const Geom &g, int es);
+int launch_backward_data_general_f32(const Geom &g, const float *dy, const float *w, float *dx, hipStream_t s);
+int launch_backward_data_general_bf16(const Geom &g, const void *dy, const void *w, float *dx, hipStream_t s);
 // bf16 storage through the fp32 kernels' structure: the pipelined kernels for the aligned shapes (bf16 MFMAs in the
 // backward-data pass, operands widened on the way in elsewhere), the masked kernels for every other shape
 bool backward_data_bf16_pipelined_supported(const Geom &g);

@@ -241,10 +241,8 @@ ForwardTile pick_tile(const Geom &g, int es) {
 template <typename T>
 int launch_general(const Geom &g, const T *x, const T *w, const float *bias, float alpha, const float *alpha_dev, float *y,
                    hipStream_t s) {
-    ForwardTile t = pick_tile(g, sizeof(T));
-#ifdef LC_TUNE
-    if (const char *e = getenv("LC_FWD")) { sscanf(e, "%d,%d,%d,%d,%d", &t.mt, &t.nt, &t.nfw, &t.tasks, &t.ks); }
-#endif
+    static thread_local TileMemo<ForwardTile> memo;
+    const ForwardTile t = memo.get(g, sizeof(T), pick_tile);
 #define LC_TILE(M, N) if (t.mt == M && t.nt == N) return launch_tile<M, N>(g, x, w, bias, alpha, alpha_dev, y, t, s)
     LC_TILE(1, 1); LC_TILE(2, 1); LC_TILE(3, 1); LC_TILE(4, 1);
     LC_TILE(1, 2); LC_TILE(2, 2); LC_TILE(3, 2); LC_TILE(4, 2);

@@ -3,6 +3,8 @@
 // fetches its own operands, four consecutive values per lane, straight from global memory into the MFMA operands; there
 // are no barriers in the main loop, and several waves can split one tile's contraction and add up through LDS.
 #pragma once
+#include <string.h>
+
 #include "lc_common.hpp"
 
 namespace lc {
@@ -60,11 +62,28 @@ __device__ __forceinline__ u32x2 column4(const Run<bf16_t, N> (&r)[4], int u) {
     }
 }
 
-// the packed pair with the elements below `skip` (0..4, counted from the quad's first) set to zero
+// the packed elements with those below `skip` (counted from the first) set to zero
+template <int N>
+__device__ __forceinline__ void clear_below(unsigned (&v)[N], int skip) {
+#pragma unroll
+    for (int q = 0; q < N; ++q) v[q] &= skip >= 2 * q + 2 ? 0u : skip == 2 * q + 1 ? 0xffff0000u : 0xffffffffu;
+}
 __device__ __forceinline__ u32x2 clear_below(u32x2 v, int skip) {
-    const unsigned lo = skip >= 2 ? 0u : skip == 1 ? 0xffff0000u : 0xffffffffu;
-    const unsigned hi = skip >= 4 ? 0u : skip == 3 ? 0xffff0000u : 0xffffffffu;
-    return (u32x2){v[0] & lo, v[1] & hi};
+    unsigned d[2] = {v[0], v[1]};
+    clear_below<2>(d, skip);
+    return (u32x2){d[0], d[1]};
+}
+
+// v_mfma_f32_16x16x32_bf16: lane l supplies the eight consecutive contraction indices 8*(l/16).. of row or column l%16
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+__device__ __forceinline__ f32x4 mfma32_bf16(u32x4 a, u32x4 b, f32x4 c) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+__device__ __forceinline__ u32x4 clear_below(u32x4 v, int skip) {
+    unsigned d[4] = {v[0], v[1], v[2], v[3]};
+    clear_below<4>(d, skip);
+    return (u32x4){d[0], d[1], d[2], d[3]};
 }
 
 // Sum of a tile over the `ks` waves (a power of two) that split its contraction: wave 0 of them ends up with it.  Pairs
@@ -87,5 +106,30 @@ __device__ __forceinline__ void add_slices(f32x4 *acc, f32x4 *buf, int group, in
         __syncthreads();
     }
 }
+
+// The tile picked for a geometry, remembered per thread: picking is a pure function of the sizes that weighs up some
+// hundred candidates, a few microseconds that a launch-bound caller would pay on every call.  64 entries, each replaced
+// by the next geometry that falls on it.
+template <typename V>
+class TileMemo {
+  public:
+    template <typename Pick>
+    const V &get(const Geom &g, int es, Pick pick) {
+        const int key[8] = {g.B, g.H, g.W, g.C, g.R, g.S, g.F, es};
+        unsigned h = 2166136261u;
+        for (int k : key) h = (h ^ (unsigned)k) * 16777619u;
+        Entry &e = entries_[(h ^ (h >> 16)) & 63u];
+        if (!e.set || memcmp(e.key, key, sizeof(key)) != 0) {
+            e.tile = pick(g, es);
+            memcpy(e.key, key, sizeof(key));
+            e.set = true;
+        }
+        return e.tile;
+    }
+
+  private:
+    struct Entry { int key[8]; V tile; bool set; };
+    Entry entries_[64] = {};
+};
 
 }  // namespace lc

@@ -85,3 +85,68 @@ def test_general_forward_covers_every_product_once(seed):
             assert ntask == LH * LW * nbt and nbt * 16 * MT >= Bn > (nbt - 1) * 16 * MT
             assert p["grid"][0] * tasks >= ntask and p["block"] == 64 * ks * nfw * tasks
     assert n_general > 100
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_general_backward_data_covers_every_product_once(seed):
+    n_general = 0
+    for geo in geometries(80, 50 + seed):
+        G = lc.geom(*geo)
+        Bn, H, W, C, R, S, F = geo
+        LH, LW, K = lc.geom_derive(G)
+        for dtype in (B.LC_F32, B.LC_BF16):
+            plans = lc.plan_query(G, B.LC_OP_BACKWARD_DATA, dtype)
+            p = plans[0]
+            if p["kernel"] != "lc_bwd_data_general":
+                assert p["kernel"] != "lc_bwd_data_generic" or F < 4, (geo, p)
+                continue
+            n_general += 1
+            MT, NT, ES, mask, ks, tasks, VW = p["tparam"][:7]
+            PR, PC, cbc, NVF, nbt, ntask = p["arg"][:6]
+            N, cbr = PR * PC * C, cdiv(H, PR)
+            assert ntask == cbr * cbc * nbt and p["grid"][0] * tasks >= ntask and p["grid"][1] * NT * 16 >= N
+            vals = np.arange(N)
+            dr, rem = vals // (PC * C), vals % (PC * C)
+            dc, c = rem // C, rem % C
+            # products formed per output value and field, summed over filters: [H, W, C] -> set of (field, filter) counts
+            for rb in {0, cbr // 2, cbr - 1}:
+                for cb in {0, cbc // 2, cbc - 1}:
+                    r0, c0 = rb * PR, cb * PC
+                    i_lo, i_hi = max(0, -(-(r0 - R + 1) // S)), min(LH - 1, (r0 + PR - 1) // S)
+                    j_lo, j_hi = max(0, -(-(c0 - R + 1) // S)), min(LW - 1, (c0 + PC - 1) // S)
+                    na, nap = i_hi - i_lo + 1, j_hi - j_lo + 1
+                    nvt = na * nap * NVF if na > 0 and nap > 0 else 0
+                    rr, cc = r0 + dr - i_lo * S, c0 + dc - j_lo * S
+                    formed = {}
+                    per = cdiv(cdiv(nvt, 4), ks) * 4 if nvt else 0
+                    vec = [vi for sl in range(ks) for vi in range(sl * per, min((sl + 1) * per, nvt))]
+                    assert vec == list(range(nvt))
+                    for vi in vec:
+                        fi, fv = vi // NVF, vi % NVF
+                        assert int((np.float32(vi) + np.float32(0.5)) * np.float32(np.float32(1) / np.float32(NVF))) == fi
+                        fa, fp = fi // nap, fi % nap
+                        assert int((np.float32(fi) + np.float32(0.5)) * np.float32(np.float32(1) / np.float32(nap))) == fa
+                        sh = (VW * NVF - F) if mask and fv == NVF - 1 else 0
+                        fo = VW * fv - sh
+                        assert 0 <= fo and fo + VW <= F
+                        ok = (rr - fa * S >= 0) & (rr - fa * S < R) & (cc - fp * S >= 0) & (cc - fp * S < R)
+                        if not mask:
+                            assert ok.all()
+                        k = (rr - fa * S) * R * C + (cc - fp * S) * C + c
+                        # the kernel's offset from the block's first field, in elements
+                        off = (fa * (LW * K - S * R * C) + fp * (K - S * C)) * F + fo + (rr * R * C + cc * C + c) * F
+                        field = (i_lo + fa) * LW + j_lo + fp
+                        want = (field - (i_lo * LW + j_lo)) * K * F + k * F + fo
+                        assert (off[ok] == want[ok]).all() and (want[ok] >= 0).all()
+                        for t in range(sh, VW):
+                            key = (field, fo + t)
+                            formed[key] = formed.get(key, 0) + ok.astype(int)
+                    for v in (0, N // 2, N - 1):
+                        row, col = r0 + int(dr[v]), c0 + int(dc[v])
+                        if row >= H or col >= W:
+                            continue
+                        cover = {(i * LW + j, f) for i in range(LH) for j in range(LW) for f in range(F)
+                                 if 0 <= row - i * S < R and 0 <= col - j * S < R}
+                        got = {key: int(n[v]) for key, n in formed.items() if n[v]}
+                        assert set(got) == cover and all(n == 1 for n in got.values()), (geo, p, row, col)
+    assert n_general > 60

@@ -74,3 +74,47 @@ def test_forward_infinities_stay_in_their_fields(dtype):
     assert np.array_equal(np.isinf(y), np.isinf(ref)) and np.array_equal(y[np.isinf(ref)], ref[np.isinf(ref)])
     m = np.isfinite(ref)
     assert rel_fro(y[m], ref[m]) <= bar(g.K)
+
+
+# backward data: besides SHAPES, filters in vectors of eight with and without a shared last vector, one and few strides per
+# block of values, and an image border that cuts a block
+DATA_SHAPES = SHAPES + [(20, 14, 15, 1, 4, 1, 8), (4, 13, 18, 2, 6, 2, 9), (33, 16, 13, 3, 8, 2, 24), (18, 25, 23, 3, 8, 4, 16),
+                        (6, 12, 10, 1, 10, 1, 4), (50, 14, 22, 64, 4, 2, 20), (2, 26, 26, 1, 7, 3, 303)]
+
+
+@pytest.mark.parametrize("shape", DATA_SHAPES, ids=str)
+@pytest.mark.parametrize("dtype", [lc.LC_F32, lc.LC_BF16], ids=["f32", "bf16"])
+def test_backward_data(shape, dtype):
+    print(f"case general backward data {shape} {dtype}", flush=True)
+    g = wl.LCGeom(*shape)
+    G = lc.geom(*shape)
+    _, w, dy = wl.lc_inputs(g, "gaussian", seed=3)
+    (yd, yv), (wd, wv) = operand(dy, dtype), operand(w, dtype)
+    dx = nan(g.B, g.H, g.W, g.C)
+    lc.lc_backward_data(G, yd, wd, dx, dtype)
+    ref = oracle.lc_backward_data(shape, yv, wv)
+    out = dx.cpu().numpy()
+    assert rel_fro(out, ref) <= bar(g.F * (-(-g.R // g.S)) ** 2)
+    assert np.all(out[ref == 0.0] == 0.0)
+    again = nan(g.B, g.H, g.W, g.C)
+    lc.lc_backward_data(G, yd, wd, again, dtype)
+    assert torch.equal(dx, again)
+
+
+@pytest.mark.parametrize("shape", [(3, 14, 15, 1, 4, 1, 12), (18, 17, 19, 3, 5, 3, 21)], ids=str)
+@pytest.mark.parametrize("dtype", [lc.LC_F32, lc.LC_BF16], ids=["f32", "bf16"])
+def test_backward_data_infinities_stay_in_their_fields(shape, dtype):
+    print(f"case general backward data infinities {shape} {dtype}", flush=True)
+    g = wl.LCGeom(*shape)
+    _, w, dy = wl.lc_inputs(g, "gaussian", seed=4)
+    dy[1, 1, 2, g.F - 1] = np.inf                # the last filter of one field, the first of another
+    dy[2, g.LH - 1, 0, 0] = np.nan
+    (yd, yv), (wd, wv) = operand(dy, dtype), operand(w, dtype)
+    dx = nan(g.B, g.H, g.W, g.C)
+    lc.lc_backward_data(lc.geom(*shape), yd, wd, dx, dtype)
+    ref = oracle.lc_backward_data(shape, yv, wv)
+    out = dx.cpu().numpy()
+    assert np.isinf(ref).sum() == np.isnan(ref).sum() == g.K
+    assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.array_equal(out[np.isinf(ref)], ref[np.isinf(ref)])
+    m = np.isfinite(ref)
+    assert rel_fro(out[m], ref[m]) <= bar(g.F * (-(-g.R // g.S)) ** 2)
