@@ -777,6 +777,8 @@ int launch_backward_weights_f32(const Geom &g, const float *x1, const float *dy1
         const int rc = launch_backward_weights_fast_path(g, x1, dy1, x2, dy2, beta, gamma, out, ssq, kblocks_out, s, &done);
         if (done) return rc;
     }
+    if (backward_weights_general_supported(g, 4))
+        return launch_backward_weights_general_f32(g, x1, dy1, x2, dy2, beta, gamma, out, ssq, kblocks_out, s);
     return launch_backward_weights_generic(g, x1, dy1, x2, dy2, beta, gamma, out, ssq, kblocks_out, s);
 }
 
@@ -787,6 +789,7 @@ int launch_backward_weights_bf16_storage(const Geom &g, const void *x, const voi
     const int rc = launch_backward_weights_fast_path(g, (const bf16_t *)x, (const bf16_t *)dy, none, none, beta, 1.f, dw,
                                                      nullptr, nullptr, s, &done);
     if (done) return rc;
+    if (backward_weights_general_supported(g, 2)) return launch_backward_weights_general_bf16(g, x, dy, beta, dw, s);
     return launch_backward_weights_generic(g, (const bf16_t *)x, (const bf16_t *)dy, none, none, beta, 1.f, dw, nullptr,
                                            nullptr, s);
 }

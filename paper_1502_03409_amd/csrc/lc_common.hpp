@@ -313,6 +313,11 @@ int launch_forward_general_bf16(const Geom &g, const void *x, const void *w, con
 bool backward_data_general_supported(const Geom &g, int es);
 int launch_backward_data_general_f32(const Geom &g, const float *dy, const float *w, float *dx, hipStream_t s);
 int launch_backward_data_general_bf16(const Geom &g, const void *dy, const void *w, float *dx, hipStream_t s);
+// the same for the weight gradient (patch rows of at least four values)
+bool backward_weights_general_supported(const Geom &g, int es);
+int launch_backward_weights_general_f32(const Geom &g, const float *x1, const float *dy1, const float *x2, const float *dy2,
+                                        float beta, float gamma, float *out, float *ssq, int *kblocks_out, hipStream_t s);
+int launch_backward_weights_general_bf16(const Geom &g, const void *x, const void *dy, float beta, float *dw, hipStream_t s);
 // bf16 storage through the fp32 kernels' structure: the pipelined kernels for the aligned shapes (bf16 MFMAs in the
 // backward-data pass, operands widened on the way in elsewhere), the masked kernels for every other shape
 bool backward_data_bf16_pipelined_supported(const Geom &g);

@@ -150,3 +150,54 @@ def test_general_backward_data_covers_every_product_once(seed):
                         got = {key: int(n[v]) for key, n in formed.items() if n[v]}
                         assert set(got) == cover and all(n == 1 for n in got.values()), (geo, p, row, col)
     assert n_general > 60
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_general_backward_weights_stores_every_element_once(seed):
+    n_general = 0
+    for geo in geometries(150, 90 + seed):
+        G_ = lc.geom(*geo)
+        Bn, H, W, C, R, S, F = geo
+        LH, LW, K = lc.geom_derive(G_)
+        RC = R * C
+        plans = [(lc.plan_query(G_, B.LC_OP_BACKWARD_WEIGHTS, dtype)[0], False) for dtype in (B.LC_F32, B.LC_BF16)]
+        plans += [(p, True) for p in lc.plan_query(G_, B.LC_OP_SAE_STEP) if p["kernel"].startswith("lc_bwd_weights")]
+        for p, squares in plans:
+            if p["kernel"] != "lc_bwd_weights_general":
+                assert p["kernel"] != "lc_bwd_weights_generic" or RC < 4, (geo, p)
+                continue
+            n_general += 1
+            G, NT, ES = p["tparam"][:3]
+            NV, nvt, kblocks, nfb, ntask = p["arg"][:5]
+            assert ntask == LH * LW * kblocks * nfb and p["grid"][0] * 4 >= ntask and p["block"] == 256
+            assert not squares or kblocks <= cdiv(K, 64)     # room for the partial sums of squares
+            # patch elements: stored by exactly one vector, all four of a vector inside the patch row
+            seen = np.zeros(K, dtype=int)
+            for vi in range(kblocks * G * 16):
+                if vi >= nvt:
+                    continue
+                assert int((np.float32(vi) + np.float32(0.5)) * np.float32(np.float32(1) / np.float32(NV))) == vi // NV
+                row, v = vi // NV, vi % NV
+                skip = 4 * NV - RC if v == NV - 1 else 0
+                assert 0 <= 4 * v - skip and 4 * v - skip + 4 <= RC
+                seen[row * RC + 4 * v:row * RC + 4 * v - skip + 4] += 1
+            assert (seen == 1).all()
+            # filters likewise
+            seen = np.zeros(F, dtype=int)
+            for f0 in range(0, nfb * NT * 16, NT * 16):
+                for m in range(16):
+                    fl = min(f0 + NT * m, F - NT)
+                    shared = f0 + NT * m - fl
+                    assert fl >= 0
+                    if shared < NT:
+                        seen[fl + shared:fl + NT] += 1
+            assert (seen == 1).all()
+            # images: each in one step, one or four per lane
+            IM = 1 if ES == 4 else 4
+            images = np.zeros(Bn, dtype=int)
+            for st in range(cdiv(Bn, 4 * IM)):
+                for kk in range(4):
+                    left = Bn - (st * 4 * IM + IM * kk)
+                    images[st * 4 * IM + IM * kk:st * 4 * IM + IM * kk + max(0, min(IM, left))] += 1
+            assert (images == 1).all()
+    assert n_general > 100

@@ -118,3 +118,48 @@ def test_backward_data_infinities_stay_in_their_fields(shape, dtype):
     assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.array_equal(out[np.isinf(ref)], ref[np.isinf(ref)])
     m = np.isfinite(ref)
     assert rel_fro(out[m], ref[m]) <= bar(g.F * (-(-g.R // g.S)) ** 2)
+
+
+# weight gradient: besides SHAPES, batches around a step of four and of sixteen images, one slice and several
+WEIGHT_SHAPES = SHAPES + [(4, 11, 12, 5, 3, 1, 30), (15, 12, 10, 3, 5, 1, 18), (31, 10, 11, 7, 2, 1, 6), (64, 9, 9, 3, 9, 1, 35),
+                          (200, 8, 9, 3, 7, 1, 21), (3, 12, 14, 1, 4, 2, 2)]
+
+
+@pytest.mark.parametrize("shape", WEIGHT_SHAPES, ids=str)
+@pytest.mark.parametrize("dtype", [lc.LC_F32, lc.LC_BF16], ids=["f32", "bf16"])
+def test_backward_weights(shape, dtype):
+    print(f"case general backward weights {shape} {dtype}", flush=True)
+    g = wl.LCGeom(*shape)
+    G = lc.geom(*shape)
+    x, _, dy = wl.lc_inputs(g, "gaussian", seed=5)
+    (xd, xv), (yd, yv) = operand(x, dtype), operand(dy, dtype)
+    dw = nan(g.LH, g.LW, g.K, g.F)
+    lc.lc_backward_weights(G, xd, yd, 0.0, dw, dtype)
+    ref = oracle.lc_backward_weights(shape, xv, yv)
+    assert rel_fro(dw.cpu().numpy(), ref) <= bar(g.B)
+    # accumulation: what vectors or runs share is added once
+    prev = torch.from_numpy(np.random.default_rng(6).standard_normal(ref.shape).astype(np.float32)).cuda()
+    acc = prev.clone()
+    lc.lc_backward_weights(G, xd, yd, 1.0, acc, dtype)
+    assert rel_fro(acc.cpu().numpy(), ref + prev.cpu().numpy().astype(np.float64)) <= bar(g.B)
+    again = nan(g.LH, g.LW, g.K, g.F)
+    lc.lc_backward_weights(G, xd, yd, 0.0, again, dtype)
+    assert torch.equal(dw, again)
+
+
+@pytest.mark.parametrize("shape", [(6, 13, 14, 5, 3, 2, 19), (18, 17, 12, 3, 7, 3, 33), (2, 20, 20, 1, 6, 2, 50)], ids=str)
+def test_sae_step_projects_with_shared_vectors(shape):
+    """The row projection's sums of squares count every updated weight once."""
+    print(f"case general sae_step projection {shape}", flush=True)
+    g = wl.LCGeom(*shape)
+    G = lc.geom(*shape)
+    x, w, _ = wl.lc_inputs(g, "gaussian", seed=7)
+    b = np.zeros((g.H, g.W, g.C), dtype=np.float32)
+    wd, bd = torch.from_numpy(w).cuda(), torch.from_numpy(b).cuda()
+    alpha, cost = torch.full((1,), 0.8, device="cuda"), nan(1)
+    ws = torch.empty(lc.workspace_bytes(G, lc.LC_OP_SAE_STEP), dtype=torch.uint8, device="cuda")
+    lc.sae_step(G, torch.from_numpy(x).cuda(), wd, bd, alpha, 0.1, 1e-6, 1e-2, lc.LC_SAE_PROJECT_ROWS, None, cost, ws)
+    _, wo, _, _, _ = oracle.sae_step(shape, x, w, b, float(np.float32(0.8)), 0.1, 1e-6, 1e-2, 1)
+    out = wd.cpu().numpy().astype(np.float64)
+    np.testing.assert_allclose(np.linalg.norm(out, axis=2), 1.0, rtol=1e-6)
+    assert rel_fro(out, wo) <= 1e-6
