@@ -3,7 +3,7 @@
 // the two-stage form (subtract the local mean, then divide by the local root mean square of the result).
 //
 // Pooled statistics run in the channel-reduction kernels of the default form (pool_lcn.hip).  This file holds the
-// per-channel kernel: every element has its own statistics, so a workgroup stages an 8x16 pixel tile, its halo and
+// per-channel kernels.  The tile kernel takes every window and channel count: every element has its own statistics, so a workgroup stages an 8x16 pixel tile, its halo and
 // up to 32 channels of the quantity under the window in LDS (as float4 where C % 4 == 0), and each thread forms
 // the Gaussian window sums for one pixel and four channels at a time.  Bandwidth-bound: the forward passes read
 // the tile once (the centre value is taken from LDS), the halo ring comes from L2.
@@ -16,6 +16,12 @@ namespace {
 
 constexpr int kTileH = 8, kTileW = 16;
 constexpr int kMaxK = 15;
+// Kernels that walk down the rows: waves per compute unit they aim at (segments are as short as that takes, but at least
+// twice the rows they re-read) and below which the tile kernel stays, whose workgroups wait for memory once and not once a
+// row (7 x 7 windows on [60,19,19,48], 1.7 waves: 21 against 22 us forward, 3.8 waves with the idle lanes of a half-filled
+// chunk: 18 against 24 us backward; 5 x 5 on [157,18,18,48], 6 waves and more: 34 against 19 and 25 against 17 us).
+constexpr int kStreamWaves = 16, kFewestWaves = 3, kRowsWaves = 12, kRowsFewest = 5;
+constexpr int kRowThreads = 512;
 constexpr int kLdsTarget = 32 * 1024;   // per workgroup: several workgroups per compute unit hide the load latency
 
 struct Taps { float g[kMaxK]; };
@@ -202,6 +208,250 @@ __global__ __launch_bounds__(256) void lcn_channel_kernel(Args a) {
     }
 }
 
+// The passes over one array (kFwdOne, kMean, kBwdTwoB) as a stream, for windows of 3, 5, 7 and 9: a work item owns one column and V channels and walks down a
+// segment of rows.  Each row it meets gives one horizontal window sum (KS loads whose neighbours in the wave read the same
+// lines); the last KS of them stay in registers, so an output costs one new row of loads and KS vertical taps instead of
+// KS*KS reads from LDS, and without barriers every wave reads and writes all the time.  Segments of RS rows re-read
+// KS-1 rows of their neighbours.  Columns outside the image are read from the item's own column and left out of the sum.
+// HBM-bound: one stage on [128,44,44,32] maps, 5 x 5 windows, 45 -> 31 us = 4.1 TB/s of the bytes it cannot do without.
+template <int OP, int V, int KS>
+__global__ __launch_bounds__(256) void lcn_channel_stream_kernel(Args a, int RS, int nseg, unsigned total) {
+    static_assert(OP == kFwdOne || OP == kMean || OP == kBwdTwoB, "passes over one array");
+    constexpr bool kTwoMaps = OP == kFwdOne;
+    constexpr int r = (KS - 1) / 2;
+    const unsigned e = remap_xcd(blockIdx.x, gridDim.x) * 256u + threadIdx.x;
+    if (e >= total) return;
+    const int H = a.H, W = a.W, CV = a.C / V, per_row = W * CV;
+    const unsigned t = e / (unsigned)per_row;
+    const int cj = (int)(e - t * (unsigned)per_row), j = cj / CV;
+    const int b = (int)(t / (unsigned)nseg), sg = (int)(t - (unsigned)b * nseg);
+    const int ro0 = sg * RS, ro1 = min(ro0 + RS, H);
+    const size_t base = (size_t)b * H * per_row + cj;          // in vectors of V
+
+    float g[KS];
+    int off[KS];
+    bool in[KS];
+#pragma unroll
+    for (int q = 0; q < KS; ++q) {
+        const int jj = j + q - r;
+        g[q] = a.taps.g[q];
+        in[q] = jj >= 0 && jj < W;
+        off[q] = in[q] ? (q - r) * CV : 0;
+    }
+    const float zc = a.zpad ? 1.f : taps_inside(a.taps, j, W, r);
+    auto row_norm = [&](int row) -> float {
+        if (a.zpad) return 1.f;
+        float z = 0.f;
+#pragma unroll
+        for (int d = 0; d < KS; ++d) z += row + d - r >= 0 && row + d - r < H ? g[d] : 0.f;
+        return z;
+    };
+
+    Pack<V> h1[KS], h2[kTwoMaps ? KS : 1];                     // horizontal sums of the last KS rows
+#pragma unroll
+    for (int d = 0; d < KS; ++d)
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            h1[d].v[k] = 0.f;
+            if (kTwoMaps) h2[d].v[k] = 0.f;
+        }
+    for (int ir = ro0 - r; ir < ro1 + r; ++ir) {
+        Pack<V> n1, n2;
+#pragma unroll
+        for (int k = 0; k < V; ++k) n1.v[k] = n2.v[k] = 0.f;
+        if (ir >= 0 && ir < H) {
+            const size_t row = base + (size_t)ir * per_row;
+#pragma unroll
+            for (int q = 0; q < KS; ++q) {
+                const size_t o = (row + off[q]) * V;
+                const Pack<V> p = load<V>((OP == kBwdTwoB ? a.field : a.x) + o);
+#pragma unroll
+                for (int k = 0; k < V; ++k) {
+                    const float v = in[q] ? p.v[k] : 0.f;
+                    n1.v[k] += g[q] * v;
+                    if (kTwoMaps) n2.v[k] += g[q] * v * v;
+                }
+            }
+        }
+#pragma unroll
+        for (int d = 0; d + 1 < KS; ++d) {
+            h1[d] = h1[d + 1];
+            if (kTwoMaps) h2[d] = h2[d + 1];
+        }
+        h1[KS - 1] = n1;
+        if (kTwoMaps) h2[kTwoMaps ? KS - 1 : 0] = n2;
+        const int ro = ir - r;
+        if (ro < ro0) continue;
+        float s1[V], s2[V];
+#pragma unroll
+        for (int k = 0; k < V; ++k) {
+            s1[k] = s2[k] = 0.f;
+#pragma unroll
+            for (int d = 0; d < KS; ++d) {
+                s1[k] += g[d] * h1[d].v[k];
+                if (kTwoMaps) s2[k] += g[d] * h2[kTwoMaps ? d : 0].v[k];
+            }
+        }
+        const size_t o = (base + (size_t)ro * per_row) * V;
+        const float z = row_norm(ro) * zc;
+        Pack<V> out;
+        if (OP == kMean) {
+#pragma unroll
+            for (int k = 0; k < V; ++k) out.v[k] = s1[k] / z;
+            store<V>(a.mu_out + o, out);
+        } else if (OP == kFwdOne) {
+            const Pack<V> xv = load<V>(a.x + o);
+            Pack<V> m, rs;
+#pragma unroll
+            for (int k = 0; k < V; ++k) {
+                m.v[k] = s1[k] / z;
+                rs.v[k] = 1.0f / sqrtf(fmaxf(s2[k] / z - m.v[k] * m.v[k], 0.f) + a.eps);
+                out.v[k] = (xv.v[k] - m.v[k]) * rs.v[k];
+            }
+            store<V>(a.mu_out + o, m);
+            store<V>(a.rstd_out + o, rs);
+            store<V>(a.out + o, out);
+        } else {
+            const Pack<V> dv = load<V>(a.out + o);
+#pragma unroll
+            for (int k = 0; k < V; ++k) out.v[k] = dv.v[k] - s1[k];
+            store<V>(a.out + o, out);
+        }
+    }
+}
+
+// The passes whose quantity under the window takes several arrays (kDivide, kBwdOne, kBwdTwoA), C % 4 == 0: forming it KS
+// times per element costs more than the window sums, so a workgroup walks down a strip of TO columns (and r on either
+// side) by CB channel quads, each thread forms its own element's quantity of a row once and leaves it in LDS, and the
+// horizontal sums come from there: one barrier a row, two row buffers in turn.  What the output needs of its own element
+// waits r rows in registers, so every array is read once (but for the r columns and rows on a strip's sides).  The next
+// row's loads are in flight meanwhile.  On the same maps: one-stage gradient 45 -> 30 us; two stages 74 -> 43 us forward,
+// 85 -> 53 us backward.  (Forming the quantity for every neighbour, as the stream above would, took 117 and 84 us backward.)
+template <int OP, int KS>
+__global__ __launch_bounds__(kRowThreads) void lcn_channel_rows_kernel(Args a, int TO, int CB, int nstrip, int RS, int nseg) {
+    static_assert(OP == kDivide || OP == kBwdOne || OP == kBwdTwoA, "passes over several arrays");
+    constexpr int r = (KS - 1) / 2;
+    constexpr bool kTwoMaps = OP == kBwdOne, kGrad = OP != kDivide;
+    typedef float f4 __attribute__((ext_vector_type(4)));
+    extern __shared__ __align__(16) float lds[];
+    const int H = a.H, W = a.W, CV = a.C / 4, TC = TO + 2 * r;
+    const int ct = threadIdx.x / CB, cq = threadIdx.x - ct * CB;
+    int blk = remap_xcd(blockIdx.x, gridDim.x);                // strips and segments of one image stay in one XCD's L2
+    const int chunk = blk % a.nchunk; blk /= a.nchunk;
+    const int strip = blk % nstrip; blk /= nstrip;
+    const int sg = blk % nseg, b = blk / nseg;
+    const int j = strip * TO + ct - r, cv = chunk * CB + cq;
+    const bool lane = ct < TC && cv < CV, col_in = lane && j >= 0 && j < W;
+    const bool owns = col_in && ct >= r && ct < r + TO;        // an output column of this strip
+    const int ro0 = sg * RS, ro1 = min(ro0 + RS, H);
+    const size_t base = ((size_t)b * H * W + (col_in ? j : 0)) * CV + (lane ? cv : 0), rstride = (size_t)W * CV;
+    f4 *row0 = (f4 *)lds + ct * CB + cq;                       // [2 buffers][maps][TC][CB]
+    const int map = TC * CB, buf = (kTwoMaps ? 2 : 1) * map;
+
+    float g[KS];
+#pragma unroll
+    for (int q = 0; q < KS; ++q) g[q] = a.taps.g[q];
+    const float zc = a.zpad ? 1.f : taps_inside(a.taps, col_in ? j : 0, W, r);
+    auto row_norm = [&](int row) -> float {
+        if (a.zpad) return 1.f;
+        float z = 0.f;
+#pragma unroll
+        for (int d = 0; d < KS; ++d) z += row + d - r >= 0 && row + d - r < H ? g[d] : 0.f;
+        return z;
+    };
+    struct Elem { f4 x, m, d, rs; };
+    auto fetch = [&](int row, Elem &e) {
+        const size_t o = base + (size_t)min(max(row, 0), H - 1) * rstride;
+        e.x = ((const f4 *)a.x)[o];
+        e.m = ((const f4 *)a.mu_in)[o];
+        if constexpr (kGrad) {
+            e.d = ((const f4 *)a.dy)[o];
+            e.rs = ((const f4 *)a.rstd_in)[o];
+        }
+    };
+    f4 h1[KS], h2[kTwoMaps ? KS : 1], k1[r + 1], k2[kGrad ? r + 1 : 1];
+#pragma unroll
+    for (int d = 0; d < KS; ++d) {
+        h1[d] = (f4)(0.f);
+        if (kTwoMaps) h2[kTwoMaps ? d : 0] = (f4)(0.f);
+    }
+    Elem cur, nxt;
+    fetch(ro0 - r, cur);
+    for (int ir = ro0 - r; ir < ro1 + r; ++ir) {
+        fetch(ir + 1, nxt);
+        f4 p1 = (f4)(0.f), p2 = (f4)(0.f);
+        const f4 diff = cur.x - cur.m;
+        if (col_in && ir >= 0 && ir < H) {
+            if constexpr (OP == kDivide) {
+                p1 = diff * diff;
+            } else {
+                // gradients of this element's window mean and second moment (or variance), over its normaliser
+                const float iz = 1.f / (row_norm(ir) * zc);
+                const f4 bc = cur.rs * cur.rs * cur.rs * cur.d * diff;
+                if constexpr (OP == kBwdOne) {
+                    p1 = (bc * cur.m - cur.rs * cur.d) * iz;
+                    p2 = bc * iz;
+                } else {
+                    p1 = -0.5f * bc * iz;
+                }
+            }
+        }
+        f4 *row = row0 + (ir & 1) * buf;
+        if (lane) {
+            row[0] = p1;
+            if constexpr (kTwoMaps) row[map] = p2;
+        }
+        // what the output of this row needs of its own element, r rows later
+#pragma unroll
+        for (int d = 0; d < r; ++d) {
+            k1[d] = k1[d + 1];
+            if constexpr (kGrad) k2[d] = k2[d + 1];
+        }
+        if constexpr (OP == kDivide) k1[r] = diff;
+        else { k1[r] = cur.d * cur.rs; k2[r] = OP == kBwdOne ? cur.x : diff; }
+        __syncthreads();
+        f4 n1 = (f4)(0.f), n2 = (f4)(0.f);
+        if (owns) {
+#pragma unroll
+            for (int q = 0; q < KS; ++q) {
+                n1 += g[q] * row[(q - r) * CB];
+                if constexpr (kTwoMaps) n2 += g[q] * row[map + (q - r) * CB];
+            }
+        }
+#pragma unroll
+        for (int d = 0; d + 1 < KS; ++d) {
+            h1[d] = h1[d + 1];
+            if constexpr (kTwoMaps) h2[d] = h2[d + 1];
+        }
+        h1[KS - 1] = n1;
+        if constexpr (kTwoMaps) h2[KS - 1] = n2;
+        const int ro = ir - r;
+        cur = nxt;
+        if (ro < ro0 || !owns) continue;
+        f4 s1 = (f4)(0.f), s2 = (f4)(0.f);
+#pragma unroll
+        for (int d = 0; d < KS; ++d) {
+            s1 += g[d] * h1[d];
+            if constexpr (kTwoMaps) s2 += g[d] * h2[d];
+        }
+        const size_t o = base + (size_t)ro * rstride;
+        const float z = row_norm(ro) * zc;
+        if constexpr (OP == kDivide) {
+            f4 rs;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) rs[k] = 1.0f / sqrtf(s1[k] / z + a.eps);
+            ((f4 *)a.rstd_out)[o] = rs;
+            ((f4 *)a.out)[o] = k1[0] * rs;
+        } else if constexpr (OP == kBwdOne) {
+            ((f4 *)a.out)[o] = k1[0] + s1 - k2[0] * s2;
+        } else {
+            const f4 dv = k1[0] + 2.f * k2[0] * s1;
+            ((f4 *)a.out)[o] = dv;
+            ((f4 *)a.field)[o] = dv / z;
+        }
+    }
+}
+
 bool make_taps(int ks, float sigma, Taps *t) {
     if (ks < 1 || ks > kMaxK || (ks & 1) == 0 || !(sigma > 0.f)) return false;
     const int r = (ks - 1) / 2;
@@ -214,8 +464,66 @@ bool make_taps(int ks, float sigma, Taps *t) {
     return true;
 }
 
+template <int OP, int V, int KS>
+int launch_stream(const Args &a, int B, hipStream_t s, const char *where, bool *done) {
+    // segments so short that the chip holds about WANT waves per compute unit, but at least twice the rows they re-read
+    const long long cols = (long long)B * a.W * (a.C / V), want = (256LL * kStreamWaves * 64 + cols - 1) / cols;
+    int RS = (int)((a.H + want - 1) / want);
+    if (RS < 2 * (KS - 1)) RS = 2 * (KS - 1);
+    const int nseg = (a.H + RS - 1) / RS;
+    const long long total = cols * nseg;
+    if (total >= (1LL << 31) || total < 256LL * 64 * kFewestWaves) return LC_OK;
+    *done = true;
+    hipLaunchKernelGGL((lcn_channel_stream_kernel<OP, V, KS>), dim3((unsigned)((total + 255) / 256)), dim3(256), 0, s, a, RS,
+                       nseg, (unsigned)total);
+    LC_HIP_LAUNCH_CHECK(where);
+    return LC_OK;
+}
+
+template <int OP, int KS>
+int launch_rows(Args a, int B, hipStream_t s, const char *where, bool *done) {
+    constexpr int r = (KS - 1) / 2;
+    const int CV = a.C / 4;
+    // whole 128-byte lines of a pixel per chunk; strips that split the image evenly within a workgroup's threads
+    const int CB = CV < 8 ? CV : 8, most = kRowThreads / CB - 2 * r;
+    if (most < 1) return LC_OK;
+    a.nchunk = (CV + CB - 1) / CB;
+    const int nstrip = (a.W + most - 1) / most, TO = (a.W + nstrip - 1) / nstrip, TC = TO + 2 * r;
+    const int nthr = (TC * CB + 63) / 64 * 64;
+    const long long strips = (long long)B * nstrip * a.nchunk, want = 256LL * kRowsWaves * 64;
+    long long nseg = (want + strips * nthr - 1) / (strips * nthr);
+    int RS = (int)((a.H + nseg - 1) / nseg);
+    if (RS < 2 * (KS - 1)) RS = 2 * (KS - 1);
+    nseg = (a.H + RS - 1) / RS;
+    if (strips * nseg > 0x7fffffffLL || strips * nseg * nthr < 256LL * 64 * kRowsFewest) return LC_OK;
+    const size_t lds = (size_t)2 * (OP == kBwdOne ? 2 : 1) * TC * CB * 16;
+    *done = true;
+    hipLaunchKernelGGL((lcn_channel_rows_kernel<OP, KS>), dim3((unsigned)(strips * nseg)), dim3(nthr), lds, s, a, TO, CB, nstrip,
+                       RS, (int)nseg);
+    LC_HIP_LAUNCH_CHECK(where);
+    return LC_OK;
+}
+
+// one pass through the streaming kernels where they take the window; *done tells whether one was launched
+template <int OP, int V, int KS>
+int launch_walk(const Args &a, int B, hipStream_t s, const char *where, bool *done) {
+    if constexpr (OP == kDivide || OP == kBwdOne || OP == kBwdTwoA) {
+        if constexpr (V == 4) return launch_rows<OP, KS>(a, B, s, where, done);
+        else return LC_OK;
+    } else {
+        return launch_stream<OP, V, KS>(a, B, s, where, done);
+    }
+}
+
 template <int OP, int V>
 int launch_pass_v(Args a, int B, hipStream_t s, const char *where) {
+    bool done = false;
+    int rc = LC_OK;
+    if (a.ks == 3) rc = launch_walk<OP, V, 3>(a, B, s, where, &done);
+    else if (a.ks == 5) rc = launch_walk<OP, V, 5>(a, B, s, where, &done);
+    else if (a.ks == 7) rc = launch_walk<OP, V, 7>(a, B, s, where, &done);
+    else if (a.ks == 9) rc = launch_walk<OP, V, 9>(a, B, s, where, &done);
+    if (done || rc != LC_OK) return rc;
     const int tiles_h = (a.H + kTileH - 1) / kTileH;
     a.tiles_w = (a.W + kTileW - 1) / kTileW;
     a.tiles_per_img = tiles_h * a.tiles_w;

@@ -163,3 +163,26 @@ def test_sae_step_projects_with_shared_vectors(shape):
     out = wd.cpu().numpy().astype(np.float64)
     np.testing.assert_allclose(np.linalg.norm(out, axis=2), 1.0, rtol=1e-6)
     assert rel_fro(out, wo) <= 1e-6
+
+
+# Per-channel normalisation on maps large enough for the kernels that walk down the rows: windows of 3 to 9, channels that
+# fill a chunk of 32, leave one partly filled or are no multiple of four, strips and segments that end off the grid
+@pytest.mark.parametrize("shape,ks", [((40, 21, 26, 32), 5), ((3, 70, 75, 52), 5), ((9, 40, 37, 36), 3), ((24, 33, 18, 24), 7),
+                                      ((6, 31, 130, 16), 9), ((130, 13, 12, 20), 9), ((64, 23, 29, 6), 5), ((2, 150, 170, 7), 3)], ids=str)
+@pytest.mark.parametrize("flags", [1, 3, 5, 7])
+def test_channel_normalisation_walks(shape, ks, flags):
+    print(f"case channel normalisation {shape} {ks} {flags}", flush=True)
+    rng = np.random.default_rng(8)
+    x = (rng.standard_normal(shape) + 0.5).astype(np.float32)
+    dy = rng.standard_normal(shape).astype(np.float32)
+    xd, dyd = torch.from_numpy(x).cuda(), torch.from_numpy(dy).cuda()
+    y, mu, rstd, dx = (nan(*shape) for _ in range(4))
+    nbytes = lc.lcn_variant_workspace_bytes(shape, flags)
+    ws = torch.full((nbytes // 4,), float("nan"), device="cuda").view(torch.uint8) if nbytes else None
+    lc.lcn_variant_fwd(xd, y, mu, rstd, ks, 1.0, 1e-4, flags)
+    lc.lcn_variant_bwd(xd, mu, rstd, dyd, dx, ks, 1.0, flags, ws)
+    yo, muo, rso = oracle.lcn_var_fwd(x, ks, 1.0, 1e-4, flags)
+    dxo = oracle.lcn_var_bwd(x, muo, rso, dy, ks, 1.0, flags)
+    # window sums of ks*ks terms; the one-stage variance is a difference of two of them, a few times their size
+    for got, ref in ((mu, muo), (rstd, rso), (y, yo), (dx, dxo)):
+        assert rel_fro(got.cpu().numpy(), ref) <= 8 * bar(ks * ks)
