@@ -319,6 +319,82 @@ __global__ __launch_bounds__(256) void l2pool_fwd_stream_kernel(const float *__r
     }
 }
 
+// Backward pooling as a stream, stride 1 and a KS x KS window: a thread owns one input column and channel quad and walks
+// down RS rows.  Each output row it meets gives one horizontal sum of dy/y over the KS output columns that cover the
+// column; the last KS-1 of them stay in registers.  DIV: dy and y are two arrays; otherwise dy/y is handed in as one.  A
+// quotient is formed KS times, which still takes less than the arrays' way from memory.
+template <int KS, int RU, bool DIV>
+__global__ __launch_bounds__(256) void l2pool_bwd_stream_kernel(const float *__restrict__ x, const float *__restrict__ y,
+                                                                const float *__restrict__ dy, float *__restrict__ dx,
+                                                                int H, int W, int CV, int Ho, int Wo, int RS, int nseg,
+                                                                long long total) {
+    const long long e = (long long)remap_xcd(blockIdx.x, gridDim.x) * 256 + threadIdx.x;
+    if (e >= total) return;
+    const int per_row = W * CV;
+    const int cj = (int)(e % per_row), col = cj / CV;
+    const long long t = e / per_row;
+    const int sg = (int)(t % nseg), b = (int)(t / nseg);
+    const int r0 = sg * RS, r1 = min(r0 + RS, H);
+    const size_t xrow = (size_t)W * CV, yrow = (size_t)Wo * CV;     // row strides in float4
+    const f32x4 *xp = (const f32x4 *)x + (size_t)b * H * xrow + cj;
+    f32x4 *dp = (f32x4 *)dx + (size_t)b * H * xrow + cj;
+    const size_t ybase = (size_t)b * Ho * yrow;
+    int off[KS];
+    bool in[KS];
+#pragma unroll
+    for (int d = 0; d < KS; ++d) {
+        in[d] = col - d >= 0 && col - d < Wo;
+        off[d] = min(max(col - d, 0), Wo - 1) * CV + (cj - col * CV);
+    }
+    // horizontal sum of output row i (zero outside the map); every lane loads, from an address clamped into it
+    struct Raw { f32x4 g[KS], y[DIV ? KS : 1]; };
+    auto fetch = [&](int i, Raw &v) {
+        const size_t o = ybase + (size_t)min(max(i, 0), Ho - 1) * yrow;
+#pragma unroll
+        for (int d = 0; d < KS; ++d) {
+            v.g[d] = ((const f32x4 *)dy)[o + off[d]];
+            if constexpr (DIV) v.y[d] = ((const f32x4 *)y)[o + off[d]];
+        }
+    };
+    auto sum = [&](int i, const Raw &v) -> f32x4 {
+        f32x4 h = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int d = 0; d < KS; ++d) {
+            f32x4 q = v.g[d];
+            if constexpr (DIV) q = q / v.y[d];
+            h += in[d] && i >= 0 && i < Ho ? q : (f32x4){0.f, 0.f, 0.f, 0.f};
+        }
+        return h;
+    };
+    f32x4 ring[KS - 1];
+#pragma unroll
+    for (int d = 0; d < KS - 1; ++d) {
+        Raw v;
+        fetch(r0 - (KS - 1) + d, v);
+        ring[d] = sum(r0 - (KS - 1) + d, v);
+    }
+    for (int row = r0; row < r1; row += RU) {
+        Raw v[RU];
+        f32x4 xv[RU];
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+            fetch(row + u, v[u]);
+            xv[u] = xp[(size_t)min(row + u, H - 1) * xrow];
+        }
+#pragma unroll
+        for (int u = 0; u < RU; ++u) {
+            const f32x4 h = sum(row + u, v[u]);
+            f32x4 acc = h;
+#pragma unroll
+            for (int d = 0; d < KS - 1; ++d) acc += ring[d];
+            if (row + u < r1) dp[(size_t)(row + u) * xrow] = xv[u] * acc;
+#pragma unroll
+            for (int d = 0; d + 1 < KS - 1; ++d) ring[d] = ring[d + 1];
+            ring[KS - 2] = h;
+        }
+    }
+}
+
 // ------------------------------------------------------------------------ LCN
 constexpr int kLcnTile = 16;   // output tile edge
 constexpr int kLcnMaxK = 15;   // largest window
@@ -346,34 +422,48 @@ __device__ __forceinline__ float tap_norm(const GaussTaps &t, int p, int n, int 
 //   MODE 2  x -> mu;                          MODE 3  x, mu -> rstd, y = (x - mu) rstd;
 //   MODE 4  x, mu, rstd, dy -> dv (into out) and field[p] = sum_c dv[p,c] / normaliser(p);
 //   MODE 5  out = dv - window sum of field (in place).
+// divx (MODE 1): leave dx / x.  Latency-bound on small maps: th x tw tiles (lcn_tile) and lpp lanes a pixel
+// (lanes_per_pixel) put two workgroups on every compute unit and several loads in flight per lane; with 16 x 16 tiles and a
+// lane for every vector of a pixel [4,70,70,384] took 180 us forward (now 27), [104,25,13,72] 53 (now 9).
 template <int VEC, int MODE>
 __global__ __launch_bounds__(256) void lcn_kernel(const float *__restrict__ x, const float *__restrict__ dy,
                                                   float *__restrict__ out, float *__restrict__ mu,
                                                   float *__restrict__ rstd, float *__restrict__ field, int H, int W,
-                                                  int C, int ks, float eps, GaussTaps taps, int lpp, int tiles_w,
-                                                  int tiles_per_img, int zpad) {
+                                                  int C, int ks, float eps, GaussTaps taps, int lpp, int th, int tw,
+                                                  int tiles_w, int tiles_per_img, int zpad, int divx) {
     constexpr bool kTwoMaps = MODE == 0 || MODE == 1;
     __shared__ float m1[kLcnHalo * kLcnHalo], m2[kTwoMaps ? kLcnHalo * kLcnHalo : 1];
     __shared__ float t1[kLcnTile * kLcnTile], t2[kLcnTile * kLcnTile];
-    const int r = (ks - 1) / 2, halo = kLcnTile + 2 * r;
+    const int r = (ks - 1) / 2, hh = th + 2 * r, hw = tw + 2 * r;
     const int tid = threadIdx.x;
     // each XCD walks a contiguous range of tiles: the tiles of one image, whose halos overlap, share an L2
     const int blk = remap_xcd(blockIdx.x, gridDim.x);
     const int b = blk / tiles_per_img, tile = blk - b * tiles_per_img;
-    const int ti = (tile / tiles_w) * kLcnTile, tj = (tile % tiles_w) * kLcnTile;
+    const int ti = (tile / tiles_w) * th, tj = (tile % tiles_w) * tw;
     const int CV = C / VEC;
     const size_t img = (size_t)b * H * W;
     // window normalisers of the staged rows and columns, once per workgroup (a pixel's is their product times C)
     __shared__ float zr[kLcnHalo], zc[kLcnHalo];
-    if (tid < halo) zr[tid] = zpad ? 1.f : tap_norm(taps, ti - r + tid, H, r);
-    else if (tid >= 64 && tid < 64 + halo) zc[tid - 64] = zpad ? 1.f : tap_norm(taps, tj - r + tid - 64, W, r);
+    if (tid < hh) zr[tid] = zpad ? 1.f : tap_norm(taps, ti - r + tid, H, r);
+    else if (tid >= 64 && tid < 64 + hw) zc[tid - 64] = zpad ? 1.f : tap_norm(taps, tj - r + tid - 64, W, r);
     if (MODE == 1 || MODE == 4) __syncthreads();   // the other modes first use them after phase 1's barrier
     auto norm_at = [&](int row, int col) { return zr[row - ti + r] * zc[col - tj + r] * (float)C; };
 
-    // phase 1: per-pixel channel sums over the tile and its halo; lpp lanes share a pixel
+    // phase 1: per-pixel channel sums over the tile and its halo; lpp lanes share a pixel, four of a lane's vectors of it
+    // are in flight together
     const int grp = tid / lpp, gl = tid % lpp, ngrp = 256 / lpp;
-    for (int hp = grp; hp < halo * halo; hp += ngrp) {
-        const int hi = hp / halo, hj = hp - hi * halo;
+    constexpr int NF = 4;
+    typedef float fv __attribute__((ext_vector_type(VEC == 4 ? 4 : 2)));   // VEC = 1: the second component stays zero
+    auto fetch = [&](const float *p) -> fv {
+        if constexpr (VEC == 4) return *(const fv *)p;
+        else return (fv){*p, 0.f};
+    };
+    auto total = [&](const fv &v) -> float {
+        if constexpr (VEC == 4) return (v[0] + v[1]) + (v[2] + v[3]);
+        else return v[0];
+    };
+    for (int hp = grp; hp < hh * hw; hp += ngrp) {
+        const int hi = hp / hw, hj = hp - hi * hw;
         const int row = ti - r + hi, col = tj - r + hj;
         float a = 0.f, c2 = 0.f;
         const bool in = row >= 0 && row < H && col >= 0 && col < W;
@@ -385,31 +475,27 @@ __global__ __launch_bounds__(256) void lcn_kernel(const float *__restrict__ x, c
             if (in) a = field[img + (size_t)row * W + col];
         } else if (in) {
             const size_t pix = img + (size_t)row * W + col;
-            const float *xp = x + pix * C;
-            if (MODE == 0 || MODE == 2 || MODE == 3) {
-                for (int cv = gl; cv < CV; cv += lpp) {
-                    float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-                    if (VEC == 4) v = *(const float4 *)(xp + cv * 4);
-                    else v.x = xp[cv];
-                    if (MODE == 3) {   // squared differences from the pixel's own mean (unused lanes of v stay out)
-                        v.x -= mp;
-                        if (VEC == 4) { v.y -= mp; v.z -= mp; v.w -= mp; }
-                        a += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
-                    } else {
-                        a += (v.x + v.y) + (v.z + v.w);
-                        c2 += (v.x * v.x + v.y * v.y) + (v.z * v.z + v.w * v.w);
-                    }
+            const float *xp = x + pix * C, *gp = dy + pix * C;
+            for (int c0 = gl; c0 < CV; c0 += NF * lpp) {
+                fv v[NF], d[NF];
+#pragma unroll
+                for (int u = 0; u < NF; ++u) {
+                    const int cv = min(c0 + u * lpp, CV - 1);      // past the end: the last vector again, left out below
+                    v[u] = fetch(xp + cv * VEC);
+                    if (MODE == 1 || MODE == 4) d[u] = fetch(gp + cv * VEC);
                 }
-            } else {
-                const float *gp = dy + pix * C;
-                for (int cv = gl; cv < CV; cv += lpp) {
-                    if (VEC == 4) {
-                        const float4 v = *(const float4 *)(xp + cv * 4), d = *(const float4 *)(gp + cv * 4);
-                        a += (d.x + d.y) + (d.z + d.w);
-                        c2 += (d.x * (v.x - mp) + d.y * (v.y - mp)) + (d.z * (v.z - mp) + d.w * (v.w - mp));
+#pragma unroll
+                for (int u = 0; u < NF; ++u) {
+                    if (c0 + u * lpp >= CV) continue;
+                    fv e = v[u];
+                    if (MODE == 1 || MODE == 3 || MODE == 4) e -= mp;   // differences from the pixel's own mean
+                    if (VEC == 1) e[1] = 0.f;
+                    if (MODE == 1 || MODE == 4) {
+                        a += total(d[u]);
+                        c2 += total(d[u] * e);
                     } else {
-                        a += gp[cv];
-                        c2 += gp[cv] * (xp[cv] - mp);
+                        a += MODE == 3 ? total(e * e) : total(e);
+                        if (MODE == 0) c2 += total(e * e);
                     }
                 }
             }
@@ -444,14 +530,14 @@ __global__ __launch_bounds__(256) void lcn_kernel(const float *__restrict__ x, c
 
     // phase 2: window sums, one thread per output pixel
     {
-        const int oi = tid / kLcnTile, oj = tid % kLcnTile;
+        const int oi = tid / tw, oj = tid - oi * tw;
         const int row = ti + oi, col = tj + oj;
-        if (row < H && col < W) {
+        if (oi < th && row < H && col < W) {
             float s1 = 0.f, s2 = 0.f;
             for (int p = 0; p < ks; ++p)
                 for (int q = 0; q < ks; ++q) {
                     const float wt = taps.g[p] * taps.g[q];
-                    const int hp = (oi + p) * halo + oj + q;
+                    const int hp = (oi + p) * hw + oj + q;
                     s1 += wt * m1[hp];   // out-of-image halo entries are zero
                     if (kTwoMaps) s2 += wt * m2[hp];
                 }
@@ -482,38 +568,35 @@ __global__ __launch_bounds__(256) void lcn_kernel(const float *__restrict__ x, c
     __syncthreads();
 
     if (MODE == 4) {
-        // phase 3 of the two-stage gradient: a pixel's lanes write dv and reduce it over the channels
-        for (int op = grp; op < kLcnTile * kLcnTile; op += ngrp) {
-            const int oi = op / kLcnTile, oj = op % kLcnTile;
+        // phase 3 of the two-stage gradient: a pixel's lanes, here as many as write whole lines, write dv and reduce it over
+        // the channels
+        int lp3 = 1;
+        while (lp3 < CV && lp3 < 64) lp3 <<= 1;
+        const int g3 = tid / lp3, l3 = tid % lp3, n3 = 256 / lp3;
+        for (int op = g3; op < th * tw; op += n3) {
+            const int oi = op / tw, oj = op - oi * tw;
             const int row = ti + oi, col = tj + oj;
             if (row >= H || col >= W) continue;   // uniform over the group
             const size_t pix = img + (size_t)row * W + col;
             const float rs = rstd[pix], m = mu[pix], gs = 2.f * t1[op];
             float acc = 0.f;
-            for (int cv = gl; cv < CV; cv += lpp) {
+            for (int cv = l3; cv < CV; cv += lp3) {
                 const size_t o = pix * C + cv * VEC;
-                if (VEC == 4) {
-                    const float4 xv = *(const float4 *)(x + o), d = *(const float4 *)(dy + o);
-                    const float4 g = make_float4(d.x * rs + (xv.x - m) * gs, d.y * rs + (xv.y - m) * gs,
-                                                 d.z * rs + (xv.z - m) * gs, d.w * rs + (xv.w - m) * gs);
-                    *(float4 *)(out + o) = g;
-                    acc += (g.x + g.y) + (g.z + g.w);
-                } else {
-                    const float g = dy[o] * rs + (x[o] - m) * gs;
-                    out[o] = g;
-                    acc += g;
-                }
+                const fv xv = fetch(x + o), d = fetch(dy + o), g = d * rs + (xv - m) * gs;
+                if constexpr (VEC == 4) *(fv *)(out + o) = g;
+                else out[o] = g[0];
+                acc += total(g);
             }
-            acc = group_sum(acc, lpp);
-            if (gl == 0) field[pix] = acc / norm_at(row, col);
+            acc = group_sum(acc, lp3);
+            if (l3 == 0) field[pix] = acc / norm_at(row, col);
         }
         return;
     }
 
     // phase 3: elementwise pass over the tile
-    for (int e = tid; e < kLcnTile * kLcnTile * CV; e += 256) {
-        const int cv = e % CV, op = e / CV;
-        const int oi = op / kLcnTile, oj = op % kLcnTile;
+    for (int e = tid; e < th * tw * CV; e += 256) {
+        const int op = e / CV, cv = e - op * CV;
+        const int oi = op / tw, oj = op - oi * tw;
         const int row = ti + oi, col = tj + oj;
         if (row >= H || col >= W) continue;
         const size_t pix = img + (size_t)row * W + col;
@@ -529,11 +612,13 @@ __global__ __launch_bounds__(256) void lcn_kernel(const float *__restrict__ x, c
         } else if (MODE == 1) {
             const float rs = rstd[pix];
             if (VEC == 4) {
-                const float4 xv = *(const float4 *)(x + o), d = *(const float4 *)(dy + o);
-                *(float4 *)(out + o) = make_float4(d.x * rs + u - xv.x * v, d.y * rs + u - xv.y * v,
-                                                   d.z * rs + u - xv.z * v, d.w * rs + u - xv.w * v);
+                const fv xv = fetch(x + o), d = fetch(dy + o);
+                fv g = d * rs + u - xv * v;
+                if (divx) g = g / xv;                 // the quotient the pooling gradient takes (x is its output)
+                *(fv *)(out + o) = g;
             } else {
-                out[o] = dy[o] * rs + u - x[o] * v;
+                const float g = dy[o] * rs + u - x[o] * v;
+                out[o] = divx ? g / x[o] : g;
             }
         } else {   // MODE 5
             if (VEC == 4) {
@@ -961,10 +1046,28 @@ bool make_taps(int ks, float sigma, GaussTaps *t) {
     return true;
 }
 
+// Lanes that share a pixel in the tile kernel: about a third of its vectors, so that a lane has several loads in flight and
+// the workgroup many pixels at once (one vector a lane: one load and a reduction at a time, 13 times one after the other on
+// a 16 x 16 tile of 32 channels).
 int lanes_per_pixel(int cv) {
     int l = 1;
-    while (l < cv && l < 64) l <<= 1;
+    while (6 * l <= cv && l < 64) l <<= 1;
     return l;
+}
+
+// Tile of the tile kernel: at most 16 x 16 pixels, the image split evenly; halved, the longer side first, until there are two
+// workgroups per compute unit, as long as a tile with its halo is at most four times the tile.
+void lcn_tile(int B, int H, int W, int r, int *th, int *tw) {
+    int nh = (H + kLcnTile - 1) / kLcnTile, nw = (W + kLcnTile - 1) / kLcnTile;
+    for (;;) {
+        *th = (H + nh - 1) / nh;
+        *tw = (W + nw - 1) / nw;
+        if ((long long)B * nh * nw >= 2 * 256) return;
+        const int h2 = *th >= *tw ? (*th + 1) / 2 : *th, w2 = *th >= *tw ? *tw : (*tw + 1) / 2;
+        if (h2 * w2 == *th * *tw || (h2 + 2 * r) * (w2 + 2 * r) > 4 * h2 * w2) return;
+        nh = (H + h2 - 1) / h2;
+        nw = (W + w2 - 1) / w2;
+    }
 }
 
 }  // namespace
@@ -1010,15 +1113,49 @@ int launch_l2pool_fwd(const float *x, float *y, int B, int H, int W, int C, int 
     return LC_OK;
 }
 
+namespace {
+
+// 3 x 3 windows at stride 1, C % 4 == 0; y null: dy holds dy/y
+int launch_pool_bwd_stream(const float *x, const float *y, const float *dy, float *dx, int B, int H, int W, int C,
+                           hipStream_t s) {
+    const int CV = C / 4, RU = 2;
+    const long long cols = (long long)B * W * CV;
+    const long long want = std::max<long long>((256LL * 16 * 64 + cols - 1) / cols, 1);
+    const int RS = (int)std::max<long long>(((H + want - 1) / want + RU - 1) / RU * RU, 4);
+    const int nseg = (H + RS - 1) / RS;
+    const long long total = cols * nseg, nblk = (total + 255) / 256;
+    if (nblk > 0x7fffffffLL) return LC_EUNSUPPORTED;
+    if (y)
+        hipLaunchKernelGGL((l2pool_bwd_stream_kernel<3, RU, true>), dim3((unsigned)nblk), dim3(256), 0, s, x, y, dy, dx, H, W,
+                           CV, H - 2, W - 2, RS, nseg, total);
+    else
+        hipLaunchKernelGGL((l2pool_bwd_stream_kernel<3, RU, false>), dim3((unsigned)nblk), dim3(256), 0, s, x, y, dy, dx, H, W,
+                           CV, H - 2, W - 2, RS, nseg, total);
+    LC_HIP_LAUNCH_CHECK("l2pool_bwd launch");
+    return LC_OK;
+}
+
+}  // namespace
+
+// Whether the gradient of 3 x 3 stride-1 pooling streams.  The tile kernel forms each quotient once and is faster only where
+// its tiles are full and small enough for eight workgroups per compute unit: maps of about 32 channels that are not small
+// (128 images of 48 x 48 x 32: 24 us against 26; of 25 x 25 x 32: 12 against 10; of 57 x 57 x 16: 27 against 21; of
+// 30 x 30 x 64: 27 against 21; 38 of 65 x 35 x 128, where a tile does not fit LDS and the row kernel ran: 60 against 33).
+bool pool_bwd_streams(int H, int W, int C, int ks, int st) {
+    if (C % 4 != 0 || ks != 3 || st != 1) return false;
+    return !(C >= 24 && C <= 40 && H >= 32 && W >= 32);
+}
+
 int launch_l2pool_bwd(const float *x, const float *y, const float *dy, float *dx, int B, int H, int W, int C, int ks,
                       int st, hipStream_t s) {
+    if (pool_bwd_streams(H, W, C, ks, st)) return launch_pool_bwd_stream(x, y, dy, dx, B, H, W, C, s);
     const int Ho = (H - ks) / st + 1, Wo = (W - ks) / st + 1;
     const size_t patch_bytes = (size_t)(kPoolTH + ks - 1) * (kPoolTW + ks - 1) * C * sizeof(float);
     if (C % 4 == 0 && st == 1 && ks <= kPoolMaxK && patch_bytes <= 64 * 1024) {
         const int th = (H + kPoolTH - 1) / kPoolTH, tw = (W + kPoolTW - 1) / kPoolTW;
         const long long nblk = (long long)B * th * tw;
         if (nblk > 0x7fffffffLL) return LC_EUNSUPPORTED;
-        auto kern = l2pool_tile_kernel<1>;
+        auto kern = y ? l2pool_tile_kernel<1> : l2pool_tile_kernel<2>;
         if (int rc_lds = allow_dynamic_lds((const void *)kern, patch_bytes, "l2pool_bwd: hipFuncSetAttribute")) return rc_lds;
         hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(256), patch_bytes, s, x, y, dy, dx, H, W, C, Ho, Wo, ks,
                            0.f, tw, th * tw);
@@ -1097,36 +1234,20 @@ int launch_pool_lcn_band(const LaunchPlan &plan, const float *x, float *p, float
 }  // namespace
 
 // Gradient of l2pool_lcn_fwd with respect to its input: lcn_bwd, then l2pool_bwd, with `scratch` ([B,Ho,Wo,C]) between
-// them.  Where the band kernel and the tile kernel apply, the first leaves its gradient already divided by p there,
+// them.  Where the streaming or the tile kernel does the second, the first leaves its gradient already divided by p there,
 // so the second reads one array less.
 int launch_lcn_pool_bwd(const float *x, const float *p, const float *mu, const float *rstd, const float *dn,
                         float *scratch, float *dx, int B, int H, int W, int C, int pks, int pst, int ks, float sigma,
                         hipStream_t s) {
     const int Ho = (H - pks) / pst + 1, Wo = (W - pks) / pst + 1;
-    GaussTaps taps;
-    if (!make_taps(ks, sigma, &taps)) return LC_EINVAL;
     const size_t patch_bytes = (size_t)(kPoolTH + pks - 1) * (kPoolTW + pks - 1) * C * sizeof(float);
     const int th = (H + kPoolTH - 1) / kPoolTH, tw = (W + kPoolTW - 1) / kPoolTW;
-    const long long nblk = (long long)B * th * tw;
-    if (C % 4 == 0 && pst == 1 && pks <= kPoolMaxK && patch_bytes <= 64 * 1024 && nblk <= 0x7fffffffLL) {
-        bool done = false;
-        if (int rc = launch_lcn_band(1, p, dn, scratch, const_cast<float *>(mu), const_cast<float *>(rstd), B, Ho, Wo, C,
-                                     ks, 0.f, taps, s, 0, &done, 1))
-            return rc;
-        if (done) {
-            auto kern = l2pool_tile_kernel<2>;
-            if (int rc_lds = allow_dynamic_lds((const void *)kern, patch_bytes, "lcn_l2pool_bwd: hipFuncSetAttribute"))
-                return rc_lds;
-            hipLaunchKernelGGL(kern, dim3((unsigned)nblk), dim3(256), patch_bytes, s, x, (const float *)nullptr,
-                               (const float *)scratch, dx, H, W, C, Ho, Wo, pks, 0.f, tw, th * tw);
-            LC_HIP_LAUNCH_CHECK("lcn_l2pool_bwd launch");
-            return LC_OK;
-        }
-    }
+    const bool quotient = pool_bwd_streams(H, W, C, pks, pst) || (C % 4 == 0 && pst == 1 && pks <= kPoolMaxK &&
+                                                                   patch_bytes <= 64 * 1024 && (long long)B * th * tw <= 0x7fffffffLL);
     if (int rc = launch_lcn(1, p, dn, scratch, const_cast<float *>(mu), const_cast<float *>(rstd), B, Ho, Wo, C, ks, sigma,
-                            0.f, s))
+                            0.f, s, 0, nullptr, quotient))
         return rc;
-    return launch_l2pool_bwd(x, p, scratch, dx, B, H, W, C, pks, pst, s);
+    return launch_l2pool_bwd(x, quotient ? nullptr : p, scratch, dx, B, H, W, C, pks, pst, s);
 }
 
 // Host check of a pool_lcn_band_kernel launch.  tparam = {LPP, RPT}; arg = {PB, bands, WPS, rpt, H, W, ks, B}.
@@ -1191,7 +1312,7 @@ int launch_pool_lcn_fused(const float *x, float *p, float *out, float *mu, float
 }
 
 int launch_lcn(int mode, const float *x, const float *dy, float *out, float *mu, float *rstd, int B, int H, int W,
-               int C, int ks, float sigma, float eps, hipStream_t s, int zero_pad, float *field) {
+               int C, int ks, float sigma, float eps, hipStream_t s, int zero_pad, float *field, int divx) {
     GaussTaps taps;
     if (!make_taps(ks, sigma, &taps)) return LC_EINVAL;
     if (mode < 0 || mode > 5 || ((mode == 4 || mode == 5) && field == nullptr)) return LC_EINVAL;
@@ -1200,15 +1321,19 @@ int launch_lcn(int mode, const float *x, const float *dy, float *out, float *mu,
     if (nblk > 0x7fffffffLL) return LC_EUNSUPPORTED;
     if (mode == 0 || mode == 1) {
         bool done = false;
-        const int rc = launch_lcn_band(mode, x, dy, out, mu, rstd, B, H, W, C, ks, eps, taps, s, zero_pad, &done);
+        const int rc = launch_lcn_band(mode, x, dy, out, mu, rstd, B, H, W, C, ks, eps, taps, s, zero_pad, &done, divx);
         if (done) return rc;
     }
     const int vec = (C % 4 == 0) ? 4 : 1;
     const int lpp = lanes_per_pixel(C / vec);
-    dim3 grid((unsigned)nblk), block(256);
-#define LC_LCN(VEC_, MODE_)                                                                                      \
-    hipLaunchKernelGGL((lcn_kernel<VEC_, MODE_>), grid, block, 0, s, x, dy, out, mu, rstd, field, H, W, C, ks, eps, \
-                       taps, lpp, tiles_w, tiles_h * tiles_w, zero_pad)
+    int th, tw;
+    lcn_tile(B, H, W, (ks - 1) / 2, &th, &tw);
+    const int tw_n = (W + tw - 1) / tw, t_img = (H + th - 1) / th * tw_n;
+    if ((long long)B * t_img > 0x7fffffffLL) return LC_EUNSUPPORTED;
+    dim3 grid((unsigned)nblk), tgrid((unsigned)((long long)B * t_img)), block(256);
+#define LC_LCN(VEC_, MODE_)                                                                                          \
+    hipLaunchKernelGGL((lcn_kernel<VEC_, MODE_>), tgrid, block, 0, s, x, dy, out, mu, rstd, field, H, W, C, ks, eps, \
+                       taps, lpp, th, tw, tw_n, t_img, zero_pad, divx)
 #define LC_LCN_MODE(MODE_) do { if (vec == 4) LC_LCN(4, MODE_); else LC_LCN(1, MODE_); } while (0)
 #define LC_LCN_CACHED(LPP_)                                                                                    \
     hipLaunchKernelGGL((lcn_fwd_cached_kernel<LPP_>), grid, block, 0, s, x, out, mu, rstd, H, W, ks, eps, taps, \

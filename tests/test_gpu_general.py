@@ -186,3 +186,48 @@ def test_channel_normalisation_walks(shape, ks, flags):
     # window sums of ks*ks terms; the one-stage variance is a difference of two of them, a few times their size
     for got, ref in ((mu, muo), (rstd, rso), (y, yo), (dx, dxo)):
         assert rel_fro(got.cpu().numpy(), ref) <= 8 * bar(ks * ks)
+
+
+# Normalisation with statistics pooled over channels that have no band kernel, or maps these do not take: tiles of every
+# size the launcher halves down to, lanes per pixel that fill its vectors, leave some empty or take single channels
+@pytest.mark.parametrize("shape,ks", [((4, 33, 35, 96), 5), ((1, 12, 13, 40), 3), ((2, 20, 70, 384), 5), ((40, 17, 18, 24), 7),
+                                      ((600, 5, 5, 72), 9), ((3, 30, 31, 7), 5), ((2, 16, 90, 64), 15), ((1, 3, 50, 12), 9)], ids=str)
+@pytest.mark.parametrize("flags", [0, 2, 4, 6])
+def test_pooled_normalisation_tiles(shape, ks, flags):
+    print(f"case pooled normalisation {shape} {ks} {flags}", flush=True)
+    rng = np.random.default_rng(9)
+    x = (rng.standard_normal(shape) + 0.5).astype(np.float32)
+    dy = rng.standard_normal(shape).astype(np.float32)
+    xd, dyd = torch.from_numpy(x).cuda(), torch.from_numpy(dy).cuda()
+    y, dx, mu, rstd = nan(*shape), nan(*shape), nan(*shape[:3]), nan(*shape[:3])
+    nbytes = lc.lcn_variant_workspace_bytes(shape, flags)
+    ws = torch.full((nbytes // 4,), float("nan"), device="cuda").view(torch.uint8) if nbytes else None
+    lc.lcn_variant_fwd(xd, y, mu, rstd, ks, 1.0, 1e-4, flags)
+    lc.lcn_variant_bwd(xd, mu, rstd, dyd, dx, ks, 1.0, flags, ws)
+    yo, muo, rso = oracle.lcn_var_fwd(x, ks, 1.0, 1e-4, flags)
+    dxo = oracle.lcn_var_bwd(x, muo, rso, dy, ks, 1.0, flags)
+    # sums of ks*ks*C terms; the one-stage variance is a difference of two of them, a few times their size
+    for got, ref in ((mu, muo), (rstd, rso), (y, yo), (dx, dxo)):
+        assert rel_fro(got.cpu().numpy(), ref) <= 8 * bar(ks * ks * shape[3])
+
+
+# 3x3 stride-1 pooling gradient: the stream's segments and borders, the smallest map, and the sizes around the tile kernel's
+@pytest.mark.parametrize("shape", [(1, 3, 3, 4), (2, 9, 7, 128), (3, 41, 35, 16), (1, 4, 100, 8), (5, 33, 34, 44), (2, 32, 33, 24),
+                                   (2, 31, 40, 32), (1, 70, 5, 384)], ids=str)
+def test_pool_gradient_streams(shape):
+    print(f"case pool gradient {shape}", flush=True)
+    rng = np.random.default_rng(10)
+    x = rng.standard_normal(shape).astype(np.float32)
+    y = oracle.l2pool_fwd(x, 3, 1, 1e-6).astype(np.float32)
+    dy = rng.standard_normal(y.shape).astype(np.float32)
+    dx = nan(*shape)
+    lc.l2pool_bwd(*(torch.from_numpy(a).cuda() for a in (x, y, dy)), dx, 3, 1)
+    # nine quotients and a product, each a rounding or two
+    assert rel_fro(dx.cpu().numpy(), oracle.l2pool_bwd(x, y, dy, 3, 1)) <= bar(16)
+    # behind the normalisation, which leaves dp / p in the scratch array
+    n, mu, rstd = oracle.lcn_fwd(y, 3, 1.0, 1e-4)
+    mu32, rs32 = mu.astype(np.float32), rstd.astype(np.float32)
+    scratch, dx2 = nan(*y.shape), nan(*shape)
+    lc.lcn_l2pool_bwd(*(torch.from_numpy(a).cuda() for a in (x, y, mu32, rs32, dy)), scratch, dx2, 3, 1, 3, 1.0)
+    ref = oracle.l2pool_bwd(x, y, oracle.lcn_bwd(y, mu32, rs32, dy, 3, 1.0), 3, 1)
+    assert rel_fro(dx2.cpu().numpy(), ref) <= 8 * bar(9 * shape[3])
