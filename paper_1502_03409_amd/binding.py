@@ -9,6 +9,7 @@ fails loudly.
 from __future__ import annotations
 
 import ctypes as C
+from functools import lru_cache
 from pathlib import Path
 from typing import Optional, Tuple
 
@@ -88,7 +89,7 @@ def lib() -> C.CDLL:
 
 
 def _check(fn: str, rc: int) -> None:
-    if rc != LC_OK:
+    if rc:
         with_text = rc in (LC_EHIP, LC_EINTERNAL) or (rc == LC_EWORKSPACE and fn == "lcn_variant_bwd_static")
         detail = lib().lc_last_error().decode() if with_text else ""
         raise LcError(fn, rc, detail)
@@ -98,10 +99,23 @@ def geom(B: int, H: int, W: int, Cc: int, R: int, S: int, F: int) -> LcGeom:
     return LcGeom(B, H, W, Cc, R, S, F)
 
 
-def geom_derive(g: LcGeom) -> Tuple[int, int, int]:
+@lru_cache(maxsize=1024)
+def _derive(*sizes: int) -> Tuple[int, int, int]:
+    """LH, LW, K of a geometry by its seven sizes; raises (and remembers nothing) for an impossible one."""
     lh, lw, k = C.c_int32(), C.c_int32(), C.c_int32()
-    _check("lc_geom_derive", lib().lc_geom_derive(C.byref(g), C.byref(lh), C.byref(lw), C.byref(k)))
+    _check("lc_geom_derive", lib().lc_geom_derive(C.byref(LcGeom(*sizes)), C.byref(lh), C.byref(lw), C.byref(k)))
     return lh.value, lw.value, k.value
+
+
+def geom_derive(g: LcGeom) -> Tuple[int, int, int]:
+    return _derive(g.B, g.H, g.W, g.C, g.R, g.S, g.F)
+
+
+def _sizes(g: LcGeom):
+    """The sizes of the four tensors of a layer: x, w, dy or y, and LH, LW."""
+    B, H, W, Cc, R, S, F = g.B, g.H, g.W, g.C, g.R, g.S, g.F
+    LH, LW, K = _derive(B, H, W, Cc, R, S, F)
+    return (B, H, W, Cc), (LH, LW, K, F), (B, LH, LW, F)
 
 
 def workspace_bytes(g: LcGeom, op: int, dtype: int = LC_F32) -> int:
@@ -134,13 +148,20 @@ def l2pool_lcn_plan_query(shape, pool_ksize: int, pool_stride: int, lcn_ksize: i
             "grid": tuple(out[0].grid), "block": int(out[0].block), "lds_bytes": int(out[0].lds_bytes)}
 
 
+# The current stream's handle without building a Stream object (which costs as much as the launch itself).
+_raw_stream = torch._C._cuda_getCurrentRawStream
+_device = torch.cuda.current_device
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_device())
 
 
 def _dev(t: Optional[torch.Tensor], shape, dtype, name: str) -> Optional[int]:
     if t is None:
         return None
+    if t.is_cuda and t.dtype is dtype and t.is_contiguous() and (shape is None or t.shape == shape):
+        return t.data_ptr()
     if not t.is_cuda:
         raise ValueError(f"{name} must be a GPU tensor")
     if t.dtype != dtype:
@@ -163,40 +184,40 @@ def _ws(ws: Optional[torch.Tensor]):
 
 
 def lc_forward(g: LcGeom, x, w, bias, alpha: float, y, dtype: int = LC_F32, ws=None) -> None:
-    LH, LW, K = geom_derive(g)
+    xs, wsh, ys = _sizes(g)
     dt = _op_dtype(dtype)
     wp, wb = _ws(ws)
     _check("lc_forward", lib().lc_forward(
-        C.byref(g), _dev(x, (g.B, g.H, g.W, g.C), dt, "x"), _dev(w, (LH, LW, K, g.F), dt, "w"),
-        _dev(bias, (LH, LW, g.F), torch.float32, "bias"), alpha, _dev(y, (g.B, LH, LW, g.F), torch.float32, "y"),
+        C.byref(g), _dev(x, xs, dt, "x"), _dev(w, wsh, dt, "w"),
+        _dev(bias, ys[1:], torch.float32, "bias"), alpha, _dev(y, ys, torch.float32, "y"),
         dtype, wp, wb, _stream()))
 
 
 def lc_forward_dev_scale(g: LcGeom, x, w, bias, alpha_dev, y, ws=None) -> None:
-    LH, LW, K = geom_derive(g)
+    xs, wsh, ys = _sizes(g)
     wp, wb = _ws(ws)
     _check("lc_forward_dev_scale", lib().lc_forward_dev_scale(
-        C.byref(g), _dev(x, (g.B, g.H, g.W, g.C), torch.float32, "x"), _dev(w, (LH, LW, K, g.F), torch.float32, "w"),
-        _dev(bias, (LH, LW, g.F), torch.float32, "bias"), _dev(alpha_dev, None, torch.float32, "alpha_dev"),
-        _dev(y, (g.B, LH, LW, g.F), torch.float32, "y"), wp, wb, _stream()))
+        C.byref(g), _dev(x, xs, torch.float32, "x"), _dev(w, wsh, torch.float32, "w"),
+        _dev(bias, ys[1:], torch.float32, "bias"), _dev(alpha_dev, None, torch.float32, "alpha_dev"),
+        _dev(y, ys, torch.float32, "y"), wp, wb, _stream()))
 
 
 def lc_backward_data(g: LcGeom, dy, w, dx, dtype: int = LC_F32, ws=None) -> None:
-    LH, LW, K = geom_derive(g)
+    xs, wsh, ys = _sizes(g)
     dt = _op_dtype(dtype)
     wp, wb = _ws(ws)
     _check("lc_backward_data", lib().lc_backward_data(
-        C.byref(g), _dev(dy, (g.B, LH, LW, g.F), dt, "dy"), _dev(w, (LH, LW, K, g.F), dt, "w"),
-        _dev(dx, (g.B, g.H, g.W, g.C), torch.float32, "dx"), dtype, wp, wb, _stream()))
+        C.byref(g), _dev(dy, ys, dt, "dy"), _dev(w, wsh, dt, "w"),
+        _dev(dx, xs, torch.float32, "dx"), dtype, wp, wb, _stream()))
 
 
 def lc_backward_weights(g: LcGeom, x, dy, beta: float, dw, dtype: int = LC_F32, ws=None) -> None:
-    LH, LW, K = geom_derive(g)
+    xs, wsh, ys = _sizes(g)
     dt = _op_dtype(dtype)
     wp, wb = _ws(ws)
     _check("lc_backward_weights", lib().lc_backward_weights(
-        C.byref(g), _dev(x, (g.B, g.H, g.W, g.C), dt, "x"), _dev(dy, (g.B, LH, LW, g.F), dt, "dy"), beta,
-        _dev(dw, (LH, LW, K, g.F), torch.float32, "dw"), dtype, wp, wb, _stream()))
+        C.byref(g), _dev(x, xs, dt, "x"), _dev(dy, ys, dt, "dy"), beta,
+        _dev(dw, wsh, torch.float32, "dw"), dtype, wp, wb, _stream()))
 
 
 def _pool_out(H: int, ks: int, st: int) -> int:
@@ -299,10 +320,10 @@ def lcn_variant_bwd_static(x, mu, rstd, dy, dx, ksize: int, gauss_sigma: float, 
 
 def sae_step(g: LcGeom, x, w, b, alpha, lam: float, eps_sparse: float, lr: float, flags: int, h_out, cost_out,
              ws) -> None:
-    LH, LW, K = geom_derive(g)
+    xs, wsh, ys = _sizes(g)
     wp, wb = _ws(ws)
     _check("sae_step", lib().sae_step(
-        C.byref(g), _dev(x, (g.B, g.H, g.W, g.C), torch.float32, "x"), _dev(w, (LH, LW, K, g.F), torch.float32, "w"),
-        _dev(b, (g.H, g.W, g.C), torch.float32, "b"), _dev(alpha, None, torch.float32, "alpha"), lam, eps_sparse, lr,
-        flags, _dev(h_out, (g.B, LH, LW, g.F), torch.float32, "h_out"),
+        C.byref(g), _dev(x, xs, torch.float32, "x"), _dev(w, wsh, torch.float32, "w"),
+        _dev(b, xs[1:], torch.float32, "b"), _dev(alpha, None, torch.float32, "alpha"), lam, eps_sparse, lr,
+        flags, _dev(h_out, ys, torch.float32, "h_out"),
         _dev(cost_out, None, torch.float32, "cost_out"), wp, wb, _stream()))

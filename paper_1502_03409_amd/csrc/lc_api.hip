@@ -30,7 +30,7 @@ LaunchPlan make_plan(const char *kernel, std::initializer_list<int> tparam, std:
                      unsigned block, size_t lds_bytes) {
     LaunchPlan p;
     memset(&p, 0, sizeof(p));
-    snprintf(p.kernel, sizeof(p.kernel), "%s", kernel);
+    strncpy(p.kernel, kernel, sizeof(p.kernel) - 1);
     int n = 0;
     for (int v : tparam)
         if (n < 12) p.tparam[n++] = v;

@@ -201,3 +201,16 @@ def test_general_backward_weights_stores_every_element_once(seed):
                     images[st * 4 * IM + IM * kk:st * 4 * IM + IM * kk + max(0, min(IM, left))] += 1
             assert (images == 1).all()
     assert n_general > 100
+
+
+def test_derived_sizes_follow_the_geometry():
+    """The binding remembers derived sizes by value: a geometry whose fields change, or an impossible one, is seen as it is."""
+    G = lc.geom(2, 20, 20, 3, 5, 3, 8)
+    assert lc.geom_derive(G) == (6, 6, 75)
+    G.W, G.S = 29, 4
+    assert lc.geom_derive(G) == (4, 7, 75)
+    G.R = 21
+    for _ in range(2):
+        with pytest.raises(lc.LcError) as e:
+            lc.geom_derive(G)
+        assert e.value.code == B.LC_EINVAL
