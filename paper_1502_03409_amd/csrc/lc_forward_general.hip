@@ -218,6 +218,10 @@ ForwardTile pick_tile(const Geom &g, int es) {
         if (mt > 1 && 16 * (mt - 1) >= g.B) break;
         for (int nt = 1; nt <= 4; ++nt) {
             if (nt > g.F || (nt > 1 && 16 * (nt - 1) >= g.F) || (es == 2 && nt == 3)) continue;
+            // bf16: a single tile of filters is 32 bytes of each weight row, a quarter of a cache line (128 images of
+            // 52 x 160 x 16, 8 x 8 at stride 4, 48 filters: 102 -> 68 us with two, 96 of 48 x 60 x 16: 42 -> 20; no
+            // slower on any of 13 layers.  fp32: between 0.74 and 1.36 times the time)
+            if (es == 2 && nt == 1 && g.F > 16) continue;
             const double tasks = (double)g.L * ceil_div(g.B, 16 * mt) * ceil_div(g.F, 16 * nt);
             const double mm = (es == 4 ? 128.0 : 32.0) * mt * nt, flight = mt * nt <= 4 ? 4 : 2;
             for (int ks = 1, lg = 0; ks <= kForwardWaves(mt, nt) && (ks == 1 || 2 * ks <= groups); ks *= 2, ++lg) {
