@@ -981,6 +981,32 @@ int launch_fast(const Geom &g, const T *dy, const T *w, float *dx, hipStream_t s
 // The pipelined kernels address a batch tile's dy (64 images) with 32-bit byte offsets.
 inline bool pipelined_offsets_fit(const Geom &g) { return (long long)64 * g.L * g.F * 4 < (1LL << 32); }
 
+// Where the pipelined kernels keep a layer the general kernel could take, for fields of three strides and more.  What
+// decides is how much of their tiles is real: they pad a cell's values to whole workgroups (12 values of 48, 75 of 128) and
+// the batch to 64 images, where the general kernel gathers several small cells in a tile and steps the batch tile down.
+//   fp32: they stay where more than 70 % is real, where more than 45 % is and they have over 300 workgroups, or more than
+//     35 % and over 1000 (general faster on the layers let go: 40 images of 72 x 64 x 3, 10 x 10 at stride 2, 256 filters 552
+//     -> 197 us; 128 of 63 x 33 x 2, 9 x 9 at stride 3, 96 filters 38 -> 25; 128 of 27 x 17 x 32, 5 x 5 at stride 1, 128
+//     filters 225 -> 136; slower on those kept: 64 of 84 x 63 x 8, 9 x 9 at stride 3, 128 filters 120 against 147; 128 of
+//     55 x 55 x 16, 6 x 6 at stride 2, 32 filters 46 against 84; 100 of 102 x 102 x 4, 8 x 8 at stride 2, 16 filters 53
+//     against 60);
+//   bf16: they stay below 96 filters, whose vectors of eight let the general kernel load a row's cache line at once (128 of
+//     117 x 75 x 3, 12 x 12 at stride 3, 256 filters 214 -> 173; 64 of 300 x 300 x 3, 16 x 16 at stride 4, 384 filters 2.22 ->
+//     1.20 ms), unless 64 to 95 filters meet less than 60 % real values (40 of 165 x 70 x 2, 20 x 20 at stride 5, 80 filters 33
+//     -> 20; kept: 128 of 129 x 54 x 3, 9 x 9 at stride 3, 80 filters 30 against 35; 64 of 76 x 152 x 2, 20 x 20 at stride 4,
+//     64 filters 39 against 47).
+template <size_t ES>
+bool pipelined_stays(const Geom &g, int ap, int ntt) {
+    // values and cells per workgroup as chosen below
+    const int block = ap == 8 ? (ntt == 1 ? 16 : 64) : ntt > 4 ? 128 : 16 * std::max(ntt, ap == 5 ? 3 : 2);
+    const int cells = ap == 8 ? (ntt == 1 ? 8 : 2) : ntt > 4 ? 2 : 4;
+    const int NCV = g.S * g.S * g.C, nblk = ceil_div(NCV, block), nbt = ceil_div(g.B, 64);
+    const double real = (double)NCV / (nblk * block) * g.B / (64.0 * nbt);
+    if (ES == 2) return !(g.F >= 96 || (g.F >= 64 && real < 0.6));
+    const long long wgs = (long long)ceil_div(ceil_div(g.W, g.S), cells) * ceil_div(g.H, g.S) * nbt * nblk;
+    return real > 0.7 || (real > 0.35 && wgs > (real > 0.45 ? 300 : 1000));
+}
+
 // The pipelined kernel for filters in blocks of 16 and fields that tile the cells exactly; *done tells whether a
 // kernel was launched.  T = float or bf16_t (bf16 storage widened on the way in).
 template <typename T>
@@ -989,6 +1015,7 @@ int launch_backward_data_fast_path(const Geom &g, const T *dy, const T *w, float
     // pipelined kernel: filters in blocks of 16, fields that tile the cells exactly, a batch tile of 64 images
     if (g.F % 16 == 0 && g.R % g.S == 0 && g.B > 32 && pipelined_offsets_fit(g)) {
         const int ap = g.R / g.S, ntt = (g.S * g.S * g.C + 15) / 16;   // steps per chunk, tiles of 16 cell values
+        if (ap >= 3 && backward_data_general_supported(g, sizeof(T)) && !pipelined_stays<sizeof(T)>(g, ap, ntt)) return LC_OK;
 #define LC_BD(AP_, NT_, NCELL_) do { *done = true; return launch_fast<4, NT_, NCELL_, AP_>(g, dy, w, dx, s); } while (0)
         if (ap == 2) {
             if (ntt <= 3) LC_BD(2, 3, 4);
@@ -1054,6 +1081,19 @@ int launch_backward_data_generic(const Geom &g, const T *dy, const T *w, float *
     return launch_mt<1>(g, dy, w, dx, s);
 }
 
+// fp32 layers of large cells that the masked kernel keeps: 512 values and more per cell and 16 to 64 images make its tile
+// (all images by 64 values, a cell per task) as full as the general kernel's, and it stages nothing per cell; whole vectors
+// of filters, and ten tasks per compute unit.  (16 images of 45 x 87 x 64, 3 x 3 at stride 3, 128 filters: 31 us against
+// 41; 64 of 144 x 144 x 32, 4 x 4 at stride 4, 16 filters: 45 against 65; 20 of 114 x 96 x 64, 12 x 12 at stride 3, 16
+// filters: 182 against 209; within 5 % either way on 4 of 11.  The general kernel is faster outside: 128 of 81 x 29 x 32,
+// 13 x 13 at stride 4, 48 filters 413 -> 168 us; 8 of 45 x 20 x 64, 13 x 13 at stride 6, 112 filters 51 -> 32; 39 x 93 x 32,
+// 9 x 9 at stride 3, 288 values, 52 -> 41.)
+bool masked_kernel_stays(const Geom &g) {
+    const int NCV = g.S * g.S * g.C;
+    return NCV >= 512 && g.B >= 16 && g.B <= 64 && g.F % 4 == 0 &&
+           (long long)ceil_div(g.H, g.S) * ceil_div(g.W, g.S) * ceil_div(NCV, 64) >= 10 * 256;
+}
+
 }  // namespace
 
 int launch_backward_data_f32(const Geom &g, const float *dy, const float *w, float *dx, hipStream_t s) {
@@ -1065,7 +1105,7 @@ int launch_backward_data_f32(const Geom &g, const float *dy, const float *w, flo
         const int rc = launch_backward_data_fast_path(g, dy, w, dx, s, &done);
         if (done) return rc;
     }
-    if (backward_data_general_supported(g, 4)) return launch_backward_data_general_f32(g, dy, w, dx, s);
+    if (backward_data_general_supported(g, 4) && !masked_kernel_stays(g)) return launch_backward_data_general_f32(g, dy, w, dx, s);
     return launch_backward_data_generic(g, dy, w, dx, s);
 }
 

@@ -735,6 +735,14 @@ int launch_backward_weights_fast_path(const Geom &g, const T *x1, const T *dy1, 
             return launch_strip<8, 3, 32, 7, 28>(g, x1, dy1, x2, dy2, beta, gamma, out, ssq, kblocks_out, s);
         }
     }
+    // Where the general kernel comes first: bf16 storage (whose values this kernel widens to fp32 MFMAs) from 32 images on
+    // (40 images of 136 x 88 x 32, 4 x 4 at stride 4, 80 filters 49 -> 37 us; 200 of 75 x 78 x 2, 9 x 9 at stride 3, 16
+    // filters 22 -> 10; below, up to 1.3 times slower: steps of 16 images); in fp32 odd numbers of 16-filter tiles, three and
+    // more, which leave this kernel one tile per wave, if the contraction is 100 images and a patch 256 elements long (128 of
+    // 52 x 160 x 16, 8 x 8 at stride 4, 48 filters 78 -> 63; 128 of 52 x 78 x 32, 6 x 6 at stride 2, 80 filters 280 -> 250;
+    // shorter ones are up to 1.3 times slower).
+    const bool general = sizeof(T) == 2 ? g.B >= 32 : g.F % 32 == 16 && g.F >= 48 && g.B >= 100 && g.K >= 256;
+    if (general && backward_weights_general_supported(g, sizeof(T))) return LC_OK;
     const int va = patch_vector_width(g);
     if ((g.B & 3) == 0 && va == 4) {
         if (g.F % 64 == 0) { *done = true; return launch_fast_pf<1, 4, 4>(g, x1, dy1, x2, dy2, beta, gamma, out, ssq, kblocks_out, s); }
@@ -768,6 +776,12 @@ int launch_backward_weights_generic(const Geom &g, const T *x1, const T *dy1, co
     return launch_nt<4>(g, x1, dy1, x2, dy2, beta, gamma, out, ssq, kblocks_out, s);
 }
 
+// One image and at most 32 filters over a large gradient: little but its stores, which the masked kernel's wider tiles
+// issue faster (173 x 47 x 8, 18 x 18 at stride 3, 30 filters, 162 MB of gradient: 28.8 us against 31.0, bf16 operands 30.9
+// against 38.2; 81 x 131 x 8, 20 x 20 at stride 3, 32 filters: 60 against 69).  More filters, images or less gradient:
+// the general kernel (126 x 173 x 2, 13 x 13 at stride 6, 96 filters: 28.8 -> 16.3; 4 images, 29 filters: 138 -> 129).
+bool masked_kernel_stays(const Geom &g) { return g.B == 1 && g.F <= 32 && (long long)g.L * g.K * g.F >= (1LL << 24); }
+
 }  // namespace
 
 int launch_backward_weights_f32(const Geom &g, const float *x1, const float *dy1, const float *x2, const float *dy2,
@@ -777,7 +791,7 @@ int launch_backward_weights_f32(const Geom &g, const float *x1, const float *dy1
         const int rc = launch_backward_weights_fast_path(g, x1, dy1, x2, dy2, beta, gamma, out, ssq, kblocks_out, s, &done);
         if (done) return rc;
     }
-    if (backward_weights_general_supported(g, 4))
+    if (backward_weights_general_supported(g, 4) && !masked_kernel_stays(g))
         return launch_backward_weights_general_f32(g, x1, dy1, x2, dy2, beta, gamma, out, ssq, kblocks_out, s);
     return launch_backward_weights_generic(g, x1, dy1, x2, dy2, beta, gamma, out, ssq, kblocks_out, s);
 }
@@ -789,7 +803,8 @@ int launch_backward_weights_bf16_storage(const Geom &g, const void *x, const voi
     const int rc = launch_backward_weights_fast_path(g, (const bf16_t *)x, (const bf16_t *)dy, none, none, beta, 1.f, dw,
                                                      nullptr, nullptr, s, &done);
     if (done) return rc;
-    if (backward_weights_general_supported(g, 2)) return launch_backward_weights_general_bf16(g, x, dy, beta, dw, s);
+    if (backward_weights_general_supported(g, 2) && !masked_kernel_stays(g))
+        return launch_backward_weights_general_bf16(g, x, dy, beta, dw, s);
     return launch_backward_weights_generic(g, (const bf16_t *)x, (const bf16_t *)dy, none, none, beta, 1.f, dw, nullptr,
                                            nullptr, s);
 }

@@ -309,12 +309,28 @@ int launch_backward_data_simple(const Geom &g, const void *dy, const void *w, fl
 // the strip-sharing / pipelined / transposing kernels of the narrow layers (faster than the one-wave-per-task
 // kernels of this file wherever both apply), the kernels of this file, the fp32 pipelined kernels on bf16 storage,
 // and for every other shape the masked fp32 kernels on bf16 storage.
+//
+// Where the general kernels come first (both sides measured on some 130 layers):
+//  - forward: instead of the strip kernel where that has fewer than 320 workgroups (35 of 36 layers faster, by up to six
+//    times: 96 images of 19 x 20 x 16, 15 x 15 at stride 1, 64 filters 107 -> 16 us; from 350 workgroups on 26 of 42 are
+//    slower, by up to 1.9 times), and instead of the one-wave-per-task kernel but for patches of at most 128 elements (128
+//    images of 36 x 54 x 32, 16 x 16 at stride 2, 64 filters 470 -> 151 us; 16 of 84 x 76 x 8, 4 x 4 at stride 2: 7.2
+//    against 8.8 us);
+//  - backward data: instead of the one-wave-per-task kernel (10 layers of 11 faster, by 1.2 to 3.4 times: 32 images of
+//    128 x 128 x 8, 8 x 8 at stride 4, 128 filters 75 -> 35 us);
+//  - weight gradient: instead of the strip kernel for patches of at most 512 elements (18 of 18, 100 of 102 x 102 x 4, 8 x 8
+//    at stride 2, 16 filters 42 -> 21 us; longer ones are up to 1.5 times slower).
 int launch_forward_bf16(const Geom &g, const void *x, const void *w, const float *bias, float alpha, float *y,
                         hipStream_t s) {
+    const bool general = forward_general_supported(g, 2);
     if (bf16_shape_supported(g) && bf16_tiled_forward_supported(g))
         return launch_forward_bf16_tiled(g, x, w, bias, alpha, y, s);
-    if (bf16_strip_forward_supported(g)) return launch_forward_bf16_strip(g, x, w, bias, alpha, y, s);
+    if (bf16_strip_forward_supported(g)) {
+        if (general && bf16_strip_forward_workgroups(g) < 320) return launch_forward_general_bf16(g, x, w, bias, alpha, y, s);
+        return launch_forward_bf16_strip(g, x, w, bias, alpha, y, s);
+    }
     if (!bf16_shape_supported(g)) return launch_forward_bf16_storage(g, x, w, bias, alpha, y, s);
+    if (general && g.K > 128) return launch_forward_general_bf16(g, x, w, bias, alpha, y, s);
     if (g.B >= 64) return launch_forward_simple<4>(g, x, w, bias, alpha, y, s);
     return launch_forward_simple<1>(g, x, w, bias, alpha, y, s);
 }
@@ -323,7 +339,8 @@ int launch_backward_data_bf16(const Geom &g, const void *dy, const void *w, floa
     if (bf16_shape_supported(g) && bf16_tiled_backward_data_supported(g))
         return launch_backward_data_bf16_tiled(g, dy, w, dx, s);
     if (!bf16_shape_supported(g) || backward_data_bf16_pipelined_supported(g))
-        return launch_backward_data_bf16_storage(g, dy, w, dx, s);   // pipelined (bf16 MFMAs) or masked kernel
+        return launch_backward_data_bf16_storage(g, dy, w, dx, s);   // pipelined (bf16 MFMAs), general or masked kernel
+    if (backward_data_general_supported(g, 2)) return launch_backward_data_general_bf16(g, dy, w, dx, s);
     if (g.B >= 128) return launch_backward_data_simple<8>(g, dy, w, dx, s);
     if (g.B >= 64) return launch_backward_data_simple<4>(g, dy, w, dx, s);
     return launch_backward_data_simple<1>(g, dy, w, dx, s);
@@ -333,6 +350,8 @@ int launch_backward_weights_bf16(const Geom &g, const void *x, const void *dy, f
                                  hipStream_t s) {
     if (bf16_shape_supported(g) && bf16_tiled_backward_weights_supported(g))
         return launch_backward_weights_bf16_tiled(g, x, dy, beta, dw, s);
+    if (g.K <= 512 && bf16_strip_backward_weights_supported(g) && backward_weights_general_supported(g, 2))
+        return launch_backward_weights_general_bf16(g, x, dy, beta, dw, s);
     if (bf16_rows_backward_weights_supported(g)) return launch_backward_weights_bf16_rows(g, x, dy, beta, dw, s);
     if (!bf16_shape_supported(g)) return launch_backward_weights_bf16_storage(g, x, dy, beta, dw, s);
     const int kblocks = (g.K + 127) / 128;

@@ -632,6 +632,8 @@ int launch_wstrip_nbk(const Geom &g, const bf16_t *x, const bf16_t *dy, float be
 
 // Shapes: patch rows in whole 4-value vectors, filters in blocks of 16, and either batches in steps of 16 images or
 // a shape the strip-sharing kernel takes (any batch up to 128: it stages the missing images as zeros).
+bool bf16_strip_backward_weights_supported(const Geom &g) { return g.RC % 4 == 0 && g.F % 16 == 0 && wstrip_supported(g); }
+
 bool bf16_rows_backward_weights_supported(const Geom &g) {
     return g.RC % 4 == 0 && g.F % 16 == 0 && (g.B % 16 == 0 || wstrip_supported(g));
 }
@@ -654,6 +656,11 @@ bool bf16_strip_forward_supported(const Geom &g) {
     const int SC = g.S * g.C;
     if (g.RC % 4 || SC % 4 || (g.W * g.C) % 4 || g.F % 16 || g.B <= 16) return false;
     return strip_chunk(g, g.B > 32 ? 64 : 32) != 0;
+}
+
+long long bf16_strip_forward_workgroups(const Geom &g) {
+    const int nt = g.F % 64 == 0 ? 4 : g.F % 32 == 0 ? 2 : 1, bt = g.B > 32 ? 64 : 32;
+    return (long long)((g.LW + 3) / 4) * g.LH * ((g.B + bt - 1) / bt) * (g.F / (16 * nt));
 }
 
 int launch_forward_bf16_strip(const Geom &g, const void *xv, const void *wv, const float *bias, float alpha, float *y,

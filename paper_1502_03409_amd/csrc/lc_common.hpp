@@ -330,10 +330,12 @@ int launch_backward_weights_bf16_storage(const Geom &g, const void *x, const voi
                                          hipStream_t s);
 // strip-sharing bf16 forward for patch rows that are not multiples of 16 values and filters in blocks of 16 or 32
 bool bf16_strip_forward_supported(const Geom &g);
+long long bf16_strip_forward_workgroups(const Geom &g);
 int launch_forward_bf16_strip(const Geom &g, const void *x, const void *w, const float *bias, float alpha, float *y,
                               hipStream_t s);
 // bf16 weight gradient for patch rows in whole 4-value vectors and filters in blocks of 16 (batches in steps of 16)
 bool bf16_rows_backward_weights_supported(const Geom &g);
+bool bf16_strip_backward_weights_supported(const Geom &g);   // whether the above runs its strip kernel
 int launch_backward_weights_bf16_rows(const Geom &g, const void *x, const void *dy, float beta, float *dw,
                                       hipStream_t s);
 // workgroup-tiled bf16 forward for wide layers; LC_EUNSUPPORTED outside bf16_tiled_forward_supported()

@@ -915,6 +915,38 @@ long long fast_workgroups(const Geom &g, int mt, int nt) {
     return strips * g.LH * ((g.B + 16 * mt - 1) / (16 * mt)) * (g.F / ((4 / nloc) * ntf * 16));
 }
 
+// Everything the pipelined kernels leave goes to the general kernel, whatever its size: against the masked kernel above it
+// is faster on every layer measured (37 images of 75 x 99 x 3 under 11 x 11 fields at stride 3, 40 filters: 110 -> 19 us;
+// 128 images of 80 x 169 x 3, 10 x 10 fields at stride 3, 83 filters: 270 -> 107 us; 2 images of 51 x 64 x 64, 16 x 16
+// fields at stride 6, 60 filters: 1100 -> 62 us), because it needs no barrier per patch row and can cut a
+// contraction into slices where a layer has few fields.  The masked kernel stays for patch rows of fewer than four
+// values and for tensors beyond the general kernel's 32-bit offsets, and keeps deciding which patch rows are too long.
+bool takes_general(const Geom &g, int es) {
+    return forward_general_supported(g, es) && ((size_t)16 * lds_row_stride(g.RC) + 8) * sizeof(float) <= 160 * 1024;
+}
+
+// The workgroup-tiled kernel of lc_forward_wide.hip keeps layers of fewer than kWideFields fields and at least kWidePatch
+// elements per patch: its slices across workgroups reach further than the general kernel's eight waves (96 images of 18 x
+// 20 x 16, 16 x 16 at stride 1, 128 filters: 26.7 us against 40.6; 80 of 26 x 26 x 8, 24 x 24 at stride 1, 256 filters: 41
+// against 47).  With more fields or shorter patches the general kernel is faster (the same 24 x 24 fields on 28 x 28 pixels:
+// 72 -> 49 us; 128 images of 8 x 8 x 32, 8 x 8, 1024 filters: 27 -> 19; 256 of 64 x 64 x 32, 8 x 8 at stride 2, 128 filters:
+// 995 -> 870; 128 of 40 x 40 x 64, 4 x 4 at stride 2: 150 -> 105; 96 images, 256 filters, 8 x 8 at stride 2: 730 -> 721).
+constexpr int kWideFields = 16, kWidePatch = 4096;
+
+// Where the register-staged kernel (mt, nt: the tile it would take) keeps a layer the general kernel could take: fields
+// that overlap four times or more and few MFMAs per staged value, so that sharing the staged strip is worth its barriers.
+// That is one 32-image batch tile with two or four filter tiles per wave (32 images of 160 x 140 x 3, 16 x 16 fields at
+// stride 4, 96 filters: 90 us against the general kernel's 113; 32 of 300 x 300 x 3, 384 filters: 1.32 against 1.42 ms), or
+// more than 64 images of 16 filters that fill the chip (96 of 140 x 124 x 4, 16 x 16 at stride 4: 47 against 55 us).
+// Everywhere else the general kernel is faster, on 60 of 66 layers timed, by 1.5 times in the middle (64 images of
+// 96 x 96 x 3, 16 x 16 at stride 8, 64 filters: 28 -> 15 us; 128 of 36 x 54 x 32, 16 x 16 at stride 2, 64 filters: 525 ->
+// 271 us; 128 of 160 x 160 x 3, 16 x 16 at stride 4, 96 filters: 328 -> 275 us): it steps the tile down without staging
+// the strip once per smaller tile, and slices long contractions.
+bool staged_kernel_stays(const Geom &g, int mt, int nt) {
+    if (g.R < 4 * g.S) return false;
+    return (g.B <= 32 && nt >= 2) || (g.B > 64 && g.F == 16 && fast_workgroups(g, mt, nt) >= kComputeUnits * kBigTilesPerCu);
+}
+
 // The pipelined kernel for aligned shapes: patch rows that are whole 4-element runs, strips that start on a
 // 4-element boundary (4 fields x S x C elements, or 2 when 128 filters are split over the waves).  *done_out tells
 // whether a kernel was launched.
@@ -1003,6 +1035,9 @@ int launch_forward_fast_path(const Geom &g, const T *x, const T *w, const float 
         const bool one_tile = g.F % 16 == 0 && (g.F % 32 != 0 || nt == 1);
         if (mt == 8 && one_tile && g.LW >= 8 && (8 * g.S * g.C) % 4 == 0)
             rc = launch_fast_wide(g, x, w, bias, alpha, alpha_dev, y, s, &done);
+        // (bf16 storage: 128 images of 23 x 23 x 32, 6 x 6 at stride 2, 32 filters 29 -> 11 us; 200 of 185 x 137 x 16,
+        // 5 x 5 at stride 6, 128 filters 189 -> 89 us; faster on all of 20)
+        if (!done && takes_general(g, sizeof(T)) && (sizeof(T) == 2 || !staged_kernel_stays(g, mt, nt))) return LC_OK;
         if (!done && mt == 8) rc = launch_fast_mt<8>(g, x, w, bias, alpha, alpha_dev, y, s, &done, nt);
         if (!done && mt >= 4 && g.B > 32) rc = launch_fast_mt<4>(g, x, w, bias, alpha, alpha_dev, y, s, &done, nt);
         if (!done) rc = launch_fast_mt<2>(g, x, w, bias, alpha, alpha_dev, y, s, &done, nt);
@@ -1053,22 +1088,14 @@ int launch_forward_generic(const Geom &g, const T *x, const T *w, const float *b
 #undef LC_TRY
 }
 
-// Everything the pipelined kernels leave goes to the general kernel, whatever its size: against the masked kernel above it
-// is faster on every layer measured (37 images of 75 x 99 x 3 under 11 x 11 fields at stride 3, 40 filters: 110 -> 19 us;
-// 128 images of 80 x 169 x 3, 10 x 10 fields at stride 3, 83 filters: 270 -> 107 us; 2 images of 51 x 64 x 64, 16 x 16
-// fields at stride 6, 60 filters: 1100 -> 62 us), because it needs no barrier per patch row and can cut a
-// contraction into slices where a layer has few fields.  The masked kernel stays for patch rows of fewer than four
-// values and for tensors beyond the general kernel's 32-bit offsets, and keeps deciding which patch rows are too long.
-bool takes_general(const Geom &g, int es) {
-    return forward_general_supported(g, es) && ((size_t)16 * lds_row_stride(g.RC) + 8) * sizeof(float) <= 160 * 1024;
-}
-
 }  // namespace
 
 int launch_forward_f32(const Geom &g, const float *x, const float *w, const float *bias, float alpha,
                        const float *alpha_dev, float *y, hipStream_t s, void *ws, size_t ws_bytes) {
-    // layers with 128-filter blocks: one field per workgroup, patches through LDS, 128 x 128 output tiles
-    if (forward_wide_supported(g)) return launch_forward_wide_f32(g, x, w, bias, alpha, alpha_dev, y, ws, ws_bytes, s);
+    // layers with 128-filter blocks and hardly any, large fields: one field per workgroup, patches through LDS, 128 x 128
+    // output tiles, the contraction in slices
+    if (forward_wide_supported(g) && ((g.L < kWideFields && g.K >= kWidePatch) || !takes_general(g, 4)))
+        return launch_forward_wide_f32(g, x, w, bias, alpha, alpha_dev, y, ws, ws_bytes, s);
     // aligned shapes take the pipelined kernel: patch rows that are whole dwordx4 runs, strips that start on a
     // 16-byte boundary (4 fields x S x C floats, or 2 when 128 filters are split over the waves)
     {

@@ -231,3 +231,54 @@ def test_pool_gradient_streams(shape):
     lc.lcn_l2pool_bwd(*(torch.from_numpy(a).cuda() for a in (x, y, mu32, rs32, dy)), scratch, dx2, 3, 1, 3, 1.0)
     ref = oracle.l2pool_bwd(x, y, oracle.lcn_bwd(y, mu32, rs32, dy, 3, 1.0), 3, 1)
     assert rel_fro(dx2.cpu().numpy(), ref) <= 8 * bar(9 * shape[3])
+
+
+# Aligned layers on both sides of the lines between the general kernels and the others: (op, dtype, shape, kernel).
+ROUTES = [
+    ("forward", "f32", (40, 20, 21, 16, 4, 2, 32), "lc_forward_generic"),       # little overlap
+    ("forward", "f32", (64, 56, 56, 8, 8, 2, 64), "lc_forward_generic"),        # two batch tiles
+    ("forward", "f32", (32, 80, 80, 8, 8, 2, 64), "lc_forward_fast"),           # one, overlap of four
+    ("forward", "f32", (96, 18, 18, 16, 16, 1, 128), "lc_forward_wide"),        # 9 fields, long patches
+    ("forward", "f32", (96, 19, 19, 16, 16, 1, 128), "lc_forward_generic"),     # 16 fields
+    ("forward", "f32", (96, 10, 10, 16, 8, 1, 128), "lc_forward_generic"),      # 9 fields, short patches
+    ("forward", "bf16", (64, 12, 12, 8, 4, 2, 32), "lc_forward_generic"),       # K at the line
+    ("forward", "bf16", (64, 19, 20, 16, 15, 1, 64), "lc_forward_generic"),     # few workgroups in strips
+    ("backward_data", "f32", (16, 72, 72, 32, 4, 4, 16), "lc_bwd_data_generic"),    # large cells, enough of them
+    ("backward_data", "f32", (16, 40, 40, 32, 4, 4, 16), "lc_bwd_data_general"),    # too few
+    ("backward_data", "f32", (15, 72, 72, 32, 4, 4, 16), "lc_bwd_data_general"),    # a batch below
+    ("backward_data", "f32", (64, 26, 26, 16, 6, 2, 32), "lc_bwd_data_direct"),     # full tiles
+    ("backward_data", "f32", (40, 30, 32, 3, 10, 2, 64), "lc_bwd_data_general"),    # mostly padding
+    ("backward_data", "bf16", (64, 26, 26, 16, 6, 2, 64), "lc_bwd_data_fast"),
+    ("backward_data", "bf16", (64, 26, 26, 16, 6, 2, 96), "lc_bwd_data_general"),
+    ("backward_data", "bf16", (32, 24, 24, 8, 8, 4, 128), "lc_bwd_data_general"),
+    ("backward_weights", "f32", (100, 20, 22, 16, 4, 2, 48), "lc_bwd_weights_general"),
+    ("backward_weights", "f32", (96, 20, 22, 16, 4, 2, 48), "lc_bwd_weights_fast"),
+    ("backward_weights", "f32", (1, 44, 49, 16, 20, 3, 31), "lc_bwd_weights_generic"),   # a gradient beyond 2^24 elements
+    ("backward_weights", "f32", (1, 44, 49, 16, 20, 3, 33), "lc_bwd_weights_general"),
+    ("backward_weights", "bf16", (1, 44, 49, 16, 20, 3, 31), "lc_bwd_weights_generic"),
+    ("backward_weights", "bf16", (64, 20, 20, 4, 8, 2, 16), "lc_bwd_weights_general"),
+]
+OPS = {"forward": 0, "backward_data": 1, "backward_weights": 2}
+
+
+@pytest.mark.parametrize("op,dtype,shape,kernel", ROUTES, ids=str)
+def test_routes(op, dtype, shape, kernel):
+    print(f"case route {op} {dtype} {shape}", flush=True)
+    G, g = lc.geom(*shape), wl.LCGeom(*shape)
+    dt = lc.LC_BF16 if dtype == "bf16" else lc.LC_F32
+    assert kernel in [p["kernel"] for p in lc.plan_query(G, OPS[op], dt)]
+    x, w, dy = wl.lc_inputs(g, "gaussian", seed=6)
+    (xd, xv), (wd, wv), (dyd, dyv) = operand(x, dt), operand(w, dt), operand(dy, dt)
+    if op == "forward":
+        out, n = nan(g.B, g.LH, g.LW, g.F), g.K
+        lc.lc_forward(G, xd, wd, None, 1.0, out, dt)
+        ref = oracle.lc_forward(shape, xv, wv, None, 1.0)
+    elif op == "backward_data":
+        out, n = nan(g.B, g.H, g.W, g.C), g.F * (-(-g.R // g.S)) ** 2
+        lc.lc_backward_data(G, dyd, wd, out, dt)
+        ref = oracle.lc_backward_data(shape, dyv, wv)
+    else:
+        out, n = nan(g.LH, g.LW, g.K, g.F), g.B
+        lc.lc_backward_weights(G, xd, dyd, 0.0, out, dt)
+        ref = oracle.lc_backward_weights(shape, xv, dyv)
+    assert rel_fro(out.cpu().numpy(), ref) <= bar(n)
