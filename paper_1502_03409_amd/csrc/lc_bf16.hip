@@ -7,7 +7,8 @@
 // k of w[k][f]; backward weights: the batch) a lane loads four rows of four consecutive free indices
 // and transposes the 4x4 block in registers (v_perm_b32): it then owns column i of four different
 // tiles, free index 4i+u in tile u, and 16 lanes still cover whole 128-byte lines.
-// Waves are independent (no LDS); loads run one or two steps ahead in a register ring.
+// Waves are independent (no LDS); loads run one or two steps ahead in a register ring.  What the kernels of this file
+// keep is short patches (forward), tensors beyond the general kernel's offsets (backward data) and the weight gradient.
 #include "lc_common.hpp"
 
 namespace lc {
@@ -308,25 +309,38 @@ int launch_backward_data_simple(const Geom &g, const void *dy, const void *w, fl
 // LC_BF16 covers every valid geometry.  Order of preference, every pass: the workgroup-tiled kernels (wide layers),
 // the strip-sharing / pipelined / transposing kernels of the narrow layers (faster than the one-wave-per-task
 // kernels of this file wherever both apply), the kernels of this file, the fp32 pipelined kernels on bf16 storage,
-// and for every other shape the masked fp32 kernels on bf16 storage.
+// for nearly every other shape the general kernels, and for the rest the masked fp32 kernels on bf16 storage.
 //
 // Where the general kernels come first (both sides measured on some 130 layers):
-//  - forward: instead of the strip kernel where that has fewer than 320 workgroups (35 of 36 layers faster, by up to six
-//    times: 96 images of 19 x 20 x 16, 15 x 15 at stride 1, 64 filters 107 -> 16 us; from 350 workgroups on 26 of 42 are
-//    slower, by up to 1.9 times), and instead of the one-wave-per-task kernel but for patches of at most 128 elements (128
+//  - forward: instead of the strip kernel where that has fewer workgroups than the chip compute units (faster on all of 28
+//    layers, by up to six times: 96 images of 19 x 20 x 16, 15 x 15 at stride 1, 64 filters 107 -> 16 us; at 300 workgroups
+//    17.9 against 21.7 on 300 images of 12 x 14 x 16, 4 x 4 at stride 2, 384 filters; from 350 on 26 of 42 are slower, by up
+//    to 1.9 times), and instead of the one-wave-per-task kernel but for patches of at most 128 elements (128
 //    images of 36 x 54 x 32, 16 x 16 at stride 2, 64 filters 470 -> 151 us; 16 of 84 x 76 x 8, 4 x 4 at stride 2: 7.2
 //    against 8.8 us);
 //  - backward data: instead of the one-wave-per-task kernel (10 layers of 11 faster, by 1.2 to 3.4 times: 32 images of
 //    128 x 128 x 8, 8 x 8 at stride 4, 128 filters 75 -> 35 us);
 //  - weight gradient: instead of the strip kernel for patches of at most 512 elements (18 of 18, 100 of 102 x 102 x 4, 8 x 8
-//    at stride 2, 16 filters 42 -> 21 us; longer ones are up to 1.5 times slower).
+//    at stride 2, 16 filters 42 -> 21 us; longer ones are up to 1.5 times slower);
+//  - instead of the workgroup-tiled kernels of the wide layers where these have at most kFewTiles tiles, a quarter of the
+//    compute units, or for the weight gradient kFewGradTiles, whose workgroups also split the patch (128 images of 32 x 32 x 16,
+//    one field, 1024 filters: forward 246 -> 65 us, weight gradient 59 -> 26; 14 x 14 x 32, 8 x 8 at stride 2, 256 filters:
+//    forward 34 -> 18, backward data 79 -> 34; at 64 tiles 36 -> 27, at 102 the same, from 128 on the tiled kernels are up to
+//    2.5 times faster; backward data at 49 workgroups 40 -> 24, at 121 to 128 between 0.88 and 1.16 times; weight gradient at
+//    16 tiles 11.3 -> 10.6, at 32 14 against 17).
+constexpr int kFewTiles = 64, kFewGradTiles = 16;
+
+static long long tiles128(long long places, const Geom &g, int per_place) { return places * per_place * ceil_div(g.B, 128); }
+
 int launch_forward_bf16(const Geom &g, const void *x, const void *w, const float *bias, float alpha, float *y,
                         hipStream_t s) {
     const bool general = forward_general_supported(g, 2);
-    if (bf16_shape_supported(g) && bf16_tiled_forward_supported(g))
+    if (bf16_shape_supported(g) && bf16_tiled_forward_supported(g)) {
+        if (general && tiles128(g.L, g, g.F / 128) <= kFewTiles) return launch_forward_general_bf16(g, x, w, bias, alpha, y, s);
         return launch_forward_bf16_tiled(g, x, w, bias, alpha, y, s);
+    }
     if (bf16_strip_forward_supported(g)) {
-        if (general && bf16_strip_forward_workgroups(g) < 320) return launch_forward_general_bf16(g, x, w, bias, alpha, y, s);
+        if (general && bf16_strip_forward_workgroups(g) < 256) return launch_forward_general_bf16(g, x, w, bias, alpha, y, s);
         return launch_forward_bf16_strip(g, x, w, bias, alpha, y, s);
     }
     if (!bf16_shape_supported(g)) return launch_forward_bf16_storage(g, x, w, bias, alpha, y, s);
@@ -336,8 +350,12 @@ int launch_forward_bf16(const Geom &g, const void *x, const void *w, const float
 }
 
 int launch_backward_data_bf16(const Geom &g, const void *dy, const void *w, float *dx, hipStream_t s) {
-    if (bf16_shape_supported(g) && bf16_tiled_backward_data_supported(g))
+    if (bf16_shape_supported(g) && bf16_tiled_backward_data_supported(g)) {
+        const long long cells = (long long)ceil_div(g.H, g.S) * ceil_div(g.W, g.S);
+        if (tiles128(cells, g, g.S * g.S * g.C / 128) <= kFewTiles && backward_data_general_supported(g, 2))
+            return launch_backward_data_general_bf16(g, dy, w, dx, s);
         return launch_backward_data_bf16_tiled(g, dy, w, dx, s);
+    }
     if (!bf16_shape_supported(g) || backward_data_bf16_pipelined_supported(g))
         return launch_backward_data_bf16_storage(g, dy, w, dx, s);   // pipelined (bf16 MFMAs), general or masked kernel
     if (backward_data_general_supported(g, 2)) return launch_backward_data_general_bf16(g, dy, w, dx, s);
@@ -348,8 +366,11 @@ int launch_backward_data_bf16(const Geom &g, const void *dy, const void *w, floa
 
 int launch_backward_weights_bf16(const Geom &g, const void *x, const void *dy, float beta, float *dw,
                                  hipStream_t s) {
-    if (bf16_shape_supported(g) && bf16_tiled_backward_weights_supported(g))
+    if (bf16_shape_supported(g) && bf16_tiled_backward_weights_supported(g)) {
+        if ((long long)g.L * (g.F / 128) <= kFewGradTiles && backward_weights_general_supported(g, 2))
+            return launch_backward_weights_general_bf16(g, x, dy, beta, dw, s);
         return launch_backward_weights_bf16_tiled(g, x, dy, beta, dw, s);
+    }
     if (g.K <= 512 && bf16_strip_backward_weights_supported(g) && backward_weights_general_supported(g, 2))
         return launch_backward_weights_general_bf16(g, x, dy, beta, dw, s);
     if (bf16_rows_backward_weights_supported(g)) return launch_backward_weights_bf16_rows(g, x, dy, beta, dw, s);

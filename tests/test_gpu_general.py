@@ -257,6 +257,13 @@ ROUTES = [
     ("backward_weights", "f32", (1, 44, 49, 16, 20, 3, 33), "lc_bwd_weights_general"),
     ("backward_weights", "bf16", (1, 44, 49, 16, 20, 3, 31), "lc_bwd_weights_generic"),
     ("backward_weights", "bf16", (64, 20, 20, 4, 8, 2, 16), "lc_bwd_weights_general"),
+    # 128-wide tiles: few and enough of them
+    ("forward", "bf16", (96, 11, 11, 32, 4, 1, 128), "lc_forward_generic"),             # 64 tiles
+    ("forward", "bf16", (96, 11, 17, 32, 4, 1, 128), "lc_forward_bf16_tiled"),          # 112
+    ("backward_data", "bf16", (96, 16, 16, 32, 6, 2, 64), "lc_bwd_data_general"),       # 64
+    ("backward_data", "bf16", (96, 16, 18, 32, 6, 2, 64), "lc_bwd_data_bf16_tiled"),    # 72
+    ("backward_weights", "bf16", (96, 7, 7, 32, 4, 1, 128), "lc_bwd_weights_general"),      # 16
+    ("backward_weights", "bf16", (96, 7, 8, 32, 4, 1, 128), "lc_bwd_weights_bf16_tiled"),   # 20
 ]
 OPS = {"forward": 0, "backward_data": 1, "backward_weights": 2}
 
