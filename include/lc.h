@@ -19,14 +19,11 @@
  *    from lc_backward_data).
  *  - `dtype` names the storage type of the x / w / dy operands: LC_F32, or LC_BF16 (bf16
  *    operands, fp32 accumulation).  Outputs are always fp32.  Every shape is accepted in
- *    either type.  The bf16 kernels use bf16 matrix instructions wherever the layout allows
- *    whole vectors of bf16 (always for lc_backward_data with R % S == 0, R/S in
- *    {2, 3, 4, 5, 8}, F % 16 == 0 and B > 32; for lc_forward if S*C % 4 == 0, R*C % 4 == 0,
- *    W*C % 4 == 0 and F % 16 == 0; for lc_backward_weights if R*C % 4 == 0 and either
- *    B % 16 == 0 or B <= 128 with S*C % 4 == 0); other shapes widen the bf16 values on their
- *    way in (exactly) and multiply with the fp32 matrix instruction through the same masked
- *    kernels the fp32 path falls back to: the same results either way, at the speed of the
- *    fp32 path with half the operand bytes.
+ *    either type.  bf16 operands meet bf16 matrix instructions on nearly every shape; those
+ *    with patch rows of fewer than four values (forward, weight gradient) or fewer than four
+ *    filters (backward data), tensors beyond 32-bit offsets, and some of the weight gradient's
+ *    layers of fewer than 32 images widen the values on their way in (exactly) and multiply with the fp32 matrix instruction: the same
+ *    results either way.
  *  - `hip_stream` is a hipStream_t passed as void* (NULL = the default stream).  Calls
  *    only enqueue work; none synchronises.  Arguments are validated on the host before
  *    anything is launched, so every error except LC_EHIP is returned without touching

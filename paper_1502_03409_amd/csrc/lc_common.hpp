@@ -291,7 +291,7 @@ int launch_lcn_variant_fwd(const float *x, float *y, float *mu, float *rstd, int
                            float sigma, float eps, unsigned flags, hipStream_t s);
 int launch_lcn_variant_bwd(const float *x, const float *mu, const float *rstd, const float *dy, float *dx, int B, int H,
                            int W, int C, int ks, float sigma, unsigned flags, void *ws, size_t ws_bytes, hipStream_t s);
-// wide layers (128-filter blocks): workgroup-tiled forward; LC_EUNSUPPORTED outside forward_wide_supported()
+// few fields in 128-filter blocks: workgroup-tiled forward; LC_EUNSUPPORTED outside forward_wide_supported()
 bool forward_wide_supported(const Geom &g);
 size_t forward_wide_workspace_bytes(const Geom &g);   // optional workspace: K-slices for layers with few fields
 int launch_forward_wide_f32(const Geom &g, const float *x, const float *w, const float *bias, float alpha,
@@ -321,7 +321,8 @@ int launch_backward_weights_general_f32(const Geom &g, const float *x1, const fl
                                         float beta, float gamma, float *out, float *ssq, int *kblocks_out, hipStream_t s);
 int launch_backward_weights_general_bf16(const Geom &g, const void *x, const void *dy, float beta, float *dw, hipStream_t s);
 // bf16 storage through the fp32 kernels' structure: the pipelined kernels for the aligned shapes (bf16 MFMAs in the
-// backward-data pass, operands widened on the way in elsewhere), the masked kernels for every other shape
+// backward-data pass, operands widened on the way in elsewhere), the general kernels for nearly every other shape, the
+// masked kernels for the rest
 bool backward_data_bf16_pipelined_supported(const Geom &g);
 int launch_forward_bf16_storage(const Geom &g, const void *x, const void *w, const float *bias, float alpha, float *y,
                                 hipStream_t s);

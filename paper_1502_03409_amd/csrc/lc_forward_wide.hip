@@ -1,5 +1,5 @@
-// lc_forward for wide layers (F a multiple of 128, patch rows that split into chunks of 32 or 16 values): Eq. 1's
-// encoder term with a workgroup tile of one field x 128 filters x 32*MT images.
+// lc_forward for layers of few fields and long patches (F a multiple of 128, patch rows that split into chunks of 32 or
+// 16 values): Eq. 1's encoder term with a workgroup tile of one field x 128 filters x 32*MT images.
 //
 // The four waves form a 2 x 2 grid (16*MT images x 64 filters each).  The field's patch rows reach the waves
 // through LDS in chunks of 32 contraction indices (128 contiguous bytes per image, two buffers, one barrier per

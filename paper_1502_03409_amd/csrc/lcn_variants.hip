@@ -3,8 +3,9 @@
 // the two-stage form (subtract the local mean, then divide by the local root mean square of the result).
 //
 // Pooled statistics run in the channel-reduction kernels of the default form (pool_lcn.hip).  This file holds the
-// per-channel kernels.  The tile kernel takes every window and channel count: every element has its own statistics, so a workgroup stages an 8x16 pixel tile, its halo and
-// up to 32 channels of the quantity under the window in LDS (as float4 where C % 4 == 0), and each thread forms
+// per-channel kernels: two that walk down the rows of maps large enough for them, and a tile kernel that takes every
+// window, channel count and map size.  There every element has its own statistics, so a workgroup stages an 8x16 pixel
+// tile, its halo and up to 32 channels of the quantity under the window in LDS (as float4 where C % 4 == 0), and each thread forms
 // the Gaussian window sums for one pixel and four channels at a time.  Bandwidth-bound: the forward passes read
 // the tile once (the centre value is taken from LDS), the halo ring comes from L2.
 #include <mutex>
