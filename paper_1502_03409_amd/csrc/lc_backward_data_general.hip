@@ -18,6 +18,7 @@
 namespace lc {
 
 constexpr int kBackDataWaves = 8;   // per workgroup at most
+constexpr int kMostBlocks = 65535;  // blocks of a pixel block's values: the grid's second dimension
 
 // floor(a / d) for 0 <= a < 2^20 from inv = 1 / d
 __device__ __forceinline__ int small_div(int a, float inv) { return (int)(((float)a + 0.5f) * inv); }
@@ -318,6 +319,7 @@ DataTile pick_tile(const Geom &g, int es) {
                 if (mt > 1 && 16 * (mt - 1) >= g.B) break;
                 for (int nt = 1; nt <= 4; ++nt) {
                     if (nt > 1 && 16 * (nt - 1) >= N) break;
+                    if ((N + 16 * nt - 1) / (16 * nt) > kMostBlocks) continue;
                     const double tiles = (double)ceil_div(g.B, 16 * mt) * (double)((N + 16 * nt - 1) / (16 * nt));
                     const double mm = per_mfma * mt * nt, group = mm + 11 + 96.0 * mt + 16.0 * nt;
                     for (int ks = 1, lg = 0; ks <= kBackDataWaves && (ks == 1 || 2 * ks <= groups); ks *= 2, ++lg) {
@@ -357,7 +359,8 @@ int launch_general(const Geom &g, const T *dy, const T *w, float *dx, hipStream_
 
 bool backward_data_general_supported(const Geom &g, int es) {
     const long long NVF = ceil_div(g.F, 4), nf = 17 + (g.R - 1) / g.S;   // at most 16 strides per block
-    return g.F >= 4 && nf * nf * NVF < (1LL << 20) && (long long)64 * g.L * g.F * es < (1LL << 32) &&
+    // the widest tile's blocks of a cell's values fit the grid: strides of hundreds of pixels leave to the masked kernel
+    return g.F >= 4 && (long long)g.S * g.S * g.C <= 64LL * kMostBlocks && nf * nf * NVF < (1LL << 20) && (long long)64 * g.L * g.F * es < (1LL << 32) &&
            (nf * g.LW + nf) * g.K * g.F * es < (1LL << 32);
 }
 

@@ -214,3 +214,17 @@ def test_derived_sizes_follow_the_geometry():
         with pytest.raises(lc.LcError) as e:
             lc.geom_derive(G)
         assert e.value.code == B.LC_EINVAL
+
+
+def test_strides_of_hundreds_of_pixels_plan_backward_data():
+    """A cell of S x S x C values beyond what the general kernel's grid holds in blocks of its tile: such layers plan on a
+    wider tile or on the masked kernel (S*S*C just below, at and beyond each tile's limit of 16*NT*65535 values)."""
+    for geo in ((21, 72, 102, 7, 42, 784, 1263), (1902, 16, 39, 13, 16, 669, 884), (2, 9, 9, 1, 3, 1023, 8), (2, 9, 9, 1, 3, 1024, 8),
+                (2, 9, 9, 1, 3, 1025, 8), (2, 9, 9, 2, 3, 1023, 5), (1, 9, 9, 4, 3, 1023, 9), (1, 9, 9, 4, 3, 1024, 9), (2, 9, 9, 1, 3, 2047, 8), (2, 9, 9, 1, 3, 2049, 8)):
+        G = lc.geom(*geo)
+        for dtype in (B.LC_F32, B.LC_BF16):
+            p = lc.plan_query(G, B.LC_OP_BACKWARD_DATA, dtype)[0]
+            cell = geo[5] ** 2 * geo[3]
+            assert p["kernel"] == ("lc_bwd_data_general" if cell <= 64 * 65535 else "lc_bwd_data_generic"), (geo, p)
+            assert p["grid"][1] <= 65535
+        assert lc.plan_query(G, B.LC_OP_SAE_STEP)

@@ -77,9 +77,10 @@ def test_forward_infinities_stay_in_their_fields(dtype):
 
 
 # backward data: besides SHAPES, filters in vectors of eight with and without a shared last vector, one and few strides per
-# block of values, and an image border that cuts a block
+# block of values, an image border that cuts a block, and strides far beyond the image (on either side of the grid's limit)
 DATA_SHAPES = SHAPES + [(20, 14, 15, 1, 4, 1, 8), (4, 13, 18, 2, 6, 2, 9), (33, 16, 13, 3, 8, 2, 24), (18, 25, 23, 3, 8, 4, 16),
-                        (6, 12, 10, 1, 10, 1, 4), (50, 14, 22, 64, 4, 2, 20), (2, 26, 26, 1, 7, 3, 303)]
+                        (6, 12, 10, 1, 10, 1, 4), (50, 14, 22, 64, 4, 2, 20), (2, 26, 26, 1, 7, 3, 303),
+                        (3, 9, 11, 4, 3, 1023, 9), (3, 9, 11, 1, 3, 2049, 9)]
 
 
 @pytest.mark.parametrize("shape", DATA_SHAPES, ids=str)
