@@ -17,6 +17,7 @@ namespace lc {
 
 // waves of a workgroup at most: what lets a tile's accumulators and operands in flight stay in registers
 constexpr int kForwardWaves(int mt, int nt) { return mt * nt <= 4 ? 16 : 8; }
+constexpr int kMostBlocks = 65535;   // blocks of filters: the grid's second dimension
 
 template <int MT, int NT, typename T, bool RAG>
 __global__ __launch_bounds__(64 * kForwardWaves(MT, NT)) void lc_forward_general_kernel(
@@ -222,6 +223,7 @@ ForwardTile pick_tile(const Geom &g, int es) {
             // 52 x 160 x 16, 8 x 8 at stride 4, 48 filters: 102 -> 68 us with two, 96 of 48 x 60 x 16: 42 -> 20; no
             // slower on any of 13 layers.  fp32: between 0.74 and 1.36 times the time)
             if (es == 2 && nt == 1 && g.F > 16) continue;
+            if (ceil_div(g.F, 16 * nt) > kMostBlocks) continue;
             const double tasks = (double)g.L * ceil_div(g.B, 16 * mt) * ceil_div(g.F, 16 * nt);
             const double mm = (es == 4 ? 128.0 : 32.0) * mt * nt, flight = mt * nt <= 4 ? 4 : 2;
             for (int ks = 1, lg = 0; ks <= kForwardWaves(mt, nt) && (ks == 1 || 2 * ks <= groups); ks *= 2, ++lg) {
@@ -259,7 +261,8 @@ int launch_general(const Geom &g, const T *x, const T *w, const float *bias, flo
 }  // namespace
 
 bool forward_general_supported(const Geom &g, int es) {
-    return g.RC >= 4 && (long long)64 * g.H * g.W * g.C * es < (1LL << 32) && (long long)g.K * g.F * es < (1LL << 32);
+    // the widest tile's blocks of filters fit the grid: millions of filters leave to the masked kernel
+    return g.RC >= 4 && g.F <= 64 * kMostBlocks && (long long)64 * g.H * g.W * g.C * es < (1LL << 32) && (long long)g.K * g.F * es < (1LL << 32);
 }
 
 int launch_forward_general_f32(const Geom &g, const float *x, const float *w, const float *bias, float alpha,

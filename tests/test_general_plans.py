@@ -228,3 +228,13 @@ def test_strides_of_hundreds_of_pixels_plan_backward_data():
             assert p["kernel"] == ("lc_bwd_data_general" if cell <= 64 * 65535 else "lc_bwd_data_generic"), (geo, p)
             assert p["grid"][1] <= 65535
         assert lc.plan_query(G, B.LC_OP_SAE_STEP)
+
+
+def test_millions_of_filters_plan_forward():
+    """Filter blocks beyond the second grid dimension of the general kernel: a wider tile, or the masked kernel."""
+    for geo in ((5, 2, 2, 2, 2, 5, 16173454), (54, 1, 1, 33, 1, 13, 11130312), (2, 9, 9, 1, 9, 2, 9843871), (1, 2, 2, 4, 2, 1, 16 * 65535),
+                (1, 2, 2, 4, 2, 1, 16 * 65535 + 1), (1, 2, 2, 4, 2, 1, 64 * 65535), (1, 2, 2, 4, 2, 1, 64 * 65535 + 1)):
+        G = lc.geom(*geo)
+        for dtype in (B.LC_F32, B.LC_BF16):
+            p = lc.plan_query(G, B.LC_OP_FORWARD, dtype)[0]
+            assert p["grid"][1] <= 65535 and (p["arg"][4] > 0) == (geo[6] <= 64 * 65535), (geo, p)
