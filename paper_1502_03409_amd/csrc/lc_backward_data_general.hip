@@ -279,7 +279,6 @@ template <int MT, int NT, int VW, typename T>
 int launch_tile(const Geom &g, const T *dy, const T *w, float *dx, const DataTile &t, hipStream_t s) {
     const int PR = g.S * t.qr, PC = g.S * t.qc, cbc = ceil_div(g.W, PC), NVF = ceil_div(g.F, VW), nbt = ceil_div(g.B, 16 * MT);
     const long long ntask = (long long)ceil_div(g.H, PR) * cbc * nbt;
-    if (ntask > (1LL << 30)) return LC_EUNSUPPORTED;
     const bool mask = !(t.qr == 1 && t.qc == 1 && g.R % g.S == 0 && g.F % VW == 0);
     const size_t lds = (size_t)t.tasks * (t.ks / 2) * MT * NT * 1024;
     dim3 grid((unsigned)((ntask + t.tasks - 1) / t.tasks), ceil_div(PR * PC * g.C, NT * 16));
@@ -317,6 +316,7 @@ DataTile pick_tile(const Geom &g, int es) {
             const int groups = ceil_div(mr * mc * NVF, 4);
             for (int mt = 1; mt <= 4; ++mt) {
                 if (mt > 1 && 16 * (mt - 1) >= g.B) break;
+                if (blocks * ceil_div(g.B, 16 * mt) > kMostTasks) continue;
                 for (int nt = 1; nt <= 4; ++nt) {
                     if (nt > 1 && 16 * (nt - 1) >= N) break;
                     if ((N + 16 * nt - 1) / (16 * nt) > kMostBlocks) continue;
@@ -359,9 +359,11 @@ int launch_general(const Geom &g, const T *dy, const T *w, float *dx, hipStream_
 
 bool backward_data_general_supported(const Geom &g, int es) {
     const long long NVF = ceil_div(g.F, 4), nf = 17 + (g.R - 1) / g.S;   // at most 16 strides per block
-    // the widest tile's blocks of a cell's values fit the grid: strides of hundreds of pixels leave to the masked kernel
-    return g.F >= 4 && (long long)g.S * g.S * g.C <= 64LL * kMostBlocks && nf * nf * NVF < (1LL << 20) && (long long)64 * g.L * g.F * es < (1LL << 32) &&
-           (nf * g.LW + nf) * g.K * g.F * es < (1LL << 32);
+    // the widest tile's blocks of a cell's values fit the grid, and its tasks their numbers: strides of hundreds of pixels
+    // and billions of cells leave to the masked kernel
+    return g.F >= 4 && (long long)ceil_div(g.H, g.S) * ceil_div(g.W, g.S) * ceil_div(g.B, 64) <= kMostTasks &&
+           (long long)g.S * g.S * g.C <= 64LL * kMostBlocks && nf * nf * NVF < (1LL << 20) &&
+           (long long)64 * g.L * g.F * es < (1LL << 32) && (nf * g.LW + nf) * g.K * g.F * es < (1LL << 32);
 }
 
 int launch_backward_data_general_f32(const Geom &g, const float *dy, const float *w, float *dx, hipStream_t s) {

@@ -222,7 +222,6 @@ int launch_tile(const Geom &g, const T *x1, const T *dy1, const T *x2, const T *
     constexpr int G = SSQ ? 2 : 1;
     const int NV = ceil_div(g.RC, 4), nvt = g.R * NV, kblocks = ceil_div(nvt, 16 * G), nfb = ceil_div(g.F, 16 * NT);
     const long long ntask = (long long)g.L * kblocks * nfb;
-    if (ntask > (1LL << 30)) return LC_EUNSUPPORTED;
     const LaunchPlan plan = make_plan("lc_bwd_weights_general", {G, NT, (int)sizeof(T)}, {NV, nvt, kblocks, nfb, (int)ntask},
                                       dim3((unsigned)((ntask + 3) / 4)), 256, 0);
     if (int rc = check_backward_weights_general(g, plan)) return rc;
@@ -267,8 +266,9 @@ int launch_general(const Geom &g, const T *x1, const T *dy1, const T *x2, const 
 }  // namespace
 
 bool backward_weights_general_supported(const Geom &g, int es) {
-    const long long images = es == 4 ? 4 : 16;
-    return g.RC >= 4 && (long long)g.R * ceil_div(g.RC, 4) < (1 << 20) && images * g.H * g.W * g.C * es < (1LL << 32) &&
+    const long long images = es == 4 ? 4 : 16, nvt = (long long)g.R * ceil_div(g.RC, 4);
+    // (in blocks of 16 filters, the most tasks there can be: gradients of terabytes leave to the masked kernel)
+    return g.RC >= 4 && nvt < (1 << 20) && (long long)g.L * ((nvt + 15) / 16) <= kMostTasks / ceil_div(g.F, 16) && images * g.H * g.W * g.C * es < (1LL << 32) &&
            images * g.L * g.F * es < (1LL << 32);
 }
 

@@ -189,7 +189,6 @@ int launch_tile(const Geom &g, const T *x, const T *w, const float *bias, float 
     const int NV = ceil_div(g.RC, 4), nvt = g.R * NV, per = ceil_div(ceil_div(nvt, 4), t.ks) * 4;
     const int nbt = ceil_div(g.B, 16 * MT), rag = g.RC % 4 != 0;
     const long long ntask = (long long)g.L * nbt;
-    if (ntask > (1LL << 30)) return LC_EUNSUPPORTED;
     const size_t lds = (size_t)t.nfw * t.tasks * (t.ks / 2) * MT * NT * 1024;
     dim3 grid((unsigned)((ntask + t.tasks - 1) / t.tasks), ceil_div(g.F, t.nfw * NT * 16));
     const LaunchPlan plan = make_plan("lc_forward_generic", {MT, NT, 4 / t.nfw, (int)sizeof(T), rag, t.ks, t.tasks},
@@ -217,6 +216,7 @@ ForwardTile pick_tile(const Geom &g, int es) {
     double best_t = 1e300;
     for (int mt = 1; mt <= 4; ++mt) {
         if (mt > 1 && 16 * (mt - 1) >= g.B) break;
+        if ((long long)g.L * ceil_div(g.B, 16 * mt) > kMostTasks) continue;
         for (int nt = 1; nt <= 4; ++nt) {
             if (nt > g.F || (nt > 1 && 16 * (nt - 1) >= g.F) || (es == 2 && nt == 3)) continue;
             // bf16: a single tile of filters is 32 bytes of each weight row, a quarter of a cache line (128 images of
@@ -261,8 +261,9 @@ int launch_general(const Geom &g, const T *x, const T *w, const float *bias, flo
 }  // namespace
 
 bool forward_general_supported(const Geom &g, int es) {
-    // the widest tile's blocks of filters fit the grid: millions of filters leave to the masked kernel
-    return g.RC >= 4 && g.F <= 64 * kMostBlocks && (long long)64 * g.H * g.W * g.C * es < (1LL << 32) && (long long)g.K * g.F * es < (1LL << 32);
+    // the widest tile's blocks of filters fit the grid, and its tasks their numbers: millions of filters and billions of
+    // fields leave to the masked kernel
+    return g.RC >= 4 && g.F <= 64 * kMostBlocks && (long long)g.L * ceil_div(g.B, 64) <= kMostTasks && (long long)64 * g.H * g.W * g.C * es < (1LL << 32) && (long long)g.K * g.F * es < (1LL << 32);
 }
 
 int launch_forward_general_f32(const Geom &g, const float *x, const float *w, const float *bias, float alpha,

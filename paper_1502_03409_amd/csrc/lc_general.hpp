@@ -9,6 +9,8 @@
 
 namespace lc {
 
+constexpr long long kMostTasks = 1LL << 30;   // tasks are numbered in 32 bits, with room for the last workgroup's
+
 typedef const __attribute__((address_space(1))) char *gbytes;
 
 // four consecutive elements at any element-aligned address (unaligned vector loads are one instruction on this chip)

@@ -238,3 +238,13 @@ def test_millions_of_filters_plan_forward():
         for dtype in (B.LC_F32, B.LC_BF16):
             p = lc.plan_query(G, B.LC_OP_FORWARD, dtype)[0]
             assert p["grid"][1] <= 65535 and (p["arg"][4] > 0) == (geo[6] <= 64 * 65535), (geo, p)
+
+
+def test_layers_beyond_the_task_limit_plan_on_other_kernels():
+    """More tasks than the general kernels number (2^30): not refused, but planned on the kernels that took them."""
+    for op, geo in ((B.LC_OP_BACKWARD_WEIGHTS, (1, 200, 242, 64, 47, 1, 310)), (B.LC_OP_BACKWARD_WEIGHTS, (31, 2048, 49, 44, 35, 1, 3705)),
+                    (B.LC_OP_FORWARD, (3735, 2515, 8804, 1, 5, 1, 11)), (B.LC_OP_FORWARD, (3826, 818, 32230, 1, 5, 1, 10)),
+                    (B.LC_OP_BACKWARD_DATA, (4000, 5000, 7000, 1, 4, 1, 5))):
+        for dtype in (B.LC_F32, B.LC_BF16):
+            p = lc.plan_query(lc.geom(*geo), op, dtype)[0]
+            assert all(0 < g <= 0x7fffffff for g in p["grid"]), (op, geo, p)
