@@ -148,8 +148,9 @@ def l2pool_lcn_plan_query(shape, pool_ksize: int, pool_stride: int, lcn_ksize: i
             "grid": tuple(out[0].grid), "block": int(out[0].block), "lds_bytes": int(out[0].lds_bytes)}
 
 
-# The current stream's handle without building a Stream object (which costs as much as the launch itself).
-_raw_stream = torch._C._cuda_getCurrentRawStream
+# The current stream's handle without building a Stream object (which costs as much as the launch itself).  A torch without
+# GPU support has none; there the device lookup below raises first.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _device = torch.cuda.current_device
 
 

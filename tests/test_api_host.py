@@ -3,6 +3,8 @@ derives geometry, and rejects bad arguments before anything is launched."""
 import ctypes as C
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -133,3 +135,13 @@ def test_static_scratch_entry_point_checks_on_the_host():
     assert L.lcn_variant_workspace_bytes(40, 64, 64, 64, 5) > B.LCN_STATIC_SCRATCH_BYTES
     assert L.lcn_variant_bwd_static(FAKE, FAKE, FAKE, FAKE, FAKE + 16, 40, 64, 64, 64, 5, 1.0, 5, None) == B.LC_EWORKSPACE
     assert b"static" in L.lc_last_error()
+
+
+def test_package_imports_on_a_torch_without_gpu_support():
+    """A build of torch without GPU support has no raw stream handle; the host side (geometry, plans) works there too."""
+    code = ("import torch\n"
+            "if hasattr(torch._C, '_cuda_getCurrentRawStream'): del torch._C._cuda_getCurrentRawStream\n"
+            "import paper_1502_03409_amd as lc\n"
+            "assert lc.geom_derive(lc.geom(2, 20, 20, 3, 5, 3, 8)) == (6, 6, 75)\n"
+            "assert lc.plan_query(lc.geom(2, 20, 20, 3, 5, 3, 8), lc.LC_OP_FORWARD)\n")
+    subprocess.run([sys.executable, "-c", code], cwd=ROOT, check=True, timeout=300)
