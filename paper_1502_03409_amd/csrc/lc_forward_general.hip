@@ -160,14 +160,15 @@ namespace {
 
 struct ForwardTile { int mt, nt, nfw, tasks, ks; };
 
-// Host check of a lc_forward_general_kernel launch.  tparam = {MT, NT, 4 / filter blocks per workgroup, bytes per
-// operand element, RAG, slices of the contraction, tasks per workgroup}; arg = {vectors per patch row, vectors per patch,
-// vectors per slice, batch tiles, filter blocks per workgroup, tasks}.
+// Host check of a lc_forward_general_kernel launch.  tparam = {MT, NT, filter blocks per workgroup, bytes per operand
+// element, RAG, slices of the contraction, tasks per workgroup}; arg = {vectors per patch row, vectors per patch, vectors
+// per slice, batch tiles, tasks}.
 int check_forward_general(const Geom &g, const LaunchPlan &p) {
-    const int MT = p.tparam[0], NT = p.tparam[1], ES = p.tparam[3], RAG = p.tparam[4], ks = p.tparam[5], tasks = p.tparam[6];
-    const int NV = p.arg[0], nvt = p.arg[1], per = p.arg[2], nbt = p.arg[3], nfw = p.arg[4], ntask = p.arg[5];
+    const int MT = p.tparam[0], NT = p.tparam[1], nfw = p.tparam[2], ES = p.tparam[3], RAG = p.tparam[4];
+    const int ks = p.tparam[5], tasks = p.tparam[6];
+    const int NV = p.arg[0], nvt = p.arg[1], per = p.arg[2], nbt = p.arg[3], ntask = p.arg[4];
     LC_PLAN_REQUIRE(p, MT >= 1 && MT <= 4 && NT >= 1 && NT <= 4 && (ES == 4 || (ES == 2 && NT != 3)));
-    LC_PLAN_REQUIRE(p, (nfw == 1 || nfw == 2 || nfw == 4) && p.tparam[2] * nfw == 4);
+    LC_PLAN_REQUIRE(p, nfw == 1 || nfw == 2);
     LC_PLAN_REQUIRE(p, (int)p.block <= 64 * kForwardWaves(MT, NT));
     LC_PLAN_REQUIRE(p, ks >= 1 && ks <= 16 && (ks & (ks - 1)) == 0 && tasks >= 1 && (int)p.block == 64 * ks * nfw * tasks);
     // whole vectors inside a patch row and whole runs inside the filters; every vector in one slice, slices in groups
@@ -191,8 +192,8 @@ int launch_tile(const Geom &g, const T *x, const T *w, const float *bias, float 
     const long long ntask = (long long)g.L * nbt;
     const size_t lds = (size_t)t.nfw * t.tasks * (t.ks / 2) * MT * NT * 1024;
     dim3 grid((unsigned)((ntask + t.tasks - 1) / t.tasks), ceil_div(g.F, t.nfw * NT * 16));
-    const LaunchPlan plan = make_plan("lc_forward_generic", {MT, NT, 4 / t.nfw, (int)sizeof(T), rag, t.ks, t.tasks},
-                                      {NV, nvt, per, nbt, t.nfw, (int)ntask}, grid, 64 * t.ks * t.nfw * t.tasks, lds);
+    const LaunchPlan plan = make_plan("lc_forward_general", {MT, NT, t.nfw, (int)sizeof(T), rag, t.ks, t.tasks},
+                                      {NV, nvt, per, nbt, (int)ntask}, grid, 64 * t.ks * t.nfw * t.tasks, lds);
     if (int rc = check_forward_general(g, plan)) return rc;
     if (rag)
         LC_LAUNCH(plan, "lc_forward launch", (lc_forward_general_kernel<MT, NT, T, true>), s, g, x, w, bias, alpha, alpha_dev,

@@ -319,14 +319,14 @@ def test_headline_workload_takes_the_tiered_forward_plan():
 
 def test_filter_counts_off_the_tile_size_never_take_a_tiled_plan():
     """Layers with at least 512 workgroups of work and F not a multiple of 16 (Sec. 3.1 allows any F): the
-    pipelined kernels' grids count F in whole tiles, so these must go to the masked kernel."""
+    pipelined kernels' grids count F in whole tiles, so these must go to the general kernel, whose runs of filters end at F."""
     for F in (20, 24, 40, 17, 63):
         for base in (wl.LCGeom(B=128, H=128, W=128, C=3, R=16, S=2, F=F), wl.LCGeom(B=100, H=102, W=102, C=4, R=8, S=2, F=F)):
             plans = lc.plan_query(lc.geom(*base.as_tuple()), B.LC_OP_FORWARD)
-            assert [p["kernel"] for p in plans] == ["lc_forward_generic"], (base, plans)
+            assert [p["kernel"] for p in plans] == ["lc_forward_general"], (base, plans)
             p = plans[0]
-            NLOC, NT = p["tparam"][2], p["tparam"][1]
-            assert p["grid"][1] * (4 // NLOC) * NT * 16 >= F
+            NT, nfw = p["tparam"][1:3]
+            assert p["grid"][1] * nfw * NT * 16 >= F
 
 
 def test_eight_wave_forward_variants_are_reachable():
@@ -363,8 +363,9 @@ def test_seeded_geometries_plan_within_their_invariants(chunk):
                 check_plans(g, op, dtype, plans, replay)
                 families.update(p["kernel"] for p in plans)
     # the sampler reaches every family of the fp32 path and the bf16 ones
-    assert {"lc_forward_fast", "lc_forward_generic", "lc_forward_wide", "lc_bwd_data_fast", "lc_bwd_data_generic",
-            "lc_bwd_data_wide", "lc_bwd_weights_fast", "lc_bwd_weights_generic"} <= families, families
+    assert {"lc_forward_fast", "lc_forward_general", "lc_forward_generic", "lc_forward_wide", "lc_bwd_data_fast",
+            "lc_bwd_data_general", "lc_bwd_data_generic", "lc_bwd_data_wide", "lc_bwd_weights_fast", "lc_bwd_weights_general",
+            "lc_bwd_weights_generic"} <= families, families
 
 
 def test_bf16_is_never_refused_on_shape_alone():

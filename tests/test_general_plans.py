@@ -59,12 +59,13 @@ def test_general_forward_covers_every_product_once(seed):
         for dtype in (B.LC_F32, B.LC_BF16):
             plans = lc.plan_query(G, B.LC_OP_FORWARD, dtype)
             p = plans[0]
-            if p["kernel"] != "lc_forward_generic" or p["arg"][0] != cdiv(RC, 4) or p["tparam"][5] < 1:
+            if p["kernel"] != "lc_forward_general":
                 assert p["kernel"] != "lc_forward_generic" or RC < 4, (geo, p)
                 continue
             n_general += 1
-            MT, NT, _, ES, rag, ks, tasks = p["tparam"][:7]
-            NV, nvt, per, nbt, nfw, ntask = p["arg"][:6]
+            MT, NT, nfw, ES, rag, ks, tasks = p["tparam"][:7]
+            NV, nvt, per, nbt, ntask = p["arg"][:5]
+            assert NV == cdiv(RC, 4)
             # patch elements: each exactly once over slices, lane groups and steps; four elements inside the patch row
             seen = np.zeros(K, dtype=int)
             for _, _, row, off, skip in forward_vectors(R, RC, NV, nvt, per, ks):
@@ -237,7 +238,8 @@ def test_millions_of_filters_plan_forward():
         G = lc.geom(*geo)
         for dtype in (B.LC_F32, B.LC_BF16):
             p = lc.plan_query(G, B.LC_OP_FORWARD, dtype)[0]
-            assert p["grid"][1] <= 65535 and (p["arg"][4] > 0) == (geo[6] <= 64 * 65535), (geo, p)
+            assert p["kernel"] == ("lc_forward_general" if geo[6] <= 64 * 65535 else "lc_forward_generic"), (geo, p)
+            assert p["grid"][1] <= 65535
 
 
 def test_layers_beyond_the_task_limit_plan_on_other_kernels():

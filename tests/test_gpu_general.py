@@ -236,14 +236,14 @@ def test_pool_gradient_streams(shape):
 
 # Aligned layers on both sides of the lines between the general kernels and the others: (op, dtype, shape, kernel).
 ROUTES = [
-    ("forward", "f32", (40, 20, 21, 16, 4, 2, 32), "lc_forward_generic"),       # little overlap
-    ("forward", "f32", (64, 56, 56, 8, 8, 2, 64), "lc_forward_generic"),        # two batch tiles
+    ("forward", "f32", (40, 20, 21, 16, 4, 2, 32), "lc_forward_general"),       # little overlap
+    ("forward", "f32", (64, 56, 56, 8, 8, 2, 64), "lc_forward_general"),        # two batch tiles
     ("forward", "f32", (32, 80, 80, 8, 8, 2, 64), "lc_forward_fast"),           # one, overlap of four
     ("forward", "f32", (96, 18, 18, 16, 16, 1, 128), "lc_forward_wide"),        # 9 fields, long patches
-    ("forward", "f32", (96, 19, 19, 16, 16, 1, 128), "lc_forward_generic"),     # 16 fields
-    ("forward", "f32", (96, 10, 10, 16, 8, 1, 128), "lc_forward_generic"),      # 9 fields, short patches
-    ("forward", "bf16", (64, 12, 12, 8, 4, 2, 32), "lc_forward_generic"),       # K at the line
-    ("forward", "bf16", (64, 19, 20, 16, 15, 1, 64), "lc_forward_generic"),     # few workgroups in strips
+    ("forward", "f32", (96, 19, 19, 16, 16, 1, 128), "lc_forward_general"),     # 16 fields
+    ("forward", "f32", (96, 10, 10, 16, 8, 1, 128), "lc_forward_general"),      # 9 fields, short patches
+    ("forward", "bf16", (64, 12, 12, 8, 4, 2, 32), "lc_forward_general"),       # K at the line
+    ("forward", "bf16", (64, 19, 20, 16, 15, 1, 64), "lc_forward_general"),     # few workgroups in strips
     ("backward_data", "f32", (16, 72, 72, 32, 4, 4, 16), "lc_bwd_data_generic"),    # large cells, enough of them
     ("backward_data", "f32", (16, 40, 40, 32, 4, 4, 16), "lc_bwd_data_general"),    # too few
     ("backward_data", "f32", (15, 72, 72, 32, 4, 4, 16), "lc_bwd_data_general"),    # a batch below
@@ -259,7 +259,7 @@ ROUTES = [
     ("backward_weights", "bf16", (1, 44, 49, 16, 20, 3, 31), "lc_bwd_weights_generic"),
     ("backward_weights", "bf16", (64, 20, 20, 4, 8, 2, 16), "lc_bwd_weights_general"),
     # 128-wide tiles: few and enough of them
-    ("forward", "bf16", (96, 11, 11, 32, 4, 1, 128), "lc_forward_generic"),             # 64 tiles
+    ("forward", "bf16", (96, 11, 11, 32, 4, 1, 128), "lc_forward_general"),             # 64 tiles
     ("forward", "bf16", (96, 11, 17, 32, 4, 1, 128), "lc_forward_bf16_tiled"),          # 112
     ("backward_data", "bf16", (96, 16, 16, 32, 6, 2, 64), "lc_bwd_data_general"),       # 64
     ("backward_data", "bf16", (96, 16, 18, 32, 6, 2, 64), "lc_bwd_data_bf16_tiled"),    # 72
