@@ -121,6 +121,63 @@ def test_backward_data_infinities_stay_in_their_fields(shape, dtype):
     assert rel_fro(out[m], ref[m]) <= bar(g.F * (-(-g.R // g.S)) ** 2)
 
 
+# what a tile with a NaN is formed again from: tiles of several batch and value blocks, sliced contractions, both vector widths
+NAN_SHAPES = [(40, 18, 19, 3, 5, 3, 21), (70, 20, 17, 4, 7, 4, 40), (9, 31, 29, 3, 11, 4, 50), (33, 12, 13, 1, 4, 1, 9), (5, 23, 25, 2, 7, 3, 130)]
+
+
+@pytest.mark.parametrize("shape", NAN_SHAPES, ids=str)
+@pytest.mark.parametrize("dtype", [lc.LC_F32, lc.LC_BF16], ids=["f32", "bf16"])
+def test_backward_data_of_images_without_a_finite_value(shape, dtype):
+    """Positive weights: an image whose dy is infinite everywhere comes out infinite wherever a field reaches, one with
+    infinities of both signs NaN where they meet; images around them stay what they are."""
+    print(f"case general backward data infinite images {shape} {dtype}", flush=True)
+    g = wl.LCGeom(*shape)
+    _, w, dy = wl.lc_inputs(g, "gaussian", seed=11)
+    w = np.abs(w) + np.float32(2.0 ** -6)
+    dy[1] = np.inf
+    dy[2, g.LH // 2] = -np.inf
+    dy[3, :, ::2] = np.inf
+    dy[3, 0, :, g.F // 2] = -np.inf
+    dy[4, g.LH - 1, g.LW - 1, g.F - 1] = np.nan
+    (yd, yv), (wd, wv) = operand(dy, dtype), operand(w, dtype)
+    dx = nan(g.B, g.H, g.W, g.C)
+    lc.lc_backward_data(lc.geom(*shape), yd, wd, dx, dtype)
+    ref = oracle.lc_backward_data(shape, yv, wv)
+    out = dx.cpu().numpy()
+    assert np.isinf(ref).any() and np.isnan(ref).any()
+    assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.array_equal(out[np.isinf(ref)], ref[np.isinf(ref)])
+    m = np.isfinite(ref)
+    assert rel_fro(out[m], ref[m]) <= bar(g.F * (-(-g.R // g.S)) ** 2)
+
+
+@pytest.mark.parametrize("dtype", [lc.LC_F32, lc.LC_BF16], ids=["f32", "bf16"])
+def test_backward_data_takes_its_time_whatever_the_data(dtype):
+    """Tiles are formed again at most once, by matrix instructions: infinite gradients cost a small multiple of finite ones."""
+    shape = (32, 60, 60, 3, 11, 4, 96)
+    print(f"case general backward data time {shape} {dtype}", flush=True)
+    g, G = wl.LCGeom(*shape), lc.geom(*shape)
+    _, w, dy = wl.lc_inputs(g, "gaussian", seed=12)
+    wd, _ = operand(np.abs(w), dtype)
+    dx = nan(g.B, g.H, g.W, g.C)
+
+    def time(values):
+        yd, _ = operand(values, dtype)
+        best = float("inf")
+        for _ in range(4):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            lc.lc_backward_data(G, yd, wd, dx, dtype)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    finite, infinite = time(dy), time(np.full_like(dy, np.inf))
+    print(f"finite {1e3 * finite:.1f} us, infinite {1e3 * infinite:.1f} us", flush=True)
+    # one of a task's eight waves forms its six tiles again (5 times the finite pass measured; value by value it was 110)
+    assert torch.isinf(dx).any() and infinite <= 16 * finite
+
+
 # weight gradient: besides SHAPES, batches around a step of four and of sixteen images, one slice and several
 WEIGHT_SHAPES = SHAPES + [(4, 11, 12, 5, 3, 1, 30), (15, 12, 10, 3, 5, 1, 18), (31, 10, 11, 7, 2, 1, 6), (64, 9, 9, 3, 9, 1, 35),
                           (200, 8, 9, 3, 7, 1, 21), (3, 12, 14, 1, 4, 2, 2)]
