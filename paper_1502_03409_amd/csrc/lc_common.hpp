@@ -293,6 +293,7 @@ int launch_lcn_variant_bwd(const float *x, const float *mu, const float *rstd, c
                            int W, int C, int ks, float sigma, unsigned flags, void *ws, size_t ws_bytes, hipStream_t s);
 // few fields in 128-filter blocks: workgroup-tiled forward; LC_EUNSUPPORTED outside forward_wide_supported()
 bool forward_wide_supported(const Geom &g);
+bool forward_takes_wide(const Geom &g);               // whether lc_forward in fp32 runs it (launch_forward_f32)
 size_t forward_wide_workspace_bytes(const Geom &g);   // optional workspace: K-slices for layers with few fields
 int launch_forward_wide_f32(const Geom &g, const float *x, const float *w, const float *bias, float alpha,
                             const float *alpha_dev, float *y, void *ws, size_t ws_bytes, hipStream_t s);

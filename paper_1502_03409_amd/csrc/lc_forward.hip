@@ -1090,11 +1090,15 @@ int launch_forward_generic(const Geom &g, const T *x, const T *w, const float *b
 
 }  // namespace
 
+bool forward_takes_wide(const Geom &g) {
+    return forward_wide_supported(g) && ((g.L < kWideFields && g.K >= kWidePatch) || !takes_general(g, 4));
+}
+
 int launch_forward_f32(const Geom &g, const float *x, const float *w, const float *bias, float alpha,
                        const float *alpha_dev, float *y, hipStream_t s, void *ws, size_t ws_bytes) {
     // layers with 128-filter blocks and hardly any, large fields: one field per workgroup, patches through LDS, 128 x 128
     // output tiles, the contraction in slices
-    if (forward_wide_supported(g) && ((g.L < kWideFields && g.K >= kWidePatch) || !takes_general(g, 4)))
+    if (forward_takes_wide(g))
         return launch_forward_wide_f32(g, x, w, bias, alpha, alpha_dev, y, ws, ws_bytes, s);
     // aligned shapes take the pipelined kernel: patch rows that are whole dwordx4 runs, strips that start on a
     // 16-byte boundary (4 fields x S x C floats, or 2 when 128 filters are split over the waves)

@@ -237,9 +237,10 @@ bool forward_wide_supported(const Geom &g) {
            (long long)g.L * (g.F / 128) * ((g.B + 127) / 128) * 16 < (1ll << 31);
 }
 
-// workspace that lets lc_forward cut the contraction of a layer with few fields into slices (0: not needed)
+// workspace that lets lc_forward cut the contraction of a layer with few fields into slices (0: not needed, or the layer
+// runs another kernel)
 size_t forward_wide_workspace_bytes(const Geom &g) {
-    if (!forward_wide_supported(g)) return 0;
+    if (!forward_takes_wide(g)) return 0;
     const int ns = wide_slices(g);
     return ns > 1 ? (size_t)ns * g.B * g.L * g.F * sizeof(float) : 0;
 }

@@ -61,6 +61,26 @@ def test_workspace_query():
     assert lc.workspace_bytes(lc.geom(128, 200, 200, 3, 20, 4, 32), B.LC_OP_FORWARD) == 0
 
 
+def test_workspace_is_asked_for_only_where_it_is_used():
+    """lc_forward's workspace holds slices of the contraction: a layer reports one if and only if its plan adds slices up,
+    and the training step's workspace grows by that much."""
+    asked = 0
+    for R, S, C, side, F, Bn in [(8, 1, 32, 8, 1024, 128), (16, 1, 16, 18, 128, 96), (16, 1, 16, 19, 128, 96), (8, 1, 16, 10, 128, 96),
+                                 (24, 1, 8, 26, 256, 80), (24, 1, 8, 28, 256, 80), (62, 1, 24, 62, 4096, 192), (64, 1, 64, 66, 128, 65),
+                                 (4, 2, 64, 40, 128, 128), (8, 2, 32, 64, 128, 256), (4, 1, 640, 8, 128, 70), (13, 1, 16, 14, 128, 64)]:
+        g = lc.geom(Bn, side, side, C, R, S, F)
+        n = lc.workspace_bytes(g, B.LC_OP_FORWARD)
+        slices = [p for p in lc.plan_query(g, B.LC_OP_FORWARD) if p["kernel"] == "lc_forward_slices"]
+        assert (n > 0) == (len(slices) == 1), (Bn, side, C, R, S, F, n)
+        if slices:
+            LH, LW, _ = lc.geom_derive(g)
+            assert n == 4 * slices[0]["arg"][0] * Bn * LH * LW * F
+            asked += 1
+        step = [p for p in lc.plan_query(g, B.LC_OP_SAE_STEP) if p["kernel"] == "lc_forward_slices"]
+        assert len(step) == 2 * len(slices)
+    assert 3 <= asked <= 9
+
+
 def test_argument_validation_happens_before_any_launch():
     L = lc.lib()
     g = lc.geom(8, 32, 32, 3, 8, 4, 16)
