@@ -1,14 +1,14 @@
-// bf16-operand, fp32-accumulate variants of the three layer contractions (x, w, dy stored as bf16;
-// y, dx, dw fp32).  Same mathematics and layouts as the fp32 kernels (Eq. 1 / Sec. 3.1 geometry).
+// bf16-operand, fp32-accumulate contractions (x, w, dy stored as bf16; y, dx, dw fp32): the choice between the bf16
+// kernels, and two of one wave per task, forward and backward data.  Same mathematics and layouts as the fp32 kernels
+// (Eq. 1 / Sec. 3.1 geometry).
 //
-// All three use v_mfma_f32_16x16x16_bf16: lane (i, kk) of an operand holds four consecutive
-// contraction indices 4kk..4kk+3 of row/column i.  Where the contraction index is contiguous in memory
-// (backward data: f) a lane's four values are one 8-byte load.  Where it is the strided index (forward:
-// k of w[k][f]; backward weights: the batch) a lane loads four rows of four consecutive free indices
-// and transposes the 4x4 block in registers (v_perm_b32): it then owns column i of four different
-// tiles, free index 4i+u in tile u, and 16 lanes still cover whole 128-byte lines.
-// Waves are independent (no LDS); loads run one or two steps ahead in a register ring.  What the kernels of this file
-// keep is short patches (forward), tensors beyond the general kernel's offsets (backward data) and the weight gradient.
+// Both use v_mfma_f32_16x16x16_bf16: lane (i, kk) of an operand holds four consecutive contraction indices 4kk..4kk+3 of
+// row/column i.  Where the contraction index is contiguous in memory (backward data: f) a lane's four values are one 8-byte
+// load.  Where it is the strided index (forward: k of w[k][f]) a lane loads four rows of four consecutive free indices and
+// transposes the 4x4 block in registers (v_perm_b32): it then owns column i of four different tiles, free index 4i+u in
+// tile u, and 16 lanes still cover whole 128-byte lines.
+// Waves are independent (no LDS); loads run one or two steps ahead in a register ring.  What these two keep is short
+// patches (forward) and layers beyond the general kernels' limits.
 #include "lc_common.hpp"
 
 namespace lc {
@@ -164,84 +164,12 @@ __global__ __launch_bounds__(256) void lc_bwd_data_bf16_kernel(Geom g, const uns
     }
 }
 
-// --------------------------------------------------------------------------- backward weights
-// wave task = (location, 128 patch elements) x 64 filters; contraction over the batch, 16 images per step.
-__global__ __launch_bounds__(256) void lc_bwd_weights_bf16_kernel(Geom g, const unsigned short *__restrict__ x,
-                                                                  const unsigned short *__restrict__ dy, float beta,
-                                                                  float *__restrict__ out, int kblocks, int ntasks) {
-    constexpr int G = 2;                      // groups of 4 M-tiles: 128 patch elements per task
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m = lane & 15, kk = lane >> 4;
-    const int task = remap_xcd(blockIdx.x, gridDim.x) * 4 + wave;
-    if (task >= ntasks) return;
-    const int loc = task / kblocks, k0 = (task - loc * kblocks) * (G * 64);
-    const int i = loc / g.LW, j = loc - i * g.LW;
-    const int f0 = blockIdx.y * 64;
-    const size_t img = (size_t)g.H * g.W * g.C, dyimg = (size_t)g.L * g.F;
-
-    int off[G];
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg) {
-        const int k = k0 + gg * 64 + 4 * m;
-        const int kc = k < g.K ? k : 0;
-        const int kh = kc / g.RC, rem = kc - kh * g.RC;
-        off[gg] = ((i * g.S + kh) * g.W + j * g.S) * g.C + rem;
-    }
-    f32x4 acc[G][4][4];
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg)
-#pragma unroll
-        for (int t = 0; t < 4; ++t)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) acc[gg][t][u] = (f32x4){0.f, 0.f, 0.f, 0.f};
-
-    gh_ptr xb = (gh_ptr)x + (size_t)(4 * kk) * img;
-    gh_ptr db = (gh_ptr)dy + (size_t)(4 * kk) * dyimg + (size_t)loc * g.F + f0 + 4 * m;
-    for (int b0 = 0; b0 < g.B; b0 += 16) {              // B % 16 == 0 on this path
-        u32x2 r[4], ao[G][4], bo[4];
-#pragma unroll
-        for (int gg = 0; gg < G; ++gg) {
-#pragma unroll
-            for (int t = 0; t < 4; ++t) r[t] = *(g2_ptr)(xb + (size_t)(b0 + t) * img + off[gg]);
-            transpose4x4_bf16(r, ao[gg]);
-        }
-#pragma unroll
-        for (int t = 0; t < 4; ++t) r[t] = *(g2_ptr)(db + (size_t)(b0 + t) * dyimg);
-        transpose4x4_bf16(r, bo);
-#pragma unroll
-        for (int gg = 0; gg < G; ++gg)
-#pragma unroll
-            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                for (int u = 0; u < 4; ++u) acc[gg][t][u] = mfma16_bf16(ao[gg][t], bo[u], acc[gg][t][u]);
-    }
-    float *ol = out + (size_t)loc * g.K * g.F + f0 + 4 * m;
-#pragma unroll
-    for (int gg = 0; gg < G; ++gg)
-#pragma unroll
-        for (int rr = 0; rr < 4; ++rr)
-#pragma unroll
-            for (int t = 0; t < 4; ++t) {
-                const int k = k0 + gg * 64 + 4 * (4 * kk + rr) + t;
-                if (k >= g.K) continue;
-                f32x4 *o = (f32x4 *)(ol + (size_t)k * g.F);
-                f32x4 v;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = acc[gg][t][u][rr];
-                if (beta != 0.f) v += beta * *o;
-                *o = v;
-            }
-}
-
 // Shapes this file handles: patch rows, strides and filter counts that keep every 8-byte access aligned.
 bool bf16_shape_supported(const Geom &g) {
     return g.RC % 16 == 0 && (g.S * g.C) % 4 == 0 && (g.W * g.C) % 4 == 0 && g.F % 64 == 0 && g.B % 16 == 0 &&
            g.R % g.S == 0;
 }
 
-// Order of preference, every pass: the workgroup-tiled kernels (wide layers), the strip-sharing / pipelined / transposing
-// kernels of the narrow layers (faster than the one-wave-per-task kernels of this file wherever both apply: the small 32 x 32 x 4 layer
-// 30 / 13 / 9 us against 37 / 21 / 10 us), the kernels of this file, the fp32 kernels on bf16 storage.
 // Host checks of the one-wave-per-task kernels of this file.  tparam = {MT}; arg as listed per function.
 namespace {
 
@@ -263,16 +191,6 @@ int check_backward_data_bf16_simple(const Geom &g, const LaunchPlan &p) {
     LC_PLAN_REQUIRE(p, (long long)ntasks == (long long)ceil_div(g.H, g.S) * CW * nblocks * btiles);
     LC_PLAN_REQUIRE(p, (long long)p.grid[0] * 4 >= ntasks && (long long)(p.grid[0] - 1) * 4 < ntasks);
     LC_PLAN_REQUIRE(p, (long long)g.K * g.F < (1LL << 31));
-    return LC_OK;
-}
-
-// arg = {blocks of 128 patch elements per field, wave tasks}
-int check_backward_weights_bf16_simple(const Geom &g, const LaunchPlan &p) {
-    const int kblocks = p.arg[0], ntasks = p.arg[1];
-    LC_PLAN_REQUIRE(p, p.block == 256 && bf16_shape_supported(g));
-    LC_PLAN_REQUIRE(p, kblocks == ceil_div(g.K, 128) && (long long)ntasks == (long long)g.L * kblocks);
-    LC_PLAN_REQUIRE(p, (long long)p.grid[0] * 4 >= ntasks && (long long)(p.grid[0] - 1) * 4 < ntasks);
-    LC_PLAN_REQUIRE(p, (int)p.grid[1] == g.F / 64 && (long long)g.H * g.W * g.C < (1LL << 31));
     return LC_OK;
 }
 
@@ -306,10 +224,10 @@ int launch_backward_data_simple(const Geom &g, const void *dy, const void *w, fl
 
 }  // namespace
 
-// LC_BF16 covers every valid geometry.  Order of preference, every pass: the workgroup-tiled kernels (wide layers),
-// the strip-sharing / pipelined / transposing kernels of the narrow layers (faster than the one-wave-per-task
-// kernels of this file wherever both apply), the kernels of this file, the fp32 pipelined kernels on bf16 storage,
-// for nearly every other shape the general kernels, and for the rest the masked fp32 kernels on bf16 storage.
+// Order of preference, every pass: the workgroup-tiled kernels (wide layers), the strip-sharing / pipelined / transposing
+// kernels of the narrow layers (faster than the one-wave-per-task kernels of this file wherever both apply: a 32 x 32 x 4
+// layer forward 30 against 37 us, backward data 13 against 21), the kernels of this file, the fp32 pipelined kernels on
+// bf16 storage, for nearly every other shape the general kernels, and for the rest the masked fp32 kernels on bf16 storage.
 //
 // Where the general kernels come first (both sides measured on some 130 layers):
 //  - forward: instead of the strip kernel where that has fewer workgroups than the chip compute units (faster on all of 28
@@ -374,16 +292,7 @@ int launch_backward_weights_bf16(const Geom &g, const void *x, const void *dy, f
     if (g.K <= 512 && bf16_strip_backward_weights_supported(g) && backward_weights_general_supported(g, 2))
         return launch_backward_weights_general_bf16(g, x, dy, beta, dw, s);
     if (bf16_rows_backward_weights_supported(g)) return launch_backward_weights_bf16_rows(g, x, dy, beta, dw, s);
-    if (!bf16_shape_supported(g)) return launch_backward_weights_bf16_storage(g, x, dy, beta, dw, s);
-    const int kblocks = (g.K + 127) / 128;
-    const long long ntasks = (long long)g.L * kblocks;
-    if (ntasks > (1LL << 30)) return LC_EUNSUPPORTED;
-    const LaunchPlan plan = make_plan("lc_bwd_weights_bf16_simple", {}, {kblocks, (int)ntasks},
-                                      dim3((unsigned)((ntasks + 3) / 4), g.F / 64), 256, 0);
-    if (int rc = check_backward_weights_bf16_simple(g, plan)) return rc;
-    LC_LAUNCH(plan, "lc_backward_weights (bf16) launch", lc_bwd_weights_bf16_kernel, s, g, (const unsigned short *)x,
-              (const unsigned short *)dy, beta, dw, kblocks, (int)ntasks);
-    return LC_OK;
+    return launch_backward_weights_bf16_storage(g, x, dy, beta, dw, s);
 }
 
 }  // namespace lc

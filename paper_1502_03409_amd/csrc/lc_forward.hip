@@ -767,13 +767,18 @@ int launch_fast_tiered(const Geom &g, const T *x, const T *w, const float *bias,
     if constexpr (MT == 8) {
         if (zb == 1 && rounds >= 1 && rounds <= 6 && rem > 0 && rem <= slots / 4) {
             const int first = rounds * slots;
-            // whole patch rows of 15 k-steps that fill every staging slot: the variant with compile-time counts
+            // whole patch rows of 15 k-steps that fill every staging slot: the variant with compile-time counts (32 filters,
+            // NT = 2, with such rows run in lc_forward_direct_kernel)
+            constexpr bool kRow15 = UNR == 5 && NT == 1 && sizeof(T) == 4;
             const int sqc = (CQ + (NLOC - 1) * g.S * g.C + 3) & ~3;
-            const bool fixed = UNR == 5 && sizeof(T) == 4 && CQ == g.RC && (CQ >> 2) == 15 &&
+            const bool fixed = kRow15 && CQ == g.RC && (CQ >> 2) == 15 &&
                                (16 * MT * (sqc / 4) + 255) / 256 == kFwdStageSlots &&
                                (long long)g.B * g.H * g.W * g.C < (1LL << 31);
-            int rc = fixed ? launch_fast<MT, NT, NLOC, UNR, 4, 15>(g, x, w, bias, alpha, alpha_dev, y, CQ, 1, 0, first, s)
-                           : launch_fast<MT, NT, NLOC, UNR>(g, x, w, bias, alpha, alpha_dev, y, CQ, 1, 0, first, s);
+            int rc = LC_OK;
+            if constexpr (kRow15) {
+                if (fixed) rc = launch_fast<MT, NT, NLOC, UNR, 4, 15>(g, x, w, bias, alpha, alpha_dev, y, CQ, 1, 0, first, s);
+            }
+            if (!fixed) rc = launch_fast<MT, NT, NLOC, UNR>(g, x, w, bias, alpha, alpha_dev, y, CQ, 1, 0, first, s);
             if (rc != LC_OK) return rc;
             // the short workgroups stage four patch rows at a time (same LDS footprint as the long ones),
             // so that a chunk's MFMAs still cover the latency of fetching the next one
@@ -784,8 +789,10 @@ int launch_fast_tiered(const Geom &g, const T *x, const T *w, const float *bias,
             }
             // their k-steps are short (2 x NT MFMAs), so the weight ring is made as deep as a whole patch row;
             // four whole rows of 15 k-steps that fill every staging slot: the variant with compile-time counts
-            if ((CQ >> 2) == 15 && fixed && nr == 4 && 32 * 4 * (sqc / 4) == kFwdStageSlots * 256)
-                return launch_fast<2, NT, NLOC, 15, 4, 15, 4>(g, x, w, bias, alpha, alpha_dev, y, CQ, nr, first, ntask - first, s);
+            if constexpr (kRow15) {
+                if (fixed && nr == 4 && 32 * 4 * (sqc / 4) == kFwdStageSlots * 256)
+                    return launch_fast<2, NT, NLOC, 15, 4, 15, 4>(g, x, w, bias, alpha, alpha_dev, y, CQ, nr, first, ntask - first, s);
+            }
             if ((CQ >> 2) % 15 == 0)
                 return launch_fast<2, NT, NLOC, 15>(g, x, w, bias, alpha, alpha_dev, y, CQ, nr, first, ntask - first, s);
             if ((CQ >> 2) % 16 == 0)
@@ -900,8 +907,10 @@ template <int MT, typename T>
 int launch_fast_mt(const Geom &g, const T *x, const T *w, const float *bias, float alpha,
                    const float *alpha_dev, float *y, hipStream_t s, bool *done, int nt_cap) {
     *done = false;
-    if (g.F % 128 == 0 && nt_cap >= 4) return launch_fast_unr<MT, 4, 2>(g, x, w, bias, alpha, alpha_dev, y, s, done);
-    if (g.F % 64 == 0 && nt_cap >= 4) return launch_fast_unr<MT, 4, 4>(g, x, w, bias, alpha, alpha_dev, y, s, done);
+    if constexpr (MT < 8) {   // 128-image tiles only meet filters in blocks of 16 and 32
+        if (g.F % 128 == 0 && nt_cap >= 4) return launch_fast_unr<MT, 4, 2>(g, x, w, bias, alpha, alpha_dev, y, s, done);
+        if (g.F % 64 == 0 && nt_cap >= 4) return launch_fast_unr<MT, 4, 4>(g, x, w, bias, alpha, alpha_dev, y, s, done);
+    }
     if (g.F % 32 == 0 && nt_cap >= 2) return launch_fast_unr<MT, 2, 4>(g, x, w, bias, alpha, alpha_dev, y, s, done);
     if (g.F % 16 == 0) return launch_fast_unr<MT, 1, 4>(g, x, w, bias, alpha, alpha_dev, y, s, done);
     return LC_OK;

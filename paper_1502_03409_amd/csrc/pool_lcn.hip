@@ -422,7 +422,7 @@ __device__ __forceinline__ float tap_norm(const GaussTaps &t, int p, int n, int 
 //   MODE 2  x -> mu;                          MODE 3  x, mu -> rstd, y = (x - mu) rstd;
 //   MODE 4  x, mu, rstd, dy -> dv (into out) and field[p] = sum_c dv[p,c] / normaliser(p);
 //   MODE 5  out = dv - window sum of field (in place).
-// divx (MODE 1): leave dx / x.  Latency-bound on small maps: th x tw tiles (lcn_tile) and lpp lanes a pixel
+// divx (MODE 1, VEC 4): leave dx / x.  Latency-bound on small maps: th x tw tiles (lcn_tile) and lpp lanes a pixel
 // (lanes_per_pixel) put two workgroups on every compute unit and several loads in flight per lane; with 16 x 16 tiles and a
 // lane for every vector of a pixel [4,70,70,384] took 180 us forward (now 27), [104,25,13,72] 53 (now 9).
 template <int VEC, int MODE>
@@ -617,8 +617,7 @@ __global__ __launch_bounds__(256) void lcn_kernel(const float *__restrict__ x, c
                 if (divx) g = g / xv;                 // the quotient the pooling gradient takes (x is its output)
                 *(fv *)(out + o) = g;
             } else {
-                const float g = dy[o] * rs + u - x[o] * v;
-                out[o] = divx ? g / x[o] : g;
+                out[o] = dy[o] * rs + u - x[o] * v;   // (divx only with whole vectors)
             }
         } else {   // MODE 5
             if (VEC == 4) {
