@@ -322,6 +322,13 @@ ROUTES = [
     ("backward_data", "bf16", (96, 16, 18, 32, 6, 2, 64), "lc_bwd_data_bf16_tiled"),    # 72
     ("backward_weights", "bf16", (96, 7, 7, 32, 4, 1, 128), "lc_bwd_weights_general"),      # 16
     ("backward_weights", "bf16", (96, 7, 8, 32, 4, 1, 128), "lc_bwd_weights_bf16_tiled"),   # 20
+    # patch rows and rows of dy that other kernels' staging does not hold
+    ("forward", "f32", (70, 8, 8, 640, 4, 1, 128), "lc_forward_wide"),                      # 25 fields, rows of 2560 values
+    ("forward", "bf16", (33, 50, 49, 64, 49, 1, 16), "lc_forward_fast"),                    # rows of 3136
+    ("backward_data", "f32", (20, 42, 83, 8, 39, 1, 4), "lc_bwd_data_general"),
+    ("backward_data", "bf16", (20, 42, 83, 8, 39, 1, 4), "lc_bwd_data_general"),
+    ("backward_data", "bf16", (32, 62, 60, 64, 60, 1, 64), "lc_bwd_data_bf16_simple"),
+    ("backward_data", "bf16", (128, 46, 50, 8, 46, 2, 832), "lc_bwd_data_bf16_simple"),
 ]
 OPS = {"forward": 0, "backward_data": 1, "backward_weights": 2}
 
@@ -347,3 +354,42 @@ def test_routes(op, dtype, shape, kernel):
         lc.lc_backward_weights(G, xd, dyd, 0.0, out, dt)
         ref = oracle.lc_backward_weights(shape, xv, dyv)
     assert rel_fro(out.cpu().numpy(), ref) <= bar(n)
+
+
+# Images of 2^24 values and more (2^25 in bf16), beyond the general kernel's 32-bit offsets: the register-staged kernel keeps
+# every aligned layer there, at tiles (MT, NT) that smaller images no longer reach.
+LARGE_IMAGES = [("f32", (33, 8192, 1024, 2, 10, 26, 16), (4, 1)), ("f32", (33, 131072, 64, 2, 10, 28, 32), (4, 2)),
+                ("f32", (33, 16384, 256, 4, 5, 42, 128), (4, 4)), ("f32", (33, 10952, 383, 4, 5, 14, 64), (4, 4)),
+                ("f32", (33, 8192, 512, 4, 8, 39, 128), (4, 4)), ("f32", (65, 131072, 64, 2, 10, 12, 32), (8, 2)),
+                ("f32", (65, 131072, 64, 2, 12, 12, 32), (8, 2)), ("bf16", (17, 262144, 64, 2, 10, 57, 32), (2, 2)),
+                ("bf16", (17, 10181, 824, 4, 5, 63, 128), (2, 4)), ("bf16", (17, 65536, 256, 2, 10, 43, 64), (2, 4)),
+                ("bf16", (33, 131072, 128, 2, 10, 27, 32), (4, 2)), ("bf16", (33, 16384, 512, 4, 5, 42, 128), (4, 4)),
+                ("bf16", (33, 32768, 512, 2, 12, 23, 64), (4, 4)), ("bf16", (65, 262144, 64, 2, 10, 11, 32), (8, 2))]
+
+
+@pytest.mark.parametrize("dtype,shape,tile", LARGE_IMAGES, ids=str)
+def test_forward_of_large_images(dtype, shape, tile):
+    print(f"case forward of large images {dtype} {shape}", flush=True)
+    G, g = lc.geom(*shape), wl.LCGeom(*shape)
+    dt, td = (lc.LC_BF16, torch.bfloat16) if dtype == "bf16" else (lc.LC_F32, torch.float32)
+    plans = lc.plan_query(G, lc.LC_OP_FORWARD, dt)
+    assert ("lc_forward_fast", tile) in [(p["kernel"], tuple(p["tparam"][:2])) for p in plans], plans
+    torch.manual_seed(13)
+    x = torch.randn(g.B, g.H, g.W, g.C, device="cuda", dtype=td)
+    w = torch.randn(g.LH, g.LW, g.K, g.F, device="cuda", dtype=td)
+    bias = torch.randn(g.LH, g.LW, g.F, device="cuda")
+    y = nan(g.B, g.LH, g.LW, g.F)
+    lc.lc_forward(G, x, w, bias, 0.75, y, dt)
+    # fp64 products of all fields, some field rows at a time
+    fields = x.unfold(1, g.R, g.S).unfold(2, g.R, g.S)         # [B, LH, LW, C, R, R]
+    rows = max(1, 30_000_000 // (g.LW * g.K * max(g.B, g.F)))
+    diff = norm = 0.0
+    for i in range(0, g.LH, rows):
+        n = min(rows, g.LH - i)
+        a = fields[:, i:i + n].permute(1, 2, 0, 4, 5, 3).double().reshape(n * g.LW, g.B, g.K)
+        ref = 0.75 * torch.bmm(a, w[i:i + n].double().reshape(n * g.LW, g.K, g.F)) + bias[i:i + n].double().reshape(-1, 1, g.F)
+        got = y[:, i:i + n].permute(1, 2, 0, 3).double().reshape(n * g.LW, g.B, g.F)
+        diff, norm = diff + (got - ref).square().sum(), norm + ref.square().sum()
+    assert float((diff / norm).sqrt()) <= bar(g.K)
+    del x, w, y, fields
+    torch.cuda.empty_cache()
