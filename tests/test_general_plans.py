@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 
 import paper_1502_03409_amd as lc
+from general_tiles import TILES
 from paper_1502_03409_amd import binding as B
 
 
@@ -250,3 +251,28 @@ def test_layers_beyond_the_task_limit_plan_on_other_kernels():
         for dtype in (B.LC_F32, B.LC_BF16):
             p = lc.plan_query(lc.geom(*geo), op, dtype)[0]
             assert all(0 < g <= 0x7fffffff for g in p["grid"]), (op, geo, p)
+
+
+def test_tile_layers_reach_every_tile():
+    """The layers that the GPU tests run tile by tile reach every instance of the general kernels: images per wave (MT),
+    columns per wave (NT), operand type, ragged or whole vectors, vector width, and contractions whole and in slices."""
+    ops = {"forward": B.LC_OP_FORWARD, "backward_data": B.LC_OP_BACKWARD_DATA, "backward_weights": B.LC_OP_BACKWARD_WEIGHTS}
+    slices = {"forward": set(), "backward_data": set()}
+    for (op, dtype), shapes in TILES.items():
+        seen = set()
+        for shape in shapes:
+            (p,) = lc.plan_query(lc.geom(*shape), ops[op], B.LC_BF16 if dtype == "bf16" else B.LC_F32)
+            assert p["kernel"].endswith("_general"), (op, dtype, shape, p)
+            t = p["tparam"]
+            seen.add((t[0], t[1], t[4]) if op == "forward" else (t[0], t[1], t[3], t[6]) if op == "backward_data" else t[1])
+            if op != "backward_weights":
+                slices[op].add(t[5] if op == "forward" else t[4])
+        runs = (1, 2, 4) if dtype == "bf16" else (1, 2, 3, 4)
+        if op == "forward":
+            want = {(mt, nt, rag) for mt in (1, 2, 3, 4) for nt in runs for rag in (0, 1)}
+        elif op == "backward_data":
+            want = {(mt, nt, mask, vw) for mt in (1, 2, 3, 4) for nt in (1, 2, 3, 4) for mask in (0, 1) for vw in (4, 8)}
+        else:
+            want = set(runs)
+        assert seen == want, (op, dtype, want - seen, seen - want)
+    assert slices["forward"] == {1, 2, 4, 8, 16} and slices["backward_data"] == {1, 2, 4, 8}, slices

@@ -1,4 +1,5 @@
-"""The general kernels on the GPU, at the sizes where their tiles, vectors and slices end, against the fp64 oracle.
+"""The general kernels on the GPU, at the sizes where their tiles, vectors and slices end and at every tile they dispatch,
+against the fp64 oracle.
 
 Tolerance: a sum of n products in fp32 (bf16 products are exact in fp32) is off by about sqrt(n) roundings of 2^-24
 relative to its terms' norm; four times that."""
@@ -10,6 +11,7 @@ import oracle
 import paper_1502_03409_amd as lc
 import workloads as wl
 from conftest import rel_fro
+from general_tiles import TILES
 
 pytestmark = pytest.mark.gpu
 
@@ -291,6 +293,33 @@ def test_pool_gradient_streams(shape):
     assert rel_fro(dx2.cpu().numpy(), ref) <= 8 * bar(9 * shape[3])
 
 
+def run_pass(op, shape, dt):
+    """One pass over seeded operands: (result, fp64 oracle, products per result)."""
+    G, g = lc.geom(*shape), wl.LCGeom(*shape)
+    x, w, dy = wl.lc_inputs(g, "gaussian", seed=6)
+    (xd, xv), (wd, wv), (dyd, dyv) = operand(x, dt), operand(w, dt), operand(dy, dt)
+    if op == "forward":
+        out, n = nan(g.B, g.LH, g.LW, g.F), g.K
+        lc.lc_forward(G, xd, wd, None, 1.0, out, dt)
+        ref = oracle.lc_forward(shape, xv, wv, None, 1.0)
+    elif op == "backward_data":
+        out, n = nan(g.B, g.H, g.W, g.C), g.F * (-(-g.R // g.S)) ** 2
+        lc.lc_backward_data(G, dyd, wd, out, dt)
+        ref = oracle.lc_backward_data(shape, dyv, wv)
+    else:
+        out, n = nan(g.LH, g.LW, g.K, g.F), g.B
+        lc.lc_backward_weights(G, xd, dyd, 0.0, out, dt)
+        ref = oracle.lc_backward_weights(shape, xv, dyv)
+    return out.cpu().numpy(), ref, n
+
+
+@pytest.mark.parametrize("op,dtype,shape", [(*k, s) for k, shapes in TILES.items() for s in shapes], ids=str)
+def test_every_tile(op, dtype, shape):
+    print(f"case tile {op} {dtype} {shape}", flush=True)
+    out, ref, n = run_pass(op, shape, lc.LC_BF16 if dtype == "bf16" else lc.LC_F32)
+    assert rel_fro(out, ref) <= bar(n)
+
+
 # Aligned layers on both sides of the lines between the general kernels and the others: (op, dtype, shape, kernel).
 ROUTES = [
     ("forward", "f32", (40, 20, 21, 16, 4, 2, 32), "lc_forward_general"),       # little overlap
@@ -336,24 +365,10 @@ OPS = {"forward": 0, "backward_data": 1, "backward_weights": 2}
 @pytest.mark.parametrize("op,dtype,shape,kernel", ROUTES, ids=str)
 def test_routes(op, dtype, shape, kernel):
     print(f"case route {op} {dtype} {shape}", flush=True)
-    G, g = lc.geom(*shape), wl.LCGeom(*shape)
     dt = lc.LC_BF16 if dtype == "bf16" else lc.LC_F32
-    assert kernel in [p["kernel"] for p in lc.plan_query(G, OPS[op], dt)]
-    x, w, dy = wl.lc_inputs(g, "gaussian", seed=6)
-    (xd, xv), (wd, wv), (dyd, dyv) = operand(x, dt), operand(w, dt), operand(dy, dt)
-    if op == "forward":
-        out, n = nan(g.B, g.LH, g.LW, g.F), g.K
-        lc.lc_forward(G, xd, wd, None, 1.0, out, dt)
-        ref = oracle.lc_forward(shape, xv, wv, None, 1.0)
-    elif op == "backward_data":
-        out, n = nan(g.B, g.H, g.W, g.C), g.F * (-(-g.R // g.S)) ** 2
-        lc.lc_backward_data(G, dyd, wd, out, dt)
-        ref = oracle.lc_backward_data(shape, dyv, wv)
-    else:
-        out, n = nan(g.LH, g.LW, g.K, g.F), g.B
-        lc.lc_backward_weights(G, xd, dyd, 0.0, out, dt)
-        ref = oracle.lc_backward_weights(shape, xv, dyv)
-    assert rel_fro(out.cpu().numpy(), ref) <= bar(n)
+    assert kernel in [p["kernel"] for p in lc.plan_query(lc.geom(*shape), OPS[op], dt)]
+    out, ref, n = run_pass(op, shape, dt)
+    assert rel_fro(out, ref) <= bar(n)
 
 
 # Images of 2^24 values and more (2^25 in bf16), beyond the general kernel's 32-bit offsets: the register-staged kernel keeps
