@@ -207,6 +207,32 @@ def test_backward_weights(shape, dtype):
     assert torch.equal(dw, again)
 
 
+@pytest.mark.parametrize("shape", [(17, 9, 14, 3, 2, 3, 17), (5, 31, 29, 3, 11, 4, 50), (37, 17, 23, 3, 3, 5, 11)], ids=str)
+@pytest.mark.parametrize("dtype", [lc.LC_F32, lc.LC_BF16], ids=["f32", "bf16"])
+def test_backward_weights_infinities_stay_in_their_rows(shape, dtype):
+    """An infinite pixel reaches its weight rows alone, an infinite dy its filter's columns, in every batch position; a NaN
+    that no field covers reaches nothing."""
+    print(f"case general backward weights infinities {shape} {dtype}", flush=True)
+    g = wl.LCGeom(*shape)
+    x, _, dy = wl.lc_inputs(g, "gaussian", seed=14)
+    if g.R < g.S:
+        x[:, g.R:g.S] = np.nan
+        x[:, :, g.R:g.S] = np.nan
+    x[g.B - 1, 0, 0, g.C - 1] = np.inf                         # the last image of a partly filled step
+    x[1, g.S + g.R - 1, g.R - 1, 0] = -np.inf                  # first vector of a patch row's last pixel
+    dy[g.B - 2, g.LH - 1, g.LW - 1, g.F - 1] = np.inf          # the filter that the last run shares
+    dy[0, g.LH - 1, 0, 0] = np.nan
+    (xd, xv), (yd, yv) = operand(x, dtype), operand(dy, dtype)
+    dw = nan(g.LH, g.LW, g.K, g.F)
+    lc.lc_backward_weights(lc.geom(*shape), xd, yd, 0.0, dw, dtype)
+    ref = oracle.lc_backward_weights(shape, xv, yv)
+    out = dw.cpu().numpy()
+    assert np.isinf(ref).any() and np.isnan(ref).any()
+    assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.array_equal(out[np.isinf(ref)], ref[np.isinf(ref)])
+    m = np.isfinite(ref)
+    assert rel_fro(out[m], ref[m]) <= bar(g.B)
+
+
 @pytest.mark.parametrize("shape", [(6, 13, 14, 5, 3, 2, 19), (18, 17, 12, 3, 7, 3, 33), (2, 20, 20, 1, 6, 2, 50)], ids=str)
 def test_sae_step_projects_with_shared_vectors(shape):
     """The row projection's sums of squares count every updated weight once."""
@@ -271,6 +297,34 @@ def test_pooled_normalisation_tiles(shape, ks, flags):
         assert rel_fro(got.cpu().numpy(), ref) <= 8 * bar(ks * ks * shape[3])
 
 
+# one shape per kernel: the two walks (whole, part-filled and scalar chunks), the tiles, and the band kernel beside them
+@pytest.mark.parametrize("shape,ks", [((40, 21, 26, 32), 5), ((3, 70, 75, 52), 5), ((64, 23, 29, 6), 5), ((6, 31, 130, 16), 9),
+                                      ((4, 33, 35, 96), 5), ((3, 30, 31, 7), 5), ((2, 16, 90, 64), 3)], ids=str)
+@pytest.mark.parametrize("flags", range(8))
+def test_normalisation_keeps_a_nan_in_its_windows(shape, ks, flags):
+    """A NaN in x (forward) or dy (gradient) makes NaN of what its windows reach, of its channel or of all, and changes no
+    other value by a bit."""
+    print(f"case normalisation with a NaN {shape} {ks} {flags}", flush=True)
+    torch.manual_seed(15)
+    stats = shape if flags & 1 else shape[:3]
+    nbytes = lc.lcn_variant_workspace_bytes(shape, flags)
+    ws = torch.zeros(nbytes, dtype=torch.uint8, device="cuda") if nbytes else None
+    x, dy = torch.randn(*shape, device="cuda"), torch.randn(*shape, device="cuda")
+    y, dx, mu, rstd = nan(*shape), nan(*shape), nan(*stats), nan(*stats)
+    lc.lcn_variant_fwd(x, y, mu, rstd, ks, 1.0, 1e-4, flags)
+    lc.lcn_variant_bwd(x, mu, rstd, dy, dx, ks, 1.0, flags, ws)
+    reach = (ks - 1) // 2 * (2 if flags & 4 else 1)
+    for b, i, j, c in ((0, 0, 0, 0), (shape[0] - 1, shape[1] - 1, shape[2] - 1, shape[3] - 1), (1, shape[1] // 2, shape[2] // 2, 3)):
+        touched = torch.zeros(shape, dtype=torch.bool, device="cuda")
+        touched[b, max(0, i - reach):i + reach + 1, max(0, j - reach):j + reach + 1, slice(c, c + 1) if flags & 1 else slice(None)] = True
+        x1, dy1, y1, dx1, mu1, rstd1 = x.clone(), dy.clone(), nan(*shape), nan(*shape), nan(*stats), nan(*stats)
+        x1[b, i, j, c] = dy1[b, i, j, c] = float("nan")
+        lc.lcn_variant_fwd(x1, y1, mu1, rstd1, ks, 1.0, 1e-4, flags)
+        lc.lcn_variant_bwd(x, mu, rstd, dy1, dx1, ks, 1.0, flags, ws)
+        for got, clean in ((y1, y), (dx1, dx)):
+            assert torch.equal(got.isnan(), touched) and torch.equal(got[~touched], clean[~touched])
+
+
 # 3x3 stride-1 pooling gradient: the stream's segments and borders, the smallest map, and the sizes around the tile kernel's
 @pytest.mark.parametrize("shape", [(1, 3, 3, 4), (2, 9, 7, 128), (3, 41, 35, 16), (1, 4, 100, 8), (5, 33, 34, 44), (2, 32, 33, 24),
                                    (2, 31, 40, 32), (1, 70, 5, 384)], ids=str)
@@ -318,6 +372,28 @@ def test_every_tile(op, dtype, shape):
     print(f"case tile {op} {dtype} {shape}", flush=True)
     out, ref, n = run_pass(op, shape, lc.LC_BF16 if dtype == "bf16" else lc.LC_F32)
     assert rel_fro(out, ref) <= bar(n)
+
+
+@pytest.mark.parametrize("shape", [(2, 9, 7, 128), (3, 41, 35, 16), (5, 33, 34, 44), (2, 64, 64, 32), (1, 3, 3, 4)], ids=str)
+def test_pool_gradient_keeps_a_nan_in_its_window(shape):
+    print(f"case pool gradient with a NaN {shape}", flush=True)
+    torch.manual_seed(16)
+    B, H, W, C = shape
+    x = torch.randn(*shape, device="cuda")
+    y, dx = nan(B, H - 2, W - 2, C), nan(*shape)
+    lc.l2pool_fwd(x, y, 3, 1, 1e-6)
+    dy = torch.randn_like(y)
+    lc.l2pool_bwd(x, y, dy, dx, 3, 1)
+    for b, i, j, c in ((0, 0, 0, 0), (B - 1, H - 3, W - 3, C - 1), (B // 2, (H - 3) // 2, (W - 3) // 3, C // 2)):
+        for value, quotient in ((float("nan"), None), (float("inf"), None), (0.0, 0.0)):
+            dy1, y1, dx1 = dy.clone(), y.clone(), nan(*shape)
+            dy1[b, i, j, c] = value
+            if quotient is not None:
+                y1[b, i, j, c] = quotient                      # 0 / 0
+            lc.l2pool_bwd(x, y1, dy1, dx1, 3, 1)
+            touched = torch.zeros(shape, dtype=torch.bool, device="cuda")
+            touched[b, i:i + 3, j:j + 3, c] = True
+            assert torch.equal(~dx1.isfinite(), touched) and torch.equal(dx1[~touched], dx[~touched])
 
 
 # Aligned layers on both sides of the lines between the general kernels and the others: (op, dtype, shape, kernel).
