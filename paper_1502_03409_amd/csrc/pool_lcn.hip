@@ -1136,18 +1136,26 @@ int launch_pool_bwd_stream(const float *x, const float *y, const float *dy, floa
 
 }  // namespace
 
-// Whether the gradient of 3 x 3 stride-1 pooling streams.  The tile kernel forms each quotient once and is faster only where
-// its tiles are full and small enough for eight workgroups per compute unit: maps of about 32 channels that are not small
-// (128 images of 48 x 48 x 32: 24 us against 26; of 25 x 25 x 32: 12 against 10; of 57 x 57 x 16: 27 against 21; of
-// 30 x 30 x 64: 27 against 21; 38 of 65 x 35 x 128, where a tile does not fit LDS and the row kernel ran: 60 against 33).
-bool pool_bwd_streams(int H, int W, int C, int ks, int st) {
+// Whether the gradient of 3 x 3 stride-1 pooling streams.  The tile kernel forms each quotient once and is faster only at
+// around 32 channels, where several of its workgroups share a compute unit's LDS, and only with tiles that are nearly full
+// and at least four of them per compute unit: 128 images of 48 x 48 x 32 24 us against 26, of 200 x 200 x 32 465 against
+// 553.  Fewer tiles (16 images of 48 x 48 x 36 9.6 against 7.8, one of 96 x 96 x 40 8.2 against 5.7), tiles that hang over the
+// border (128 of 33 x 40 x 24 18 against 15) or other channels stream (128 of 57 x 57 x 16: 27 against 21; of 30 x 30 x 64: 27
+// against 21; 38 of 65 x 35 x 128, where a tile does not fit LDS and the row kernel ran: 60 against 33).  Over 40 maps of 24
+// to 40 channels and 32 to 300 pixels a side, at 1 to 128 images, the kernel picked is on average 0.5 % slower than the
+// faster one, at most 13 %.  (With dy / y handed in as one array, behind the normalisation, the line lies higher, but the two
+// are within 12 % of each other where it would differ.)
+bool pool_bwd_streams(int B, int H, int W, int C, int ks, int st) {
     if (C % 4 != 0 || ks != 3 || st != 1) return false;
-    return !(C >= 24 && C <= 40 && H >= 32 && W >= 32);
+    if (C < 24 || C > 40 || H < 32 || W < 32) return true;
+    const long long tiles = (long long)((H + kPoolTH - 1) / kPoolTH) * ((W + kPoolTW - 1) / kPoolTW);
+    const bool full = (long long)H * W * 100 >= tiles * (kPoolTH * kPoolTW) * 85;
+    return !(full && B * tiles >= 4 * 256);
 }
 
 int launch_l2pool_bwd(const float *x, const float *y, const float *dy, float *dx, int B, int H, int W, int C, int ks,
                       int st, hipStream_t s) {
-    if (pool_bwd_streams(H, W, C, ks, st)) return launch_pool_bwd_stream(x, y, dy, dx, B, H, W, C, s);
+    if (pool_bwd_streams(B, H, W, C, ks, st)) return launch_pool_bwd_stream(x, y, dy, dx, B, H, W, C, s);
     const int Ho = (H - ks) / st + 1, Wo = (W - ks) / st + 1;
     const size_t patch_bytes = (size_t)(kPoolTH + ks - 1) * (kPoolTW + ks - 1) * C * sizeof(float);
     if (C % 4 == 0 && st == 1 && ks <= kPoolMaxK && patch_bytes <= 64 * 1024) {
@@ -1241,7 +1249,7 @@ int launch_lcn_pool_bwd(const float *x, const float *p, const float *mu, const f
     const int Ho = (H - pks) / pst + 1, Wo = (W - pks) / pst + 1;
     const size_t patch_bytes = (size_t)(kPoolTH + pks - 1) * (kPoolTW + pks - 1) * C * sizeof(float);
     const int th = (H + kPoolTH - 1) / kPoolTH, tw = (W + kPoolTW - 1) / kPoolTW;
-    const bool quotient = pool_bwd_streams(H, W, C, pks, pst) || (C % 4 == 0 && pst == 1 && pks <= kPoolMaxK &&
+    const bool quotient = pool_bwd_streams(B, H, W, C, pks, pst) || (C % 4 == 0 && pst == 1 && pks <= kPoolMaxK &&
                                                                    patch_bytes <= 64 * 1024 && (long long)B * th * tw <= 0x7fffffffLL);
     if (int rc = launch_lcn(1, p, dn, scratch, const_cast<float *>(mu), const_cast<float *>(rstd), B, Ho, Wo, C, ks, sigma,
                             0.f, s, 0, nullptr, quotient))

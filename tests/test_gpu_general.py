@@ -325,9 +325,9 @@ def test_normalisation_keeps_a_nan_in_its_windows(shape, ks, flags):
             assert torch.equal(got.isnan(), touched) and torch.equal(got[~touched], clean[~touched])
 
 
-# 3x3 stride-1 pooling gradient: the stream's segments and borders, the smallest map, and the sizes around the tile kernel's
+# 3x3 stride-1 pooling gradient: the stream's segments and borders, the smallest map, and both sides of the tile kernel's sizes
 @pytest.mark.parametrize("shape", [(1, 3, 3, 4), (2, 9, 7, 128), (3, 41, 35, 16), (1, 4, 100, 8), (5, 33, 34, 44), (2, 32, 33, 24),
-                                   (2, 31, 40, 32), (1, 70, 5, 384)], ids=str)
+                                   (2, 31, 40, 32), (1, 70, 5, 384), (127, 32, 32, 32), (128, 32, 32, 32), (160, 33, 40, 24)], ids=str)
 def test_pool_gradient_streams(shape):
     print(f"case pool gradient {shape}", flush=True)
     rng = np.random.default_rng(10)
@@ -374,7 +374,7 @@ def test_every_tile(op, dtype, shape):
     assert rel_fro(out, ref) <= bar(n)
 
 
-@pytest.mark.parametrize("shape", [(2, 9, 7, 128), (3, 41, 35, 16), (5, 33, 34, 44), (2, 64, 64, 32), (1, 3, 3, 4)], ids=str)
+@pytest.mark.parametrize("shape", [(2, 9, 7, 128), (3, 41, 35, 16), (5, 33, 34, 44), (2, 64, 64, 32), (32, 64, 64, 32), (1, 3, 3, 4)], ids=str)
 def test_pool_gradient_keeps_a_nan_in_its_window(shape):
     print(f"case pool gradient with a NaN {shape}", flush=True)
     torch.manual_seed(16)
