@@ -717,6 +717,15 @@ int launch_fast_pf(const Geom &g, const T *x1, const T *dy1, const T *x2, const 
     return launch_fast<G, VA, NT, 1>(g, x1, dy1, x2, dy2, beta, gamma, out, ssq, kblocks_out, s);
 }
 
+// Whether the pipelined kernel's waves, at 128 patch elements by one filter tile, are a whole round of one per SIMD (256
+// images of 24 x 123 x 2, 14 x 14 at stride 4, 48 filters: 13.6 us against the general kernel's 19.8) or nearly two (192 of
+// 27 x 62 x 12, 11 x 11 at stride 6, 80 filters: 20.7 against 26.2); a second round of few waves costs as much as the first
+// (256 of 97 x 25 x 8, 7 x 7 at stride 7, 144 filters: 33.5 against 20.5).
+bool whole_rounds(const Geom &g) {
+    const long long waves = (long long)g.L * ceil_div(g.K, 128) * (g.F / 16), simds = 4 * 256;
+    return waves <= simds || (2 * waves > 3 * simds && waves <= 2 * simds);
+}
+
 // The whole-line kernel for aligned shapes; *done tells whether a kernel was launched.  T = float or bf16_t.
 template <typename T>
 int launch_backward_weights_fast_path(const Geom &g, const T *x1, const T *dy1, const T *x2, const T *dy2, float beta,
@@ -740,8 +749,10 @@ int launch_backward_weights_fast_path(const Geom &g, const T *x1, const T *dy1, 
     // filters 22 -> 10; below, up to 1.3 times slower: steps of 16 images); in fp32 odd numbers of 16-filter tiles, three and
     // more, which leave this kernel one tile per wave, if the contraction is 100 images and a patch 256 elements long (128 of
     // 52 x 160 x 16, 8 x 8 at stride 4, 48 filters 78 -> 63; 128 of 52 x 78 x 32, 6 x 6 at stride 2, 80 filters 280 -> 250;
-    // shorter ones are up to 1.3 times slower).
-    const bool general = sizeof(T) == 2 ? g.B >= 32 : g.F % 32 == 16 && g.F >= 48 && g.B >= 100 && g.K >= 256;
+    // shorter ones are up to 1.3 times slower), unless this kernel's waves fill their rounds, with eight images and more in
+    // flight, over a gradient that is overwritten (accumulating, the general kernel stays 1.2 times faster there).
+    const bool odd_tiles = g.F % 32 == 16 && g.F >= 48 && g.B >= 100 && g.K >= 256;
+    const bool general = sizeof(T) == 2 ? g.B >= 32 : odd_tiles && !(beta == 0.f && g.B % 8 == 0 && whole_rounds(g));
     if (general && backward_weights_general_supported(g, sizeof(T))) return LC_OK;
     const int va = patch_vector_width(g);
     if ((g.B & 3) == 0 && va == 4) {
@@ -776,11 +787,28 @@ int launch_backward_weights_generic(const Geom &g, const T *x1, const T *dy1, co
     return launch_nt<4>(g, x1, dy1, x2, dy2, beta, gamma, out, ssq, kblocks_out, s);
 }
 
-// One image and at most 32 filters over a large gradient: little but its stores, which the masked kernel's wider tiles
-// issue faster (173 x 47 x 8, 18 x 18 at stride 3, 30 filters, 162 MB of gradient: 28.8 us against 31.0, bf16 operands 30.9
-// against 38.2; 81 x 131 x 8, 20 x 20 at stride 3, 32 filters: 60 against 69).  More filters, images or less gradient:
-// the general kernel (126 x 173 x 2, 13 x 13 at stride 6, 96 filters: 28.8 -> 16.3; 4 images, 29 filters: 138 -> 129).
-bool masked_kernel_stays(const Geom &g) { return g.B == 1 && g.F <= 32 && (long long)g.L * g.K * g.F >= (1LL << 24); }
+// Layers without a pipelined kernel that the masked kernel keeps when it overwrites the gradient: small batches, which are
+// little but stores (a step of the general kernel is four images, sixteen in bf16: the limits are half as high there).  An
+// accumulated gradient always goes to the general kernel, which has the old values in flight together (1 image of 161 x 56 x
+// 5, 5 x 5 at stride 2, 164 filters: up to four times faster; the training step, which updates in place, 209 us against 403).
+//   At most 32 filters: the general kernel's wave stores 16 or 32 filters of 64 patch elements, this one's of up to 128
+//     (3 images of 106 x 43 x 64, 16 x 16 at stride 6, 18 filters: 25.5 us against 29.5, bf16 30.6 against 37.2).
+//   More filters, padded to whole blocks of 64 by a third at most: patches of 64 elements and less, which leave the general
+//     kernel's 64-element tiles partly empty (11 images of 82 x 71 x 3, 5 x 5, 112 filters: 40 against 55; 7 of 64 x 198, 4 x 4
+//     at stride 2, 224 filters: 21 against 33), and longer ones that fill at most 78 % of them, short patch rows in
+//     vectors of four, under a gradient of 2^22 elements and more (3 of 55 x 69, 9 x 9, 323 filters: 80 against 105, bf16 82
+//     against 159).
+// The general kernel is faster outside, by 1.3 times on average (30 images and more: up to 10 times in bf16).  Over 3500 layers
+// of 1 to 256 images in either type the kernel picked is on average 1.1 % slower than the faster one.
+bool masked_kernel_stays(const Geom &g, int es, float beta) {
+    if (beta != 0.f) return false;
+    const int b = es == 4 ? 2 : 1;
+    if (g.F <= 32) return g.B <= 4 * b;
+    if (4 * g.F < 3 * 64 * ceil_div(g.F, 64)) return false;
+    if (g.K <= 64) return g.B <= 8 * b;
+    const int tiles = ceil_div(g.R * ceil_div(g.RC, 4), 16);
+    return g.B <= 8 * b && 100LL * g.K <= 78LL * 64 * tiles && (long long)g.L * g.K * g.F >= (1LL << 22);
+}
 
 }  // namespace
 
@@ -791,7 +819,7 @@ int launch_backward_weights_f32(const Geom &g, const float *x1, const float *dy1
         const int rc = launch_backward_weights_fast_path(g, x1, dy1, x2, dy2, beta, gamma, out, ssq, kblocks_out, s, &done);
         if (done) return rc;
     }
-    if (backward_weights_general_supported(g, 4) && !masked_kernel_stays(g))
+    if (backward_weights_general_supported(g, 4) && !masked_kernel_stays(g, 4, beta))
         return launch_backward_weights_general_f32(g, x1, dy1, x2, dy2, beta, gamma, out, ssq, kblocks_out, s);
     return launch_backward_weights_generic(g, x1, dy1, x2, dy2, beta, gamma, out, ssq, kblocks_out, s);
 }
@@ -803,7 +831,7 @@ int launch_backward_weights_bf16_storage(const Geom &g, const void *x, const voi
     const int rc = launch_backward_weights_fast_path(g, (const bf16_t *)x, (const bf16_t *)dy, none, none, beta, 1.f, dw,
                                                      nullptr, nullptr, s, &done);
     if (done) return rc;
-    if (backward_weights_general_supported(g, 2) && !masked_kernel_stays(g))
+    if (backward_weights_general_supported(g, 2) && !masked_kernel_stays(g, 2, beta))
         return launch_backward_weights_general_bf16(g, x, dy, beta, dw, s);
     return launch_backward_weights_generic(g, (const bf16_t *)x, (const bf16_t *)dy, none, none, beta, 1.f, dw, nullptr,
                                            nullptr, s);

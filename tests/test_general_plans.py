@@ -166,7 +166,8 @@ def test_general_backward_weights_stores_every_element_once(seed):
         plans += [(p, True) for p in lc.plan_query(G_, B.LC_OP_SAE_STEP) if p["kernel"].startswith("lc_bwd_weights")]
         for p, squares in plans:
             if p["kernel"] != "lc_bwd_weights_general":
-                assert p["kernel"] != "lc_bwd_weights_generic" or RC < 4, (geo, p)
+                # the masked kernel: short patch rows, and small batches of some layers
+                assert p["kernel"] != "lc_bwd_weights_generic" or RC < 4 or Bn <= 16, (geo, p)
                 continue
             n_general += 1
             G, NT, ES = p["tparam"][:3]
@@ -276,3 +277,36 @@ def test_tile_layers_reach_every_tile():
             want = set(runs)
         assert seen == want, (op, dtype, want - seen, seen - want)
     assert slices["forward"] == {1, 2, 4, 8, 16} and slices["backward_data"] == {1, 2, 4, 8}, slices
+
+
+# (images, height, width, channels, field, stride, filters), kernel in fp32, kernel in bf16: layers on both sides of the lines
+# between the weight gradient's general kernel and the two it displaces
+WEIGHT_ROUTES = [
+    # small batches: at most 32 filters, four images in bf16 and eight in fp32
+    ((8, 106, 43, 64, 16, 6, 18), "generic", "general"), ((9, 106, 43, 64, 16, 6, 18), "general", "general"),
+    ((4, 106, 43, 64, 16, 6, 18), "generic", "generic"), ((5, 23, 26, 5, 5, 3, 32), "generic", "general"),
+    ((4, 23, 26, 5, 5, 3, 33), "general", "general"),
+    # patches of 64 elements at most
+    ((16, 64, 198, 1, 8, 2, 223), "generic", "general"), ((8, 64, 198, 1, 8, 2, 223), "generic", "generic"),
+    ((17, 64, 198, 1, 8, 2, 223), "general", "general"), ((7, 64, 198, 65, 1, 2, 223), "generic", "generic"),
+    # filters that pad blocks of 64 by more than a third
+    ((7, 64, 198, 1, 4, 2, 95), "general", "general"), ((7, 64, 198, 1, 4, 2, 97), "generic", "generic"),
+    ((7, 64, 198, 1, 4, 2, 80), "general", "general"),
+    # tiles of patch elements partly filled, over 2^22 elements of gradient
+    ((3, 55, 69, 1, 9, 1, 323), "generic", "generic"), ((3, 20, 20, 1, 9, 1, 323), "general", "general"),
+    ((3, 55, 69, 1, 16, 1, 323), "general", "general"),
+    # fp32, odd numbers of 16-filter tiles: rounds of the pipelined kernel's waves
+    ((256, 24, 123, 2, 14, 4, 48), "fast", "bf16_rows"), ((256, 97, 25, 8, 7, 7, 144), "general", "bf16_rows"),
+    ((192, 27, 62, 12, 11, 6, 80), "fast", "bf16_rows"), ((196, 27, 62, 12, 11, 6, 80), "general", "general"),
+    ((128, 15, 24, 32, 4, 2, 80), "general", "bf16_rows"),
+]
+
+
+@pytest.mark.parametrize("geo,f32,bf16", WEIGHT_ROUTES, ids=str)
+def test_weight_gradient_routes(geo, f32, bf16):
+    for dtype, kernel in ((B.LC_F32, f32), (B.LC_BF16, bf16)):
+        (p,) = lc.plan_query(lc.geom(*geo), B.LC_OP_BACKWARD_WEIGHTS, dtype)
+        assert p["kernel"] == "lc_bwd_weights_" + kernel, (geo, dtype, p)
+    # the training step accumulates: the general kernel
+    step = [p["kernel"] for p in lc.plan_query(lc.geom(*geo), B.LC_OP_SAE_STEP) if p["kernel"].startswith("lc_bwd_weights")]
+    assert step == ["lc_bwd_weights_general"], (geo, step)

@@ -182,7 +182,8 @@ def test_backward_data_takes_its_time_whatever_the_data(dtype):
 
 # weight gradient: besides SHAPES, batches around a step of four and of sixteen images, one slice and several
 WEIGHT_SHAPES = SHAPES + [(4, 11, 12, 5, 3, 1, 30), (15, 12, 10, 3, 5, 1, 18), (31, 10, 11, 7, 2, 1, 6), (64, 9, 9, 3, 9, 1, 35),
-                          (200, 8, 9, 3, 7, 1, 21), (3, 12, 14, 1, 4, 2, 2)]
+                          (200, 8, 9, 3, 7, 1, 21), (3, 12, 14, 1, 4, 2, 2),
+                          (1, 17, 15, 8, 4, 2, 40), (2, 20, 20, 3, 6, 2, 50), (9, 13, 14, 5, 3, 2, 19), (7, 9, 10, 9, 5, 1, 70)]
 
 
 @pytest.mark.parametrize("shape", WEIGHT_SHAPES, ids=str)
@@ -233,7 +234,8 @@ def test_backward_weights_infinities_stay_in_their_rows(shape, dtype):
     assert rel_fro(out[m], ref[m]) <= bar(g.B)
 
 
-@pytest.mark.parametrize("shape", [(6, 13, 14, 5, 3, 2, 19), (18, 17, 12, 3, 7, 3, 33), (2, 20, 20, 1, 6, 2, 50)], ids=str)
+@pytest.mark.parametrize("shape", [(6, 13, 14, 5, 3, 2, 19), (18, 17, 12, 3, 7, 3, 33), (2, 20, 20, 1, 6, 2, 50), (9, 13, 14, 5, 3, 2, 19),
+                                   (2, 20, 20, 3, 6, 2, 50)], ids=str)
 def test_sae_step_projects_with_shared_vectors(shape):
     """The row projection's sums of squares count every updated weight once."""
     print(f"case general sae_step projection {shape}", flush=True)
@@ -414,7 +416,8 @@ ROUTES = [
     ("backward_data", "bf16", (64, 26, 26, 16, 6, 2, 64), "lc_bwd_data_fast"),
     ("backward_data", "bf16", (64, 26, 26, 16, 6, 2, 96), "lc_bwd_data_general"),
     ("backward_data", "bf16", (32, 24, 24, 8, 8, 4, 128), "lc_bwd_data_general"),
-    ("backward_weights", "f32", (100, 20, 22, 16, 4, 2, 48), "lc_bwd_weights_general"),
+    ("backward_weights", "f32", (100, 26, 38, 16, 4, 2, 48), "lc_bwd_weights_general"),
+    ("backward_weights", "f32", (104, 20, 22, 16, 4, 2, 48), "lc_bwd_weights_fast"),        # one round of waves
     ("backward_weights", "f32", (96, 20, 22, 16, 4, 2, 48), "lc_bwd_weights_fast"),
     ("backward_weights", "f32", (1, 44, 49, 16, 20, 3, 31), "lc_bwd_weights_generic"),   # a gradient beyond 2^24 elements
     ("backward_weights", "f32", (1, 44, 49, 16, 20, 3, 33), "lc_bwd_weights_general"),
