@@ -422,15 +422,17 @@ __device__ __forceinline__ float tap_norm(const GaussTaps &t, int p, int n, int 
 //   MODE 2  x -> mu;                          MODE 3  x, mu -> rstd, y = (x - mu) rstd;
 //   MODE 4  x, mu, rstd, dy -> dv (into out) and field[p] = sum_c dv[p,c] / normaliser(p);
 //   MODE 5  out = dv - window sum of field (in place).
-// divx (MODE 1, VEC 4): leave dx / x.  Latency-bound on small maps: th x tw tiles (lcn_tile) and lpp lanes a pixel
+// DIVX (MODE 1, VEC 4): leave dx / x (as a runtime flag the compiler divided always and chose afterwards: up to 14 % of the
+// plain gradient on large maps).  Latency-bound on small maps: th x tw tiles (lcn_tile) and lpp lanes a pixel
 // (lanes_per_pixel) put two workgroups on every compute unit and several loads in flight per lane; with 16 x 16 tiles and a
 // lane for every vector of a pixel [4,70,70,384] took 180 us forward (now 27), [104,25,13,72] 53 (now 9).
-template <int VEC, int MODE>
+// NF: a lane's vectors of a pixel that are in flight together (1 where it has one).
+template <int VEC, int MODE, int NF, bool DIVX = false>
 __global__ __launch_bounds__(256) void lcn_kernel(const float *__restrict__ x, const float *__restrict__ dy,
                                                   float *__restrict__ out, float *__restrict__ mu,
                                                   float *__restrict__ rstd, float *__restrict__ field, int H, int W,
                                                   int C, int ks, float eps, GaussTaps taps, int lpp, int th, int tw,
-                                                  int tiles_w, int tiles_per_img, int zpad, int divx) {
+                                                  int tiles_w, int tiles_per_img, int zpad) {
     constexpr bool kTwoMaps = MODE == 0 || MODE == 1;
     __shared__ float m1[kLcnHalo * kLcnHalo], m2[kTwoMaps ? kLcnHalo * kLcnHalo : 1];
     __shared__ float t1[kLcnTile * kLcnTile], t2[kLcnTile * kLcnTile];
@@ -447,12 +449,12 @@ __global__ __launch_bounds__(256) void lcn_kernel(const float *__restrict__ x, c
     if (tid < hh) zr[tid] = zpad ? 1.f : tap_norm(taps, ti - r + tid, H, r);
     else if (tid >= 64 && tid < 64 + hw) zc[tid - 64] = zpad ? 1.f : tap_norm(taps, tj - r + tid - 64, W, r);
     if (MODE == 1 || MODE == 4) __syncthreads();   // the other modes first use them after phase 1's barrier
+    const float inv_tw = 1.0f / (float)tw;
+    auto tile_row = [&](int op) { return (int)(((float)op + 0.5f) * inv_tw); };   // op / tw, exact below 2^20
     auto norm_at = [&](int row, int col) { return zr[row - ti + r] * zc[col - tj + r] * (float)C; };
 
-    // phase 1: per-pixel channel sums over the tile and its halo; lpp lanes share a pixel, four of a lane's vectors of it
-    // are in flight together
+    // phase 1: per-pixel channel sums over the tile and its halo; lpp lanes share a pixel
     const int grp = tid / lpp, gl = tid % lpp, ngrp = 256 / lpp;
-    constexpr int NF = 4;
     typedef float fv __attribute__((ext_vector_type(VEC == 4 ? 4 : 2)));   // VEC = 1: the second component stays zero
     auto fetch = [&](const float *p) -> fv {
         if constexpr (VEC == 4) return *(const fv *)p;
@@ -488,8 +490,11 @@ __global__ __launch_bounds__(256) void lcn_kernel(const float *__restrict__ x, c
                 for (int u = 0; u < NF; ++u) {
                     if (c0 + u * lpp >= CV) continue;
                     fv e = v[u];
-                    if (MODE == 1 || MODE == 3 || MODE == 4) e -= mp;   // differences from the pixel's own mean
-                    if (VEC == 1) e[1] = 0.f;
+                    if (MODE == 1 || MODE == 3 || MODE == 4) {          // differences from the pixel's own mean
+                        // value by value: a vector of four means would be waited for before the values are asked for
+#pragma unroll
+                        for (int k = 0; k < VEC; ++k) e[k] -= mp;
+                    }
                     if (MODE == 1 || MODE == 4) {
                         a += total(d[u]);
                         c2 += total(d[u] * e);
@@ -574,7 +579,7 @@ __global__ __launch_bounds__(256) void lcn_kernel(const float *__restrict__ x, c
         while (lp3 < CV && lp3 < 64) lp3 <<= 1;
         const int g3 = tid / lp3, l3 = tid % lp3, n3 = 256 / lp3;
         for (int op = g3; op < th * tw; op += n3) {
-            const int oi = op / tw, oj = op - oi * tw;
+            const int oi = tile_row(op), oj = op - oi * tw;
             const int row = ti + oi, col = tj + oj;
             if (row >= H || col >= W) continue;   // uniform over the group
             const size_t pix = img + (size_t)row * W + col;
@@ -596,7 +601,7 @@ __global__ __launch_bounds__(256) void lcn_kernel(const float *__restrict__ x, c
     // phase 3: elementwise pass over the tile
     for (int e = tid; e < th * tw * CV; e += 256) {
         const int op = e / CV, cv = e - op * CV;
-        const int oi = op / tw, oj = op - oi * tw;
+        const int oi = tile_row(op), oj = op - oi * tw;
         const int row = ti + oi, col = tj + oj;
         if (row >= H || col >= W) continue;
         const size_t pix = img + (size_t)row * W + col;
@@ -614,10 +619,10 @@ __global__ __launch_bounds__(256) void lcn_kernel(const float *__restrict__ x, c
             if (VEC == 4) {
                 const fv xv = fetch(x + o), d = fetch(dy + o);
                 fv g = d * rs + u - xv * v;
-                if (divx) g = g / xv;                 // the quotient the pooling gradient takes (x is its output)
+                if constexpr (DIVX) g = g / xv;       // the quotient the pooling gradient takes (x is its output)
                 *(fv *)(out + o) = g;
             } else {
-                out[o] = dy[o] * rs + u - x[o] * v;   // (divx only with whole vectors)
+                out[o] = dy[o] * rs + u - x[o] * v;
             }
         } else {   // MODE 5
             if (VEC == 4) {
@@ -1047,20 +1052,26 @@ bool make_taps(int ks, float sigma, GaussTaps *t) {
 
 // Lanes that share a pixel in the tile kernel: about a third of its vectors, so that a lane has several loads in flight and
 // the workgroup many pixels at once (one vector a lane: one load and a reduction at a time, 13 times one after the other on
-// a 16 x 16 tile of 32 channels).
-int lanes_per_pixel(int cv) {
+// a 16 x 16 tile of 32 channels).  The gradients' two arrays on maps of fewer than 48 channels whose three arrays the 256 MB
+// Infinity Cache does not hold: a lane for every vector, whose wave reads whole lines from HBM ([105,251,58,20] 168 us with
+// the former, 119 with this; [102,56,209,44] 284 and 201; [151,24,199,24], a quarter of the cache each, 61 and 72).
+int lanes_per_pixel(int cv, bool whole_lines) {
     int l = 1;
-    while (6 * l <= cv && l < 64) l <<= 1;
+    while ((whole_lines ? l < cv : 6 * l <= cv) && l < 64) l <<= 1;
     return l;
 }
 
 // Tile of the tile kernel: at most 16 x 16 pixels, the image split evenly; halved, the longer side first, until there are two
-// workgroups per compute unit, as long as a tile with its halo is at most four times the tile.
+// workgroups per compute unit, as long as a tile with its halo is at most four times the tile.  On maps of eight such tiles
+// per compute unit and more 16 columns where the last tile's missing ones are few (tiles then start on whole lines at few
+// channels: [64,224,104,4] 26 us against 29 in tiles of 15).
 void lcn_tile(int B, int H, int W, int r, int *th, int *tw) {
     int nh = (H + kLcnTile - 1) / kLcnTile, nw = (W + kLcnTile - 1) / kLcnTile;
+    const bool many = (long long)B * nh * nw >= 8 * 256;
     for (;;) {
         *th = (H + nh - 1) / nh;
         *tw = (W + nw - 1) / nw;
+        if (many && 8 * nw * kLcnTile <= 9 * W) *tw = kLcnTile;
         if ((long long)B * nh * nw >= 2 * 256) return;
         const int h2 = *th >= *tw ? (*th + 1) / 2 : *th, w2 = *th >= *tw ? *tw : (*tw + 1) / 2;
         if (h2 * w2 == *th * *tw || (h2 + 2 * r) * (w2 + 2 * r) > 4 * h2 * w2) return;
@@ -1332,16 +1343,22 @@ int launch_lcn(int mode, const float *x, const float *dy, float *out, float *mu,
         if (done) return rc;
     }
     const int vec = (C % 4 == 0) ? 4 : 1;
-    const int lpp = lanes_per_pixel(C / vec);
     int th, tw;
     lcn_tile(B, H, W, (ks - 1) / 2, &th, &tw);
     const int tw_n = (W + tw - 1) / tw, t_img = (H + th - 1) / th * tw_n;
     if ((long long)B * t_img > 0x7fffffffLL) return LC_EUNSUPPORTED;
+    const bool large = C < 48 && (long long)B * H * W * C >= 24LL << 20;
+    const int lpp = lanes_per_pixel(C / vec, vec == 4 && (mode == 1 || mode == 4) && large);
     dim3 grid((unsigned)nblk), tgrid((unsigned)((long long)B * t_img)), block(256);
-#define LC_LCN(VEC_, MODE_)                                                                                          \
-    hipLaunchKernelGGL((lcn_kernel<VEC_, MODE_>), tgrid, block, 0, s, x, dy, out, mu, rstd, field, H, W, C, ks, eps, \
-                       taps, lpp, th, tw, tw_n, t_img, zero_pad, divx)
-#define LC_LCN_MODE(MODE_) do { if (vec == 4) LC_LCN(4, MODE_); else LC_LCN(1, MODE_); } while (0)
+#define LC_LCN(...)                                                                                                 \
+    hipLaunchKernelGGL((lcn_kernel<__VA_ARGS__>), tgrid, block, 0, s, x, dy, out, mu, rstd, field, H, W, C, ks, eps, \
+                       taps, lpp, th, tw, tw_n, t_img, zero_pad)
+#define LC_LCN_MODE(MODE_)                                             \
+    do {                                                               \
+        if (vec == 4 && lpp >= C / 4) LC_LCN(4, MODE_, 1);             \
+        else if (vec == 4) LC_LCN(4, MODE_, 4);                        \
+        else LC_LCN(1, MODE_, 4);                                      \
+    } while (0)
 #define LC_LCN_CACHED(LPP_)                                                                                    \
     hipLaunchKernelGGL((lcn_fwd_cached_kernel<LPP_>), grid, block, 0, s, x, out, mu, rstd, H, W, ks, eps, taps, \
                        tiles_w, tiles_h * tiles_w, zero_pad)
@@ -1349,6 +1366,9 @@ int launch_lcn(int mode, const float *x, const float *dy, float *out, float *mu,
     else if (mode == 0 && C == 16) LC_LCN_CACHED(4);
     else if (mode == 0 && C == 8) LC_LCN_CACHED(2);
     else if (mode == 0) LC_LCN_MODE(0);
+    else if (mode == 1 && divx && vec != 4) return LC_EINTERNAL;   // the quotient is asked for with whole vectors only
+    else if (mode == 1 && divx && lpp >= C / 4) LC_LCN(4, 1, 1, true);
+    else if (mode == 1 && divx) LC_LCN(4, 1, 4, true);
     else if (mode == 1) LC_LCN_MODE(1);
     else if (mode == 2) LC_LCN_MODE(2);
     else if (mode == 3) LC_LCN_MODE(3);

@@ -277,9 +277,11 @@ def test_channel_normalisation_walks(shape, ks, flags):
 
 
 # Normalisation with statistics pooled over channels that have no band kernel, or maps these do not take: tiles of every
-# size the launcher halves down to, lanes per pixel that fill its vectors, leave some empty or take single channels
+# size the launcher halves down to, lanes per pixel that fill its vectors, leave some empty or take single channels, one
+# vector per lane (four channels, and maps the caches do not hold)
 @pytest.mark.parametrize("shape,ks", [((4, 33, 35, 96), 5), ((1, 12, 13, 40), 3), ((2, 20, 70, 384), 5), ((40, 17, 18, 24), 7),
-                                      ((600, 5, 5, 72), 9), ((3, 30, 31, 7), 5), ((2, 16, 90, 64), 15), ((1, 3, 50, 12), 9)], ids=str)
+                                      ((600, 5, 5, 72), 9), ((3, 30, 31, 7), 5), ((2, 16, 90, 64), 15), ((1, 3, 50, 12), 9),
+                                      ((2, 40, 300, 4), 5), ((64, 110, 84, 44), 3)], ids=str)
 @pytest.mark.parametrize("flags", [0, 2, 4, 6])
 def test_pooled_normalisation_tiles(shape, ks, flags):
     print(f"case pooled normalisation {shape} {ks} {flags}", flush=True)
@@ -329,7 +331,7 @@ def test_normalisation_keeps_a_nan_in_its_windows(shape, ks, flags):
 
 # 3x3 stride-1 pooling gradient: the stream's segments and borders, the smallest map, and both sides of the tile kernel's sizes
 @pytest.mark.parametrize("shape", [(1, 3, 3, 4), (2, 9, 7, 128), (3, 41, 35, 16), (1, 4, 100, 8), (5, 33, 34, 44), (2, 32, 33, 24),
-                                   (2, 31, 40, 32), (1, 70, 5, 384), (127, 32, 32, 32), (128, 32, 32, 32), (160, 33, 40, 24)], ids=str)
+                                   (2, 31, 40, 32), (1, 70, 5, 384), (127, 32, 32, 32), (128, 32, 32, 32), (160, 33, 40, 24), (2, 40, 300, 4)], ids=str)
 def test_pool_gradient_streams(shape):
     print(f"case pool gradient {shape}", flush=True)
     rng = np.random.default_rng(10)
