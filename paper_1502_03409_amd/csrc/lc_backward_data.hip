@@ -1088,10 +1088,19 @@ int launch_backward_data_generic(const Geom &g, const T *dy, const T *w, float *
 // filters: 182 against 209; within 5 % either way on 4 of 11.  The general kernel is faster outside: 128 of 81 x 29 x 32,
 // 13 x 13 at stride 4, 48 filters 413 -> 168 us; 8 of 45 x 20 x 64, 13 x 13 at stride 6, 112 filters 51 -> 32; 39 x 93 x 32,
 // 9 x 9 at stride 3, 288 values, 52 -> 41.)
-bool masked_kernel_stays(const Geom &g) {
+// And layers of fields that don't overlap and few filters (32 at most, 16 in bf16, where the general kernel loads half as
+// much): a value is one short sum, most of the general kernel's time is its first loads and its stores, and this kernel
+// keeps more tasks in flight (fp32: 1 image of 197 x 153 x 48, 7 x 7 at stride 7, 5 filters 24 us against 42; 4 of 143 x 165 x 48, 2 x 2 at stride
+// 3, 16 filters 27 against 41; 3 of 81 x 103 x 32, 6 x 6 at stride 6, 16 filters 8.1 against 12.1; bf16: the first of these 25
+// against 35).  Of 2100 layers left by the pipelined kernels, short contractions among them, the kernel picked is on average
+// 0.6 % slower than the faster one in fp32, 0.2 % in bf16.
+bool masked_kernel_stays(const Geom &g, int es) {
     const int NCV = g.S * g.S * g.C;
-    return NCV >= 512 && g.B >= 16 && g.B <= 64 && g.F % 4 == 0 &&
-           (long long)ceil_div(g.H, g.S) * ceil_div(g.W, g.S) * ceil_div(NCV, 64) >= 10 * 256;
+    const long long tasks = (long long)ceil_div(g.H, g.S) * ceil_div(g.W, g.S) * ceil_div(NCV, 64);
+    const bool one_field = g.R <= g.S;
+    if (es == 2) return one_field && g.F <= 16 && g.B <= 16 && NCV >= 1024 && tasks >= 10 * 256;
+    if (one_field && g.F <= 32 && g.B <= 64 && NCV >= 256 && tasks >= 4 * 256) return true;
+    return NCV >= 512 && g.B >= 16 && g.B <= 64 && g.F % 4 == 0 && tasks >= 10 * 256;
 }
 
 }  // namespace
@@ -1105,7 +1114,7 @@ int launch_backward_data_f32(const Geom &g, const float *dy, const float *w, flo
         const int rc = launch_backward_data_fast_path(g, dy, w, dx, s, &done);
         if (done) return rc;
     }
-    if (backward_data_general_supported(g, 4) && !masked_kernel_stays(g)) return launch_backward_data_general_f32(g, dy, w, dx, s);
+    if (backward_data_general_supported(g, 4) && !masked_kernel_stays(g, 4)) return launch_backward_data_general_f32(g, dy, w, dx, s);
     return launch_backward_data_generic(g, dy, w, dx, s);
 }
 
@@ -1120,7 +1129,7 @@ int launch_backward_data_bf16_storage(const Geom &g, const void *dy, const void 
     bool done = false;
     const int rc = launch_backward_data_fast_path(g, (const bf16_t *)dy, (const bf16_t *)w, dx, s, &done);
     if (done) return rc;
-    if (backward_data_general_supported(g, 2)) return launch_backward_data_general_bf16(g, dy, w, dx, s);
+    if (backward_data_general_supported(g, 2) && !masked_kernel_stays(g, 2)) return launch_backward_data_general_bf16(g, dy, w, dx, s);
     return launch_backward_data_generic(g, (const bf16_t *)dy, (const bf16_t *)w, dx, s);
 }
 

@@ -100,7 +100,8 @@ def test_general_backward_data_covers_every_product_once(seed):
             plans = lc.plan_query(G, B.LC_OP_BACKWARD_DATA, dtype)
             p = plans[0]
             if p["kernel"] != "lc_bwd_data_general":
-                assert p["kernel"] != "lc_bwd_data_generic" or F < 4, (geo, p)
+                short = R <= S and F <= 32                     # few products a value
+                assert p["kernel"] != "lc_bwd_data_generic" or F < 4 or short, (geo, p)
                 continue
             n_general += 1
             MT, NT, ES, mask, ks, tasks, VW = p["tparam"][:7]
@@ -222,8 +223,9 @@ def test_derived_sizes_follow_the_geometry():
 def test_strides_of_hundreds_of_pixels_plan_backward_data():
     """A cell of S x S x C values beyond what the general kernel's grid holds in blocks of its tile: such layers plan on a
     wider tile or on the masked kernel (S*S*C just below, at and beyond each tile's limit of 16*NT*65535 values)."""
-    for geo in ((21, 72, 102, 7, 42, 784, 1263), (1902, 16, 39, 13, 16, 669, 884), (2, 9, 9, 1, 3, 1023, 8), (2, 9, 9, 1, 3, 1024, 8),
-                (2, 9, 9, 1, 3, 1025, 8), (2, 9, 9, 2, 3, 1023, 5), (1, 9, 9, 4, 3, 1023, 9), (1, 9, 9, 4, 3, 1024, 9), (2, 9, 9, 1, 3, 2047, 8), (2, 9, 9, 1, 3, 2049, 8)):
+    for geo in ((21, 72, 102, 7, 42, 784, 1263), (1902, 16, 39, 13, 16, 669, 884), (2, 9, 9, 1, 3, 1023, 40), (2, 9, 9, 1, 3, 1024, 40),
+                (2, 9, 9, 1, 3, 1025, 40), (2, 9, 9, 2, 3, 1023, 37), (1, 9, 9, 4, 3, 1023, 41), (1, 9, 9, 4, 3, 1024, 41),
+                (2, 9, 9, 1, 3, 2047, 40), (2, 9, 9, 1, 3, 2049, 40)):
         G = lc.geom(*geo)
         for dtype in (B.LC_F32, B.LC_BF16):
             p = lc.plan_query(G, B.LC_OP_BACKWARD_DATA, dtype)[0]
@@ -310,3 +312,20 @@ def test_weight_gradient_routes(geo, f32, bf16):
     # the training step accumulates: the general kernel
     step = [p["kernel"] for p in lc.plan_query(lc.geom(*geo), B.LC_OP_SAE_STEP) if p["kernel"].startswith("lc_bwd_weights")]
     assert step == ["lc_bwd_weights_general"], (geo, step)
+
+
+# the same for backward data's general kernel and short contractions: filters, images, overlap, values a cell, tasks
+DATA_ROUTES = [
+    ((1, 197, 153, 48, 7, 7, 5), "generic", "generic"), ((17, 197, 153, 48, 7, 7, 5), "generic", "general"),
+    ((64, 143, 165, 48, 3, 3, 31), "generic", "general"), ((65, 143, 165, 48, 3, 3, 31), "general", "general"),
+    ((4, 143, 165, 48, 3, 3, 33), "general", "general"), ((4, 143, 165, 48, 4, 3, 9), "general", "general"),
+    ((4, 143, 165, 28, 3, 3, 31), "general", "general"), ((4, 40, 50, 48, 3, 3, 31), "generic", "general"),
+    ((4, 30, 40, 48, 3, 3, 31), "general", "general"), ((16, 150, 150, 64, 4, 4, 16), "generic", "generic"),
+]
+
+
+@pytest.mark.parametrize("geo,f32,bf16", DATA_ROUTES, ids=str)
+def test_backward_data_routes(geo, f32, bf16):
+    for dtype, kernel in ((B.LC_F32, f32), (B.LC_BF16, bf16)):
+        (p,) = lc.plan_query(lc.geom(*geo), B.LC_OP_BACKWARD_DATA, dtype)
+        assert p["kernel"] == "lc_bwd_data_" + kernel, (geo, dtype, p)

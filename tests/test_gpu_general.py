@@ -82,7 +82,7 @@ def test_forward_infinities_stay_in_their_fields(dtype):
 # block of values, an image border that cuts a block, and strides far beyond the image (on either side of the grid's limit)
 DATA_SHAPES = SHAPES + [(20, 14, 15, 1, 4, 1, 8), (4, 13, 18, 2, 6, 2, 9), (33, 16, 13, 3, 8, 2, 24), (18, 25, 23, 3, 8, 4, 16),
                         (6, 12, 10, 1, 10, 1, 4), (50, 14, 22, 64, 4, 2, 20), (2, 26, 26, 1, 7, 3, 303),
-                        (3, 9, 11, 4, 3, 1023, 9), (3, 9, 11, 1, 3, 2049, 9)]
+                        (3, 9, 11, 4, 3, 1023, 41), (3, 9, 11, 1, 3, 2049, 41)]
 
 
 @pytest.mark.parametrize("shape", DATA_SHAPES, ids=str)
@@ -412,7 +412,9 @@ ROUTES = [
     ("forward", "bf16", (64, 19, 20, 16, 15, 1, 64), "lc_forward_general"),     # few workgroups in strips
     ("backward_data", "f32", (16, 72, 72, 32, 4, 4, 16), "lc_bwd_data_generic"),    # large cells, enough of them
     ("backward_data", "f32", (16, 40, 40, 32, 4, 4, 16), "lc_bwd_data_general"),    # too few
-    ("backward_data", "f32", (15, 72, 72, 32, 4, 4, 16), "lc_bwd_data_general"),    # a batch below
+    ("backward_data", "f32", (15, 72, 72, 32, 4, 4, 40), "lc_bwd_data_general"),    # a batch below
+    ("backward_data", "f32", (15, 72, 72, 32, 4, 4, 16), "lc_bwd_data_generic"),    # one short sum a value
+    ("backward_data", "bf16", (16, 72, 72, 64, 4, 4, 13), "lc_bwd_data_generic"),
     ("backward_data", "f32", (64, 26, 26, 16, 6, 2, 32), "lc_bwd_data_direct"),     # full tiles
     ("backward_data", "f32", (40, 30, 32, 3, 10, 2, 64), "lc_bwd_data_general"),    # mostly padding
     ("backward_data", "bf16", (64, 26, 26, 16, 6, 2, 64), "lc_bwd_data_fast"),
