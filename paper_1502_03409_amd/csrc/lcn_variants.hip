@@ -490,6 +490,10 @@ int launch_rows(Args a, int B, hipStream_t s, const char *where, bool *done) {
     if (most < 1) return LC_OK;
     a.nchunk = (CV + CB - 1) / CB;
     const int nstrip = (a.W + most - 1) / most, TO = (a.W + nstrip - 1) / nstrip, TC = TO + 2 * r;
+    // narrow maps of four and eight channels leave most lanes of a wave without work ([210,161,11,4], 7 x 7 windows, two
+    // stages: 46 us forward and 41 backward here, 36 and 33 in tiles; [124,259,16,4]: 43 and 40 against 33 and 32; from 17
+    // columns on the two are even and, where the last tile is ragged, [112,248,20,4]: 38 and 29 against 39 and 40)
+    if (CB <= 2 && TO * CB <= 16) return LC_OK;
     const int nthr = (TC * CB + 63) / 64 * 64;
     const long long strips = (long long)B * nstrip * a.nchunk, want = 256LL * kRowsWaves * 64;
     long long nseg = (want + strips * nthr - 1) / (strips * nthr);

@@ -256,7 +256,8 @@ def test_sae_step_projects_with_shared_vectors(shape):
 # Per-channel normalisation on maps large enough for the kernels that walk down the rows: windows of 3 to 9, channels that
 # fill a chunk of 32, leave one partly filled or are no multiple of four, strips and segments that end off the grid
 @pytest.mark.parametrize("shape,ks", [((40, 21, 26, 32), 5), ((3, 70, 75, 52), 5), ((9, 40, 37, 36), 3), ((24, 33, 18, 24), 7),
-                                      ((6, 31, 130, 16), 9), ((130, 13, 12, 20), 9), ((64, 23, 29, 6), 5), ((2, 150, 170, 7), 3)], ids=str)
+                                      ((6, 31, 130, 16), 9), ((130, 13, 12, 20), 9), ((64, 23, 29, 6), 5), ((2, 150, 170, 7), 3), ((150, 40, 11, 4), 7),
+                                      ((300, 33, 12, 8), 5), ((300, 33, 13, 8), 5)], ids=str)
 @pytest.mark.parametrize("flags", [1, 3, 5, 7])
 def test_channel_normalisation_walks(shape, ks, flags):
     print(f"case channel normalisation {shape} {ks} {flags}", flush=True)
