@@ -18,12 +18,16 @@
  *    rows/columns that no field covers are ignored by the forward pass and receive zero
  *    from lc_backward_data).
  *  - `dtype` names the storage type of the x / w / dy operands: LC_F32, or LC_BF16 (bf16
- *    operands, fp32 accumulation).  Outputs are always fp32.  Every shape is accepted in
- *    either type.  bf16 operands meet bf16 matrix instructions on nearly every shape; those
- *    with patch rows of fewer than four values (forward, weight gradient) or fewer than four
- *    filters (backward data), tensors beyond 32-bit offsets, and some of the weight gradient's
- *    layers of fewer than 32 images widen the values on their way in (exactly) and multiply with the fp32 matrix instruction: the same
- *    results either way.
+ *    operands, fp32 accumulation).  Outputs are always fp32.  Two limits of the local data
+ *    share lead to LC_EUNSUPPORTED: lc_forward refuses patch rows of more than 2527 values
+ *    (R*C) where no aligned kernel takes the layer, and lc_backward_data refuses layers
+ *    beyond the 32-bit offsets of its general kernel whose strip of dy does not fit 160 KB.
+ *    bf16 operands meet bf16 matrix instructions on nearly every shape.  Where they do not,
+ *    the values are widened on their way in (exactly) and multiplied with the fp32 matrix
+ *    instruction, which gives the same results: patch rows of fewer than four values
+ *    (forward, weight gradient), fewer than four filters (backward data), tensors beyond
+ *    32-bit offsets, layers of few filters whose fields do not overlap (backward data), and
+ *    most weight gradients of fewer than 32 images.
  *  - `hip_stream` is a hipStream_t passed as void* (NULL = the default stream).  Calls
  *    only enqueue work; none synchronises.  Arguments are validated on the host before
  *    anything is launched, so every error except LC_EHIP is returned without touching

@@ -928,18 +928,22 @@ long long fast_workgroups(const Geom &g, int mt, int nt) {
 // is faster on every layer measured (37 images of 75 x 99 x 3 under 11 x 11 fields at stride 3, 40 filters: 110 -> 19 us;
 // 128 images of 80 x 169 x 3, 10 x 10 fields at stride 3, 83 filters: 270 -> 107 us; 2 images of 51 x 64 x 64, 16 x 16
 // fields at stride 6, 60 filters: 1100 -> 62 us), because it needs no barrier per patch row and can cut a
-// contraction into slices where a layer has few fields.  The masked kernel stays for patch rows of fewer than four
-// values and for tensors beyond the general kernel's 32-bit offsets, and keeps deciding which patch rows are too long.
+// contraction into slices where a layer has few fields.  The masked kernel stays for what the general one does not index
+// (patch rows of fewer than four values, tensors beyond 32-bit offsets, more than 2^30 tasks).  Patch rows that its staged
+// strip of 16 images cannot hold (R C > 2527 at 160 KB) stay refused, LC_EUNSUPPORTED in both types, unless an aligned
+// kernel above takes the layer: the general kernel stages nothing and has no such limit, but what a call refuses is
+// part of its contract, and a caller may probe for it.
 bool takes_general(const Geom &g, int es) {
     return forward_general_supported(g, es) && ((size_t)16 * lds_row_stride(g.RC) + 8) * sizeof(float) <= 160 * 1024;
 }
 
 // The workgroup-tiled kernel of lc_forward_wide.hip keeps layers of fewer than kWideFields fields and at least kWidePatch
-// elements per patch: its slices across workgroups reach further than the general kernel's eight waves (96 images of 18 x
-// 20 x 16, 16 x 16 at stride 1, 128 filters: 26.7 us against 40.6; 80 of 26 x 26 x 8, 24 x 24 at stride 1, 256 filters: 41
-// against 47).  With more fields or shorter patches the general kernel is faster (the same 24 x 24 fields on 28 x 28 pixels:
-// 72 -> 49 us; 128 images of 8 x 8 x 32, 8 x 8, 1024 filters: 27 -> 19; 256 of 64 x 64 x 32, 8 x 8 at stride 2, 128 filters:
-// 995 -> 870; 128 of 40 x 40 x 64, 4 x 4 at stride 2: 150 -> 105; 96 images, 256 filters, 8 x 8 at stride 2: 730 -> 721).
+// elements per patch: its slices across workgroups reach further than the general kernel's sixteen waves at most (96
+// images of 18 x 20 x 16, 16 x 16 at stride 1, 128 filters: 26.7 us against 40.6; 80 of 26 x 26 x 8, 24 x 24 at stride
+// 1, 256 filters: 41 against 47).  With more fields or shorter patches the general kernel is faster (the same 24 x 24
+// fields on 28 x 28 pixels: 72 -> 49 us; 128 images of 8 x 8 x 32, 8 x 8, 1024 filters: 27 -> 19; 256 of 64 x 64 x 32,
+// 8 x 8 at stride 2, 128 filters: 995 -> 870; 128 of 40 x 40 x 64, 4 x 4 at stride 2: 150 -> 105; 96 images, 256
+// filters, 8 x 8 at stride 2: 730 -> 721).
 constexpr int kWideFields = 16, kWidePatch = 4096;
 
 // Where the register-staged kernel (mt, nt: the tile it would take) keeps a layer the general kernel could take: fields
@@ -1047,6 +1051,8 @@ int launch_forward_fast_path(const Geom &g, const T *x, const T *w, const float 
         // (bf16 storage: 128 images of 23 x 23 x 32, 6 x 6 at stride 2, 32 filters 29 -> 11 us; 200 of 185 x 137 x 16,
         // 5 x 5 at stride 6, 128 filters 189 -> 89 us; faster on all of 20)
         if (!done && takes_general(g, sizeof(T)) && (sizeof(T) == 2 || !staged_kernel_stays(g, mt, nt))) return LC_OK;
+        // below: the layers of staged_kernel_stays, and in either type those the general kernel leaves (long patch rows,
+        // images of 2^24 fp32 or 2^25 bf16 values and more)
         if (!done && mt == 8) rc = launch_fast_mt<8>(g, x, w, bias, alpha, alpha_dev, y, s, &done, nt);
         if (!done && mt >= 4 && g.B > 32) rc = launch_fast_mt<4>(g, x, w, bias, alpha, alpha_dev, y, s, &done, nt);
         if (!done) rc = launch_fast_mt<2>(g, x, w, bias, alpha, alpha_dev, y, s, &done, nt);
