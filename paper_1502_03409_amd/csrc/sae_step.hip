@@ -215,7 +215,7 @@ __global__ __launch_bounds__(kSparsityThreads) void sae_sparsity_kernel(const fl
 // A filter that is all zeros has no direction: it is left as it is (inv = 0 avoids 0 * inf).
 // A workgroup takes 16 or more neighbouring filters of the flat (l,f) list and `split` lanes for each, which add every
 // split-th block; their sums meet in LDS.  Bound by latency: one lane per filter is a serial chain of kblocks loads, and the
-// paper's dense layer (1442 blocks of 4096 filters, 22 MiB) ran on 16 workgroups: 547 us; the figure now stands at the launch.
+// paper's dense layer (1442 blocks of 4096 filters, 22 MiB) ran on 16 workgroups: 547 us, 11 us now.
 __global__ __launch_bounds__(kNormThreads) void sae_row_norm_kernel(const float *__restrict__ ssq, int kblocks, int F,
                                                                     long long LF, int split, float *__restrict__ inv) {
     __shared__ float sums[kNormThreads];
@@ -239,24 +239,37 @@ __global__ __launch_bounds__(kNormThreads) void sae_row_norm_kernel(const float 
     if (slot == 0 && e < LF) inv[e] = t > 0.f ? 1.0f / sqrtf(t) : 0.f;
 }
 
-// The flat list of weights in vectors of four, kRescale of them in flight per lane; a lane's field l, its place in the
-// field's K x F matrix and its filter move on by constant steps, with no division in the loop.  A vector of a layer whose
-// filters are no multiple of four (WHOLE false, at least four filters) may cross the end of a filter row, or of a field.
+// The flat list of weights in vectors of four: a workgroup takes kRescale * 256 neighbouring ones at a time, all in flight.
+// A lane's field l, its place in the field's K x F matrix and its filter move on by constant steps, with no division in the
+// loop.  A vector of a layer whose filters are no multiple of four (WHOLE false, at least four filters) may cross the end of
+// a filter row, or of a field.  HBM-bound: 542 us for the dense layer's 1.5 GB read and written (5.6 TB/s; one vector at a
+// time with two divisions each 595 us, trips whose four vectors lie a grid apart 630 us, non-temporal accesses 523 us, not
+// taken: smaller layers find their weights in the caches again), 364 MB with 27 filters 146 us against 207 us by scalars.
 constexpr int kRescale = 4;
-struct RescaleStep { long long l, pos; int f; };        // one trip's step in fields, in a field's elements, in filters
+struct RescaleStep {                                    // a step in fields, in a field's elements, in filters
+    long long l, pos;
+    int f;
+};
+__device__ __forceinline__ void move_on(long long &l, long long &pos, int &f, const RescaleStep &s, int F, long long KF) {
+    l += s.l;
+    pos += s.pos;
+    f += s.f;
+    if (pos >= KF) { pos -= KF; ++l; }
+    if (f >= F) f -= F;
+}
 template <bool WHOLE>
 __global__ __launch_bounds__(256) void sae_rescale_kernel(float *__restrict__ w, const float *__restrict__ inv, int F,
-                                                          long long KF, long long n, RescaleStep step) {
-    const long long nv = n / 4, stride = (long long)gridDim.x * 256;
-    long long e = (long long)blockIdx.x * 256 + threadIdx.x;
+                                                          long long KF, long long n, RescaleStep near, RescaleStep hop) {
+    const long long nv = n / 4;
+    long long e = (long long)blockIdx.x * (256 * kRescale) + threadIdx.x;
     long long l = 4 * e / KF, pos = 4 * e - l * KF;
     int f = (int)(pos % F);
-    for (; e < nv; e += kRescale * stride) {
+    for (; e < nv; e += (long long)gridDim.x * (256 * kRescale)) {
         f32x4 v[kRescale], s[kRescale];
 #pragma unroll
         for (int j = 0; j < kRescale; ++j) {
-            if (e + j * stride < nv) {
-                v[j] = ((const f32x4 *)w)[e + j * stride];
+            if (e + j * 256 < nv) {
+                v[j] = ((const f32x4 *)w)[e + j * 256];
                 const float *iv = inv + l * F + f;
                 if (WHOLE) {
                     s[j] = *(const f32x4 *)iv;
@@ -265,15 +278,11 @@ __global__ __launch_bounds__(256) void sae_rescale_kernel(float *__restrict__ w,
                     for (int c = 0; c < 4; ++c) s[j][c] = iv[f + c >= F && pos + c < KF ? c - F : c];
                 }
             }
-            l += step.l;
-            pos += step.pos;
-            f += step.f;
-            if (pos >= KF) { pos -= KF; ++l; }
-            if (f >= F) f -= F;
+            move_on(l, pos, f, j < kRescale - 1 ? near : hop, F, KF);
         }
 #pragma unroll
         for (int j = 0; j < kRescale; ++j)
-            if (e + j * stride < nv) ((f32x4 *)w)[e + j * stride] = v[j] * s[j];
+            if (e + j * 256 < nv) ((f32x4 *)w)[e + j * 256] = v[j] * s[j];
     }
     if (blockIdx.x == 0 && (long long)threadIdx.x < n - 4 * nv) {       // up to three weights behind the last vector
         const long long t = 4 * nv + threadIdx.x;
@@ -377,14 +386,14 @@ int launch_sae_step(const Geom &g, const float *x, float *w, float *b, float *al
         const long long nv = nw / 4;
         const unsigned blocks = (unsigned)(nv / (256 * kRescale) + 1 < kRescaleBlocks ? nv / (256 * kRescale) + 1 : kRescaleBlocks);
         const LaunchPlan pr = make_plan("sae_rescale", {g.F >= 4 ? 4 : 1}, {}, dim3(blocks), 256, 0);
-        const long long hop = 4LL * blocks * 256;
-        const RescaleStep step = {hop / KF, hop % KF, (int)(hop % g.F)};
+        auto step = [&](long long floats) { return RescaleStep{floats / KF, floats % KF, (int)(floats % g.F)}; };
+        const RescaleStep near = step(1024), hop = step(4096LL * (blocks - 1) + 1024);
         if (g.F < 4)
             LC_LAUNCH(pr, "sae_step projection launch", sae_rescale_few_kernel, s, w, inv, g.F, KF, nw);
         else if (g.F % 4 == 0)
-            LC_LAUNCH(pr, "sae_step projection launch", sae_rescale_kernel<true>, s, w, inv, g.F, KF, nw, step);
+            LC_LAUNCH(pr, "sae_step projection launch", sae_rescale_kernel<true>, s, w, inv, g.F, KF, nw, near, hop);
         else
-            LC_LAUNCH(pr, "sae_step projection launch", sae_rescale_kernel<false>, s, w, inv, g.F, KF, nw, step);
+            LC_LAUNCH(pr, "sae_step projection launch", sae_rescale_kernel<false>, s, w, inv, g.F, KF, nw, near, hop);
     }
     return LC_OK;
 }
