@@ -3,8 +3,8 @@
 // the two-stage form (subtract the local mean, then divide by the local root mean square of the result).
 //
 // Pooled statistics run in the channel-reduction kernels of the default form (pool_lcn.hip).  This file holds the
-// per-channel kernels: two that walk down the rows of maps large enough for them, and a tile kernel that takes every
-// window, channel count and map size.  There every element has its own statistics, so a workgroup stages an 8x16 pixel
+// per-channel kernels: two that walk down the rows of maps large enough for them, one that walks both stages of the two-stage
+// form at once, and a tile kernel that takes every window, channel count and map size.  There every element has its own statistics, so a workgroup stages an 8x16 pixel
 // tile, its halo and up to 32 channels of the quantity under the window in LDS (as float4 where C % 4 == 0), and each thread forms
 // the Gaussian window sums for one pixel and four channels at a time.  Bandwidth-bound: the forward passes read
 // the tile once (the centre value is taken from LDS), the halo ring comes from L2.
@@ -453,6 +453,151 @@ __global__ __launch_bounds__(kRowThreads) void lcn_channel_rows_kernel(Args a, i
     }
 }
 
+// waves per SIMD that the two-stage kernel's registers are kept to
+constexpr int two_stage_waves(bool grad, int V, int KS) {
+    if (V == 4) return grad ? (KS == 3 ? 3 : 2) : (KS == 3 ? 5 : 3);
+    if (V == 2) return grad ? (KS == 3 ? 6 : KS == 5 ? 4 : 3) : (KS == 3 ? 8 : KS == 5 ? 5 : 4);
+    return grad ? (KS <= 5 ? 8 : KS == 7 ? 7 : 5) : (KS == 3 ? 8 : KS == 5 ? 7 : KS == 7 ? 5 : 4);
+}
+
+// Both stages of the two-stage form in one walk, forward (GRAD false: x -> mu, rstd, y) or backward (x, mu, rstd, dy -> dx).
+// A workgroup walks down a strip of TO columns, 2r more on either side, by CB work items of V channels; each row it loads
+// goes through two rings of KS rows in registers.  A stage sums its ring vertically, leaves the sum in LDS and adds it up
+// horizontally from there: the first stage's row is r rows behind the load and gives the quantity under the second window
+// (the squared difference from the mean, or dv over its normaliser), the second stage's is r + 1 rows behind that, so one
+// barrier a row serves both.  The ring slots are named by the row loop, which is unrolled over KS rows.  Values outside the
+// image are zeros.  Every array is read once, but for the 2 r columns and rows at a strip's sides: on [128,44,44,32], 5 x 5, 36
+// us forward and 30 backward where the two passes take 45 and 54, which move the mean, dv and its normalised field through memory
+// (the arrays alone are 21 and 26 us at 6 TB/s); what is left is the row's chain of load, vertical sum, LDS, horizontal sum twice over, with
+// the 8 to 20 waves a compute unit holds.  Maps of tens of microseconds and less wait for launches and that chain, and halve.
+template <bool GRAD, int V, int KS>
+__global__ __launch_bounds__(kRowThreads, two_stage_waves(GRAD, V, KS)) void lcn_channel_two_stage_kernel(Args a, int TO, int CB, int nstrip, int RS,
+                                                                            int nseg) {
+    constexpr int r = (KS - 1) / 2;
+    typedef typename FVec<V>::T VT;
+    extern __shared__ __align__(16) float lds[];
+    const int H = a.H, W = a.W, CV = a.C / V, TC = TO + 4 * r;
+    const int ct = threadIdx.x / CB, cq = threadIdx.x - ct * CB;
+    int blk = remap_xcd(blockIdx.x, gridDim.x);                // strips and segments of one image stay in one XCD's L2
+    const int chunk = blk % a.nchunk; blk /= a.nchunk;
+    const int strip = blk % nstrip; blk /= nstrip;
+    const int sg = blk % nseg, b = blk / nseg;
+    const int j = strip * TO + ct - 2 * r, cv = chunk * CB + cq;
+    const bool lane = ct < TC && cv < CV, col_in = lane && j >= 0 && j < W;
+    const bool inner = col_in && ct >= r && ct < TC - r;       // a column of the first stage
+    const bool owns = col_in && ct >= 2 * r && ct < 2 * r + TO;
+    const int ro0 = sg * RS, ro1 = min(ro0 + RS, H);
+    const size_t base = ((size_t)b * H * W + (col_in ? j : 0)) * CV + (lane ? cv : 0), rstride = (size_t)W * CV;
+    VT *row0 = (VT *)lds + ct * CB + cq;                       // [2 buffers][2 stages][TC][CB]
+    const int map = TC * CB;
+
+    float g[KS], full = 0.f;
+#pragma unroll
+    for (int q = 0; q < KS; ++q) { g[q] = a.taps.g[q]; full += g[q]; }
+    const float zc = a.zpad ? 1.f : taps_inside(a.taps, col_in ? j : 0, W, r);
+    const float whole = 1.f / (full * zc);
+    auto inv_norm = [&](int row) -> float {                    // 1 / normaliser of the window around an element of this row
+        if (a.zpad) return 1.f;
+        if (row >= r && row + r < H) return whole;
+        float z = 0.f;
+#pragma unroll
+        for (int d = 0; d < KS; ++d) z += row + d - r >= 0 && row + d - r < H ? g[d] : 0.f;
+        return 1.f / (z * zc);
+    };
+    constexpr int AHEAD = GRAD || KS < 5 || V * KS > 16 ? 2 : 3;          // rows whose loads are in flight
+    struct Elem { VT x, m, d, rs; } e[KS];
+    auto fetch = [&](int row, Elem &e) {
+        const size_t o = base + (size_t)min(max(row, 0), H - 1) * rstride;
+        e.x = ((const VT *)a.x)[o];
+        if constexpr (GRAD) {
+            e.m = ((const VT *)a.mu_in)[o];
+            e.d = ((const VT *)a.dy)[o];
+            e.rs = ((const VT *)a.rstd_in)[o];
+        }
+    };
+    // q1: what the first window sums.  q2: what the second one sums; c2: what the output needs of the same element.
+    // c1, d1 (GRAD): dy rstd and x - mu of the rows the first stage has not reached
+    VT q1[KS], q2[KS], c2[KS], c1[GRAD ? KS : 1], d1[GRAD ? KS : 1];
+#pragma unroll
+    for (int d = 0; d < KS; ++d) q1[d] = q2[d] = c2[d] = (VT)(0.f);
+    if constexpr (GRAD)
+#pragma unroll
+        for (int d = 0; d < KS; ++d) c1[d] = d1[d] = (VT)(0.f);
+    const int first = max(ro0 - 2 * r, 0), last = ro1 + 2 * r;   // rows of the walk; the last one only ends the second stage
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) fetch(first + u, e[u]);
+    for (int top = first; top <= last; top += KS) {
+#pragma unroll
+        for (int u = 0; u < KS; ++u) {
+            const int ir = top + u, ra = ir - r, rb = ir - 2 * r - 1;
+            if (ir > last) break;
+            const bool in = col_in && ir >= 0 && ir < H;
+            if constexpr (GRAD) {
+                const VT diff = e[u].x - e[u].m;
+                d1[u] = diff;
+                c1[u] = e[u].d * e[u].rs;
+                // gradient of this element's window variance, over its normaliser
+                q1[u] = in ? -0.5f * (e[u].rs * e[u].rs * e[u].rs * e[u].d * diff) * inv_norm(ir) : (VT)(0.f);
+            } else {
+                q1[u] = in ? e[u].x : (VT)(0.f);
+            }
+            fetch(ir + AHEAD, e[(u + AHEAD) % KS]);
+            VT v1 = (VT)(0.f), v2 = (VT)(0.f);
+#pragma unroll
+            for (int d = 0; d < KS; ++d) {
+                v1 += g[d] * q1[(u + 1 + d) % KS];
+                v2 += g[d] * q2[(u + d) % KS];
+            }
+            VT *row = row0 + (u & 1 ? 2 * map : 0);
+            if (top - first & 1) row = row0 + (u & 1 ? 0 : 2 * map);   // KS is odd: the buffers change places every trip
+            if (lane) {
+                row[0] = v1;
+                row[map] = v2;
+            }
+            __syncthreads();
+            VT n2 = (VT)(0.f), m2 = (VT)(0.f);
+            if (inner && ra >= 0 && ra < H) {
+                VT s = (VT)(0.f);
+#pragma unroll
+                for (int q = 0; q < KS; ++q) s += g[q] * row[(q - r) * CB];
+                const float iz = inv_norm(ra);
+                if constexpr (GRAD) {
+                    m2 = c1[(u + KS - r) % KS] + 2.f * d1[(u + KS - r) % KS] * s;
+                    n2 = m2 * iz;
+                } else {
+                    const VT mu = s * iz;
+                    if (owns && ra >= ro0 && ra < ro1) ((VT *)a.mu_out)[base + (size_t)ra * rstride] = mu;
+                    m2 = q1[(u + KS - r) % KS] - mu;
+                    n2 = m2 * m2;
+                }
+            }
+            if (owns && rb >= ro0) {                           // rb < ro1 by the end of the loop
+                VT s = (VT)(0.f);
+#pragma unroll
+                for (int q = 0; q < KS; ++q) s += g[q] * row[map + (q - r) * CB];
+                const size_t o = base + (size_t)rb * rstride;
+                const VT c = c2[(u + KS - 1 - r) % KS];
+                if constexpr (GRAD) {
+                    ((VT *)a.out)[o] = c - s;
+                } else {
+                    const float iz = inv_norm(rb);
+                    VT rs;
+                    if constexpr (V > 1) {
+#pragma unroll
+                        for (int k = 0; k < V; ++k) rs[k] = 1.0f / sqrtf(s[k] * iz + a.eps);
+                    } else {
+                        rs = 1.0f / sqrtf(s * iz + a.eps);
+                    }
+                    ((VT *)a.rstd_out)[o] = rs;
+                    ((VT *)a.out)[o] = c * rs;
+                }
+            }
+            q2[u] = n2;
+            c2[u] = m2;
+        }
+    }
+}
+
 bool make_taps(int ks, float sigma, Taps *t) {
     if (ks < 1 || ks > kMaxK || (ks & 1) == 0 || !(sigma > 0.f)) return false;
     const int r = (ks - 1) / 2;
@@ -522,13 +667,16 @@ int launch_walk(const Args &a, int B, hipStream_t s, const char *where, bool *do
 
 template <int OP, int V>
 int launch_pass_v(Args a, int B, hipStream_t s, const char *where) {
-    bool done = false;
-    int rc = LC_OK;
-    if (a.ks == 3) rc = launch_walk<OP, V, 3>(a, B, s, where, &done);
-    else if (a.ks == 5) rc = launch_walk<OP, V, 5>(a, B, s, where, &done);
-    else if (a.ks == 7) rc = launch_walk<OP, V, 7>(a, B, s, where, &done);
-    else if (a.ks == 9) rc = launch_walk<OP, V, 9>(a, B, s, where, &done);
-    if (done || rc != LC_OK) return rc;
+    // (the two-stage form takes these windows in one kernel where C is no multiple of four)
+    if constexpr (V == 4 || OP == kFwdOne) {
+        bool done = false;
+        int rc = LC_OK;
+        if (a.ks == 3) rc = launch_walk<OP, V, 3>(a, B, s, where, &done);
+        else if (a.ks == 5) rc = launch_walk<OP, V, 5>(a, B, s, where, &done);
+        else if (a.ks == 7) rc = launch_walk<OP, V, 7>(a, B, s, where, &done);
+        else if (a.ks == 9) rc = launch_walk<OP, V, 9>(a, B, s, where, &done);
+        if (done || rc != LC_OK) return rc;
+    }
     const int tiles_h = (a.H + kTileH - 1) / kTileH;
     a.tiles_w = (a.W + kTileW - 1) / kTileW;
     a.tiles_per_img = tiles_h * a.tiles_w;
@@ -553,6 +701,69 @@ int launch_pass(const Args &a, int B, hipStream_t s, const char *where) {
     return a.C % 4 == 0 ? launch_pass_v<OP, 4>(a, B, s, where) : launch_pass_v<OP, 1>(a, B, s, where);
 }
 
+// Both stages in one kernel.  CB work items a pixel side by side and segments of RS rows by estimated time: a compute unit
+// walks its workgroups in rounds of as many as the registers hold, a row takes a round 0.2 us per channel of a work item and
+// 0.05 us per wave, narrow pieces of a pixel take longer; short segments walk the 4 r rows at their sides for fewer rows of
+// their own.  The constants are a fit to 24 maps timed with every CB and 17 numbers of segments: the pick is on average 2 % slower
+// than the fastest backward and 5 % forward.  CB is a power of two, or a whole pixel: pieces of 24 or 96 bytes share sectors
+// with the next workgroup's.
+template <bool GRAD, int V, int KS>
+int launch_two_stage(Args a, int B, hipStream_t s, const char *where, bool *done) {
+    constexpr int r = (KS - 1) / 2;
+    const int CV = a.C / V;
+    constexpr int resident = 4 * two_stage_waves(GRAD, V, KS);
+    int CB = 0, nstrip = 1, TO = 1, nthr = 64, RS = a.H;
+    double least = 1e300;
+    for (int cb = 1; cb <= 8 && cb <= CV; ++cb) {
+        if ((cb & (cb - 1)) != 0 && cb != CV) continue;
+        const int most = kRowThreads / cb - 4 * r, n = (a.W + most - 1) / most, to = (a.W + n - 1) / n;
+        const int t = ((to + 4 * r) * cb + 63) / 64 * 64, waves = t / 64, slots = resident / waves > 0 ? resident / waves : 1;
+        const long long strips = (long long)B * n * ((CV + cb - 1) / cb);
+        for (int seg = 1; seg <= a.H; seg += seg < 8 ? 1 : seg / 4) {
+            const int rs = (a.H + seg - 1) / seg;
+            const long long per_cu = (strips * seg + 255) / 256;
+            const double rows = rs + 2 * r + 1 + (seg > 1 ? 2 * r : 0);
+            const double us = rows * (1.0 + 0.4 / cb) *
+                              ((double)(per_cu / slots) * (0.2 * V + 0.05 * slots * waves) +
+                               (per_cu % slots ? 0.2 * V + 0.05 * (per_cu % slots) * waves : 0.0));
+            if (us < least) { least = us; CB = cb; nstrip = n; TO = to; nthr = t; RS = rs; }
+        }
+    }
+    a.nchunk = (CV + CB - 1) / CB;
+    const int TC = TO + 4 * r, nseg = (a.H + RS - 1) / RS;
+    const long long strips = (long long)B * nstrip * a.nchunk;
+    if (strips * nseg > 0x7fffffffLL) return LC_OK;
+    const size_t lds = (size_t)4 * TC * CB * V * 4;
+    *done = true;
+    hipLaunchKernelGGL((lcn_channel_two_stage_kernel<GRAD, V, KS>), dim3((unsigned)(strips * nseg)), dim3(nthr), lds, s, a, TO,
+                       CB, nstrip, RS, nseg);
+    LC_HIP_LAUNCH_CHECK(where);
+    return LC_OK;
+}
+
+// Channels per work item: the wider, the fewer loads and index steps; two where four leave the chip too few waves (5 x 5 on
+// [2,12,48,64]: 8.6 us with four, 6.9 with two), and two and one where the rings of 7 and 9 rows would take the registers.
+// Large maps keep the two passes where those move the rows at the rate of memory and the one kernel re-walks too many: maps
+// narrower than the window ([175,62,4,128] 5 x 5: 43 and 44 us against 50 and 49), windows of 7 and 9 beyond 2 million
+// values ([25,116,107,32] 7 x 7: 63 and 75 us against 89 and 143; [20,43,97,32], 2.7 million, 40 and 42 against 23 and 20) and
+// the forward pass of 5 x 5 beyond 8 million ([78,88,83,32]: 97 us against 109; [132,38,44,48] 72 against 49).  The two passes
+// have no vectors where C is no multiple of four and are never faster there ([20,20,44,130]: 62 and 65 us against 25 and 35).
+template <bool GRAD>
+int launch_both_stages(const Args &a, int B, hipStream_t s, const char *where, bool *done) {
+    *done = false;
+    const long long values = (long long)B * a.H * a.W * a.C;
+    const bool pairs = a.C % 2 == 0, quads = a.C % 4 == 0 && values >= (1 << 19);
+    if (a.C % 4 == 0 && ((values > (1 << 20) && a.W < a.ks) || (values > (1 << 21) && a.ks >= 7) ||
+                         (values > (1 << 23) && a.ks == 5 && !GRAD)))
+        return LC_OK;
+#define LC_WIDTH(K, V) if (a.ks == K) return launch_two_stage<GRAD, V, K>(a, B, s, where, done)
+    if (quads) { LC_WIDTH(3, 4); if constexpr (GRAD) LC_WIDTH(5, 4); }
+    if (pairs) { LC_WIDTH(3, 2); LC_WIDTH(5, 2); LC_WIDTH(7, 2); }
+    LC_WIDTH(3, 1); LC_WIDTH(5, 1); LC_WIDTH(7, 1); LC_WIDTH(9, 1);
+#undef LC_WIDTH
+    return LC_OK;
+}
+
 }  // namespace
 
 size_t lcn_variant_scratch_bytes(int B, int H, int W, int C, unsigned flags) {
@@ -573,6 +784,9 @@ int launch_lcn_variant_fwd(const float *x, float *y, float *mu, float *rstd, int
     a.x = x; a.out = y; a.mu_out = mu; a.rstd_out = rstd; a.mu_in = mu;
     a.H = H; a.W = W; a.C = C; a.ks = ks; a.zpad = zp; a.eps = eps;
     if (!two) return launch_pass<kFwdOne>(a, B, s, "lcn_variant_fwd");
+    bool done;
+    if (int rc = launch_both_stages<false>(a, B, s, "lcn_variant_fwd (two stages)", &done)) return rc;
+    if (done) return LC_OK;
     if (int rc = launch_pass<kMean>(a, B, s, "lcn_variant_fwd (mean)")) return rc;
     return launch_pass<kDivide>(a, B, s, "lcn_variant_fwd (divide)");
 }
@@ -592,6 +806,9 @@ int launch_lcn_variant_bwd(const float *x, const float *mu, const float *rstd, c
     a.x = x; a.dy = dy; a.mu_in = mu; a.rstd_in = rstd; a.out = dx; a.field = (float *)ws;
     a.H = H; a.W = W; a.C = C; a.ks = ks; a.zpad = zp;
     if (!two) return launch_pass<kBwdOne>(a, B, s, "lcn_variant_bwd");
+    bool done;
+    if (int rc = launch_both_stages<true>(a, B, s, "lcn_variant_bwd (two stages)", &done)) return rc;
+    if (done) return LC_OK;
     if (int rc = launch_pass<kBwdTwoA>(a, B, s, "lcn_variant_bwd (dv)")) return rc;
     return launch_pass<kBwdTwoB>(a, B, s, "lcn_variant_bwd (mean)");
 }
