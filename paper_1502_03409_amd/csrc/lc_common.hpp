@@ -271,13 +271,12 @@ int launch_l2pool_fwd(const float *x, float *y, int B, int H, int W, int C, int 
 // y null: dy holds dy / y (only where the streaming or the tile kernel runs: launch_lcn_pool_bwd)
 int launch_l2pool_bwd(const float *x, const float *y, const float *dy, float *dx, int B, int H, int W, int C, int ks,
                       int st, hipStream_t s);
-// Statistics pooled over the channels.  mode 0: forward (out = y; mu, rstd written).  mode 1: backward (out = dx;
-// mu, rstd read).  modes 2..5: the passes of the two-stage form (mean; divide; gradient up to dv and the field of
-// its channel sums; dx = dv - window sum of field), field = B*H*W floats of scratch for modes 4 and 5.
+// Statistics pooled over the channels, one stage: op 0 forward (out = y; mu, rstd written), op 1 gradient (out = dx; mu, rstd
+// read); two stages: op 2 forward, op 3 gradient.
 // zero_pad: pixels outside the image count as zeros and the window keeps its full-window normalisation.
-int launch_lcn(int mode, const float *x, const float *dy, float *out, float *mu, float *rstd, int B, int H, int W,
-               int C, int ks, float sigma, float eps, hipStream_t s, int zero_pad = 0, float *field = nullptr,
-               int divx = 0);   // divx (mode 1): leave dx / x instead of dx
+int launch_lcn(int op, const float *x, const float *dy, float *out, float *mu, float *rstd, int B, int H, int W,
+               int C, int ks, float sigma, float eps, hipStream_t s, int zero_pad = 0,
+               int divx = 0);   // divx (op 1): leave dx / x instead of dx
 // 3x3 stride-1 pooling and the one-stage pooled LCN of its result in one kernel; *done: whether the shape took it
 int launch_pool_lcn_fused(const float *x, float *p, float *out, float *mu, float *rstd, int B, int H, int W, int C,
                           float peps, int ks, float sigma, float eps, hipStream_t s, bool *done);

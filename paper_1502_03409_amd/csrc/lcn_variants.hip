@@ -775,9 +775,7 @@ int launch_lcn_variant_fwd(const float *x, float *y, float *mu, float *rstd, int
                            float sigma, float eps, unsigned flags, hipStream_t s) {
     const bool pc = flags & LCN_PER_CHANNEL, zp = flags & LCN_ZERO_PAD, two = flags & LCN_TWO_STAGE;
     if (!pc) {
-        if (!two) return launch_lcn(0, x, nullptr, y, mu, rstd, B, H, W, C, ks, sigma, eps, s, zp);
-        if (int rc = launch_lcn(2, x, nullptr, y, mu, rstd, B, H, W, C, ks, sigma, eps, s, zp)) return rc;
-        return launch_lcn(3, x, nullptr, y, mu, rstd, B, H, W, C, ks, sigma, eps, s, zp);
+        return launch_lcn(two ? 2 : 0, x, nullptr, y, mu, rstd, B, H, W, C, ks, sigma, eps, s, zp);
     }
     Args a{};
     if (!make_taps(ks, sigma, &a.taps)) return LC_EINVAL;
@@ -797,9 +795,7 @@ int launch_lcn_variant_bwd(const float *x, const float *mu, const float *rstd, c
     if (two && (ws == nullptr || ws_bytes < lcn_variant_scratch_bytes(B, H, W, C, flags))) return LC_EWORKSPACE;
     float *mu_ = const_cast<float *>(mu), *rstd_ = const_cast<float *>(rstd);   // read only in these modes
     if (!pc) {
-        if (!two) return launch_lcn(1, x, dy, dx, mu_, rstd_, B, H, W, C, ks, sigma, 0.f, s, zp);
-        if (int rc = launch_lcn(4, x, dy, dx, mu_, rstd_, B, H, W, C, ks, sigma, 0.f, s, zp, (float *)ws)) return rc;
-        return launch_lcn(5, x, dy, dx, mu_, rstd_, B, H, W, C, ks, sigma, 0.f, s, zp, (float *)ws);
+        return launch_lcn(two ? 3 : 1, x, dy, dx, mu_, rstd_, B, H, W, C, ks, sigma, 0.f, s, zp);
     }
     Args a{};
     if (!make_taps(ks, sigma, &a.taps)) return LC_EINVAL;

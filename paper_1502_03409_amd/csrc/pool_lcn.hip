@@ -6,6 +6,7 @@
 // (Sec. 3.1) and is taken here as Gaussian-windowed local standardisation with statistics pooled over
 // the channels: the channel sums are wavefront reductions, the window sums a small LDS stencil.
 #include <algorithm>
+#include <type_traits>
 
 #include "lc_common.hpp"
 
@@ -416,221 +417,290 @@ __device__ __forceinline__ float tap_norm(const GaussTaps &t, int p, int n, int 
     return z;
 }
 
-// Statistics pooled over the channels.  One-stage form: MODE 0 forward, MODE 1 backward (x, mu, rstd, dy -> dx).
-// Two-stage form (subtract the window mean, divide by the root of the window mean of the neighbours' own squared
-// differences) as two passes each way:
-//   MODE 2  x -> mu;                          MODE 3  x, mu -> rstd, y = (x - mu) rstd;
-//   MODE 4  x, mu, rstd, dy -> dv (into out) and field[p] = sum_c dv[p,c] / normaliser(p);
-//   MODE 5  out = dv - window sum of field (in place).
-// DIVX (MODE 1, VEC 4): leave dx / x (as a runtime flag the compiler divided always and chose afterwards: up to 14 % of the
-// plain gradient on large maps).  Latency-bound on small maps: th x tw tiles (lcn_tile) and lpp lanes a pixel
-// (lanes_per_pixel) put two workgroups on every compute unit and several loads in flight per lane; with 16 x 16 tiles and a
-// lane for every vector of a pixel [4,70,70,384] took 180 us forward (now 27), [104,25,13,72] 53 (now 9).
-// NF: a lane's vectors of a pixel that are in flight together (1 where it has one).
-template <int VEC, int MODE, int NF, bool DIVX = false>
-__global__ __launch_bounds__(256) void lcn_kernel(const float *__restrict__ x, const float *__restrict__ dy,
-                                                  float *__restrict__ out, float *__restrict__ mu,
-                                                  float *__restrict__ rstd, float *__restrict__ field, int H, int W,
-                                                  int C, int ks, float eps, GaussTaps taps, int lpp, int th, int tw,
-                                                  int tiles_w, int tiles_per_img, int zpad) {
-    constexpr bool kTwoMaps = MODE == 0 || MODE == 1;
-    __shared__ float m1[kLcnHalo * kLcnHalo], m2[kTwoMaps ? kLcnHalo * kLcnHalo : 1];
-    __shared__ float t1[kLcnTile * kLcnTile], t2[kLcnTile * kLcnTile];
-    const int r = (ks - 1) / 2, hh = th + 2 * r, hw = tw + 2 * r;
+// Statistics pooled over the channels, tile by tile.  One stage: OP 0 forward (x -> mu, rstd, y), OP 1 gradient (x, mu, rstd,
+// dy -> dx).  Two stages (subtract the window mean, divide by the root of the window mean of the neighbours' own squared
+// differences), both in one kernel: OP 2 forward, OP 3 gradient.
+//
+// A workgroup takes a th x tw tile and a halo of one window radius, or of two.  Per-pixel sums over the channels come first:
+// lpp lanes share a pixel, and a lane has NF vectors of each of PX pixels in flight.  The window sums of those run in LDS,
+// rows first, then columns.  The two-stage forward pass forms the squared differences from the window means of tile and inner
+// halo in a second round over x; the gradient needs none: the channel sum of dv is rstd sum(dy) + 2 s sum(x - mu), s the
+// window sum of the variances' gradients.  The last round writes the tile, several vectors a lane in flight.
+//
+// VEC 4 with RAG takes channels that are no multiple of four: vectors at any element, the last one of a pixel starting at
+// C - 4 and its elements that the one before it holds left out of the sums (they are written twice, alike).  VEC 1 is left
+// for one to three channels.  DIVX (OP 1, VEC 4): leave dx / x.
+// Bound by latency on small maps (a round of loads, a reduction and two window passes, one after the other) and by the reads
+// of tile, halo and tile again on large ones.  Before, the two-stage form took two kernels each way that moved the mean, dv and its
+// channel sums through memory, window sums took KS*KS steps, a group of lanes had one pixel in flight, and channels that are no
+// multiple of four came one by one.  Over 250 maps (10 thousand to 20 million values, windows of 3 to 9): two stages 1.6 times
+// as fast forward and backward, 2.0 and 2.2 with odd channels; one stage 1.1 and 1.1, 1.7 and 1.7 with odd channels; the
+// slowest 0.92 ([5,26,60,48] forward 6.5 -> 7.1 us: one barrier more).
+constexpr int kLcnThreads = 1024;   // at most
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+template <int VEC, int OP, int NF, bool RAG, bool DIVX>
+__global__ __launch_bounds__(kLcnThreads) void lcn_pooled_kernel(const float *__restrict__ x, const float *__restrict__ dy,
+                                                         float *__restrict__ out, float *__restrict__ mu,
+                                                         float *__restrict__ rstd, int H, int W, int C, int ks, float eps,
+                                                         GaussTaps taps, int lpp, int th, int tw, int tiles_w,
+                                                         int tiles_per_img, int zpad) {
+    constexpr bool kGrad = OP == 1 || OP == 3, kTwo = OP >= 2;
+    constexpr int PX = 8 / NF / (kGrad && NF < 4 ? 2 : 1), U = kGrad ? 4 : 8;
+    const int nthr = blockDim.x;
+    extern __shared__ __attribute__((aligned(16))) float lds[];
+    __shared__ float zr[kLcnTile + 2 * kLcnMaxK], zc[kLcnTile + 2 * kLcnMaxK], gt[kLcnMaxK + 1];
+    const int r = (ks - 1) / 2, R = kTwo ? 2 * r : r, hh = th + 2 * R, hw = tw + 2 * R;
+    const int iw = tw + 2 * r, ih = th + 2 * r, hcols = hw - 2 * r;
+    float *const m1 = lds, *const m2 = m1 + hh * hw;                       // sums per pixel of tile and halo
+    float *const m3 = m2 + (OP == 2 ? 0 : hh * hw);
+    float *const h1 = m3 + (OP == 3 ? hh * hw : 0), *const h2 = h1 + hh * hcols;   // row sums
+    float *const n1 = h2 + (kTwo ? 0 : hh * hcols), *const n2 = n1 + (kTwo ? ih * iw : 0);   // inner halo: second window's
+    float *const t1 = n2 + (OP == 2 ? ih * iw : 0), *const t2 = t1 + th * tw, *const tm = t2 + th * tw, *const tr = tm + th * tw;
     const int tid = threadIdx.x;
     // each XCD walks a contiguous range of tiles: the tiles of one image, whose halos overlap, share an L2
     const int blk = remap_xcd(blockIdx.x, gridDim.x);
     const int b = blk / tiles_per_img, tile = blk - b * tiles_per_img;
     const int ti = (tile / tiles_w) * th, tj = (tile % tiles_w) * tw;
-    const int CV = C / VEC;
+    const int CV = VEC == 4 ? (C + 3) >> 2 : C;
     const size_t img = (size_t)b * H * W;
-    // window normalisers of the staged rows and columns, once per workgroup (a pixel's is their product times C)
-    __shared__ float zr[kLcnHalo], zc[kLcnHalo];
-    if (tid < hh) zr[tid] = zpad ? 1.f : tap_norm(taps, ti - r + tid, H, r);
-    else if (tid >= 64 && tid < 64 + hw) zc[tid - 64] = zpad ? 1.f : tap_norm(taps, tj - r + tid - 64, W, r);
-    if (MODE == 1 || MODE == 4) __syncthreads();   // the other modes first use them after phase 1's barrier
-    const float inv_tw = 1.0f / (float)tw;
-    auto tile_row = [&](int op) { return (int)(((float)op + 0.5f) * inv_tw); };   // op / tw, exact below 2^20
-    auto norm_at = [&](int row, int col) { return zr[row - ti + r] * zc[col - tj + r] * (float)C; };
+    if (tid < hh) zr[tid] = zpad ? 1.f : tap_norm(taps, ti - R + tid, H, r);
+    else if (tid >= 64 && tid < 64 + hw) zc[tid - 64] = zpad ? 1.f : tap_norm(taps, tj - R + tid - 64, W, r);
+    else if (tid >= 128 && tid < 128 + ks) gt[tid - 128] = taps.g[tid - 128];
+    if (kGrad) __syncthreads();
+    // a pixel's normaliser, by its place among the staged ones
+    auto norm_at = [&](int hi, int hj) { return zr[hi] * zc[hj] * (float)C; };
+    const float inv_tw = 1.0f / (float)tw, inv_hw = 1.0f / (float)hw, inv_iw = 1.0f / (float)iw, inv_hc = 1.0f / (float)hcols;
+    auto divided = [&](int a, float inv) { return (int)(((float)a + 0.5f) * inv); };   // exact below 2^20
 
-    // phase 1: per-pixel channel sums over the tile and its halo; lpp lanes share a pixel
-    const int grp = tid / lpp, gl = tid % lpp, ngrp = 256 / lpp;
     typedef float fv __attribute__((ext_vector_type(VEC == 4 ? 4 : 2)));   // VEC = 1: the second component stays zero
     auto fetch = [&](const float *p) -> fv {
-        if constexpr (VEC == 4) return *(const fv *)p;
+        if constexpr (VEC == 4 && RAG) return (fv)(*(const f32x4u *)p);
+        else if constexpr (VEC == 4) return *(const fv *)p;
         else return (fv){*p, 0.f};
     };
+    auto at = [&](int cv) { return RAG && cv == CV - 1 ? C - 4 : cv * VEC; };
     auto total = [&](const fv &v) -> float {
         if constexpr (VEC == 4) return (v[0] + v[1]) + (v[2] + v[3]);
         else return v[0];
     };
-    for (int hp = grp; hp < hh * hw; hp += ngrp) {
-        const int hi = hp / hw, hj = hp - hi * hw;
-        const int row = ti - r + hi, col = tj - r + hj;
-        float a = 0.f, c2 = 0.f;
-        const bool in = row >= 0 && row < H && col >= 0 && col < W;
-        // the pixel's own statistics are fetched with its values, not after the reduction
-        float mp = 0.f, rsp = 0.f;
-        if ((MODE == 1 || MODE == 3 || MODE == 4) && in) mp = mu[img + (size_t)row * W + col];
-        if ((MODE == 1 || MODE == 4) && in) rsp = rstd[img + (size_t)row * W + col];
-        if (MODE == 5) {
-            if (in) a = field[img + (size_t)row * W + col];
-        } else if (in) {
-            const size_t pix = img + (size_t)row * W + col;
-            const float *xp = x + pix * C, *gp = dy + pix * C;
-            for (int c0 = gl; c0 < CV; c0 += NF * lpp) {
-                fv v[NF], d[NF];
-#pragma unroll
-                for (int u = 0; u < NF; ++u) {
-                    const int cv = min(c0 + u * lpp, CV - 1);      // past the end: the last vector again, left out below
-                    v[u] = fetch(xp + cv * VEC);
-                    if (MODE == 1 || MODE == 4) d[u] = fetch(gp + cv * VEC);
-                }
-#pragma unroll
-                for (int u = 0; u < NF; ++u) {
-                    if (c0 + u * lpp >= CV) continue;
-                    fv e = v[u];
-                    if (MODE == 1 || MODE == 3 || MODE == 4) {          // differences from the pixel's own mean
-                        // value by value: a vector of four means would be waited for before the values are asked for
-#pragma unroll
-                        for (int k = 0; k < VEC; ++k) e[k] -= mp;
-                    }
-                    if (MODE == 1 || MODE == 4) {
-                        a += total(d[u]);
-                        c2 += total(d[u] * e);
-                    } else {
-                        a += MODE == 3 ? total(e * e) : total(e);
-                        if (MODE == 0) c2 += total(e * e);
-                    }
-                }
-            }
-        }
-        if (MODE != 5) a = group_sum(a, lpp);
-        if (MODE == 0 || MODE == 1 || MODE == 4) c2 = group_sum(c2, lpp);
-        if (gl == 0) {
-            if (MODE == 0) {
-                m1[hp] = a;
-                m2[hp] = c2;
-            } else if (MODE == 1) {
-                // backward: fold this pixel's own normaliser and statistics into the two maps the
-                // transposed window sums need
-                float p1 = 0.f, p2 = 0.f;
-                if (in) {
-                    const float z = norm_at(row, col);
-                    const float bc = rsp * rsp * rsp * c2;
-                    p1 = (bc * mp - rsp * a) / z;
-                    p2 = bc / z;
-                }
-                m1[hp] = p1;
-                m2[hp] = p2;
-            } else if (MODE == 4) {
-                // gradient of this pixel's variance, divided by its normaliser
-                m1[hp] = in ? -0.5f * rsp * rsp * rsp * c2 / norm_at(row, col) : 0.f;
-            } else {
-                m1[hp] = a;
-            }
-        }
-    }
-    __syncthreads();
+    const int grp = tid / lpp, gl = tid % lpp, ngrp = nthr / lpp, back = RAG ? 4 * CV - C : 0;
 
-    // phase 2: window sums, one thread per output pixel
-    {
-        const int oi = tid / tw, oj = tid - oi * tw;
-        const int row = ti + oi, col = tj + oj;
-        if (oi < th && row < H && col < W) {
-            float s1 = 0.f, s2 = 0.f;
-            for (int p = 0; p < ks; ++p)
-                for (int q = 0; q < ks; ++q) {
-                    const float wt = taps.g[p] * taps.g[q];
-                    const int hp = (oi + p) * hw + oj + q;
-                    s1 += wt * m1[hp];   // out-of-image halo entries are zero
-                    if (kTwoMaps) s2 += wt * m2[hp];
+    // A round over the pixels of an area of ph x pw at (ti - ro, tj - ro), PX of them per group of lanes in flight.
+    // SQ: sums of squared differences from n1, into n2; otherwise the sums of the first window, into m1 to m3.
+    auto round = [&](int ph, int pw, float inv_pw, int ro, auto squares) {
+        constexpr bool SQ = decltype(squares)::value;
+        for (int base = grp; base < ph * pw; base += ngrp * PX) {
+            size_t pix[PX];
+            bool in[PX];
+            float mp[PX], rsp[PX], s1[PX], s2[PX], s3[PX];
+#pragma unroll
+            for (int k = 0; k < PX; ++k) {
+                const int hp = min(base + k * ngrp, ph * pw - 1), hi = divided(hp, inv_pw), hj = hp - hi * pw;
+                const int row = ti - ro + hi, col = tj - ro + hj;
+                in[k] = row >= 0 && row < H && col >= 0 && col < W;
+                pix[k] = img + (in[k] ? (size_t)row * W + col : 0);        // outside: the image's first, left out below
+                mp[k] = rsp[k] = s1[k] = s2[k] = s3[k] = 0.f;
+                if constexpr (SQ) mp[k] = n1[hp];
+                if constexpr (kGrad) { mp[k] = mu[pix[k]]; rsp[k] = rstd[pix[k]]; }
+            }
+            for (int c0 = gl; c0 < CV; c0 += NF * lpp) {
+                fv v[PX][NF], d[kGrad ? PX : 1][NF];
+#pragma unroll
+                for (int k = 0; k < PX; ++k)
+                    if (base + k * ngrp < ph * pw)
+#pragma unroll
+                    for (int u = 0; u < NF; ++u) {
+                        const size_t o = pix[k] * C + at(min(c0 + u * lpp, CV - 1));   // past the end: the last again, left out below
+                        v[k][u] = fetch(x + o);
+                        if constexpr (kGrad) d[kGrad ? k : 0][u] = fetch(dy + o);
+                    }
+#pragma unroll
+                for (int k = 0; k < PX; ++k)
+#pragma unroll
+                    for (int u = 0; u < NF; ++u) {
+                        const int cv = c0 + u * lpp;
+                        if (cv >= CV) continue;
+                        fv e = v[k][u], dv = d[kGrad ? k : 0][u];
+                        if constexpr (SQ || kGrad) {
+#pragma unroll
+                            for (int q = 0; q < VEC; ++q) e[q] -= mp[k];
+                        }
+                        if constexpr (RAG) {
+                            const int skip = cv == CV - 1 ? back : 0;
+#pragma unroll
+                            for (int q = 0; q < 3; ++q)
+                                if (q < skip) e[q] = dv[q] = 0.f;
+                        }
+                        if constexpr (kGrad) {
+                            s1[k] += total(dv);
+                            s2[k] += total(dv * e);
+                            if (OP == 3) s3[k] += total(e);
+                        } else if constexpr (SQ) {
+                            s1[k] += total(e * e);
+                        } else {
+                            s1[k] += total(e);
+                            if (OP == 0) s2[k] += total(e * e);
+                        }
+                    }
+            }
+            for (int o = lpp >> 1; o > 0; o >>= 1) {
+#pragma unroll
+                for (int k = 0; k < PX; ++k) {
+                    s1[k] += __shfl_xor(s1[k], o, 64);
+                    if (kGrad || OP == 0) s2[k] += __shfl_xor(s2[k], o, 64);
+                    if (OP == 3) s3[k] += __shfl_xor(s3[k], o, 64);
                 }
-            const size_t pix = img + (size_t)row * W + col;
-            if (MODE == 0) {
-                const float z = norm_at(row, col);
-                const float m = s1 / z, q2 = s2 / z;
-                const float var = fmaxf(q2 - m * m, 0.f);
+            }
+            if (gl != 0) continue;
+#pragma unroll
+            for (int k = 0; k < PX; ++k) {
+                const int hp = base + k * ngrp;
+                if (hp >= ph * pw) continue;
+                if constexpr (SQ) {
+                    n2[hp] = in[k] ? s1[k] : 0.f;
+                } else if constexpr (!kGrad) {
+                    m1[hp] = in[k] ? s1[k] : 0.f;
+                    if (OP == 0) m2[hp] = in[k] ? s2[k] : 0.f;
+                } else {
+                    const int hi = divided(hp, inv_pw), hj = hp - hi * pw;
+                    const float z = norm_at(hi, hj), bc = rsp[k] * rsp[k] * rsp[k] * s2[k];
+                    if (OP == 1) {
+                        // this pixel's own normaliser and statistics, folded into the two maps of the transposed window sums
+                        m1[hp] = in[k] ? (bc * mp[k] - rsp[k] * s1[k]) / z : 0.f;
+                        m2[hp] = in[k] ? bc / z : 0.f;
+                    } else {
+                        m1[hp] = in[k] ? -0.5f * bc / z : 0.f;            // gradient of its variance, over its normaliser
+                        m2[hp] = rsp[k] * s1[k];
+                        m3[hp] = s3[k];
+                    }
+                    const int oi = hi - ro, oj = hj - ro;
+                    if (oi >= 0 && oi < th && oj >= 0 && oj < tw) { tm[oi * tw + oj] = mp[k]; tr[oi * tw + oj] = rsp[k]; }
+                }
+            }
+        }
+    };
+    // window sums along the rows: of mh x (ow + 2r) values, mh x ow
+    auto along = [&](const float *m, const float *q, float *h, float *hq, int mh, int ow, float inv_ow, auto both) {
+        constexpr bool TWO = decltype(both)::value;
+        const int mw = ow + 2 * r;
+        for (int e = tid; e < mh * ow; e += nthr) {
+            const int i = divided(e, inv_ow), o = i * mw + (e - i * ow) + r;
+            float s = gt[r] * m[o], s2 = TWO ? gt[r] * q[o] : 0.f;
+#pragma unroll 2
+            for (int d = 1; d <= r; ++d) {
+                const float g = gt[r + d];
+                s += g * (m[o - d] + m[o + d]);
+                if (TWO) s2 += g * (q[o - d] + q[o + d]);
+            }
+            h[e] = s;
+            if (TWO) hq[e] = s2;
+        }
+    };
+    // and down a column of them, around element o
+    auto down = [&](const float *h, int o, int ow) -> float {
+        float s = gt[r] * h[o];
+#pragma unroll 2
+        for (int d = 1; d <= r; ++d) s += gt[r + d] * (h[o - d * ow] + h[o + d * ow]);
+        return s;
+    };
+
+    round(hh, hw, inv_hw, R, std::false_type{});
+    __syncthreads();
+    along(m1, m2, h1, h2, hh, hcols, inv_hc, std::bool_constant<!kTwo>{});
+    __syncthreads();
+    if constexpr (!kTwo) {
+        for (int e = tid; e < th * tw; e += nthr) {
+            const int oi = divided(e, inv_tw), oj = e - oi * tw, row = ti + oi, col = tj + oj;
+            if (row >= H || col >= W) continue;
+            const float s1 = down(h1, e + r * tw, tw), s2 = down(h2, e + r * tw, tw);
+            if (OP == 0) {
+                const float z = norm_at(oi + R, oj + R), m = s1 / z, var = fmaxf(s2 / z - m * m, 0.f);
                 const float rs = 1.0f / sqrtf(var + eps);
+                const size_t pix = img + (size_t)row * W + col;
                 mu[pix] = m;
                 rstd[pix] = rs;
-                t1[tid] = m;
-                t2[tid] = rs;
-            } else if (MODE == 2) {
-                mu[pix] = s1 / norm_at(row, col);
-            } else if (MODE == 3) {
-                const float rs = 1.0f / sqrtf(s1 / norm_at(row, col) + eps);
-                rstd[pix] = rs;
-                t1[tid] = mu[pix];
-                t2[tid] = rs;
+                t1[e] = m;
+                t2[e] = rs;
             } else {
-                t1[tid] = s1;
-                t2[tid] = s2;
+                t1[e] = s1;
+                t2[e] = s2;
+            }
+        }
+    } else {
+        for (int e = tid; e < ih * iw; e += nthr) {
+            const int i = divided(e, inv_iw), j = e - i * iw, row = ti - r + i, col = tj - r + j;
+            const bool in = row >= 0 && row < H && col >= 0 && col < W, own = in && i >= r && i < r + th && j >= r && j < r + tw;
+            const float s = down(h1, e + r * iw, iw), z = norm_at(i + r, j + r);
+            if (OP == 2) {
+                const float m = in ? s / z : 0.f;
+                n1[e] = m;
+                if (own) {
+                    mu[img + (size_t)row * W + col] = m;
+                    t1[(i - r) * tw + j - r] = m;
+                }
+            } else {
+                const int o = (i + r) * hw + j + r;
+                n1[e] = in ? (m2[o] + 2.f * s * m3[o]) / z : 0.f;
+                if (own) t2[(i - r) * tw + j - r] = 2.f * s;
+            }
+        }
+        __syncthreads();
+        if constexpr (OP == 2) {
+            round(ih, iw, inv_iw, r, std::true_type{});
+            __syncthreads();
+        }
+        along(OP == 2 ? n2 : n1, nullptr, h1, nullptr, ih, tw, inv_tw, std::false_type{});
+        __syncthreads();
+        for (int e = tid; e < th * tw; e += nthr) {
+            const int oi = divided(e, inv_tw), oj = e - oi * tw, row = ti + oi, col = tj + oj;
+            if (row >= H || col >= W) continue;
+            const float s = down(h1, e + r * tw, tw);
+            if (OP == 2) {
+                const float rs = 1.0f / sqrtf(s / norm_at(oi + R, oj + R) + eps);
+                rstd[img + (size_t)row * W + col] = rs;
+                t2[e] = rs;
+            } else {
+                t1[e] = s;
             }
         }
     }
-    if (MODE == 2) return;
     __syncthreads();
 
-    if (MODE == 4) {
-        // phase 3 of the two-stage gradient: a pixel's lanes, here as many as write whole lines, write dv and reduce it over
-        // the channels
-        int lp3 = 1;
-        while (lp3 < CV && lp3 < 64) lp3 <<= 1;
-        const int g3 = tid / lp3, l3 = tid % lp3, n3 = 256 / lp3;
-        for (int op = g3; op < th * tw; op += n3) {
-            const int oi = tile_row(op), oj = op - oi * tw;
+    // the tile's outputs
+    const int count = th * tw * CV;
+    for (int e0 = tid; e0 < count; e0 += nthr * U) {
+        fv xv[U], d[kGrad ? U : 1];
+        size_t o[U];
+        int op[U];
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            const int e = e0 + nthr * k;
+            op[k] = -1;
+            if (e >= count) continue;
+            const int px = e / CV, cv = e - px * CV, oi = divided(px, inv_tw), oj = px - oi * tw;
             const int row = ti + oi, col = tj + oj;
-            if (row >= H || col >= W) continue;   // uniform over the group
-            const size_t pix = img + (size_t)row * W + col;
-            const float rs = rstd[pix], m = mu[pix], gs = 2.f * t1[op];
-            float acc = 0.f;
-            for (int cv = l3; cv < CV; cv += lp3) {
-                const size_t o = pix * C + cv * VEC;
-                const fv xv = fetch(x + o), d = fetch(dy + o), g = d * rs + (xv - m) * gs;
-                if constexpr (VEC == 4) *(fv *)(out + o) = g;
-                else out[o] = g[0];
-                acc += total(g);
-            }
-            acc = group_sum(acc, lp3);
-            if (l3 == 0) field[pix] = acc / norm_at(row, col);
+            if (row >= H || col >= W) continue;
+            op[k] = px;
+            o[k] = (img + (size_t)row * W + col) * C + at(cv);
+            xv[k] = fetch(x + o[k]);
+            if constexpr (kGrad) d[kGrad ? k : 0] = fetch(dy + o[k]);
         }
-        return;
-    }
-
-    // phase 3: elementwise pass over the tile
-    for (int e = tid; e < th * tw * CV; e += 256) {
-        const int op = e / CV, cv = e - op * CV;
-        const int oi = tile_row(op), oj = op - oi * tw;
-        const int row = ti + oi, col = tj + oj;
-        if (row >= H || col >= W) continue;
-        const size_t pix = img + (size_t)row * W + col;
-        const size_t o = pix * C + cv * VEC;
-        const float u = t1[op], v = t2[op];
-        if (MODE == 0 || MODE == 3) {
-            if (VEC == 4) {
-                const float4 xv = *(const float4 *)(x + o);
-                *(float4 *)(out + o) = make_float4((xv.x - u) * v, (xv.y - u) * v, (xv.z - u) * v, (xv.w - u) * v);
+#pragma unroll
+        for (int k = 0; k < U; ++k) {
+            if (op[k] < 0) continue;
+            const float u = t1[op[k]], v = t2[op[k]];
+            fv g;
+            if constexpr (!kGrad) {
+                g = (xv[k] - u) * v;
             } else {
-                out[o] = (x[o] - u) * v;
+                const fv dv = d[kGrad ? k : 0];
+                if (OP == 1) g = dv * tr[op[k]] + u - xv[k] * v;
+                else g = dv * tr[op[k]] + (xv[k] - tm[op[k]]) * v - u;
+                if constexpr (DIVX) g = g / xv[k];            // the quotient the pooling gradient takes (x is its output)
             }
-        } else if (MODE == 1) {
-            const float rs = rstd[pix];
-            if (VEC == 4) {
-                const fv xv = fetch(x + o), d = fetch(dy + o);
-                fv g = d * rs + u - xv * v;
-                if constexpr (DIVX) g = g / xv;       // the quotient the pooling gradient takes (x is its output)
-                *(fv *)(out + o) = g;
-            } else {
-                out[o] = dy[o] * rs + u - x[o] * v;
-            }
-        } else {   // MODE 5
-            if (VEC == 4) {
-                const float4 d = *(const float4 *)(out + o);
-                *(float4 *)(out + o) = make_float4(d.x - u, d.y - u, d.z - u, d.w - u);
-            } else {
-                out[o] -= u;
-            }
+            if constexpr (VEC == 4 && RAG) *(f32x4u *)(out + o[k]) = g;
+            else if constexpr (VEC == 4) *(fv *)(out + o[k]) = g;
+            else out[o[k]] = g[0];
         }
     }
 }
@@ -1050,15 +1120,25 @@ bool make_taps(int ks, float sigma, GaussTaps *t) {
     return true;
 }
 
-// Lanes that share a pixel in the tile kernel: about a third of its vectors, so that a lane has several loads in flight and
-// the workgroup many pixels at once (one vector a lane: one load and a reduction at a time, 13 times one after the other on
-// a 16 x 16 tile of 32 channels).  The gradients' two arrays on maps of fewer than 48 channels whose three arrays the 256 MB
-// Infinity Cache does not hold: a lane for every vector, whose wave reads whole lines from HBM ([105,251,58,20] 168 us with
-// the former, 119 with this; [102,56,209,44] 284 and 201; [151,24,199,24], a quarter of the cache each, 61 and 72).
-int lanes_per_pixel(int cv, bool whole_lines) {
+// Lanes that share a pixel in the tile kernel, and how many of its vectors each has in flight (*nf): four where a pixel has
+// them, and as few lanes as take the pixel at once (fewer lanes reduce in fewer steps); half of them, and two rounds, where over
+// two fifths would be idle ([158,6,52,72]: 15.4 us with eight lanes, 14.4 with four).  The gradients' two arrays on maps of
+// fewer than 48 channels whose three arrays the 256 MB Infinity Cache does not hold: a lane for every vector, whose wave reads
+// whole lines from HBM ([105,251,58,20] 168 us with the former, 119 with this; [102,56,209,44] 284 and 201; [151,24,199,24], a
+// quarter of the cache each, 61 and 72).
+int lanes_per_pixel(int cv, bool whole_lines, int *nf) {
+    *nf = whole_lines || cv == 1 ? 1 : cv == 2 ? 2 : 4;
     int l = 1;
-    while ((whole_lines ? l < cv : 6 * l <= cv) && l < 64) l <<= 1;
-    return l;
+    while (l * *nf < cv && l < 64) l <<= 1;
+    return *nf == 4 && l > 1 && 5 * cv <= 3 * l * *nf ? l / 2 : l;
+}
+
+// Threads of a workgroup: more where its lanes would have over 16 vectors each, one after the other, and the chip holds few
+// workgroups (two-stage gradient of [1,34,5,384], 7 x 7: 65 us with 256 threads on its few tiles, 32 with 1024).
+int lcn_threads(int pixels, int cv, int arrays, long long workgroups) {
+    int n = 256;
+    while (n < kLcnThreads && (long long)pixels * cv * arrays > 16LL * n && workgroups * n * 2 <= 256LL * 1024) n *= 2;
+    return n;
 }
 
 // Tile of the tile kernel: at most 16 x 16 pixels, the image split evenly; halved, the longer side first, until there are two
@@ -1263,7 +1343,7 @@ int launch_lcn_pool_bwd(const float *x, const float *p, const float *mu, const f
     const bool quotient = pool_bwd_streams(B, H, W, C, pks, pst) || (C % 4 == 0 && pst == 1 && pks <= kPoolMaxK &&
                                                                    patch_bytes <= 64 * 1024 && (long long)B * th * tw <= 0x7fffffffLL);
     if (int rc = launch_lcn(1, p, dn, scratch, const_cast<float *>(mu), const_cast<float *>(rstd), B, Ho, Wo, C, ks, sigma,
-                            0.f, s, 0, nullptr, quotient))
+                            0.f, s, 0, quotient))
         return rc;
     return launch_l2pool_bwd(x, quotient ? nullptr : p, scratch, dx, B, H, W, C, pks, pst, s);
 }
@@ -1329,53 +1409,62 @@ int launch_pool_lcn_fused(const float *x, float *p, float *out, float *mu, float
 #undef LC_PLB
 }
 
-int launch_lcn(int mode, const float *x, const float *dy, float *out, float *mu, float *rstd, int B, int H, int W,
-               int C, int ks, float sigma, float eps, hipStream_t s, int zero_pad, float *field, int divx) {
+// op: 0 and 1 one stage, forward and gradient; 2 and 3 two stages
+int launch_lcn(int op, const float *x, const float *dy, float *out, float *mu, float *rstd, int B, int H, int W,
+               int C, int ks, float sigma, float eps, hipStream_t s, int zero_pad, int divx) {
     GaussTaps taps;
     if (!make_taps(ks, sigma, &taps)) return LC_EINVAL;
-    if (mode < 0 || mode > 5 || ((mode == 4 || mode == 5) && field == nullptr)) return LC_EINVAL;
+    if (op < 0 || op > 3) return LC_EINVAL;
     const int tiles_h = (H + kLcnTile - 1) / kLcnTile, tiles_w = (W + kLcnTile - 1) / kLcnTile;
     const long long nblk = (long long)B * tiles_h * tiles_w;
     if (nblk > 0x7fffffffLL) return LC_EUNSUPPORTED;
-    if (mode == 0 || mode == 1) {
+    if (op < 2) {
         bool done = false;
-        const int rc = launch_lcn_band(mode, x, dy, out, mu, rstd, B, H, W, C, ks, eps, taps, s, zero_pad, &done, divx);
+        const int rc = launch_lcn_band(op, x, dy, out, mu, rstd, B, H, W, C, ks, eps, taps, s, zero_pad, &done, divx);
         if (done) return rc;
     }
-    const int vec = (C % 4 == 0) ? 4 : 1;
+    const int vec = C >= 4 ? 4 : 1, CV = vec == 4 ? (C + 3) / 4 : C;
     int th, tw;
     lcn_tile(B, H, W, (ks - 1) / 2, &th, &tw);
     const int tw_n = (W + tw - 1) / tw, t_img = (H + th - 1) / th * tw_n;
     if ((long long)B * t_img > 0x7fffffffLL) return LC_EUNSUPPORTED;
     const bool large = C < 48 && (long long)B * H * W * C >= 24LL << 20;
-    const int lpp = lanes_per_pixel(C / vec, vec == 4 && (mode == 1 || mode == 4) && large);
-    dim3 grid((unsigned)nblk), tgrid((unsigned)((long long)B * t_img)), block(256);
-#define LC_LCN(...)                                                                                                 \
-    hipLaunchKernelGGL((lcn_kernel<__VA_ARGS__>), tgrid, block, 0, s, x, dy, out, mu, rstd, field, H, W, C, ks, eps, \
+    int nf;
+    const int lpp = lanes_per_pixel(CV, C % 4 == 0 && (op & 1) && large, &nf);
+    dim3 grid((unsigned)nblk), tgrid((unsigned)((long long)B * t_img));
+    const int R = op >= 2 ? ks - 1 : (ks - 1) / 2, hh = th + 2 * R, hw = tw + 2 * R, inner = (th + ks - 1) * (tw + ks - 1);
+    const int hrows = hh * (hw - (ks - 1));
+    const int nthr = lcn_threads(hh * hw, CV, (op & 1) + 1, (long long)B * t_img);
+    const size_t lds = sizeof(float) * (4 * th * tw + (op < 2 ? 2 * hh * hw + 2 * hrows
+                                                        : op == 2 ? hh * hw + hrows + 2 * inner : 3 * hh * hw + hrows + inner));
+#define LC_LCN(...)                                                                                                   \
+    hipLaunchKernelGGL((lcn_pooled_kernel<__VA_ARGS__>), tgrid, dim3(nthr), lds, s, x, dy, out, mu, rstd, H, W, C, ks, eps, \
                        taps, lpp, th, tw, tw_n, t_img, zero_pad)
-#define LC_LCN_MODE(MODE_)                                             \
-    do {                                                               \
-        if (vec == 4 && lpp >= C / 4) LC_LCN(4, MODE_, 1);             \
-        else if (vec == 4) LC_LCN(4, MODE_, 4);                        \
-        else LC_LCN(1, MODE_, 4);                                      \
+#define LC_LCN_OP(OP_)                                                  \
+    do {                                                                \
+        if (vec == 1) LC_LCN(1, OP_, 4, false, false);                  \
+        else if (C % 4 == 0 && nf == 1) LC_LCN(4, OP_, 1, false, false); \
+        else if (C % 4 == 0 && nf == 2) LC_LCN(4, OP_, 2, false, false); \
+        else if (C % 4 == 0) LC_LCN(4, OP_, 4, false, false);           \
+        else if (nf == 2) LC_LCN(4, OP_, 2, true, false);               \
+        else LC_LCN(4, OP_, 4, true, false);                            \
     } while (0)
 #define LC_LCN_CACHED(LPP_)                                                                                    \
-    hipLaunchKernelGGL((lcn_fwd_cached_kernel<LPP_>), grid, block, 0, s, x, out, mu, rstd, H, W, ks, eps, taps, \
+    hipLaunchKernelGGL((lcn_fwd_cached_kernel<LPP_>), grid, dim3(256), 0, s, x, out, mu, rstd, H, W, ks, eps, taps, \
                        tiles_w, tiles_h * tiles_w, zero_pad)
-    if (mode == 0 && C == 32) LC_LCN_CACHED(8);
-    else if (mode == 0 && C == 16) LC_LCN_CACHED(4);
-    else if (mode == 0 && C == 8) LC_LCN_CACHED(2);
-    else if (mode == 0) LC_LCN_MODE(0);
-    else if (mode == 1 && divx && vec != 4) return LC_EINTERNAL;   // the quotient is asked for with whole vectors only
-    else if (mode == 1 && divx && lpp >= C / 4) LC_LCN(4, 1, 1, true);
-    else if (mode == 1 && divx) LC_LCN(4, 1, 4, true);
-    else if (mode == 1) LC_LCN_MODE(1);
-    else if (mode == 2) LC_LCN_MODE(2);
-    else if (mode == 3) LC_LCN_MODE(3);
-    else if (mode == 4) LC_LCN_MODE(4);
-    else LC_LCN_MODE(5);
+    if (op == 0 && C == 32) LC_LCN_CACHED(8);
+    else if (op == 0 && C == 16) LC_LCN_CACHED(4);
+    else if (op == 0 && C == 8) LC_LCN_CACHED(2);
+    else if (op == 0) LC_LCN_OP(0);
+    else if (op == 1 && divx && C % 4 != 0) return LC_EINTERNAL;   // the quotient is asked for with whole vectors only
+    else if (op == 1 && divx && nf == 1) LC_LCN(4, 1, 1, false, true);
+    else if (op == 1 && divx && nf == 2) LC_LCN(4, 1, 2, false, true);
+    else if (op == 1 && divx) LC_LCN(4, 1, 4, false, true);
+    else if (op == 1) LC_LCN_OP(1);
+    else if (op == 2) LC_LCN_OP(2);
+    else LC_LCN_OP(3);
 #undef LC_LCN_CACHED
-#undef LC_LCN_MODE
+#undef LC_LCN_OP
 #undef LC_LCN
     LC_HIP_LAUNCH_CHECK("lcn launch");
     return LC_OK;
