@@ -230,10 +230,11 @@ int launch_backward_data_simple(const Geom &g, const void *dy, const void *w, fl
 // bf16 storage, for nearly every other shape the general kernels, and for the rest the masked fp32 kernels on bf16 storage.
 //
 // Where the general kernels come first (both sides measured on some 130 layers):
-//  - forward: instead of the strip kernel where that has fewer workgroups than the chip compute units (faster on all of 28
-//    layers, by up to six times: 96 images of 19 x 20 x 16, 15 x 15 at stride 1, 64 filters 107 -> 16 us; at 300 workgroups
-//    17.9 against 21.7 on 300 images of 12 x 14 x 16, 4 x 4 at stride 2, 384 filters; from 350 on 26 of 42 are slower, by up
-//    to 1.9 times), and instead of the one-wave-per-task kernel but for patches of at most 128 elements (128
+//  - forward: instead of the strip kernel where that has fewer workgroups than the chip compute units (24 to 255 of them: faster
+//    or the same on 48 of 58 layers, 1.23 times on average and up to four: 45 images of 73 x 15 x 8, 14 x 14 at stride 6, 80
+//    filters 63 -> 16 us; the other ten, most at stride 1, are up to 2.1 times slower: 64 images of 31 x 32 x 4, 16 x 16, 96
+//    filters 34.5 against 71; from 264 workgroups on the strip kernel is faster: 147 images of 20 x 91 x 8, 6 x 6 at stride 2,
+//    16 filters 15.4), and instead of the one-wave-per-task kernel but for patches of at most 128 elements (128
 //    images of 36 x 54 x 32, 16 x 16 at stride 2, 64 filters 470 -> 151 us; 16 of 84 x 76 x 8, 4 x 4 at stride 2: 7.2
 //    against 8.8 us);
 //  - backward data: instead of the one-wave-per-task kernel (10 layers of 11 faster, by 1.2 to 3.4 times: 32 images of

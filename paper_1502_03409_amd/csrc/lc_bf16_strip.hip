@@ -3,16 +3,22 @@
 // (Sec. 3.1's untied fields overlap by R-S pixels, so a strip of adjacent fields shares the image rows it reads) and
 // v_mfma_f32_16x16x16_bf16 in place of the fp32 matrix instruction.
 //
-// Workgroup = NLOC adjacent fields of one field row x a batch tile of 16*MT images x NW/NLOC blocks of 16*NT filters.
-// A chunk is CQ values of one patch row for all fields of the strip, staged in LDS as bf16 (8-byte stores and reads);
-// the next chunk's strip travels through registers meanwhile.  The contraction runs in blocks of 16 patch values:
-// lane (m,kk) reads the four values 16 blk + 4 kk .. +3 of image m from LDS; lane (n,kk) loads the NT filters
+// Workgroup = 4 adjacent fields of one field row, one per wave, x a batch tile of 16*MT images x 16*NT filters.  A chunk is
+// CQ values of one patch row: the strip of x that the four fields share and each field's weight rows, both loaded into
+// registers while the chunk before is computed and written to LDS between two barriers.  The contraction runs in blocks of
+// 16 patch values: lane (m,kk) reads the four values 16 blk + 4 kk .. +3 of image m; lane (n,kk) reads the NT filters
 // f0 + NT n .. of the four weight rows 16 blk + 4 kk .. +3 (the filters are the fast index of w, the patch values the
 // slow one) and transposes them in registers into NT operands of four consecutive patch values each.  A patch row
 // that is not a multiple of 16 ends in a partial block: its lanes beyond the row feed zeros as weights (the LDS
-// holds the neighbouring field's pixels there).  The weights of a whole chunk are in flight ahead of their use.
-#include <algorithm>
-
+// holds the neighbouring field's pixels there).
+//
+// What bounds it is the number of loads a compute unit can have outstanding beyond L2, so they are few and wide: a lane
+// takes 16 bytes of one weight row, an instruction whole lines (asked for as the NT filters of each lane, each line came in
+// two to four pieces), and none is conditional.  Weight row r of a block lies in LDS at r % 4, r / 4: a wave's read of "row
+// 4 kk + jj, filters NT n .." is 128 NT contiguous bytes.  128 images of 200 x 200 x 3, 20 x 20 at stride 4, 32 filters:
+// 183 -> 107 us with operands out of the caches, 109 -> 72 with what fits them; 120 layers drawn from 17 to 256 images and 16
+// to 128 filters: 1.40 times (geometric mean, 0.94 to 2.28) against weights from global memory by the lane that multiplies
+// them.  Single blocks of 16 filters on 32 images gain least: 32-byte pieces of a line go to different workgroups.
 #include "lc_common.hpp"
 
 namespace lc {
@@ -37,30 +43,32 @@ __device__ __forceinline__ void rows_to_operands(const typename RawVec<bf16_t, N
     }
 }
 
-template <int MT, int NT, int NLOC, int NB, int NW>
-__global__ __launch_bounds__(64 * NW, NT == 4 ? 2 : 3) void lc_forward_bf16_strip_kernel(Geom g, const bf16_t *__restrict__ x,
-                                                                            const bf16_t *__restrict__ w,
-                                                                            const float *__restrict__ bias, float alpha,
-                                                                            float *__restrict__ y, int strips_per_row,
-                                                                            int CQ, int sq4, int RS, int nbt,
-                                                                            int work_first) {
+template <int MT, int NT, int NB, int NS, int OCC>
+__global__ __launch_bounds__(256, OCC) void lc_forward_bf16_staged_kernel(Geom g, const bf16_t *__restrict__ x,
+                                                                       const bf16_t *__restrict__ w,
+                                                                       const float *__restrict__ bias, float alpha,
+                                                                       float *__restrict__ y, int strips_per_row,
+                                                                       int CQ, int sq4, int RS, int nbt, int nslots) {
     typedef typename RawVec<bf16_t, NT>::V WV;    // NT consecutive filters of one weight row
     typedef typename FVec<NT>::T OV;              // NT consecutive outputs
-    typedef const __attribute__((address_space(1))) WV *gw_ptr;
+    typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+    typedef const __attribute__((address_space(1))) u32x4 *gw_ptr;
     typedef const __attribute__((address_space(1))) u32x2 *gx4_ptr;
-    typedef const __attribute__((address_space(1))) bf16_t *gt_ptr;
-    constexpr int BT = 16 * MT, NFW = NW / NLOC, NTHR = 64 * NW;
-    extern __shared__ __attribute__((aligned(16))) bf16_t xh[];      // [BT][RS]: the staged strip of one chunk
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    typedef const __attribute__((address_space(1))) char *gc_ptr;
+    constexpr int NLOC = 4, BT = 16 * MT, NTHR = 64 * NLOC;
+    constexpr int LPR = 2 * NT, RPL = 64 / LPR;              // lanes per weight row, rows per load
+    constexpr int NL = (16 * NB + RPL - 1) / RPL;            // loads per wave and chunk
+    constexpr int FB = 16 * NB * 16 * NT;                    // staged weights of a field, in values
+    extern __shared__ __attribute__((aligned(16))) bf16_t xh[];      // [BT][RS] strip, then [NLOC][FB] weights
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, kk = lane >> 4;
     // batch tiles of one strip are neighbours in dispatch order on the same XCD
     const int t_id = remap_xcd(blockIdx.x, gridDim.x);
-    const int work = work_first + t_id / nbt;
+    const int work = t_id / nbt;
     const int i = work / strips_per_row, j0 = (work - i * strips_per_row) * NLOC;
     const int b0 = (t_id % nbt) * BT;
-    const int wl = wave % NLOC, wf = wave / NLOC;
-    const int j = j0 + wl;
-    const int f0 = (blockIdx.y * NFW + wf) * NT * 16;
+    const int j = j0 + wave;
+    const int f0 = blockIdx.y * NT * 16;
     const bool active = j < g.LW;
     const int loc = i * g.LW + (active ? j : g.LW - 1);   // idle waves shadow the last field of the row
     const int SC = g.S * g.C, WC = g.W * g.C;
@@ -72,99 +80,96 @@ __global__ __launch_bounds__(64 * NW, NT == 4 ? 2 : 3) void lc_forward_bf16_stri
 #pragma unroll
         for (int u = 0; u < NT; ++u) acc[mt][u] = (f32x4){0.f, 0.f, 0.f, 0.f};
 
-    // staging map: slot q of this thread copies 4-value vector number e = tid + NTHR*q of the [BT][sq4] chunk.
-    // sb[q] = image << 16 | value offset in the row; bit 31: past the end of the chunk, bit 30: image beyond B.
+    // staging map: slot q of this thread copies 4-value vector number e = tid + NTHR*q of the [BT][sq4] chunk.  Lanes past
+    // the chunk's end, images beyond B and values beyond the last field of the row repeat the nearest one that exists (goff,
+    // loff: bytes), so that no load or store is conditional but for whole slots.
     const int sqc = sq4 * 4;
-    const int nslots = (BT * sq4 + NTHR - 1) / NTHR;
-    int sb[kStripSlots];
-    {
-        int vv = tid % sq4, b = tid / sq4;
-        const int dv = NTHR % sq4, db = NTHR / sq4;
+    const int vmax = (min(NLOC, g.LW - j0) - 1) * SC + CQ;   // values that the strip's fields read
+    unsigned goff[NS], loff[NS];
 #pragma unroll
-        for (int q = 0; q < kStripSlots; ++q) {
-            sb[q] = (b << 16) | (vv * 4);
-            if (b >= BT) sb[q] = (int)0x80000000;
-            else if (b0 + b >= g.B) sb[q] |= 0x40000000;
-            vv += dv; b += db;
-            if (vv >= sq4) { vv -= sq4; ++b; }
+    for (int q = 0; q < NS; ++q) {
+        const int e = min(tid + NTHR * q, BT * sq4 - 1);
+        const int b = e / sq4, v = min(4 * (e - b * sq4), vmax - 4);
+        goff[q] = 2u * ((unsigned)min(b, g.B - 1 - b0) * (unsigned)img + v);
+        loff[q] = 2u * (b * RS + v);
+    }
+    // a partial last block reads up to 12 values past a field's window: those lanes' weights are zeros, and the LDS
+    // behind the last field is cleared once so that no stale bit pattern (a NaN) meets them
+    {
+        const int nclr = (sqc + 16 - vmax) >> 2;
+        for (int e = tid; e < BT * nclr; e += NTHR) {
+            const int b = e / nclr;
+            *(u32x2 *)(xh + b * RS + vmax + 4 * (e - b * nclr)) = (u32x2){0u, 0u};
         }
     }
-    // a partial last block reads up to 12 values past the staged row: those lanes' weights are zeros, and the LDS
-    // there is cleared once so that no stale bit pattern (a NaN) meets them
-    for (int e = tid; e < BT * 4; e += NTHR) *(u32x2 *)(xh + (e >> 2) * RS + sqc + 4 * (e & 3)) = (u32x2){0u, 0u};
-    const int col0 = j0 * SC;
-    u32x2 st[kStripSlots];
+    const gc_ptr xrow = (gc_ptr)(x + (size_t)b0 * img + (size_t)(i * g.S) * WC + j0 * SC);
+    u32x2 st[NS];
     auto stage_load = [&](int kh, int sc) {
-        const bf16_t *row = x + (size_t)b0 * img + (size_t)(i * g.S + kh) * WC + col0 + sc * CQ;
-        const int lim = WC - col0 - sc * CQ;          // values of this image row that exist from the chunk start on
+        const gc_ptr row = xrow + 2 * ((size_t)kh * WC + sc * CQ);
 #pragma unroll
-        for (int q = 0; q < kStripSlots; ++q) {
-            if (q < nslots) {
-                const int b = (sb[q] >> 16) & 0x3fff, v = sb[q] & 0xffff;
-                u32x2 t = (u32x2){0u, 0u};
-                if ((sb[q] & 0xc0000000) == 0 && v < lim) t = *(gx4_ptr)(row + (size_t)b * img + v);
-                st[q] = t;
-            }
-        }
+        for (int q = 0; q < NS; ++q)
+            if (q < nslots) st[q] = *(gx4_ptr)(row + goff[q]);
     };
     auto stage_store = [&]() {
 #pragma unroll
-        for (int q = 0; q < kStripSlots; ++q) {
-            if (q < nslots && sb[q] >= 0) {
-                const int b = (sb[q] >> 16) & 0x3fff, v = sb[q] & 0xffff;
-                *(u32x2 *)(xh + b * RS + v) = st[q];
-            }
-        }
+        for (int q = 0; q < NS; ++q)
+            if (q < nslots) *(u32x2 *)((char *)xh + loff[q]) = st[q];
     };
-
-    // weights of block blk of the chunk that starts at patch value kbase: rows kbase + 16 blk + 4 kk + jj, clamped
-    // into the field's matrix (rows beyond the patch row are multiplied by zeros or zeroed below)
-    gt_ptr wfield = (gt_ptr)w + (size_t)loc * g.K * g.F + f0 + NT * n;
-    WV wr[NB][4];
-    auto load_block = [&](int kbase, int blk) {
+    // weights: load q of this wave holds row RPL q + lane / LPR of the chunk, filters 8 (lane % LPR) ..; rows past
+    // the chunk repeat its last one
+    const gc_ptr wfield = (gc_ptr)(w + (size_t)loc * g.K * g.F + f0);
+    bf16_t *wlds = xh + (size_t)BT * RS + wave * FB;
+    u32x4 wr[NL];
+    auto weights_load = [&](int kbase) {
+        const gc_ptr base = wfield + 2 * (size_t)kbase * g.F;
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-            int k = kbase + 16 * blk + 4 * kk + jj;
-            k = k < g.K ? k : g.K - 1;
-            wr[blk][jj] = *(gw_ptr)(wfield + (size_t)k * g.F);
+        for (int q = 0; q < NL; ++q) {
+            const int r = min(RPL * q + lane / LPR, CQ - 1);
+            wr[q] = *(gw_ptr)(base + 2u * (unsigned)(r * g.F + 8 * (lane % LPR)));
+        }
+    };
+    auto weights_store = [&]() {
+#pragma unroll
+        for (int q = 0; q < NL; ++q) {
+            const int r = RPL * q + lane / LPR, at = (r & ~15) | ((r & 3) << 2) | ((r >> 2) & 3);
+            if (16 * NB % RPL == 0 || r < 16 * NB) *(u32x4 *)(wlds + at * 16 * NT + 8 * (lane % LPR)) = wr[q];
         }
     };
 
-    const bf16_t *xwin = xh + (size_t)(lane & 15) * RS + wl * SC + 4 * kk;
+    const bf16_t *xwin = xh + n * RS + wave * SC + 4 * kk;
+    const bf16_t *wwin = wlds + kk * 16 * NT + n * NT;
     const int nsub = g.RC / CQ, nchunks = g.R * nsub;
-#pragma unroll
-    for (int blk = 0; blk < NB; ++blk)
-        if (16 * blk < CQ) load_block(0, blk);
     stage_load(0, 0);
+    weights_load(0);
+    int kh = 0, sc = 0;
     for (int c = 0; c < nchunks; ++c) {
         __syncthreads();                    // all waves are done reading the previous chunk
         stage_store();
+        weights_store();
         __syncthreads();
-        const int cn = c + 1 < nchunks ? c + 1 : c;
-        {
-            const int kh = cn / nsub, sc = cn - kh * nsub;
-            if (c + 1 < nchunks) stage_load(kh, sc);
+        if (++sc == nsub) { sc = 0; ++kh; }
+        if (c + 1 < nchunks) {
+            stage_load(kh, sc);
+            weights_load(kh * g.RC + sc * CQ);
         }
-        const int knext = (cn / nsub) * g.RC + (cn % nsub) * CQ;
+        __builtin_amdgcn_sched_barrier(0x2 | 0x4 | 0x8 | 0x80);   // the loads leave before the chunk's arithmetic
 #pragma unroll
         for (int blk = 0; blk < NB; ++blk) {
-            if (16 * blk < CQ) {            // uniform
-                u32x2 a[MT], bo[NT];
+            u32x2 a[MT], bo[NT];
+            WV r[4];
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt) a[mt] = *(const u32x2 *)(xwin + mt * 16 * RS + 16 * blk);
-                rows_to_operands<NT>(wr[blk], bo);
-                if (16 * blk + 4 * kk >= CQ) {   // lanes past the end of the patch row chunk
+            for (int jj = 0; jj < 4; ++jj) r[jj] = *(const WV *)(wwin + blk * 256 * NT + jj * 64 * NT);
 #pragma unroll
-                    for (int u = 0; u < NT; ++u) bo[u] = (u32x2){0u, 0u};
-                }
+            for (int mt = 0; mt < MT; ++mt) a[mt] = *(const u32x2 *)(xwin + mt * 16 * RS + 16 * blk);
+            rows_to_operands<NT>(r, bo);
+            if (16 * blk + 4 * kk >= CQ) {   // lanes past the end of the patch row chunk
 #pragma unroll
-                for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-                    for (int u = 0; u < NT; ++u) acc[mt][u] = mfma16_bf16(a[mt], bo[u], acc[mt][u]);
-                load_block(knext, blk);
-                // MFMAs and global loads keep their order (LDS reads and address arithmetic may move across)
-                __builtin_amdgcn_sched_barrier(0x2 | 0x4 | 0x80);
+                for (int u = 0; u < NT; ++u) bo[u] = (u32x2){0u, 0u};
             }
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int u = 0; u < NT; ++u) acc[mt][u] = mfma16_bf16(a[mt], bo[u], acc[mt][u]);
         }
     }
 
@@ -189,96 +194,123 @@ __global__ __launch_bounds__(64 * NW, NT == 4 ? 2 : 3) void lc_forward_bf16_stri
         }
 }
 
-// row stride in bf16 values: 16 bytes past a multiple of 128 bytes, so that the 16 image rows a wave reads at once
-// start four banks apart; the row keeps 16 values of padding behind the staged strip
-int strip_row_stride(int sqc) { return ((sqc + 8 + 63) / 64) * 64 + 8; }   // at least 16 values of padding
+// 32-bit byte offsets inside a batch tile of x and a chunk of a field's weights
+bool strip_offsets_fit(const Geom &g, int BT, int CQ) {
+    return (long long)BT * g.H * g.W * g.C < (1LL << 31) && (long long)CQ * g.F < (1LL << 30);
+}
 
-// Host check of a lc_forward_bf16_strip_kernel launch.  tparam = {MT, NT, NLOC, NB, NW}; arg = {CQ, sq4, RS (bf16
-// values), batch tiles, first strip, strips in this launch, strips per field row}.
-int check_forward_bf16_strip(const Geom &g, const LaunchPlan &p) {
-    const int MT = p.tparam[0], NT = p.tparam[1], NLOC = p.tparam[2], NB = p.tparam[3], NW = p.tparam[4];
-    const int CQ = p.arg[0], sq4 = p.arg[1], RS = p.arg[2], nbt = p.arg[3], first = p.arg[4], count = p.arg[5];
-    const int strips = p.arg[6];
-    LC_PLAN_REQUIRE(p, NLOC > 0 && NW % NLOC == 0 && (NT == 1 || NT == 2 || NT == 4));
-    const int BT = 16 * MT, NFW = NW / NLOC, NTHR = 64 * NW, SC = g.S * g.C, WC = g.W * g.C, sqc = 4 * sq4;
-    LC_PLAN_REQUIRE(p, (int)p.block == NTHR);
-    // 8-byte accesses of four bf16 values: patch rows, image rows and field offsets in whole vectors
+// Host check of a lc_forward_bf16_staged_kernel launch.  tparam = {MT, NT, NB, NS, waves per SIMD}; arg = {CQ, sq4, RS (bf16
+// values), batch tiles, strips per field row, slots}.
+int check_forward_bf16_staged(const Geom &g, const LaunchPlan &p) {
+    const int MT = p.tparam[0], NT = p.tparam[1], NB = p.tparam[2], NS = p.tparam[3];
+    const int CQ = p.arg[0], sq4 = p.arg[1], RS = p.arg[2], nbt = p.arg[3], strips = p.arg[4], nslots = p.arg[5];
+    const int BT = 16 * MT, SC = g.S * g.C, WC = g.W * g.C, sqc = 4 * sq4;
+    LC_PLAN_REQUIRE(p, (NT == 1 || NT == 2 || NT == 4) && p.block == 256);
+    // 8-byte accesses of four bf16 values in x, 16-byte ones of eight filters in w
     LC_PLAN_REQUIRE(p, g.RC % 4 == 0 && WC % 4 == 0 && SC % 4 == 0);
-    LC_PLAN_REQUIRE(p, g.F % (NFW * NT * 16) == 0 && (int)p.grid[1] == g.F / (NFW * NT * 16) && p.grid[2] == 1);
+    LC_PLAN_REQUIRE(p, g.F % (NT * 16) == 0 && (int)p.grid[1] == g.F / (NT * 16) && p.grid[2] == 1);
     // chunks of CQ values in NB blocks of 16 (the last one may be partial)
     LC_PLAN_REQUIRE(p, CQ > 0 && CQ % 4 == 0 && g.RC % CQ == 0 && NB == ceil_div(CQ, 16));
-    LC_PLAN_REQUIRE(p, sqc >= CQ + (NLOC - 1) * SC && sqc <= 0xffff && BT <= 0x3fff);
-    LC_PLAN_REQUIRE(p, (long long)BT * sq4 <= (long long)kStripSlots * NTHR);
-    // a partial last block reads up to 12 values past a field's window; 16 values behind the staged row are cleared
-    LC_PLAN_REQUIRE(p, RS % 4 == 0 && RS >= sqc + 16);
-    LC_PLAN_REQUIRE(p, p.lds_bytes >= (size_t)BT * RS * sizeof(bf16_t));
-    LC_PLAN_REQUIRE(p, strips == ceil_div(g.LW, NLOC) && nbt == ceil_div(g.B, BT));
-    LC_PLAN_REQUIRE(p, first >= 0 && count >= 1 && first + count <= strips * g.LH);
-    LC_PLAN_REQUIRE(p, (long long)p.grid[0] == (long long)count * nbt);
+    LC_PLAN_REQUIRE(p, sqc == CQ + 3 * SC);
+    LC_PLAN_REQUIRE(p, nslots <= NS && (long long)BT * sq4 <= (long long)nslots * 256);
+    LC_PLAN_REQUIRE(p, strip_offsets_fit(g, BT, CQ));
+    // a partial last block reads up to 12 values past a field's window; 16 values behind the staged row are cleared;
+    // the weights behind the strip start on 16 bytes
+    LC_PLAN_REQUIRE(p, RS % 8 == 0 && RS >= sqc + 16);
+    LC_PLAN_REQUIRE(p, p.lds_bytes >= ((size_t)BT * RS + 4 * NB * 256 * NT) * sizeof(bf16_t));
+    LC_PLAN_REQUIRE(p, strips == ceil_div(g.LW, 4) && nbt == ceil_div(g.B, BT));
+    LC_PLAN_REQUIRE(p, (long long)p.grid[0] == (long long)strips * g.LH * nbt);
     return LC_OK;
 }
 
-template <int MT, int NT, int NB>
-int launch_strip(const Geom &g, const bf16_t *x, const bf16_t *w, const float *bias, float alpha, float *y, int CQ,
-                 int work_first, int work_count, hipStream_t s) {
-    constexpr int NLOC = 4, NW = 4, BT = 16 * MT;
-    const int sqc = (CQ + (NLOC - 1) * g.S * g.C + 3) & ~3;
-    const int RS = strip_row_stride(sqc);
-    const size_t lds = (size_t)BT * RS * sizeof(bf16_t);
-    auto kern = lc_forward_bf16_strip_kernel<MT, NT, NLOC, NB, NW>;
-    const int strips = (g.LW + NLOC - 1) / NLOC, nbt = (g.B + BT - 1) / BT;
-    const long long nwg = (long long)work_count * nbt;
-    if (nwg > 0x7fffffffLL) return LC_EUNSUPPORTED;
-    dim3 grid((unsigned)nwg, g.F / (NT * 16));
-    const LaunchPlan plan = make_plan("lc_forward_bf16_strip", {MT, NT, NLOC, NB, NW},
-                                      {CQ, sqc / 4, RS, nbt, work_first, work_count, strips}, grid, 64 * NW, lds);
-    if (int rc = check_forward_bf16_strip(g, plan)) return rc;
-    LC_LAUNCH(plan, "lc_forward (bf16 strip) launch", kern, s, g, x, w, bias, alpha, y, strips, CQ, sqc / 4, RS, nbt,
-              work_first);
-    return LC_OK;
+// row stride in bf16 values: 16 bytes on or back modulo 128 bytes, so that the 16 image rows a wave reads at once start
+// four banks apart, with at least 16 values of padding behind the staged strip
+int strip_row_stride(int sqc) {
+    int rs = (sqc + 16 + 7) & ~7;
+    while (rs % 64 != 8 && rs % 64 != 56) rs += 8;
+    return rs;
+}
+size_t strip_lds(const Geom &g, int BT, int CQ, int NT) {
+    const int sqc = CQ + 3 * g.S * g.C;
+    return ((size_t)BT * strip_row_stride(sqc) + (size_t)4 * ((CQ + 15) / 16) * 256 * NT) * sizeof(bf16_t);
 }
 
-// the chunk: the largest divisor of a patch row (in whole 4-value vectors, at most 128 values) whose strip fits the
-// staging registers and 48 KB of LDS; 0 if none does
-int strip_chunk(const Geom &g, int BT) {
+// the largest chunk (a divisor of a patch row in whole 4-value vectors, at most 128 values) whose strip fits the staging
+// registers and whose strip and weights fit lds bytes; 0 if none does
+int strip_chunk(const Geom &g, int BT, int NT, size_t lds) {
     const int SC = g.S * g.C;
     for (int nsub = 1; nsub <= g.RC / 4; ++nsub) {
         if (g.RC % nsub) continue;
         const int CQ = g.RC / nsub;
         if (CQ % 4 || CQ > 128) continue;
-        const int sqc = (CQ + 3 * SC + 3) & ~3;
-        if ((size_t)BT * (sqc / 4) > (size_t)kStripSlots * 256) continue;
-        if ((size_t)BT * strip_row_stride(sqc) * sizeof(bf16_t) > 48 * 1024) continue;
-        if (sqc > 0xffff) continue;
+        const long long sqc = CQ + 3LL * SC;
+        if (BT * (sqc / 4) > kStripSlots * 256) continue;
+        if (strip_lds(g, BT, CQ, NT) > lds || !strip_offsets_fit(g, BT, CQ)) continue;
         return CQ;
     }
     return 0;
 }
 
-template <int MT, int NT>
-int launch_strip_nb(const Geom &g, const bf16_t *x, const bf16_t *w, const float *bias, float alpha, float *y, int CQ,
-                    int first, int count, hipStream_t s) {
-    switch ((CQ + 15) / 16) {
-        case 1: return launch_strip<MT, NT, 1>(g, x, w, bias, alpha, y, CQ, first, count, s);
-        case 2: return launch_strip<MT, NT, 2>(g, x, w, bias, alpha, y, CQ, first, count, s);
-        case 3: return launch_strip<MT, NT, 3>(g, x, w, bias, alpha, y, CQ, first, count, s);
-        case 4: return launch_strip<MT, NT, 4>(g, x, w, bias, alpha, y, CQ, first, count, s);
-        case 5: return launch_strip<MT, NT, 5>(g, x, w, bias, alpha, y, CQ, first, count, s);
-        case 6: return launch_strip<MT, NT, 6>(g, x, w, bias, alpha, y, CQ, first, count, s);
-        case 7: return launch_strip<MT, NT, 7>(g, x, w, bias, alpha, y, CQ, first, count, s);
-        default: return launch_strip<MT, NT, 8>(g, x, w, bias, alpha, y, CQ, first, count, s);
+// Batch tile, filters per workgroup and chunk.  64-image tiles: several workgroups fit a compute unit and the second tile of
+// a strip finds the weights in L2 (128 images in 8 waves that share the staged weights: 112 against 108 us on the 200 x 200
+// layer, and up to 1.5 times slower on others).  Wide filter blocks read the strip fewer times; where they leave room for
+// chunks of less than one block only (patch rows of 4 times a prime), narrower ones keep the whole row.
+struct StripPick {
+    int MT, NT, CQ;
+};
+StripPick strip_pick(const Geom &g) {
+    const int MT = g.B > 32 ? 4 : 2, BT = 16 * MT;
+    StripPick p = {MT, 0, 0};
+    for (int NT : {4, 2, 1}) {
+        if (g.F % (16 * NT)) continue;
+        // LDS of two (64 filters, for their registers) or three workgroups a compute unit
+        const int CQ = strip_chunk(g, BT, NT, (NT == 4 ? 80 : 53) * 1024);
+        if (CQ > p.CQ) p.NT = NT, p.CQ = CQ;
+        if (p.CQ >= 16) break;
     }
+    return p;
 }
 
-// Batch tiles of 64 images: three workgroups fit a compute unit and the second tile of a strip finds the weights in
-// L2.  128-image tiles (two per compute unit, one round of 512 plus a remainder launch where the strips do not fill a second round)
-// measured slower: 114 against 106 us.
-template <int NT>
-int launch_strip_mt(const Geom &g, const bf16_t *x, const bf16_t *w, const float *bias, float alpha, float *y, int CQ,
+template <int MT, int NT, int NB, int NS>
+int launch_strip_ns(const Geom &g, const bf16_t *x, const bf16_t *w, const float *bias, float alpha, float *y, int CQ,
                     hipStream_t s) {
-    const int ntask = ((g.LW + 3) / 4) * g.LH;
-    if (g.B > 32) return launch_strip_nb<4, NT>(g, x, w, bias, alpha, y, CQ, 0, ntask, s);
-    return launch_strip_nb<2, NT>(g, x, w, bias, alpha, y, CQ, 0, ntask, s);
+    constexpr int BT = 16 * MT, OCC = NT == 4 ? 2 : 3;
+    const int sqc = CQ + 3 * g.S * g.C, RS = strip_row_stride(sqc);
+    const int strips = (g.LW + 3) / 4, nbt = (g.B + BT - 1) / BT, nslots = ceil_div(BT * (sqc / 4), 256);
+    const long long nwg = (long long)strips * g.LH * nbt;
+    if (nwg > 0x7fffffffLL) return LC_EUNSUPPORTED;
+    dim3 grid((unsigned)nwg, g.F / (NT * 16));
+    auto kern = lc_forward_bf16_staged_kernel<MT, NT, NB, NS, OCC>;
+    const LaunchPlan plan = make_plan("lc_forward_bf16_staged", {MT, NT, NB, NS, OCC}, {CQ, sqc / 4, RS, nbt, strips, nslots},
+                                      grid, 256, strip_lds(g, BT, CQ, NT));
+    if (int rc = check_forward_bf16_staged(g, plan)) return rc;
+    LC_LAUNCH(plan, "lc_forward (bf16 strip) launch", kern, s, g, x, w, bias, alpha, y, strips, CQ, sqc / 4, RS, nbt, nslots);
+    return LC_OK;
+}
+
+template <int MT, int NT, int NB>
+int launch_strip(const Geom &g, const bf16_t *x, const bf16_t *w, const float *bias, float alpha, float *y, int CQ,
+                 hipStream_t s) {
+    if (16 * MT * (CQ + 3 * g.S * g.C) <= 6 * 4 * 256) return launch_strip_ns<MT, NT, NB, 6>(g, x, w, bias, alpha, y, CQ, s);
+    return launch_strip_ns<MT, NT, NB, kStripSlots>(g, x, w, bias, alpha, y, CQ, s);
+}
+
+template <int MT, int NT>
+int launch_strip_nb(const Geom &g, const bf16_t *x, const bf16_t *w, const float *bias, float alpha, float *y, int CQ,
+                    hipStream_t s) {
+    switch ((CQ + 15) / 16) {
+        case 1: return launch_strip<MT, NT, 1>(g, x, w, bias, alpha, y, CQ, s);
+        case 2: return launch_strip<MT, NT, 2>(g, x, w, bias, alpha, y, CQ, s);
+        case 3: return launch_strip<MT, NT, 3>(g, x, w, bias, alpha, y, CQ, s);
+        case 4: return launch_strip<MT, NT, 4>(g, x, w, bias, alpha, y, CQ, s);
+        case 5: return launch_strip<MT, NT, 5>(g, x, w, bias, alpha, y, CQ, s);
+        case 6: return launch_strip<MT, NT, 6>(g, x, w, bias, alpha, y, CQ, s);
+        case 7: return launch_strip<MT, NT, 7>(g, x, w, bias, alpha, y, CQ, s);
+        default:
+            // 64 images with blocks of 32 filters and more: beyond strip_pick's LDS
+            if constexpr (MT == 4 && NT > 1) return LC_EUNSUPPORTED;
+            else return launch_strip<MT, NT, 8>(g, x, w, bias, alpha, y, CQ, s);
+    }
 }
 
 // ------------------------------------------------------------------------------ backward weights
@@ -655,22 +687,28 @@ int launch_backward_weights_bf16_rows(const Geom &g, const void *xv, const void 
 bool bf16_strip_forward_supported(const Geom &g) {
     const int SC = g.S * g.C;
     if (g.RC % 4 || SC % 4 || (g.W * g.C) % 4 || g.F % 16 || g.B <= 16) return false;
-    return strip_chunk(g, g.B > 32 ? 64 : 32) != 0;
+    return strip_pick(g).CQ != 0;
 }
 
+// with the widest blocks of filters
 long long bf16_strip_forward_workgroups(const Geom &g) {
     const int nt = g.F % 64 == 0 ? 4 : g.F % 32 == 0 ? 2 : 1, bt = g.B > 32 ? 64 : 32;
-    return (long long)((g.LW + 3) / 4) * g.LH * ((g.B + bt - 1) / bt) * (g.F / (16 * nt));
+    return (long long)((g.LW + 3) / 4) * g.LH * ceil_div(g.B, bt) * (g.F / (16 * nt));
 }
 
 int launch_forward_bf16_strip(const Geom &g, const void *xv, const void *wv, const float *bias, float alpha, float *y,
                               hipStream_t s) {
     if (!bf16_strip_forward_supported(g)) return LC_EUNSUPPORTED;
     const bf16_t *x = (const bf16_t *)xv, *w = (const bf16_t *)wv;
-    const int CQ = strip_chunk(g, g.B > 32 ? 64 : 32);
-    if (g.F % 64 == 0) return launch_strip_mt<4>(g, x, w, bias, alpha, y, CQ, s);
-    if (g.F % 32 == 0) return launch_strip_mt<2>(g, x, w, bias, alpha, y, CQ, s);
-    return launch_strip_mt<1>(g, x, w, bias, alpha, y, CQ, s);
+    const StripPick p = strip_pick(g);
+    if (p.MT == 4) {
+        if (p.NT == 4) return launch_strip_nb<4, 4>(g, x, w, bias, alpha, y, p.CQ, s);
+        if (p.NT == 2) return launch_strip_nb<4, 2>(g, x, w, bias, alpha, y, p.CQ, s);
+        return launch_strip_nb<4, 1>(g, x, w, bias, alpha, y, p.CQ, s);
+    }
+    if (p.NT == 4) return launch_strip_nb<2, 4>(g, x, w, bias, alpha, y, p.CQ, s);
+    if (p.NT == 2) return launch_strip_nb<2, 2>(g, x, w, bias, alpha, y, p.CQ, s);
+    return launch_strip_nb<2, 1>(g, x, w, bias, alpha, y, p.CQ, s);
 }
 
 }  // namespace lc

@@ -1,0 +1,76 @@
+"""The forward pass in bf16 on strips of four fields, strip and weights through LDS: both batch tiles, every width of filter
+block, chunks of one short block to eight, partly filled strips, batch tiles and last blocks, on a GPU against fp64."""
+import pytest
+import torch
+
+import paper_1502_03409_amd as lc
+from paper_1502_03409_amd import binding as Bd
+
+pytestmark = pytest.mark.gpu
+
+# (B, H, W, C, R, S, F), (images / 16, filters / 16 of a workgroup, blocks of 16 values in a chunk, staging slots)
+LAYERS = [
+    ((17, 30, 142, 4, 3, 1, 16), (2, 1, 1, 6)),       # rows of 12 values: one block, a quarter of it empty
+    ((64, 48, 47, 4, 1, 1, 16), (4, 1, 1, 6)),        # fields of one pixel: rows of 4 values
+    ((33, 40, 70, 4, 7, 1, 48), (4, 1, 2, 6)),        # one image past half a batch tile
+    ((129, 21, 45, 16, 5, 1, 80), (4, 1, 5, 12)),     # one image past two batch tiles
+    ((40, 60, 64, 4, 29, 1, 16), (4, 1, 8, 12)),      # rows of 116 values in one chunk
+    ((65, 30, 29, 16, 8, 1, 16), (4, 1, 8, 12)),      # rows of 128 values
+    ((65, 130, 104, 3, 20, 4, 32), (4, 2, 4, 6)),       # field offsets of 12 values
+    ((40, 29, 35, 12, 9, 1, 96), (4, 2, 7, 12)),      # rows of 108
+    ((64, 60, 61, 4, 29, 1, 64), (4, 1, 8, 12)),      # narrower blocks of filters keep a row of 116 whole
+    ((30, 39, 40, 16, 8, 1, 64), (2, 4, 8, 6)),       # half a batch tile leaves room for both
+    ((50, 45, 43, 4, 3, 1, 64), (4, 4, 1, 6)),
+    ((130, 40, 33, 16, 11, 2, 128), (4, 4, 6, 12)),    # rows of 176 in chunks of 88
+    ((32, 65, 66, 24, 9, 3, 96), (2, 2, 7, 12)),      # rows of 216 in chunks of 108
+]
+
+
+def _case(t):
+    B, H, W, C, R, S, F = t
+    LH, LW, K = (H - R) // S + 1, (W - R) // S + 1, R * R * C
+    gen = torch.Generator(device="cuda").manual_seed(sum(t))
+    x = torch.randn((B, H, W, C), generator=gen, device="cuda").bfloat16()
+    w = torch.randn((LH, LW, K, F), generator=gen, device="cuda").bfloat16()
+    bias = torch.randn((LH, LW, F), generator=gen, device="cuda")
+    return (B, H, W, C, R, S, F, LH, LW, K), x, w, bias
+
+
+def _reference(dims, x, w):
+    """Sums of products and of their magnitudes in fp64, [B, LH, LW, F]."""
+    B, _, _, _, R, S, F, LH, LW, K = dims
+    y = torch.empty((2, B, LH, LW, F), dtype=torch.float64, device="cuda")
+    for i in range(LH):
+        p = x[:, i * S:i * S + R].double().unfold(2, R, S).permute(2, 0, 1, 4, 3).reshape(LW, B, K)
+        y[0, :, i] = torch.bmm(p, w[i].double()).transpose(0, 1)
+        y[1, :, i] = torch.bmm(p.abs(), w[i].double().abs()).transpose(0, 1)
+    return y
+
+
+@pytest.mark.parametrize("t,want", LAYERS, ids=["x".join(map(str, t)) for t, _ in LAYERS])
+def test_against_fp64(t, want):
+    dims, x, w, bias = _case(t)
+    g = lc.geom(*t)
+    plan = lc.plan_query(g, Bd.LC_OP_FORWARD, lc.LC_BF16)
+    assert [p["kernel"] for p in plan] == ["lc_forward_bf16_staged"] and tuple(plan[0]["tparam"][:4]) == want
+    y = torch.full((dims[0], dims[7], dims[8], dims[6]), float("nan"), device="cuda")
+    lc.lc_forward(g, x, w, bias, 0.5, y, lc.LC_BF16)
+    ref, mag = _reference(dims, x, w)
+    # products of bf16 are exact in fp32; K additions, the scale and the bias round by 2^-24 of what they add up at most
+    bound = (dims[9] + 2) * 2.0 ** -24 * (0.5 * mag + bias.double().abs())
+    assert torch.all((y.double() - (0.5 * ref + bias.double())).abs() <= bound)
+
+
+def test_pixels_outside_every_field_stay_out():
+    """The last field of a row ends in a partly filled block whose lanes reach past it; the last strip has idle waves."""
+    t = (64, 80, 64, 4, 3, 2, 32)                     # 31 fields end at pixel 63 of 64
+    dims, x, w, _ = _case(t)
+    end = (dims[8] - 1) * dims[5] + dims[4]
+    assert end < t[2]
+    g = lc.geom(*t)
+    assert lc.plan_query(g, Bd.LC_OP_FORWARD, lc.LC_BF16)[0]["kernel"] == "lc_forward_bf16_staged"
+    y, z = (torch.empty((dims[0], dims[7], dims[8], dims[6]), device="cuda") for _ in range(2))
+    lc.lc_forward(g, x, w, None, 1.0, y, lc.LC_BF16)
+    x[:, :, end:] = float("nan")
+    lc.lc_forward(g, x, w, None, 1.0, z, lc.LC_BF16)
+    assert torch.equal(y, z)
