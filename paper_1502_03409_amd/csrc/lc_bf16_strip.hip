@@ -461,12 +461,14 @@ int launch_rows_pf(const Geom &g, const bf16_t *x, const bf16_t *dy, float beta,
 // 1200 x 128 patch, and those 8-byte loads are what binds it (same layer: 152 us, 88 us with the patch loads compiled out).
 // Here a workgroup takes four adjacent fields and stages, per patch row, the image-row strip they share (as the
 // forward kernel does; 2.5x fewer patch bytes on that layer, fetched once); wave = field.  Per patch row a wave contracts
-// over the whole batch: lane (m,kk) reads the patch values 64 blk + 4 m .. +3 of the four images 16 s + 4 kk .. +3
+// over the whole batch: lane (m,kk) reads the patch values 4 m .. +3 of the four images 16 s + 4 kk .. +3
 // from LDS and transposes them in registers into four operands; the dy operands of all steps sit in registers for
 // the whole kernel (batches up to 128 images).  The 64 x 16 NT tile of a patch row is stored as soon as it is
-// complete.  Rows of a block beyond the patch row read the neighbour's pixels: they only reach output rows that
+// complete.  Rows beyond the patch row read the neighbour's pixels: they only reach output rows that
 // are not stored.  The patch rows are split over grid.z so that small layers still fill the chip.
-template <int NT, int NBK>
+// Unconditional staging loads and streamed stores: 127 -> 107 us on the 128 x 200 x 200 x 3 layer out of the caches, 111 -> 85
+// in them; 50 drawn layers of 5 to 128 images 1.19 times (geometric mean) against a branch per load.
+template <int NT, bool STREAM>
 __global__ __launch_bounds__(256, 3) void lc_bwd_weights_bf16_strip_kernel(Geom g, const bf16_t *__restrict__ x,
                                                                          const bf16_t *__restrict__ dy, float beta,
                                                                          float *__restrict__ out, int strips_per_row,
@@ -475,9 +477,10 @@ __global__ __launch_bounds__(256, 3) void lc_bwd_weights_bf16_strip_kernel(Geom 
     typedef typename FVec<NT>::T BV;               // NT consecutive outputs
     typedef const __attribute__((address_space(1))) BR *gb_ptr;
     typedef const __attribute__((address_space(1))) u32x2 *gx4_ptr;
+    typedef const __attribute__((address_space(1))) char *gc_ptr;
     constexpr int BT = 128, NSTEP = BT / 16, NLOC = 4, NTHR = 256;
     extern __shared__ __attribute__((aligned(16))) bf16_t xh[];      // [BT][RS] (+ 64 values of slack)
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = lane & 15, kk = lane >> 4;
     const int work = remap_xcd(blockIdx.x, gridDim.x);
     const int i = work / strips_per_row, j0 = (work - i * strips_per_row) * NLOC;
@@ -490,6 +493,7 @@ __global__ __launch_bounds__(256, 3) void lc_bwd_weights_bf16_strip_kernel(Geom 
     const size_t img = (size_t)g.H * WC, dyimg = (size_t)g.L * g.F;
 
     // dy operands of every step: images 16 s + 4 kk .. +3, filters f0 + NT m .. (zeros beyond the batch)
+    const bf16_t *dyl = dy + (size_t)loc * g.F + f0 + NT * m;
     u32x2 bo[NSTEP][NT];
 #pragma unroll
     for (int st = 0; st < NSTEP; ++st) {
@@ -497,51 +501,38 @@ __global__ __launch_bounds__(256, 3) void lc_bwd_weights_bf16_strip_kernel(Geom 
 #pragma unroll
         for (int jj = 0; jj < 4; ++jj) {
             const int b = 16 * st + 4 * kk + jj;
-            r[jj] = BR{};
-            if (b < g.B) r[jj] = *(gb_ptr)(dy + (size_t)b * dyimg + (size_t)loc * g.F + f0 + NT * m);
+            r[jj] = *(gb_ptr)(dyl + (size_t)min(b, g.B - 1) * dyimg);
+            if (b >= g.B) r[jj] = BR{};
         }
         rows_to_operands<NT>(r, bo[st]);
     }
 
-    // staging map as in the forward kernel: slot q copies 4-value vector number tid + 256 q of the [BT][sq4] chunk
-    const int sqc = sq4 * 4;
-    const int nslots = (BT * sq4 + NTHR - 1) / NTHR;
-    int sb[kStripSlots];
-    {
-        int vv = tid % sq4, b = tid / sq4;
-        const int dv = NTHR % sq4, db = NTHR / sq4;
+    // staging map: slot q copies 4-value vector number tid + 256 q of the [B][sq4] chunk; lanes past its end and values beyond
+    // the last field of the row repeat the nearest one that exists (goff, loff: bytes), so that no load or store is
+    // conditional but for whole slots.  Images beyond B are cleared once.
+    const int nslots = (g.B * sq4 + NTHR - 1) / NTHR;
+    const int vmax = (min(NLOC, g.LW - j0) - 1) * SC + g.RC;   // values that the strip's fields read
+    unsigned goff[kStripSlots], loff[kStripSlots];
 #pragma unroll
-        for (int q = 0; q < kStripSlots; ++q) {
-            sb[q] = (b << 16) | (vv * 4);
-            if (b >= BT) sb[q] = (int)0x80000000;
-            else if (b >= g.B) sb[q] |= 0x40000000;
-            vv += dv; b += db;
-            if (vv >= sq4) { vv -= sq4; ++b; }
-        }
+    for (int q = 0; q < kStripSlots; ++q) {
+        const int e = min(tid + NTHR * q, g.B * sq4 - 1);
+        const int b = e / sq4, v = min(4 * (e - b * sq4), vmax - 4);
+        goff[q] = 2u * ((unsigned)b * (unsigned)img + v);
+        loff[q] = 2u * (b * RS + v);
     }
-    const int col0 = j0 * SC;
+    for (int e = g.B * (RS >> 2) + tid; e < BT * (RS >> 2); e += NTHR) *(u32x2 *)(xh + 4 * e) = (u32x2){0u, 0u};
+    const gc_ptr xrow = (gc_ptr)(x + (size_t)(i * g.S) * WC + j0 * SC);
     u32x2 st[kStripSlots];
     auto stage_load = [&](int kh) {
-        const bf16_t *row = x + (size_t)(i * g.S + kh) * WC + col0;
-        const int lim = WC - col0;
+        const gc_ptr row = xrow + 2 * ((size_t)kh * WC);
 #pragma unroll
-        for (int q = 0; q < kStripSlots; ++q) {
-            if (q < nslots) {
-                const int b = (sb[q] >> 16) & 0x3fff, v = sb[q] & 0xffff;
-                u32x2 t = (u32x2){0u, 0u};
-                if ((sb[q] & 0xc0000000) == 0 && v < lim) t = *(gx4_ptr)(row + (size_t)b * img + v);
-                st[q] = t;
-            }
-        }
+        for (int q = 0; q < kStripSlots; ++q)
+            if (q < nslots) st[q] = *(gx4_ptr)(row + goff[q]);
     };
     auto stage_store = [&]() {
 #pragma unroll
-        for (int q = 0; q < kStripSlots; ++q) {
-            if (q < nslots && sb[q] >= 0) {
-                const int b = (sb[q] >> 16) & 0x3fff, v = sb[q] & 0xffff;
-                *(u32x2 *)(xh + b * RS + v) = st[q];
-            }
-        }
+        for (int q = 0; q < kStripSlots; ++q)
+            if (q < nslots) *(u32x2 *)((char *)xh + loff[q]) = st[q];
     };
 
     const bf16_t *xwin = xh + (size_t)(4 * kk) * RS + wave * SC + 4 * m;
@@ -553,9 +544,8 @@ __global__ __launch_bounds__(256, 3) void lc_bwd_weights_bf16_strip_kernel(Geom 
         stage_store();
         __syncthreads();
         if (kh + 1 < kh_hi) stage_load(kh + 1);
-#pragma unroll
-        for (int blk = 0; blk < NBK; ++blk) {
-            if (64 * blk >= g.RC) break;    // uniform
+        __builtin_amdgcn_sched_barrier(0x2 | 0x4 | 0x8 | 0x80);   // the loads leave before the row's arithmetic
+        {
             f32x4 acc[4][NT];
 #pragma unroll
             for (int t = 0; t < 4; ++t)
@@ -566,7 +556,7 @@ __global__ __launch_bounds__(256, 3) void lc_bwd_weights_bf16_strip_kernel(Geom 
                 if (sp < nsteps) {          // uniform
                     u32x2 r[4], ao[4];
 #pragma unroll
-                    for (int jj = 0; jj < 4; ++jj) r[jj] = *(const u32x2 *)(xwin + (size_t)(16 * sp + jj) * RS + 64 * blk);
+                    for (int jj = 0; jj < 4; ++jj) r[jj] = *(const u32x2 *)(xwin + (size_t)(16 * sp + jj) * RS);
                     rows_to_operands<4>(r, ao);
 #pragma unroll
                     for (int t = 0; t < 4; ++t)
@@ -579,7 +569,7 @@ __global__ __launch_bounds__(256, 3) void lc_bwd_weights_bf16_strip_kernel(Geom 
                 for (int r = 0; r < 4; ++r)
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
-                        const int kl = 64 * blk + 4 * (4 * kk + r) + t;
+                        const int kl = 4 * (4 * kk + r) + t;
                         if (kl >= g.RC) continue;
                         BV *o = (BV *)(ol + (size_t)(kh * g.RC + kl) * g.F);
                         BV v;
@@ -590,34 +580,36 @@ __global__ __launch_bounds__(256, 3) void lc_bwd_weights_bf16_strip_kernel(Geom 
                             for (int u = 0; u < NT; ++u) v[u] = acc[t][u][r];
                         }
                         if (beta != 0.f) v += beta * *o;
-                        *o = v;
+                        if constexpr (STREAM) stream_store(v, o);
+                        else *o = v;
                     }
             }
         }
     }
 }
 
-// row stride: 16 bytes past a multiple of 128 bytes, wide enough for the staged strip and for the 64-value blocks of
-// the last field (which read past its patch row)
+// row stride: 16 bytes past a multiple of 128 bytes, wide enough for the staged strip and for the 64 values of
+// the last field (which reach past its patch row)
 int wstrip_row_stride(const Geom &g, int sqc) {
-    const int nbk = (g.RC + 63) / 64, need = std::max(sqc, 3 * g.S * g.C + 64 * nbk);
+    const int need = std::max(sqc, 3 * g.S * g.C + 64);
     return ((need - 8 + 63) / 64) * 64 + 8;
 }
 
-// Host check of a lc_bwd_weights_bf16_strip_kernel launch.  tparam = {NT, NBK}; arg = {strips per field row, sq4, RS
+// Host check of a lc_bwd_weights_bf16_strip_kernel launch.  tparam = {NT, streamed stores}; arg = {strips per field row, sq4, RS
 // (bf16 values), patch rows per workgroup}.
 int check_backward_weights_bf16_strip(const Geom &g, const LaunchPlan &p) {
-    const int NT = p.tparam[0], NBK = p.tparam[1];
+    const int NT = p.tparam[0];
     const int strips = p.arg[0], sq4 = p.arg[1], RS = p.arg[2], rows_per_wg = p.arg[3];
     const int SC = g.S * g.C, WC = g.W * g.C, sqc = 4 * sq4;
     LC_PLAN_REQUIRE(p, p.block == 256 && (NT == 1 || NT == 2 || NT == 4));
     LC_PLAN_REQUIRE(p, g.RC % 4 == 0 && SC % 4 == 0 && WC % 4 == 0 && g.B <= 128);
     LC_PLAN_REQUIRE(p, g.F % (NT * 16) == 0 && (int)p.grid[1] == g.F / (NT * 16));
-    // a patch row in NBK blocks of 64 values; the last field's blocks read past its patch row inside the LDS row
-    LC_PLAN_REQUIRE(p, NBK * 64 >= g.RC);
+    // a patch row in a block of 64 values; the last field's block reads past its patch row inside the LDS row
+    LC_PLAN_REQUIRE(p, g.RC <= 64);
     LC_PLAN_REQUIRE(p, sqc >= g.RC + 3 * SC && sqc <= 0xffff);
     LC_PLAN_REQUIRE(p, (long long)128 * sq4 <= (long long)kStripSlots * 256);
-    LC_PLAN_REQUIRE(p, RS % 4 == 0 && RS >= sqc && RS >= 3 * SC + 64 * ceil_div(g.RC, 64));
+    LC_PLAN_REQUIRE(p, (long long)g.B * g.H * WC < (1LL << 31));   // 32-bit byte offsets into x
+    LC_PLAN_REQUIRE(p, RS % 4 == 0 && RS >= sqc && RS >= 3 * SC + 64);
     LC_PLAN_REQUIRE(p, p.lds_bytes >= ((size_t)128 * RS + 64) * sizeof(bf16_t));
     LC_PLAN_REQUIRE(p, strips == ceil_div(g.LW, 4) && (long long)p.grid[0] == (long long)strips * g.LH);
     LC_PLAN_REQUIRE(p, rows_per_wg >= 1 && (long long)p.grid[2] * rows_per_wg >= g.R &&
@@ -625,12 +617,12 @@ int check_backward_weights_bf16_strip(const Geom &g, const LaunchPlan &p) {
     return LC_OK;
 }
 
-template <int NT, int NBK>
-int launch_wstrip(const Geom &g, const bf16_t *x, const bf16_t *dy, float beta, float *out, hipStream_t s) {
+template <int NT, bool STREAM>
+int launch_wstrip_as(const Geom &g, const bf16_t *x, const bf16_t *dy, float beta, float *out, hipStream_t s) {
     const int sqc = (g.RC + 3 * g.S * g.C + 3) & ~3;
     const int RS = wstrip_row_stride(g, sqc);
     const size_t lds = ((size_t)128 * RS + 64) * sizeof(bf16_t);
-    auto kern = lc_bwd_weights_bf16_strip_kernel<NT, NBK>;
+    auto kern = lc_bwd_weights_bf16_strip_kernel<NT, STREAM>;
     const int strips = (g.LW + 3) / 4;
     const long long nwork = (long long)strips * g.LH;
     if (nwork > 0x7fffffffLL) return LC_EUNSUPPORTED;
@@ -639,7 +631,7 @@ int launch_wstrip(const Geom &g, const bf16_t *x, const bf16_t *dy, float beta, 
     while (zsplit < g.R && nwork * (g.F / (NT * 16)) * zsplit < 4 * 256) ++zsplit;
     const int rows_per_wg = (g.R + zsplit - 1) / zsplit;
     dim3 grid((unsigned)nwork, g.F / (NT * 16), (g.R + rows_per_wg - 1) / rows_per_wg);
-    const LaunchPlan plan = make_plan("lc_bwd_weights_bf16_strip", {NT, NBK}, {strips, sqc / 4, RS, rows_per_wg}, grid, 256, lds);
+    const LaunchPlan plan = make_plan("lc_bwd_weights_bf16_strip", {NT, (int)STREAM}, {strips, sqc / 4, RS, rows_per_wg}, grid, 256, lds);
     if (int rc = check_backward_weights_bf16_strip(g, plan)) return rc;
     LC_LAUNCH(plan, "lc_backward_weights (bf16 strip) launch", kern, s, g, x, dy, beta, out, strips, sqc / 4, RS,
               rows_per_wg);
@@ -648,16 +640,20 @@ int launch_wstrip(const Geom &g, const bf16_t *x, const bf16_t *dy, float beta, 
 
 bool wstrip_supported(const Geom &g) {
     const int SC = g.S * g.C;
-    if (g.RC % 4 || SC % 4 || (g.W * g.C) % 4 || g.F % 16 || g.B > 128 || g.RC > 128) return false;
+    if (g.RC % 4 || SC % 4 || (g.W * g.C) % 4 || g.F % 16 || g.B > 128 || g.RC > 64) return false;
     const int sqc = (g.RC + 3 * SC + 3) & ~3;
-    if ((size_t)128 * (sqc / 4) > (size_t)kStripSlots * 256) return false;
+    if ((size_t)128 * (sqc / 4) > (size_t)kStripSlots * 256 || (long long)g.B * g.H * g.W * g.C >= (1LL << 31)) return false;
     return ((size_t)128 * wstrip_row_stride(g, sqc) + 64) * sizeof(bf16_t) <= 48 * 1024 && sqc <= 0xffff;
 }
 
+// Streamed stores: whole lines (32 filters) of a gradient that is overwritten go past the caches where the reads of x weigh
+// (128 images of 200 x 200 x 3: 99 -> 85 us); below 58 images the stores bind by themselves and the caches smooth them (32 of
+// 48 x 29 x 4, 96 filters: 32 against 39), as they do with the half lines of 16 filters (72 of 54 x 108 x 4: 58 against 82).
 template <int NT>
-int launch_wstrip_nbk(const Geom &g, const bf16_t *x, const bf16_t *dy, float beta, float *out, hipStream_t s) {
-    if (g.RC <= 64) return launch_wstrip<NT, 1>(g, x, dy, beta, out, s);
-    return launch_wstrip<NT, 2>(g, x, dy, beta, out, s);
+int launch_wstrip(const Geom &g, const bf16_t *x, const bf16_t *dy, float beta, float *out, hipStream_t s) {
+    if constexpr (NT == 2)
+        if (g.B >= 64 && beta == 0.f) return launch_wstrip_as<NT, true>(g, x, dy, beta, out, s);
+    return launch_wstrip_as<NT, false>(g, x, dy, beta, out, s);
 }
 
 }  // namespace
@@ -675,8 +671,8 @@ int launch_backward_weights_bf16_rows(const Geom &g, const void *xv, const void 
     if (!bf16_rows_backward_weights_supported(g)) return LC_EUNSUPPORTED;
     const bf16_t *x = (const bf16_t *)xv, *dy = (const bf16_t *)dyv;
     if (wstrip_supported(g)) {
-        if (g.F % 32 == 0) return launch_wstrip_nbk<2>(g, x, dy, beta, dw, s);
-        return launch_wstrip_nbk<1>(g, x, dy, beta, dw, s);
+        if (g.F % 32 == 0) return launch_wstrip<2>(g, x, dy, beta, dw, s);
+        return launch_wstrip<1>(g, x, dy, beta, dw, s);
     }
     if (g.F % 64 == 0) return launch_rows_pf<1, 4>(g, x, dy, beta, dw, s);
     if (g.F % 32 == 0) return launch_rows_pf<2, 2>(g, x, dy, beta, dw, s);

@@ -1,5 +1,5 @@
-"""The forward pass in bf16 on strips of four fields, strip and weights through LDS: both batch tiles, every width of filter
-block, chunks of one short block to eight, partly filled strips, batch tiles and last blocks, on a GPU against fp64."""
+"""bf16 on strips of four fields: the forward pass (both batch tiles, every width of filter block, chunks of one short block to
+eight, partly filled strips, batch tiles and last blocks) and the weight gradient, on a GPU against fp64."""
 import pytest
 import torch
 
@@ -74,3 +74,39 @@ def test_pixels_outside_every_field_stay_out():
     x[:, :, end:] = float("nan")
     lc.lc_forward(g, x, w, None, 1.0, z, lc.LC_BF16)
     assert torch.equal(y, z)
+
+
+# (B, H, W, C, R, S, F): one image, partly filled steps of 16, both sides of the streamed stores, blocks of 16 and 32 filters,
+# rows of 45 to 64 values, strips of one to four fields
+GRADIENTS = [(1, 22, 40, 4, 12, 1, 16), (17, 24, 41, 4, 15, 2, 32), (63, 31, 48, 3, 20, 4, 32), (64, 31, 48, 3, 20, 4, 96),
+             (127, 30, 45, 4, 13, 3, 48), (128, 40, 36, 4, 14, 1, 64), (65, 37, 40, 4, 16, 1, 32), (49, 37, 44, 3, 20, 4, 16)]
+
+
+@pytest.mark.parametrize("t", GRADIENTS, ids=["x".join(map(str, t)) for t in GRADIENTS])
+@pytest.mark.parametrize("beta", [0.0, 1.0])
+def test_weight_gradient_against_fp64(t, beta):
+    dims, x, dw0, _ = _case(t)
+    B, _, _, _, R, S, F, LH, LW, K = dims
+    g = lc.geom(*t)
+    assert lc.plan_query(g, Bd.LC_OP_BACKWARD_WEIGHTS, lc.LC_BF16)[0]["kernel"] == "lc_bwd_weights_bf16_strip"
+    dy = torch.randn((B, LH, LW, F), device="cuda").bfloat16()
+    dw = dw0.float()
+    if not beta:
+        dw.fill_(float("nan"))
+    lc.lc_backward_weights(g, x, dy, beta, dw, lc.LC_BF16)
+    for i in range(LH):
+        p = x[:, i * S:i * S + R].double().unfold(2, R, S).permute(2, 1, 4, 3, 0).reshape(LW, K, B)
+        d = dy[:, i].double().transpose(0, 1).contiguous()
+        ref, mag = torch.bmm(p, d) + beta * dw0[i].double(), torch.bmm(p.abs(), d.abs()) + beta * dw0[i].double().abs()
+        assert torch.all((dw[i].double() - ref).abs() <= (B + 1) * 2.0 ** -24 * mag)
+
+
+def test_infinities_of_the_last_image_stay_infinite():
+    """The images that fill up a step of 16 count as zeros, not as copies of one that exists."""
+    t = (33, 31, 48, 3, 20, 4, 32)
+    dims, x, dw, _ = _case(t)
+    x[-1, 5, 5, 0] = float("inf")
+    dy = torch.ones((dims[0], dims[7], dims[8], dims[6]), device="cuda").bfloat16()
+    out = torch.empty(dw.shape, device="cuda")
+    lc.lc_backward_weights(lc.geom(*t), x, dy, 0.0, out, lc.LC_BF16)
+    assert not torch.isnan(out).any() and torch.isinf(out).any()
