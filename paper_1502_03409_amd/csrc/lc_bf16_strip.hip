@@ -8,9 +8,10 @@
 // registers while the chunk before is computed and written to LDS between two barriers.  The contraction runs in blocks of
 // 16 patch values: lane (m,kk) reads the four values 16 blk + 4 kk .. +3 of image m; lane (n,kk) reads the NT filters
 // f0 + NT n .. of the four weight rows 16 blk + 4 kk .. +3 (the filters are the fast index of w, the patch values the
-// slow one) and transposes them in registers into NT operands of four consecutive patch values each.  A patch row
-// that is not a multiple of 16 ends in a partial block: its lanes beyond the row feed zeros as weights (the LDS
-// holds the neighbouring field's pixels there).
+// slow one) and transposes them in registers into NT operands of four consecutive patch values each.  A chunk
+// that is no multiple of 16 ends in a partial block: its lanes beyond the chunk feed zeros in both operands (the LDS
+// holds the neighbouring field's pixels there, and the last weight row again: zeros on one side only would let an
+// infinity or a NaN into fields that do not hold it).
 //
 // What bounds it is the number of loads a compute unit can have outstanding beyond L2, so they are few and wide: a lane
 // takes 16 bytes of one weight row, an instruction whole lines (asked for as the NT filters of each lane, each line came in
@@ -83,7 +84,6 @@ __global__ __launch_bounds__(256, OCC) void lc_forward_bf16_staged_kernel(Geom g
     // staging map: slot q of this thread copies 4-value vector number e = tid + NTHR*q of the [BT][sq4] chunk.  Lanes past
     // the chunk's end, images beyond B and values beyond the last field of the row repeat the nearest one that exists (goff,
     // loff: bytes), so that no load or store is conditional but for whole slots.
-    const int sqc = sq4 * 4;
     const int vmax = (min(NLOC, g.LW - j0) - 1) * SC + CQ;   // values that the strip's fields read
     unsigned goff[NS], loff[NS];
 #pragma unroll
@@ -92,15 +92,6 @@ __global__ __launch_bounds__(256, OCC) void lc_forward_bf16_staged_kernel(Geom g
         const int b = e / sq4, v = min(4 * (e - b * sq4), vmax - 4);
         goff[q] = 2u * ((unsigned)min(b, g.B - 1 - b0) * (unsigned)img + v);
         loff[q] = 2u * (b * RS + v);
-    }
-    // a partial last block reads up to 12 values past a field's window: those lanes' weights are zeros, and the LDS
-    // behind the last field is cleared once so that no stale bit pattern (a NaN) meets them
-    {
-        const int nclr = (sqc + 16 - vmax) >> 2;
-        for (int e = tid; e < BT * nclr; e += NTHR) {
-            const int b = e / nclr;
-            *(u32x2 *)(xh + b * RS + vmax + 4 * (e - b * nclr)) = (u32x2){0u, 0u};
-        }
     }
     const gc_ptr xrow = (gc_ptr)(x + (size_t)b0 * img + (size_t)(i * g.S) * WC + j0 * SC);
     u32x2 st[NS];
@@ -162,7 +153,9 @@ __global__ __launch_bounds__(256, OCC) void lc_forward_bf16_staged_kernel(Geom g
 #pragma unroll
             for (int mt = 0; mt < MT; ++mt) a[mt] = *(const u32x2 *)(xwin + mt * 16 * RS + 16 * blk);
             rows_to_operands<NT>(r, bo);
-            if (16 * blk + 4 * kk >= CQ) {   // lanes past the end of the patch row chunk
+            if (blk == NB - 1 && 16 * blk + 4 * kk >= CQ) {   // lanes past the end of the chunk
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) a[mt] = (u32x2){0u, 0u};
 #pragma unroll
                 for (int u = 0; u < NT; ++u) bo[u] = (u32x2){0u, 0u};
             }
@@ -214,8 +207,7 @@ int check_forward_bf16_staged(const Geom &g, const LaunchPlan &p) {
     LC_PLAN_REQUIRE(p, sqc == CQ + 3 * SC);
     LC_PLAN_REQUIRE(p, nslots <= NS && (long long)BT * sq4 <= (long long)nslots * 256);
     LC_PLAN_REQUIRE(p, strip_offsets_fit(g, BT, CQ));
-    // a partial last block reads up to 12 values past a field's window; 16 values behind the staged row are cleared;
-    // the weights behind the strip start on 16 bytes
+    // a partial last block reads up to 12 values past a field's window; the weights behind the strip start on 16 bytes
     LC_PLAN_REQUIRE(p, RS % 8 == 0 && RS >= sqc + 16);
     LC_PLAN_REQUIRE(p, p.lds_bytes >= ((size_t)BT * RS + 4 * NB * 256 * NT) * sizeof(bf16_t));
     LC_PLAN_REQUIRE(p, strips == ceil_div(g.LW, 4) && nbt == ceil_div(g.B, BT));

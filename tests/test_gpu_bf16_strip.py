@@ -76,6 +76,32 @@ def test_pixels_outside_every_field_stay_out():
     assert torch.equal(y, z)
 
 
+@pytest.mark.parametrize("t,chunk", [((17, 30, 142, 4, 3, 1, 16), 12), ((193, 62, 62, 8, 14, 3, 64), 56), ((65, 130, 104, 3, 20, 4, 32), 60)],
+                         ids=["chunk12", "chunk56", "chunk60"])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")], ids=["inf", "nan"])
+def test_non_finite_pixels_stay_in_their_fields(t, chunk, value):
+    """A pixel just right of a field reaches the fields that hold it and no other, whichever field of a strip that is."""
+    print(f"case strip non-finite {t} {value}", flush=True)
+    dims, x, w, _ = _case(t)
+    B, _, _, _, R, S, F, LH, LW, _ = dims
+    g = lc.geom(*t)
+    plan = lc.plan_query(g, Bd.LC_OP_FORWARD, lc.LC_BF16)[0]
+    assert plan["kernel"] == "lc_forward_bf16_staged" and plan["arg"][0] == chunk
+    y, z = (torch.empty((B, LH, LW, F), device="cuda") for _ in range(2))
+    lc.lc_forward(g, x, w, None, 1.0, y, lc.LC_BF16)
+    holds = torch.zeros((B, LH, LW), dtype=torch.bool, device="cuda")
+    for b, j in enumerate((0, 1, 2, 3, 6)):
+        row, col = min(R, t[1] - 1) + b, j * S + R
+        x[b, row, col] = value
+        for i in range(LH):
+            for k in range(LW):
+                holds[b, i, k] = i * S <= row < i * S + R and k * S <= col < k * S + R
+    lc.lc_forward(g, x, w, None, 1.0, z, lc.LC_BF16)
+    assert 0 < int(holds.sum()) < holds.numel()
+    assert torch.equal(z[~holds], y[~holds])
+    assert not torch.isfinite(z[holds]).any()
+
+
 # (B, H, W, C, R, S, F): one image, partly filled steps of 16, both sides of the streamed stores, blocks of 16 and 32 filters,
 # rows of 45 to 64 values, strips of one to four fields
 GRADIENTS = [(1, 22, 40, 4, 12, 1, 16), (17, 24, 41, 4, 15, 2, 32), (63, 31, 48, 3, 20, 4, 32), (64, 31, 48, 3, 20, 4, 96),
