@@ -17,9 +17,11 @@
 // takes 16 bytes of one weight row, an instruction whole lines (asked for as the NT filters of each lane, each line came in
 // two to four pieces), and none is conditional.  Weight row r of a block lies in LDS at r % 4, r / 4: a wave's read of "row
 // 4 kk + jj, filters NT n .." is 128 NT contiguous bytes.  128 images of 200 x 200 x 3, 20 x 20 at stride 4, 32 filters:
-// 183 -> 107 us with operands out of the caches, 109 -> 72 with what fits them; 120 layers drawn from 17 to 256 images and 16
-// to 128 filters: 1.40 times (geometric mean, 0.94 to 2.28) against weights from global memory by the lane that multiplies
-// them.  Single blocks of 16 filters on 32 images gain least: 32-byte pieces of a line go to different workgroups.
+// 183 -> 107 us with operands out of the caches, 109 -> 72 with what fits them, against weights from global memory by the lane
+// that multiplies them.  120 layers drawn from 17 to 256 images and 16 to 192 filters, half of them with 48 or 80 filters or at
+// most 32 images: 1.58 times out of the caches (geometric mean, 1.05 to 2.6), 1.63 in them (1.10 to 2.6).  Blocks of filters of
+// one strip follow each other: at the far ends of the launch 80 filters on 26 images of 79 x 90 x 8, 19 x 19 / 3 took 145 us in
+// the caches (131 before the staged weights), side by side 67.
 #include "lc_common.hpp"
 
 namespace lc {
@@ -63,13 +65,15 @@ __global__ __launch_bounds__(256, OCC) void lc_forward_bf16_staged_kernel(Geom g
     extern __shared__ __attribute__((aligned(16))) bf16_t xh[];      // [BT][RS] strip, then [NLOC][FB] weights
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, kk = lane >> 4;
-    // batch tiles of one strip are neighbours in dispatch order on the same XCD
-    const int t_id = remap_xcd(blockIdx.x, gridDim.x);
-    const int work = t_id / nbt;
+    // blocks of filters, then batch tiles of one strip are neighbours in dispatch order on the same XCD: the blocks share
+    // the strip, and lines of the weights where a line holds several blocks (grid.y > 1: too many workgroups for that)
+    const int nfb = gridDim.y > 1 ? 1 : g.F / (16 * NT);
+    const int t_id = remap_xcd(blockIdx.x, gridDim.x), t_fb = t_id / nfb;
+    const int work = t_fb / nbt;
     const int i = work / strips_per_row, j0 = (work - i * strips_per_row) * NLOC;
-    const int b0 = (t_id % nbt) * BT;
+    const int b0 = (t_fb - work * nbt) * BT;
     const int j = j0 + wave;
-    const int f0 = blockIdx.y * NT * 16;
+    const int f0 = (blockIdx.y + t_id - t_fb * nfb) * NT * 16;
     const bool active = j < g.LW;
     const int loc = i * g.LW + (active ? j : g.LW - 1);   // idle waves shadow the last field of the row
     const int SC = g.S * g.C, WC = g.W * g.C;
@@ -201,7 +205,7 @@ int check_forward_bf16_staged(const Geom &g, const LaunchPlan &p) {
     LC_PLAN_REQUIRE(p, (NT == 1 || NT == 2 || NT == 4) && p.block == 256);
     // 8-byte accesses of four bf16 values in x, 16-byte ones of eight filters in w
     LC_PLAN_REQUIRE(p, g.RC % 4 == 0 && WC % 4 == 0 && SC % 4 == 0);
-    LC_PLAN_REQUIRE(p, g.F % (NT * 16) == 0 && (int)p.grid[1] == g.F / (NT * 16) && p.grid[2] == 1);
+    LC_PLAN_REQUIRE(p, g.F % (NT * 16) == 0 && p.grid[2] == 1);
     // chunks of CQ values in NB blocks of 16 (the last one may be partial)
     LC_PLAN_REQUIRE(p, CQ > 0 && CQ % 4 == 0 && g.RC % CQ == 0 && NB == ceil_div(CQ, 16));
     LC_PLAN_REQUIRE(p, sqc == CQ + 3 * SC);
@@ -211,7 +215,10 @@ int check_forward_bf16_staged(const Geom &g, const LaunchPlan &p) {
     LC_PLAN_REQUIRE(p, RS % 8 == 0 && RS >= sqc + 16);
     LC_PLAN_REQUIRE(p, p.lds_bytes >= ((size_t)BT * RS + 4 * NB * 256 * NT) * sizeof(bf16_t));
     LC_PLAN_REQUIRE(p, strips == ceil_div(g.LW, 4) && nbt == ceil_div(g.B, BT));
-    LC_PLAN_REQUIRE(p, (long long)p.grid[0] == (long long)strips * g.LH * nbt);
+    // blocks of filters: all in grid.x, or all in grid.y
+    const int nfb = g.F / (NT * 16);
+    LC_PLAN_REQUIRE(p, nfb <= 65535 && (p.grid[1] == 1 || (int)p.grid[1] == nfb));
+    LC_PLAN_REQUIRE(p, (long long)p.grid[0] * p.grid[1] == (long long)strips * g.LH * nbt * nfb);
     return LC_OK;
 }
 
@@ -271,7 +278,10 @@ int launch_strip_ns(const Geom &g, const bf16_t *x, const bf16_t *w, const float
     const int strips = (g.LW + 3) / 4, nbt = (g.B + BT - 1) / BT, nslots = ceil_div(BT * (sqc / 4), 256);
     const long long nwg = (long long)strips * g.LH * nbt;
     if (nwg > 0x7fffffffLL) return LC_EUNSUPPORTED;
-    dim3 grid((unsigned)nwg, g.F / (NT * 16));
+    // the runtime counts a dimension's threads in 32 bits: 2^24 workgroups of 256 and more keep the blocks of filters in y
+    const int nfb = g.F / (NT * 16);
+    const bool flat = nwg * nfb < (1 << 24);
+    dim3 grid((unsigned)(flat ? nwg * nfb : nwg), flat ? 1 : nfb);
     auto kern = lc_forward_bf16_staged_kernel<MT, NT, NB, NS, OCC>;
     const LaunchPlan plan = make_plan("lc_forward_bf16_staged", {MT, NT, NB, NS, OCC}, {CQ, sqc / 4, RS, nbt, strips, nslots},
                                       grid, 256, strip_lds(g, BT, CQ, NT));

@@ -317,6 +317,18 @@ def test_headline_workload_takes_the_tiered_forward_plan():
     assert all(p["kernel"] != "lc_forward_direct" for p in plans)
 
 
+def test_bf16_strips_keep_the_blocks_of_filters_together():
+    """The blocks of filters of one strip share its pixels and lines of its weights: they are the fastest index of the launch;
+    grids of 2^24 workgroups and more, beyond 32 bits of threads, keep them in the second dimension."""
+    for t in ((26, 79, 90, 8, 19, 3, 80), (60, 35, 167, 8, 8, 2, 80), (128, 200, 200, 3, 20, 4, 96), (20, 20, 43, 64, 4, 1, 192),
+              (17, 2097152, 4, 1, 4, 4, 1040)):
+        g = wl.LCGeom(*t)
+        p, = lc.plan_query(lc.geom(*t), B.LC_OP_FORWARD, B.LC_BF16)
+        assert p["kernel"] == "lc_forward_bf16_staged"
+        strips, tiles, blocks = cdiv(g.LW, 4) * g.LH, cdiv(g.B, 16 * p["tparam"][0]), g.F // (16 * p["tparam"][1])
+        assert p["grid"] == ((strips * tiles * blocks, 1, 1) if strips * tiles * blocks < 2 ** 24 else (strips * tiles, blocks, 1))
+
+
 def test_filter_counts_off_the_tile_size_never_take_a_tiled_plan():
     """Layers with at least 512 workgroups of work and F not a multiple of 16 (Sec. 3.1 allows any F): the
     pipelined kernels' grids count F in whole tiles, so these must go to the general kernel, whose runs of filters end at F."""
