@@ -253,7 +253,8 @@ int strip_chunk(const Geom &g, int BT, int NT, size_t lds) {
 // Batch tile, filters per workgroup and chunk.  64-image tiles: several workgroups fit a compute unit and the second tile of
 // a strip finds the weights in L2 (128 images in 8 waves that share the staged weights: 112 against 108 us on the 200 x 200
 // layer, and up to 1.5 times slower on others).  Wide filter blocks read the strip fewer times; where they leave room for
-// chunks of less than one block only (patch rows of 4 times a prime), narrower ones keep the whole row.
+// chunks of less than one block only (patch rows of 4 times a prime), or of less than a third of what narrower ones take (100
+// values: 20 under 64 filters; 173 images of 168 x 100 x 4, 25 x 25 / 7, 192 filters 250 -> 158 us), narrower ones keep the row.
 struct StripPick {
     int MT, NT, CQ;
 };
@@ -262,10 +263,15 @@ StripPick strip_pick(const Geom &g) {
     StripPick p = {MT, 0, 0};
     for (int NT : {4, 2, 1}) {
         if (g.F % (16 * NT)) continue;
-        // LDS of two (64 filters, for their registers) or three workgroups a compute unit
-        const int CQ = strip_chunk(g, BT, NT, (NT == 4 ? 80 : 53) * 1024);
-        if (CQ > p.CQ) p.NT = NT, p.CQ = CQ;
-        if (p.CQ >= 16) break;
+        // LDS of two (64 filters, for their registers) or three workgroups a compute unit; two with 32 filters where three
+        // would cut a row in three and more (40 layers 1.25 and 1.28 times, 1.07 at least; 99 images of 29 x 170 x 12, 7 x 7 / 3,
+        // 96 filters 36.6 -> 32.7 us)
+        int CQ = strip_chunk(g, BT, NT, (NT == 4 ? 80 : 53) * 1024);
+        if (NT == 2 && CQ >= 16) {
+            const int wide = strip_chunk(g, BT, NT, 80 * 1024);
+            if (wide > 2 * CQ) CQ = wide;
+        }
+        if (CQ > (p.CQ < 16 ? p.CQ : 3 * p.CQ)) p.NT = NT, p.CQ = CQ;
     }
     return p;
 }
@@ -309,8 +315,8 @@ int launch_strip_nb(const Geom &g, const bf16_t *x, const bf16_t *w, const float
         case 6: return launch_strip<MT, NT, 6>(g, x, w, bias, alpha, y, CQ, s);
         case 7: return launch_strip<MT, NT, 7>(g, x, w, bias, alpha, y, CQ, s);
         default:
-            // 64 images with blocks of 32 filters and more: beyond strip_pick's LDS
-            if constexpr (MT == 4 && NT > 1) return LC_EUNSUPPORTED;
+            // 64 images with blocks of 64 filters: beyond strip_pick's LDS
+            if constexpr (MT == 4 && NT == 4) return LC_EUNSUPPORTED;
             else return launch_strip<MT, NT, 8>(g, x, w, bias, alpha, y, CQ, s);
     }
 }

@@ -329,6 +329,16 @@ def test_bf16_strips_keep_the_blocks_of_filters_together():
         assert p["grid"] == ((strips * tiles * blocks, 1, 1) if strips * tiles * blocks < 2 ** 24 else (strips * tiles, blocks, 1))
 
 
+def test_bf16_strips_do_not_cut_rows_small():
+    """Rows of 84, 108 and 124 values under 32 filters stay whole in the LDS of two workgroups, and rows of 100 that 64 filters
+    would cut into fifths take blocks of 32; where halves fit the LDS of three, they are kept."""
+    for t, chunk in (((99, 29, 170, 12, 7, 3, 96), 84), ((256, 107, 129, 4, 27, 7, 96), 108), ((256, 50, 50, 16, 31, 1, 32), 124),
+                     ((167, 161, 166, 4, 25, 6, 64), 100), ((128, 200, 200, 3, 20, 4, 32), 60), ((256, 40, 39, 8, 16, 1, 32), 64)):
+        p, = lc.plan_query(lc.geom(*t), B.LC_OP_FORWARD, B.LC_BF16)
+        assert p["kernel"] == "lc_forward_bf16_staged" and p["tparam"][:2] == [4, 2] and p["arg"][0] == chunk
+        assert p["lds_bytes"] <= (80 if chunk > 64 else 53) * 1024
+
+
 def test_filter_counts_off_the_tile_size_never_take_a_tiled_plan():
     """Layers with at least 512 workgroups of work and F not a multiple of 16 (Sec. 3.1 allows any F): the
     pipelined kernels' grids count F in whole tiles, so these must go to the general kernel, whose runs of filters end at F."""

@@ -23,6 +23,8 @@ LAYERS = [
     ((50, 45, 43, 4, 3, 1, 64), (4, 4, 1, 6)),
     ((130, 40, 33, 16, 11, 2, 128), (4, 4, 6, 12)),    # rows of 176 in chunks of 88
     ((32, 65, 66, 24, 9, 3, 96), (2, 2, 7, 12)),      # rows of 216 in chunks of 108
+    ((99, 29, 80, 12, 7, 3, 96), (4, 2, 6, 12)),      # rows of 84 and rows of 496 in 124s with 32 filters in the LDS of two workgroups
+    ((65, 43, 70, 16, 31, 1, 32), (4, 2, 8, 12)),
 ]
 
 
