@@ -238,10 +238,8 @@ size_t strip_lds(const Geom &g, int BT, int CQ, int NT) {
 // registers and whose strip and weights fit lds bytes; 0 if none does
 int strip_chunk(const Geom &g, int BT, int NT, size_t lds) {
     const int SC = g.S * g.C;
-    for (int nsub = 1; nsub <= g.RC / 4; ++nsub) {
-        if (g.RC % nsub) continue;
-        const int CQ = g.RC / nsub;
-        if (CQ % 4 || CQ > 128) continue;
+    for (int CQ = g.RC < 128 ? g.RC : 128; CQ >= 4; CQ -= 4) {   // (RC is a multiple of four)
+        if (g.RC % CQ) continue;
         const long long sqc = CQ + 3LL * SC;
         if (BT * (sqc / 4) > kStripSlots * 256) continue;
         if (strip_lds(g, BT, CQ, NT) > lds || !strip_offsets_fit(g, BT, CQ)) continue;
