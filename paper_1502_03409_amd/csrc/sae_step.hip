@@ -239,7 +239,8 @@ __global__ __launch_bounds__(kNormThreads) void sae_row_norm_kernel(const float 
     if (slot == 0 && e < LF) inv[e] = t > 0.f ? 1.0f / sqrtf(t) : 0.f;
 }
 
-// The flat list of weights in vectors of four: a workgroup takes kRescale * 256 neighbouring ones at a time, all in flight.
+// The flat list of weights in vectors of four: a workgroup takes N * 256 neighbouring ones at a time, all in flight (kRescale,
+// or one where that would leave compute units without a workgroup: a field of 243 x 6 weights in 120 fields 3.6 -> 2.8 us).
 // A lane's field l, its place in the field's K x F matrix and its filter move on by constant steps, with no division in the
 // loop.  A vector of a layer whose filters are no multiple of four (WHOLE false, at least four filters) may cross the end of
 // a filter row, or of a field.  HBM-bound: 542 us for the dense layer's 1.5 GB read and written (5.6 TB/s; one vector at a
@@ -257,17 +258,17 @@ __device__ __forceinline__ void move_on(long long &l, long long &pos, int &f, co
     if (pos >= KF) { pos -= KF; ++l; }
     if (f >= F) f -= F;
 }
-template <bool WHOLE>
+template <bool WHOLE, int N>
 __global__ __launch_bounds__(256) void sae_rescale_kernel(float *__restrict__ w, const float *__restrict__ inv, int F,
                                                           long long KF, long long n, RescaleStep near, RescaleStep hop) {
     const long long nv = n / 4;
-    long long e = (long long)blockIdx.x * (256 * kRescale) + threadIdx.x;
+    long long e = (long long)blockIdx.x * (256 * N) + threadIdx.x;
     long long l = 4 * e / KF, pos = 4 * e - l * KF;
     int f = (int)(pos % F);
-    for (; e < nv; e += (long long)gridDim.x * (256 * kRescale)) {
-        f32x4 v[kRescale], s[kRescale];
+    for (; e < nv; e += (long long)gridDim.x * (256 * N)) {
+        f32x4 v[N], s[N];
 #pragma unroll
-        for (int j = 0; j < kRescale; ++j) {
+        for (int j = 0; j < N; ++j) {
             if (e + j * 256 < nv) {
                 v[j] = ((const f32x4 *)w)[e + j * 256];
                 const float *iv = inv + l * F + f;
@@ -278,10 +279,10 @@ __global__ __launch_bounds__(256) void sae_rescale_kernel(float *__restrict__ w,
                     for (int c = 0; c < 4; ++c) s[j][c] = iv[f + c >= F && pos + c < KF ? c - F : c];
                 }
             }
-            move_on(l, pos, f, j < kRescale - 1 ? near : hop, F, KF);
+            move_on(l, pos, f, j < N - 1 ? near : hop, F, KF);
         }
 #pragma unroll
-        for (int j = 0; j < kRescale; ++j)
+        for (int j = 0; j < N; ++j)
             if (e + j * 256 < nv) ((f32x4 *)w)[e + j * 256] = v[j] * s[j];
     }
     if (blockIdx.x == 0 && (long long)threadIdx.x < n - 4 * nv) {       // up to three weights behind the last vector
@@ -290,7 +291,8 @@ __global__ __launch_bounds__(256) void sae_rescale_kernel(float *__restrict__ w,
     }
 }
 
-// fewer than four filters
+// Fewer than four filters: one weight at a time and lane, so as many lanes as the chip holds (8 images of 64 x 64 x 3, 8 x 8
+// at stride 4, three filters: the whole step 38 us; 45 with the vectors' grid, whose lanes took sixteen one after the other).
 __global__ __launch_bounds__(256) void sae_rescale_few_kernel(float *__restrict__ w, const float *__restrict__ inv, int F,
                                                               long long KF, long long n) {
     for (long long e = (long long)blockIdx.x * 256 + threadIdx.x; e < n; e += (long long)gridDim.x * 256)
@@ -384,16 +386,22 @@ int launch_sae_step(const Geom &g, const float *x, float *w, float *b, float *al
         LC_PLAN_REQUIRE(pn, kblocks >= 1 && kblocks <= backward_weights_max_kblocks(g));
         LC_LAUNCH(pn, "sae_step projection launch", sae_row_norm_kernel, s, ssq, kblocks, g.F, LF, split, inv);
         const long long nv = nw / 4;
-        const unsigned blocks = (unsigned)(nv / (256 * kRescale) + 1 < kRescaleBlocks ? nv / (256 * kRescale) + 1 : kRescaleBlocks);
+        const int N = nv < 256 * 256 * kRescale ? 1 : kRescale;       // (at least a workgroup for every compute unit)
+        const long long want = g.F < 4 ? nw / 256 + 1 : nv / (256 * N) + 1;     // one weight a lane, or N vectors
+        const unsigned most = g.F < 4 ? 2 * kRescaleBlocks : kRescaleBlocks, blocks = (unsigned)(want < most ? want : most);
         const LaunchPlan pr = make_plan("sae_rescale", {g.F >= 4 ? 4 : 1}, {}, dim3(blocks), 256, 0);
         auto step = [&](long long floats) { return RescaleStep{floats / KF, floats % KF, (int)(floats % g.F)}; };
-        const RescaleStep near = step(1024), hop = step(4096LL * (blocks - 1) + 1024);
+        const RescaleStep near = step(1024), hop = step(1024LL * N * (blocks - 1) + 1024);
         if (g.F < 4)
             LC_LAUNCH(pr, "sae_step projection launch", sae_rescale_few_kernel, s, w, inv, g.F, KF, nw);
+        else if (g.F % 4 == 0 && N == 1)
+            LC_LAUNCH(pr, "sae_step projection launch", (sae_rescale_kernel<true, 1>), s, w, inv, g.F, KF, nw, near, hop);
+        else if (N == 1)
+            LC_LAUNCH(pr, "sae_step projection launch", (sae_rescale_kernel<false, 1>), s, w, inv, g.F, KF, nw, near, hop);
         else if (g.F % 4 == 0)
-            LC_LAUNCH(pr, "sae_step projection launch", sae_rescale_kernel<true>, s, w, inv, g.F, KF, nw, near, hop);
+            LC_LAUNCH(pr, "sae_step projection launch", (sae_rescale_kernel<true, kRescale>), s, w, inv, g.F, KF, nw, near, hop);
         else
-            LC_LAUNCH(pr, "sae_step projection launch", sae_rescale_kernel<false>, s, w, inv, g.F, KF, nw, near, hop);
+            LC_LAUNCH(pr, "sae_step projection launch", (sae_rescale_kernel<false, kRescale>), s, w, inv, g.F, KF, nw, near, hop);
     }
     return LC_OK;
 }

@@ -303,6 +303,18 @@ def test_named_workloads_plan_and_cover(name):
     assert "sae_sparsity" in names and names[-2:] == ["sae_row_norm", "sae_rescale"]
 
 
+def test_rescaling_spreads_over_the_chip():
+    """The rescaling behind the projection: one weight a lane below four filters, vectors of four from there on, one of them a
+    lane until every compute unit has a workgroup of four."""
+    for t in ((8, 64, 64, 3, 8, 4, 3), (8, 32, 32, 3, 8, 4, 1), (4, 25, 66, 3, 9, 3, 6), (64, 32, 32, 3, 8, 4, 16),
+              (8, 72, 50, 3, 11, 1, 40), (4, 200, 200, 3, 8, 1, 3)):
+        g = wl.LCGeom(*t)
+        n = g.L * g.K * g.F
+        p = lc.plan_query(lc.geom(*t), B.LC_OP_SAE_STEP)[-1]
+        per = 256 if g.F < 4 else 1024 if n // 4 < 256 * 1024 else 4096
+        assert p["kernel"] == "sae_rescale" and p["grid"][0] == min(n // per + 1, 8192 if g.F < 4 else 4096)
+
+
 def test_headline_workload_takes_the_tiered_forward_plan():
     """cfg3's forward pass: the kernel that loads x straight into LDS, 512 strips as 64-image tiles (two whole rounds
     of 2 x 256 workgroups), the last 40 strips as 32-image tiles, together every strip once; weight ring as deep as

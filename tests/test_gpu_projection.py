@@ -20,6 +20,11 @@ CASES = {
     "tail": wl.LCGeom(B=3, H=9, W=9, C=1, R=3, S=1, F=7),
     "three_filters": wl.LCGeom(B=9, H=15, W=16, C=2, R=5, S=2, F=3),
     "one_filter": wl.LCGeom(B=9, H=15, W=16, C=2, R=5, S=2, F=1),
+    # four vectors a lane, in one trip and (over 17 million weights) in several, which carry field and filter along
+    "four_vectors_odd": wl.LCGeom(B=3, H=40, W=40, C=3, R=9, S=2, F=27),
+    "four_vectors_whole": wl.LCGeom(B=3, H=40, W=40, C=3, R=9, S=2, F=20),
+    "trips_odd": wl.LCGeom(B=2, H=100, W=100, C=3, R=10, S=2, F=27),
+    "trips_whole": wl.LCGeom(B=2, H=100, W=100, C=3, R=10, S=2, F=28),
 }
 
 
