@@ -19,6 +19,7 @@ constexpr int kPartials = 1024;     // upper bound of the scalar residual pass's
 constexpr int kSparsityThreads = 1024;
 constexpr int kSparsityBlocks = 256;   // one workgroup per compute unit: the ticket counter sees few arrivals
 constexpr int kNormThreads = 1024;
+constexpr int kNormLoads = 8;         // a lane's loads in flight
 constexpr unsigned kRescaleBlocks = 256 * 16;
 constexpr int kPartialsMax = 65536;  // upper bound of the residual pass's partial sums
 
@@ -226,8 +227,13 @@ __global__ __launch_bounds__(kNormThreads) void sae_row_norm_kernel(const float 
         const long long l = e / F;
         const int f = (int)(e - l * F);
         const float *p = ssq + (size_t)l * kblocks * F + f;
-#pragma unroll 8
-        for (int kb = slot; kb < kblocks; kb += split) t += p[(size_t)kb * F];
+        for (int kb = slot; kb < kblocks; kb += kNormLoads * split) {
+            float v[kNormLoads];
+#pragma unroll
+            for (int j = 0; j < kNormLoads; ++j) v[j] = p[(size_t)min(kb + j * split, kblocks - 1) * F];
+#pragma unroll
+            for (int j = 0; j < kNormLoads; ++j) t += kb + j * split < kblocks ? v[j] : 0.f;
+        }
     }
     if (split > 1) {
         sums[threadIdx.x] = t;
