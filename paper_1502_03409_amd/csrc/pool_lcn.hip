@@ -579,7 +579,8 @@ __global__ __launch_bounds__(kLcnThreads) void lcn_pooled_kernel(const float *__
             }
         }
     };
-    // window sums along the rows: of mh x (ow + 2r) values, mh x ow
+    // window sums along the rows: of mh x (ow + 2r) values, mh x ow (the two values of a tap are weighted before they meet:
+    // their own sum leaves the range of a float where the mean does not)
     auto along = [&](const float *m, const float *q, float *h, float *hq, int mh, int ow, float inv_ow, auto both) {
         constexpr bool TWO = decltype(both)::value;
         const int mw = ow + 2 * r;
@@ -589,8 +590,10 @@ __global__ __launch_bounds__(kLcnThreads) void lcn_pooled_kernel(const float *__
 #pragma unroll 2
             for (int d = 1; d <= r; ++d) {
                 const float g = gt[r + d];
-                s += g * (m[o - d] + m[o + d]);
-                if (TWO) s2 += g * (q[o - d] + q[o + d]);
+                s += g * m[o - d];
+                s += g * m[o + d];
+                if (TWO) s2 += g * q[o - d];
+                if (TWO) s2 += g * q[o + d];
             }
             h[e] = s;
             if (TWO) hq[e] = s2;
@@ -600,7 +603,11 @@ __global__ __launch_bounds__(kLcnThreads) void lcn_pooled_kernel(const float *__
     auto down = [&](const float *h, int o, int ow) -> float {
         float s = gt[r] * h[o];
 #pragma unroll 2
-        for (int d = 1; d <= r; ++d) s += gt[r + d] * (h[o - d * ow] + h[o + d * ow]);
+        for (int d = 1; d <= r; ++d) {
+            const float g = gt[r + d];
+            s += g * h[o - d * ow];
+            s += g * h[o + d * ow];
+        }
         return s;
     };
 

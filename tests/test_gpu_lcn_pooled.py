@@ -47,6 +47,19 @@ def test_pooled_statistics(shape, ks, flags):
     assert np.linalg.norm(got - dx0) <= 4 * tol * max(np.linalg.norm(dx0), np.linalg.norm(rs0[..., None] * dy))
 
 
+@pytest.mark.parametrize("flags", [0, 2, 4, 6])
+@pytest.mark.parametrize("shape,ks", [((2, 9, 11, 1), 3), ((2, 9, 11, 6), 5), ((1, 20, 18, 20), 9)], ids=str)
+def test_means_up_to_the_largest_float(shape, ks, flags):
+    """Sums over the channels up to 0.9 of the largest float: the window means are finite (the variances are not)."""
+    print(f"case large means {shape} {ks} {flags}", flush=True)
+    x = torch.full(shape, 3.0e38 / shape[3], device="cuda")
+    y = torch.empty(shape, device="cuda")
+    mu, rs = (torch.full(shape[:3], float("nan"), device="cuda") for _ in range(2))
+    lc.lcn_variant_fwd(x, y, mu, rs, ks, wl.LCN_SIGMA, 1e-2, flags)
+    _, mu0, _ = oracle.lcn_var_fwd(x.cpu().numpy(), ks, wl.LCN_SIGMA, 1e-2, flags)
+    assert rel_fro(mu.cpu().numpy(), mu0) <= 32.0 * ks * 2.0 ** -24
+
+
 @pytest.mark.parametrize("shape", [(2, 20, 21, 12), (2, 20, 21, 24), (1, 15, 300, 8), (1, 12, 1100, 4), (2, 16, 15, 100)], ids=str)
 def test_gradient_through_normalisation_and_pooling(shape):
     """lcn_l2pool_bwd where the tile kernel hands dp / p to the pooling gradient."""
