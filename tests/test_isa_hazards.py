@@ -63,3 +63,11 @@ def test_inline_assembly_loads_carry_their_wait_states():
             if "_lds_" in body[k]:
                 assert re.fullmatch(r"s_mov_b32 m0, s\d+", body[0]), (name, body)
     assert n_mem > 100      # the three kernels are there, with their unrolled loads
+
+
+def test_normalisation_walks_keep_their_registers():
+    """The walks hold rings of rows in registers under bounds on their waves: none may spill to scratch memory."""
+    with tempfile.TemporaryDirectory() as d:
+        text = _assembly(B.CSRC / "lcn_variants.hip", Path(d) / "lcn_variants.s")
+    spills = {n: int(v) for n, v in re.findall(r"\.name: +(\S+)\n(?:.*\n)*?.*\.vgpr_spill_count: (\d+)", text)}
+    assert sum("two_stage" in n for n in spills) >= 16 and not any(spills.values()), {n: v for n, v in spills.items() if v}
