@@ -46,7 +46,8 @@ __device__ __forceinline__ void rows_to_operands(const typename RawVec<bf16_t, N
     }
 }
 
-template <int MT, int NT, int NB, int NS, int OCC>
+// OFF: byte offsets inside a batch tile of x, 64 bits where its images take 4 GB and more
+template <int MT, int NT, int NB, int NS, int OCC, typename OFF>
 __global__ __launch_bounds__(256, OCC) void lc_forward_bf16_staged_kernel(Geom g, const bf16_t *__restrict__ x,
                                                                        const bf16_t *__restrict__ w,
                                                                        const float *__restrict__ bias, float alpha,
@@ -89,12 +90,13 @@ __global__ __launch_bounds__(256, OCC) void lc_forward_bf16_staged_kernel(Geom g
     // the chunk's end, images beyond B and values beyond the last field of the row repeat the nearest one that exists (goff,
     // loff: bytes), so that no load or store is conditional but for whole slots.
     const int vmax = (min(NLOC, g.LW - j0) - 1) * SC + CQ;   // values that the strip's fields read
-    unsigned goff[NS], loff[NS];
+    OFF goff[NS];
+    unsigned loff[NS];
 #pragma unroll
     for (int q = 0; q < NS; ++q) {
         const int e = min(tid + NTHR * q, BT * sq4 - 1);
         const int b = e / sq4, v = min(4 * (e - b * sq4), vmax - 4);
-        goff[q] = 2u * ((unsigned)min(b, g.B - 1 - b0) * (unsigned)img + v);
+        goff[q] = 2 * ((OFF)min(b, g.B - 1 - b0) * (OFF)img + v);
         loff[q] = 2u * (b * RS + v);
     }
     const gc_ptr xrow = (gc_ptr)(x + (size_t)b0 * img + (size_t)(i * g.S) * WC + j0 * SC);
@@ -191,12 +193,10 @@ __global__ __launch_bounds__(256, OCC) void lc_forward_bf16_staged_kernel(Geom g
         }
 }
 
-// 32-bit byte offsets inside a batch tile of x and a chunk of a field's weights
-bool strip_offsets_fit(const Geom &g, int BT, int CQ) {
-    return (long long)BT * g.H * g.W * g.C < (1LL << 31) && (long long)CQ * g.F < (1LL << 30);
-}
+// 32-bit byte offsets inside a batch tile of x
+bool strip_offsets_fit(const Geom &g, int BT) { return (long long)BT * g.H * g.W * g.C < (1LL << 31); }
 
-// Host check of a lc_forward_bf16_staged_kernel launch.  tparam = {MT, NT, NB, NS, waves per SIMD}; arg = {CQ, sq4, RS (bf16
+// Host check of a lc_forward_bf16_staged_kernel launch.  tparam = {MT, NT, NB, NS, waves per SIMD, 64-bit offsets}; arg = {CQ, sq4, RS (bf16
 // values), batch tiles, strips per field row, slots}.
 int check_forward_bf16_staged(const Geom &g, const LaunchPlan &p) {
     const int MT = p.tparam[0], NT = p.tparam[1], NB = p.tparam[2], NS = p.tparam[3];
@@ -210,7 +210,7 @@ int check_forward_bf16_staged(const Geom &g, const LaunchPlan &p) {
     LC_PLAN_REQUIRE(p, CQ > 0 && CQ % 4 == 0 && g.RC % CQ == 0 && NB == ceil_div(CQ, 16));
     LC_PLAN_REQUIRE(p, sqc == CQ + 3 * SC);
     LC_PLAN_REQUIRE(p, nslots <= NS && (long long)BT * sq4 <= (long long)nslots * 256);
-    LC_PLAN_REQUIRE(p, strip_offsets_fit(g, BT, CQ));
+    LC_PLAN_REQUIRE(p, (p.tparam[5] == 1 || strip_offsets_fit(g, BT)) && (long long)CQ * g.F < (1LL << 30));
     // a partial last block reads up to 12 values past a field's window; the weights behind the strip start on 16 bytes
     LC_PLAN_REQUIRE(p, RS % 8 == 0 && RS >= sqc + 16);
     LC_PLAN_REQUIRE(p, p.lds_bytes >= ((size_t)BT * RS + 4 * NB * 256 * NT) * sizeof(bf16_t));
@@ -242,7 +242,7 @@ int strip_chunk(const Geom &g, int BT, int NT, size_t lds) {
         if (g.RC % CQ) continue;
         const long long sqc = CQ + 3LL * SC;
         if (BT * (sqc / 4) > kStripSlots * 256) continue;
-        if (strip_lds(g, BT, CQ, NT) > lds || !strip_offsets_fit(g, BT, CQ)) continue;
+        if (strip_lds(g, BT, CQ, NT) > lds || (long long)CQ * g.F >= (1LL << 30)) continue;
         return CQ;
     }
     return 0;
@@ -274,7 +274,7 @@ StripPick strip_pick(const Geom &g) {
     return p;
 }
 
-template <int MT, int NT, int NB, int NS>
+template <int MT, int NT, int NB, int NS, typename OFF = unsigned>
 int launch_strip_ns(const Geom &g, const bf16_t *x, const bf16_t *w, const float *bias, float alpha, float *y, int CQ,
                     hipStream_t s) {
     constexpr int BT = 16 * MT, OCC = NT == 4 ? 2 : 3;
@@ -286,8 +286,8 @@ int launch_strip_ns(const Geom &g, const bf16_t *x, const bf16_t *w, const float
     const int nfb = g.F / (NT * 16);
     const bool flat = nwg * nfb < (1 << 24);
     dim3 grid((unsigned)(flat ? nwg * nfb : nwg), flat ? 1 : nfb);
-    auto kern = lc_forward_bf16_staged_kernel<MT, NT, NB, NS, OCC>;
-    const LaunchPlan plan = make_plan("lc_forward_bf16_staged", {MT, NT, NB, NS, OCC}, {CQ, sqc / 4, RS, nbt, strips, nslots},
+    auto kern = lc_forward_bf16_staged_kernel<MT, NT, NB, NS, OCC, OFF>;
+    const LaunchPlan plan = make_plan("lc_forward_bf16_staged", {MT, NT, NB, NS, OCC, sizeof(OFF) == 8}, {CQ, sqc / 4, RS, nbt, strips, nslots},
                                       grid, 256, strip_lds(g, BT, CQ, NT));
     if (int rc = check_forward_bf16_staged(g, plan)) return rc;
     LC_LAUNCH(plan, "lc_forward (bf16 strip) launch", kern, s, g, x, w, bias, alpha, y, strips, CQ, sqc / 4, RS, nbt, nslots);
@@ -297,6 +297,8 @@ int launch_strip_ns(const Geom &g, const bf16_t *x, const bf16_t *w, const float
 template <int MT, int NT, int NB>
 int launch_strip(const Geom &g, const bf16_t *x, const bf16_t *w, const float *bias, float alpha, float *y, int CQ,
                  hipStream_t s) {
+    if (!strip_offsets_fit(g, 16 * MT))
+        return launch_strip_ns<MT, NT, NB, kStripSlots, unsigned long long>(g, x, w, bias, alpha, y, CQ, s);
     if (16 * MT * (CQ + 3 * g.S * g.C) <= 6 * 4 * 256) return launch_strip_ns<MT, NT, NB, 6>(g, x, w, bias, alpha, y, CQ, s);
     return launch_strip_ns<MT, NT, NB, kStripSlots>(g, x, w, bias, alpha, y, CQ, s);
 }
@@ -474,7 +476,8 @@ int launch_rows_pf(const Geom &g, const bf16_t *x, const bf16_t *dy, float beta,
 // are not stored.  The patch rows are split over grid.z so that small layers still fill the chip.
 // Unconditional staging loads and streamed stores: 127 -> 107 us on the 128 x 200 x 200 x 3 layer out of the caches, 111 -> 85
 // in them; 50 drawn layers of 5 to 128 images 1.19 times (geometric mean) against a branch per load.
-template <int NT, bool STREAM>
+// OFF: byte offsets into x, 64 bits from 4 GB on.
+template <int NT, bool STREAM, typename OFF>
 __global__ __launch_bounds__(256, 3) void lc_bwd_weights_bf16_strip_kernel(Geom g, const bf16_t *__restrict__ x,
                                                                          const bf16_t *__restrict__ dy, float beta,
                                                                          float *__restrict__ out, int strips_per_row,
@@ -518,12 +521,13 @@ __global__ __launch_bounds__(256, 3) void lc_bwd_weights_bf16_strip_kernel(Geom 
     // conditional but for whole slots.  Images beyond B are cleared once.
     const int nslots = (g.B * sq4 + NTHR - 1) / NTHR;
     const int vmax = (min(NLOC, g.LW - j0) - 1) * SC + g.RC;   // values that the strip's fields read
-    unsigned goff[kStripSlots], loff[kStripSlots];
+    OFF goff[kStripSlots];
+    unsigned loff[kStripSlots];
 #pragma unroll
     for (int q = 0; q < kStripSlots; ++q) {
         const int e = min(tid + NTHR * q, g.B * sq4 - 1);
         const int b = e / sq4, v = min(4 * (e - b * sq4), vmax - 4);
-        goff[q] = 2u * ((unsigned)b * (unsigned)img + v);
+        goff[q] = 2 * ((OFF)b * (OFF)img + v);
         loff[q] = 2u * (b * RS + v);
     }
     for (int e = g.B * (RS >> 2) + tid; e < BT * (RS >> 2); e += NTHR) *(u32x2 *)(xh + 4 * e) = (u32x2){0u, 0u};
@@ -601,7 +605,7 @@ int wstrip_row_stride(const Geom &g, int sqc) {
     return ((need - 8 + 63) / 64) * 64 + 8;
 }
 
-// Host check of a lc_bwd_weights_bf16_strip_kernel launch.  tparam = {NT, streamed stores}; arg = {strips per field row, sq4, RS
+// Host check of a lc_bwd_weights_bf16_strip_kernel launch.  tparam = {NT, streamed stores, 64-bit offsets}; arg = {strips per field row, sq4, RS
 // (bf16 values), patch rows per workgroup}.
 int check_backward_weights_bf16_strip(const Geom &g, const LaunchPlan &p) {
     const int NT = p.tparam[0];
@@ -614,7 +618,7 @@ int check_backward_weights_bf16_strip(const Geom &g, const LaunchPlan &p) {
     LC_PLAN_REQUIRE(p, g.RC <= 64);
     LC_PLAN_REQUIRE(p, sqc >= g.RC + 3 * SC && sqc <= 0xffff);
     LC_PLAN_REQUIRE(p, (long long)128 * sq4 <= (long long)kStripSlots * 256);
-    LC_PLAN_REQUIRE(p, (long long)g.B * g.H * WC < (1LL << 31));   // 32-bit byte offsets into x
+    LC_PLAN_REQUIRE(p, p.tparam[2] == 1 || strip_offsets_fit(g, g.B));
     LC_PLAN_REQUIRE(p, RS % 4 == 0 && RS >= sqc && RS >= 3 * SC + 64);
     LC_PLAN_REQUIRE(p, p.lds_bytes >= ((size_t)128 * RS + 64) * sizeof(bf16_t));
     LC_PLAN_REQUIRE(p, strips == ceil_div(g.LW, 4) && (long long)p.grid[0] == (long long)strips * g.LH);
@@ -623,12 +627,12 @@ int check_backward_weights_bf16_strip(const Geom &g, const LaunchPlan &p) {
     return LC_OK;
 }
 
-template <int NT, bool STREAM>
+template <int NT, bool STREAM, typename OFF>
 int launch_wstrip_as(const Geom &g, const bf16_t *x, const bf16_t *dy, float beta, float *out, hipStream_t s) {
     const int sqc = (g.RC + 3 * g.S * g.C + 3) & ~3;
     const int RS = wstrip_row_stride(g, sqc);
     const size_t lds = ((size_t)128 * RS + 64) * sizeof(bf16_t);
-    auto kern = lc_bwd_weights_bf16_strip_kernel<NT, STREAM>;
+    auto kern = lc_bwd_weights_bf16_strip_kernel<NT, STREAM, OFF>;
     const int strips = (g.LW + 3) / 4;
     const long long nwork = (long long)strips * g.LH;
     if (nwork > 0x7fffffffLL) return LC_EUNSUPPORTED;
@@ -637,7 +641,7 @@ int launch_wstrip_as(const Geom &g, const bf16_t *x, const bf16_t *dy, float bet
     while (zsplit < g.R && nwork * (g.F / (NT * 16)) * zsplit < 4 * 256) ++zsplit;
     const int rows_per_wg = (g.R + zsplit - 1) / zsplit;
     dim3 grid((unsigned)nwork, g.F / (NT * 16), (g.R + rows_per_wg - 1) / rows_per_wg);
-    const LaunchPlan plan = make_plan("lc_bwd_weights_bf16_strip", {NT, (int)STREAM}, {strips, sqc / 4, RS, rows_per_wg}, grid, 256, lds);
+    const LaunchPlan plan = make_plan("lc_bwd_weights_bf16_strip", {NT, (int)STREAM, sizeof(OFF) == 8}, {strips, sqc / 4, RS, rows_per_wg}, grid, 256, lds);
     if (int rc = check_backward_weights_bf16_strip(g, plan)) return rc;
     LC_LAUNCH(plan, "lc_backward_weights (bf16 strip) launch", kern, s, g, x, dy, beta, out, strips, sqc / 4, RS,
               rows_per_wg);
@@ -648,7 +652,7 @@ bool wstrip_supported(const Geom &g) {
     const int SC = g.S * g.C;
     if (g.RC % 4 || SC % 4 || (g.W * g.C) % 4 || g.F % 16 || g.B > 128 || g.RC > 64) return false;
     const int sqc = (g.RC + 3 * SC + 3) & ~3;
-    if ((size_t)128 * (sqc / 4) > (size_t)kStripSlots * 256 || (long long)g.B * g.H * g.W * g.C >= (1LL << 31)) return false;
+    if ((size_t)128 * (sqc / 4) > (size_t)kStripSlots * 256) return false;
     return ((size_t)128 * wstrip_row_stride(g, sqc) + 64) * sizeof(bf16_t) <= 48 * 1024 && sqc <= 0xffff;
 }
 
@@ -657,9 +661,13 @@ bool wstrip_supported(const Geom &g) {
 // 48 x 29 x 4, 96 filters: 32 against 39), as they do with the half lines of 16 filters (72 of 54 x 108 x 4: 58 against 82).
 template <int NT>
 int launch_wstrip(const Geom &g, const bf16_t *x, const bf16_t *dy, float beta, float *out, hipStream_t s) {
+    const bool fit = strip_offsets_fit(g, g.B);
     if constexpr (NT == 2)
-        if (g.B >= 64 && beta == 0.f) return launch_wstrip_as<NT, true>(g, x, dy, beta, out, s);
-    return launch_wstrip_as<NT, false>(g, x, dy, beta, out, s);
+        if (g.B >= 64 && beta == 0.f)
+            return fit ? launch_wstrip_as<NT, true, unsigned>(g, x, dy, beta, out, s)
+                       : launch_wstrip_as<NT, true, unsigned long long>(g, x, dy, beta, out, s);
+    return fit ? launch_wstrip_as<NT, false, unsigned>(g, x, dy, beta, out, s)
+               : launch_wstrip_as<NT, false, unsigned long long>(g, x, dy, beta, out, s);
 }
 
 }  // namespace
@@ -689,7 +697,10 @@ int launch_backward_weights_bf16_rows(const Geom &g, const void *xv, const void 
 bool bf16_strip_forward_supported(const Geom &g) {
     const int SC = g.S * g.C;
     if (g.RC % 4 || SC % 4 || (g.W * g.C) % 4 || g.F % 16 || g.B <= 16) return false;
-    return strip_pick(g).CQ != 0;
+    const StripPick p = strip_pick(g);
+    // (with 64-bit offsets rows in pieces of less than a block go to the kernels on bf16 storage: 64 images of 3400 x 3400 x 4,
+    // 16 x 16 / 15, 32 filters in eights 2.6 ms there, 4.4 here; whole rows of 32 to 64 values 3.0 to 6.2 ms there, 2.1 to 2.7 here)
+    return p.CQ >= (strip_offsets_fit(g, 16 * p.MT) ? 4 : 16);
 }
 
 // with the widest blocks of filters

@@ -351,6 +351,18 @@ def test_bf16_strips_do_not_cut_rows_small():
         assert p["lds_bytes"] <= (80 if chunk > 64 else 53) * 1024
 
 
+def test_bf16_strips_take_images_beyond_32_bit_offsets():
+    """Batch tiles of x of 4 GB and more keep the strip kernels, with 64-bit offsets."""
+    for t, op, kernel, big in (((64, 3400, 3400, 4, 8, 8, 32), B.LC_OP_FORWARD, "lc_forward_bf16_staged", 5),
+                               ((40, 3400, 3400, 4, 8, 8, 48), B.LC_OP_FORWARD, "lc_forward_bf16_staged", 5),
+                               ((128, 4104, 4104, 1, 24, 24, 16), B.LC_OP_BACKWARD_WEIGHTS, "lc_bwd_weights_bf16_strip", 2),
+                               ((128, 2400, 2400, 4, 12, 4, 32), B.LC_OP_BACKWARD_WEIGHTS, "lc_bwd_weights_bf16_strip", 2)):
+        p, = lc.plan_query(lc.geom(*t), op, B.LC_BF16)
+        assert p["kernel"] == kernel and p["tparam"][big] == 1
+        p, = lc.plan_query(lc.geom(*t[:1], 2000, 2000, *t[3:]), op, B.LC_BF16)
+        assert p["kernel"] != kernel or p["tparam"][big] == 0
+
+
 def test_filter_counts_off_the_tile_size_never_take_a_tiled_plan():
     """Layers with at least 512 workgroups of work and F not a multiple of 16 (Sec. 3.1 allows any F): the
     pipelined kernels' grids count F in whole tiles, so these must go to the general kernel, whose runs of filters end at F."""

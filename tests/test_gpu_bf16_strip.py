@@ -25,6 +25,7 @@ LAYERS = [
     ((32, 65, 66, 24, 9, 3, 96), (2, 2, 7, 12)),      # rows of 216 in chunks of 108
     ((99, 29, 80, 12, 7, 3, 96), (4, 2, 6, 12)),      # rows of 84 and rows of 496 in 124s with 32 filters in the LDS of two workgroups
     ((65, 43, 70, 16, 31, 1, 32), (4, 2, 8, 12)),
+    ((65, 2900, 2900, 4, 4, 14, 16), (4, 1, 1, 12)),  # offsets beyond 4 GB inside a batch tile
 ]
 
 
@@ -107,6 +108,7 @@ def test_non_finite_pixels_stay_in_their_fields(t, chunk, value):
 # (B, H, W, C, R, S, F): one image, partly filled steps of 16, both sides of the streamed stores, blocks of 16 and 32 filters,
 # rows of 45 to 64 values, strips of one to four fields
 GRADIENTS = [(1, 22, 40, 4, 12, 1, 16), (17, 24, 41, 4, 15, 2, 32), (63, 31, 48, 3, 20, 4, 32), (64, 31, 48, 3, 20, 4, 96),
+             (128, 4104, 4104, 1, 24, 24, 16), (128, 4104, 4104, 1, 24, 24, 32),      # offsets beyond 4 GB
              (127, 30, 45, 4, 13, 3, 48), (128, 40, 36, 4, 14, 1, 64), (65, 37, 40, 4, 16, 1, 32), (49, 37, 44, 3, 20, 4, 16)]
 
 
