@@ -226,9 +226,41 @@ def check_backward_data_fast(g, p):
     assert p["grid"][1] == cdiv(NCV, (NW // NCELL) * NT * 16)
 
 
+def staged_lds(g, BT, CQ, NT):
+    """Bytes that lc_forward_bf16_staged takes for chunks of CQ values: strip rows 16 bytes on or back modulo 128, and weights."""
+    sqc = CQ + 3 * g.S * g.C
+    RS = next(r for r in range((sqc + 16 + 7) // 8 * 8, sqc + 200, 8) if r % 64 in (8, 56))
+    return RS, (BT * RS + 4 * cdiv(CQ, 16) * 256 * NT) * 2
+
+
+def check_forward_bf16_staged(g, p):
+    MT, NT, NB, NS, OCC, big = p["tparam"][:6]
+    CQ, sq4, RS, nbt, strips, nslots = p["arg"][:6]
+    BT, SC, RC = 16 * MT, g.S * g.C, g.R * g.C
+    assert RC % CQ == 0 and CQ % 4 == 0 and NB == cdiv(CQ, 16) and 4 * sq4 == CQ + 3 * SC
+    assert (RS, p["lds_bytes"]) == staged_lds(g, BT, CQ, NT) and nslots <= NS and BT * sq4 <= nslots * 256
+    # a lane's window ends inside its row: the last field's, in the last block
+    assert 3 * SC + 16 * (NB - 1) + 16 <= RS
+    # three workgroups a compute unit; two with 64 filters, and with 32 where three would cut the row in three and more
+    three = [q for q in range(4, min(RC, 128) + 1, 4) if RC % q == 0 and BT * (q + 3 * SC) <= 12 * 1024
+             and staged_lds(g, BT, q, NT)[1] <= 53 * 1024]
+    if NT == 4 or (NT == 2 and max(three, default=0) >= 16 and CQ > 2 * max(three)):
+        assert p["lds_bytes"] <= 80 * 1024 and 2 * p["lds_bytes"] <= LDS_PER_CU
+    else:
+        assert p["lds_bytes"] <= 53 * 1024 and 3 * p["lds_bytes"] <= LDS_PER_CU and OCC == 3
+    blocks = g.F // (16 * NT)
+    assert g.F % (16 * NT) == 0 and strips == cdiv(g.LW, 4) and nbt == cdiv(g.B, BT)
+    assert p["grid"][0] * p["grid"][1] == strips * g.LH * nbt * blocks and p["grid"][1] in (1, blocks)
+    # the furthest value a staging slot loads lies inside x, its byte offset inside the batch tile inside its type
+    j0 = 4 * (strips - 1)
+    v = (min(4, g.LW - j0) - 1) * SC + CQ
+    assert j0 * SC + RC - CQ + v <= g.W * g.C and ((g.LH - 1) * g.S + g.R) <= g.H
+    assert big or 2 * BT * g.H * g.W * g.C < 2 ** 32
+
+
 FAMILY_LDS_BUDGET = {   # bytes per workgroup the launchers aim at (several workgroups per compute unit)
     "lc_forward_generic": LDS_PER_CU, "lc_bwd_data_generic": LDS_PER_CU, "lc_forward_wide": 80 * 1024,
-    "lc_bwd_data_wide": 80 * 1024, "lc_forward_bf16_strip": 48 * 1024, "lc_bwd_weights_bf16_strip": 48 * 1024,
+    "lc_bwd_data_wide": 80 * 1024, "lc_forward_bf16_staged": 80 * 1024, "lc_bwd_weights_bf16_strip": 48 * 1024,
     "lc_forward_bf16_tiled": 80 * 1024, "lc_bwd_data_bf16_tiled": 80 * 1024, "lc_bwd_weights_bf16_tiled": LDS_PER_CU,
 }
 
@@ -240,7 +272,9 @@ def check_plans(g, op, dtype, plans, replay):
         assert 64 <= p["block"] <= 1024 and p["block"] % 64 == 0
         assert all(d >= 1 for d in p["grid"]) and p["grid"][1] <= 65535 and p["grid"][2] <= 65535
     fams = {p["kernel"] for p in plans}
-    if fams == {"lc_forward_fast"} or fams == {"lc_forward_direct"}:
+    if fams == {"lc_forward_bf16_staged"}:
+        check_forward_bf16_staged(g, plans[0])
+    elif fams == {"lc_forward_fast"} or fams == {"lc_forward_direct"}:
         (check_forward_fast if fams == {"lc_forward_fast"} else check_forward_direct)(g, plans)
         if replay:
             seen = covered_forward_fast(g, plans)
@@ -301,6 +335,31 @@ def test_named_workloads_plan_and_cover(name):
     plans = lc.plan_query(G, B.LC_OP_SAE_STEP)
     names = [p["kernel"] for p in plans]
     assert "sae_sparsity" in names and names[-2:] == ["sae_row_norm", "sae_rescale"]
+
+
+def test_every_budget_belongs_to_a_kernel():
+    """A budget whose kernel is gone checks nothing."""
+    layers = {"lc_forward_generic": ((128, 62, 64, 1, 2, 4, 128), 0, 0), "lc_bwd_data_generic": ((16, 64, 62, 32, 10, 2, 1024), 1, 0),
+              "lc_forward_wide": ((128, 16, 32, 64, 15, 8, 256), 0, 0), "lc_bwd_data_wide": ((256, 32, 62, 32, 16, 4, 32), 1, 0),
+              "lc_forward_bf16_staged": ((128, 200, 200, 3, 20, 4, 32), 0, 1),
+              "lc_bwd_weights_bf16_strip": ((128, 200, 200, 3, 20, 4, 32), 2, 1),
+              "lc_forward_bf16_tiled": ((128, 64, 32, 64, 11, 1, 1024), 0, 1),
+              "lc_bwd_data_bf16_tiled": ((256, 64, 32, 64, 8, 4, 128), 1, 1),
+              "lc_bwd_weights_bf16_tiled": ((128, 64, 32, 64, 11, 1, 1024), 2, 1)}
+    assert set(layers) == set(FAMILY_LDS_BUDGET)
+    for kernel, (t, op, dtype) in layers.items():
+        plans = lc.plan_query(lc.geom(*t), OPS[op], dtype)
+        assert kernel in [p["kernel"] for p in plans], (kernel, plans)
+        check_plans(wl.LCGeom(*t), OPS[op], dtype, plans, replay=False)
+
+
+@pytest.mark.parametrize("t", [(99, 29, 170, 12, 7, 3, 96), (256, 107, 129, 4, 27, 7, 96), (167, 161, 166, 4, 25, 6, 64),
+                               (64, 60, 61, 4, 29, 1, 64), (256, 62, 62, 8, 14, 3, 64), (256, 40, 39, 8, 16, 1, 32),
+                               (26, 79, 90, 8, 19, 3, 80), (130, 40, 33, 16, 11, 2, 128), (64, 3400, 3400, 4, 8, 8, 32)])
+def test_bf16_strip_plans(t):
+    plans = lc.plan_query(lc.geom(*t), B.LC_OP_FORWARD, B.LC_BF16)
+    assert [p["kernel"] for p in plans] == ["lc_forward_bf16_staged"]
+    check_plans(wl.LCGeom(*t), B.LC_OP_FORWARD, B.LC_BF16, plans, replay=False)
 
 
 def test_rescaling_spreads_over_the_chip():
