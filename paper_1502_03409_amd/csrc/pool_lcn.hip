@@ -557,19 +557,19 @@ __global__ __launch_bounds__(kLcnThreads) void lcn_pooled_kernel(const float *__
                 const int hp = base + k * ngrp;
                 if (hp >= ph * pw) continue;
                 if constexpr (SQ) {
-                    n2[hp] = in[k] ? s1[k] : 0.f;
+                    n2[hp] = in[k] ? 0.5f * s1[k] : 0.f;
                 } else if constexpr (!kGrad) {
-                    m1[hp] = in[k] ? s1[k] : 0.f;
-                    if (OP == 0) m2[hp] = in[k] ? s2[k] : 0.f;
+                    m1[hp] = in[k] ? 0.5f * s1[k] : 0.f;
+                    if (OP == 0) m2[hp] = in[k] ? 0.5f * s2[k] : 0.f;
                 } else {
                     const int hi = divided(hp, inv_pw), hj = hp - hi * pw;
                     const float z = norm_at(hi, hj), bc = rsp[k] * rsp[k] * rsp[k] * s2[k];
                     if (OP == 1) {
                         // this pixel's own normaliser and statistics, folded into the two maps of the transposed window sums
-                        m1[hp] = in[k] ? (bc * mp[k] - rsp[k] * s1[k]) / z : 0.f;
-                        m2[hp] = in[k] ? bc / z : 0.f;
+                        m1[hp] = in[k] ? 0.5f * ((bc * mp[k] - rsp[k] * s1[k]) / z) : 0.f;
+                        m2[hp] = in[k] ? 0.5f * (bc / z) : 0.f;
                     } else {
-                        m1[hp] = in[k] ? -0.5f * bc / z : 0.f;            // gradient of its variance, over its normaliser
+                        m1[hp] = in[k] ? -0.25f * bc / z : 0.f;           // gradient of its variance, over its normaliser
                         m2[hp] = rsp[k] * s1[k];
                         m3[hp] = s3[k];
                     }
@@ -579,8 +579,7 @@ __global__ __launch_bounds__(kLcnThreads) void lcn_pooled_kernel(const float *__
             }
         }
     };
-    // window sums along the rows: of mh x (ow + 2r) values, mh x ow (the two values of a tap are weighted before they meet:
-    // their own sum leaves the range of a float where the mean does not)
+    // window sums along the rows: of mh x (ow + 2r) values, mh x ow
     auto along = [&](const float *m, const float *q, float *h, float *hq, int mh, int ow, float inv_ow, auto both) {
         constexpr bool TWO = decltype(both)::value;
         const int mw = ow + 2 * r;
@@ -590,25 +589,20 @@ __global__ __launch_bounds__(kLcnThreads) void lcn_pooled_kernel(const float *__
 #pragma unroll 2
             for (int d = 1; d <= r; ++d) {
                 const float g = gt[r + d];
-                s += g * m[o - d];
-                s += g * m[o + d];
-                if (TWO) s2 += g * q[o - d];
-                if (TWO) s2 += g * q[o + d];
+                s += g * (m[o - d] + m[o + d]);
+                if (TWO) s2 += g * (q[o - d] + q[o + d]);
             }
             h[e] = s;
             if (TWO) hq[e] = s2;
         }
     };
-    // and down a column of them, around element o
+    // and down a column of them, around element o.  What the windows sum lies in LDS halved: the two values of a tap meet
+    // before they are weighted, and their sum leaves the range of a float where the window's mean does not.
     auto down = [&](const float *h, int o, int ow) -> float {
         float s = gt[r] * h[o];
 #pragma unroll 2
-        for (int d = 1; d <= r; ++d) {
-            const float g = gt[r + d];
-            s += g * h[o - d * ow];
-            s += g * h[o + d * ow];
-        }
-        return s;
+        for (int d = 1; d <= r; ++d) s += gt[r + d] * (h[o - d * ow] + h[o + d * ow]);
+        return 2.f * s;
     };
 
     round(hh, hw, inv_hw, R, std::false_type{});
@@ -647,7 +641,7 @@ __global__ __launch_bounds__(kLcnThreads) void lcn_pooled_kernel(const float *__
                 }
             } else {
                 const int o = (i + r) * hw + j + r;
-                n1[e] = in ? (m2[o] + 2.f * s * m3[o]) / z : 0.f;
+                n1[e] = in ? 0.5f * ((m2[o] + 2.f * s * m3[o]) / z) : 0.f;
                 if (own) t2[(i - r) * tw + j - r] = 2.f * s;
             }
         }
