@@ -476,8 +476,9 @@ int launch_rows_pf(const Geom &g, const bf16_t *x, const bf16_t *dy, float beta,
 // are not stored.  The patch rows are split over grid.z so that small layers still fill the chip.
 // Unconditional staging loads and streamed stores: 127 -> 107 us on the 128 x 200 x 200 x 3 layer out of the caches, 111 -> 85
 // in them; 50 drawn layers of 5 to 128 images 1.19 times (geometric mean) against a branch per load.
-// OFF: byte offsets into x, 64 bits from 4 GB on.
-template <int NT, bool STREAM, typename OFF>
+// OFF: byte offsets into x, 64 bits from 4 GB on.  NSTEP: steps of 16 images the batch may have; with eight for every batch the
+// loads of dy asked for the last image again and again (29 images of 34 x 50 x 4, 13 x 13 / 2, 32 filters: 11.1 us, 8.8 with two).
+template <int NT, bool STREAM, typename OFF, int NSTEP>
 __global__ __launch_bounds__(256, 3) void lc_bwd_weights_bf16_strip_kernel(Geom g, const bf16_t *__restrict__ x,
                                                                          const bf16_t *__restrict__ dy, float beta,
                                                                          float *__restrict__ out, int strips_per_row,
@@ -487,7 +488,7 @@ __global__ __launch_bounds__(256, 3) void lc_bwd_weights_bf16_strip_kernel(Geom 
     typedef const __attribute__((address_space(1))) BR *gb_ptr;
     typedef const __attribute__((address_space(1))) u32x2 *gx4_ptr;
     typedef const __attribute__((address_space(1))) char *gc_ptr;
-    constexpr int BT = 128, NSTEP = BT / 16, NLOC = 4, NTHR = 256;
+    constexpr int BT = 16 * NSTEP, NLOC = 4, NTHR = 256;
     extern __shared__ __attribute__((aligned(16))) bf16_t xh[];      // [BT][RS] (+ 64 values of slack)
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int m = lane & 15, kk = lane >> 4;
@@ -605,14 +606,14 @@ int wstrip_row_stride(const Geom &g, int sqc) {
     return ((need - 8 + 63) / 64) * 64 + 8;
 }
 
-// Host check of a lc_bwd_weights_bf16_strip_kernel launch.  tparam = {NT, streamed stores, 64-bit offsets}; arg = {strips per field row, sq4, RS
+// Host check of a lc_bwd_weights_bf16_strip_kernel launch.  tparam = {NT, streamed stores, 64-bit offsets, steps of 16 images}; arg = {strips per field row, sq4, RS
 // (bf16 values), patch rows per workgroup}.
 int check_backward_weights_bf16_strip(const Geom &g, const LaunchPlan &p) {
     const int NT = p.tparam[0];
     const int strips = p.arg[0], sq4 = p.arg[1], RS = p.arg[2], rows_per_wg = p.arg[3];
     const int SC = g.S * g.C, WC = g.W * g.C, sqc = 4 * sq4;
     LC_PLAN_REQUIRE(p, p.block == 256 && (NT == 1 || NT == 2 || NT == 4));
-    LC_PLAN_REQUIRE(p, g.RC % 4 == 0 && SC % 4 == 0 && WC % 4 == 0 && g.B <= 128);
+    LC_PLAN_REQUIRE(p, g.RC % 4 == 0 && SC % 4 == 0 && WC % 4 == 0 && g.B <= 16 * p.tparam[3] && p.tparam[3] <= 8);
     LC_PLAN_REQUIRE(p, g.F % (NT * 16) == 0 && (int)p.grid[1] == g.F / (NT * 16));
     // a patch row in a block of 64 values; the last field's block reads past its patch row inside the LDS row
     LC_PLAN_REQUIRE(p, g.RC <= 64);
@@ -627,12 +628,12 @@ int check_backward_weights_bf16_strip(const Geom &g, const LaunchPlan &p) {
     return LC_OK;
 }
 
-template <int NT, bool STREAM, typename OFF>
-int launch_wstrip_as(const Geom &g, const bf16_t *x, const bf16_t *dy, float beta, float *out, hipStream_t s) {
+template <int NT, bool STREAM, typename OFF, int NSTEP>
+int launch_wstrip_steps(const Geom &g, const bf16_t *x, const bf16_t *dy, float beta, float *out, hipStream_t s) {
     const int sqc = (g.RC + 3 * g.S * g.C + 3) & ~3;
     const int RS = wstrip_row_stride(g, sqc);
     const size_t lds = ((size_t)128 * RS + 64) * sizeof(bf16_t);
-    auto kern = lc_bwd_weights_bf16_strip_kernel<NT, STREAM, OFF>;
+    auto kern = lc_bwd_weights_bf16_strip_kernel<NT, STREAM, OFF, NSTEP>;
     const int strips = (g.LW + 3) / 4;
     const long long nwork = (long long)strips * g.LH;
     if (nwork > 0x7fffffffLL) return LC_EUNSUPPORTED;
@@ -641,11 +642,19 @@ int launch_wstrip_as(const Geom &g, const bf16_t *x, const bf16_t *dy, float bet
     while (zsplit < g.R && nwork * (g.F / (NT * 16)) * zsplit < 4 * 256) ++zsplit;
     const int rows_per_wg = (g.R + zsplit - 1) / zsplit;
     dim3 grid((unsigned)nwork, g.F / (NT * 16), (g.R + rows_per_wg - 1) / rows_per_wg);
-    const LaunchPlan plan = make_plan("lc_bwd_weights_bf16_strip", {NT, (int)STREAM, sizeof(OFF) == 8}, {strips, sqc / 4, RS, rows_per_wg}, grid, 256, lds);
+    const LaunchPlan plan = make_plan("lc_bwd_weights_bf16_strip", {NT, (int)STREAM, sizeof(OFF) == 8, NSTEP}, {strips, sqc / 4, RS, rows_per_wg}, grid, 256, lds);
     if (int rc = check_backward_weights_bf16_strip(g, plan)) return rc;
     LC_LAUNCH(plan, "lc_backward_weights (bf16 strip) launch", kern, s, g, x, dy, beta, out, strips, sqc / 4, RS,
               rows_per_wg);
     return LC_OK;
+}
+
+template <int NT, bool STREAM, typename OFF>
+int launch_wstrip_as(const Geom &g, const bf16_t *x, const bf16_t *dy, float beta, float *out, hipStream_t s) {
+    if constexpr (!STREAM)
+        if (g.B <= 32) return launch_wstrip_steps<NT, STREAM, OFF, 2>(g, x, dy, beta, out, s);
+    return g.B <= 64 ? launch_wstrip_steps<NT, STREAM, OFF, 4>(g, x, dy, beta, out, s)
+                     : launch_wstrip_steps<NT, STREAM, OFF, 8>(g, x, dy, beta, out, s);
 }
 
 bool wstrip_supported(const Geom &g) {

@@ -109,6 +109,7 @@ def test_non_finite_pixels_stay_in_their_fields(t, chunk, value):
 # rows of 45 to 64 values, strips of one to four fields
 GRADIENTS = [(1, 22, 40, 4, 12, 1, 16), (17, 24, 41, 4, 15, 2, 32), (63, 31, 48, 3, 20, 4, 32), (64, 31, 48, 3, 20, 4, 96),
              (128, 4104, 4104, 1, 24, 24, 16), (128, 4104, 4104, 1, 24, 24, 32),      # offsets beyond 4 GB
+             (32, 37, 44, 3, 20, 4, 32), (33, 37, 44, 3, 20, 4, 16),               # two and four steps of 16 images
              (127, 30, 45, 4, 13, 3, 48), (128, 40, 36, 4, 14, 1, 64), (65, 37, 40, 4, 16, 1, 32), (49, 37, 44, 3, 20, 4, 16)]
 
 
@@ -118,7 +119,8 @@ def test_weight_gradient_against_fp64(t, beta):
     dims, x, dw0, _ = _case(t)
     B, _, _, _, R, S, F, LH, LW, K = dims
     g = lc.geom(*t)
-    assert lc.plan_query(g, Bd.LC_OP_BACKWARD_WEIGHTS, lc.LC_BF16)[0]["kernel"] == "lc_bwd_weights_bf16_strip"
+    plan = lc.plan_query(g, Bd.LC_OP_BACKWARD_WEIGHTS, lc.LC_BF16)[0]
+    assert plan["kernel"] == "lc_bwd_weights_bf16_strip" and plan["tparam"][3] == (2 if B <= 32 else 4 if B <= 64 else 8)
     dy = torch.randn((B, LH, LW, F), device="cuda").bfloat16()
     dw = dw0.float()
     if not beta:
