@@ -605,15 +605,25 @@ __global__ __launch_bounds__(kLcnThreads) void lcn_pooled_kernel(const float *__
         return 2.f * s;
     };
 
+    // both at once around element o of mh x hw values, for 3 x 3 windows of one stage: a barrier less for six reads more
+    auto nine = [&](const float *m, int o) -> float {
+        auto row = [&](int p) { return __fmaf_rn(gt[2], m[p - 1] + m[p + 1], gt[1] * m[p]); };
+        return 2.f * __fmaf_rn(gt[2], row(o - hw) + row(o + hw), gt[1] * row(o));
+    };
+
     round(hh, hw, inv_hw, R, std::false_type{});
     __syncthreads();
-    along(m1, m2, h1, h2, hh, hcols, inv_hc, std::bool_constant<!kTwo>{});
-    __syncthreads();
+    const bool three = !kTwo && r == 1;
+    if (!three) {
+        along(m1, m2, h1, h2, hh, hcols, inv_hc, std::bool_constant<!kTwo>{});
+        __syncthreads();
+    }
     if constexpr (!kTwo) {
         for (int e = tid; e < th * tw; e += nthr) {
             const int oi = divided(e, inv_tw), oj = e - oi * tw, row = ti + oi, col = tj + oj;
             if (row >= H || col >= W) continue;
-            const float s1 = down(h1, e + r * tw, tw), s2 = down(h2, e + r * tw, tw);
+            const int o = (oi + 1) * hw + oj + 1;
+            const float s1 = three ? nine(m1, o) : down(h1, e + r * tw, tw), s2 = three ? nine(m2, o) : down(h2, e + r * tw, tw);
             if (OP == 0) {
                 const float z = norm_at(oi + R, oj + R), m = s1 / z, var = fmaxf(s2 / z - m * m, 0.f);
                 const float rs = 1.0f / sqrtf(var + eps);
