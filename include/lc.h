@@ -163,7 +163,8 @@ int lcn_bwd(const float *x, const float *mu, const float *rstd, const float *dy,
  *                    mean_w is the Gaussian-window mean of lcn_fwd and mean_w(v^2) takes every neighbour's own v.
  * mu, rstd ([B,H,W], or [B,H,W,C] with LCN_PER_CHANNEL) hold the subtracted mean and the factor y = (x - mu) rstd.
  * lcn_variant_bwd overwrites dx [B,H,W,C] (which must not alias x or dy); with LCN_TWO_STAGE it needs
- * lcn_variant_workspace_bytes() of scratch (LC_EWORKSPACE otherwise), 0 bytes for the one-stage forms.
+ * lcn_variant_workspace_bytes() of scratch (LC_EWORKSPACE otherwise), 0 bytes for the one-stage forms.  (The two-stage form
+ * with pooled statistics no longer writes its B*H*W floats: callers keep the sizes and the answers they were built on.)
  * ksize odd, 1 <= ksize <= 15; unknown flag bits give LC_EINVAL. */
 #define LCN_PER_CHANNEL 1u
 #define LCN_ZERO_PAD 2u

@@ -230,11 +230,11 @@ int launch_backward_data_simple(const Geom &g, const void *dy, const void *w, fl
 // bf16 storage, for nearly every other shape the general kernels, and for the rest the masked fp32 kernels on bf16 storage.
 //
 // Where the general kernels come first (both sides measured on some 130 layers):
-//  - forward: instead of the strip kernel where that has fewer workgroups than the chip compute units (24 to 255 of them: faster
-//    or the same on 48 of 58 layers, 1.23 times on average and up to four: 45 images of 73 x 15 x 8, 14 x 14 at stride 6, 80
-//    filters 63 -> 16 us; the other ten, most at stride 1, are up to 2.1 times slower: 64 images of 31 x 32 x 4, 16 x 16, 96
-//    filters 34.5 against 71; from 264 workgroups on the strip kernel is faster: 147 images of 20 x 91 x 8, 6 x 6 at stride 2,
-//    16 filters 15.4), and instead of the one-wave-per-task kernel but for patches of at most 128 elements (128
+//  - forward: instead of the strip kernel where that would have fewer workgroups than the chip compute units, counted with its
+//    widest blocks of filters (24 to 255 of them: faster or the same on 88 of 100 layers, 1.43 times on average and up to 8.5: 64
+//    images of 82 x 85 x 8, 13 x 13 at stride 7, 16 filters 181 -> 21 us; the other twelve, most at stride 1, are up to 1.6 times
+//    slower: 69 images of 21 x 70 x 8, 14 x 14, 64 filters 53 against 85; a line by stride and patch would keep those), and
+//    instead of the one-wave-per-task kernel but for patches of at most 128 elements (128
 //    images of 36 x 54 x 32, 16 x 16 at stride 2, 64 filters 470 -> 151 us; 16 of 84 x 76 x 8, 4 x 4 at stride 2: 7.2
 //    against 8.8 us);
 //  - backward data: instead of the one-wave-per-task kernel (10 layers of 11 faster, by 1.2 to 3.4 times: 32 images of

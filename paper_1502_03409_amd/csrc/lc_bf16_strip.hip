@@ -474,8 +474,8 @@ int launch_rows_pf(const Geom &g, const bf16_t *x, const bf16_t *dy, float beta,
 // the whole kernel (batches up to 128 images).  The 64 x 16 NT tile of a patch row is stored as soon as it is
 // complete.  Rows beyond the patch row read the neighbour's pixels: they only reach output rows that
 // are not stored.  The patch rows are split over grid.z so that small layers still fill the chip.
-// Unconditional staging loads and streamed stores: 127 -> 107 us on the 128 x 200 x 200 x 3 layer out of the caches, 111 -> 85
-// in them; 50 drawn layers of 5 to 128 images 1.19 times (geometric mean) against a branch per load.
+// Unconditional staging loads and streamed stores: 127 -> 105 us on the 128 x 200 x 200 x 3 layer out of the caches, 108 -> 84
+// in them; 60 drawn layers of up to 128 images 1.33 and 1.32 times (geometric mean, 1.03 at least) against a branch per load.
 // OFF: byte offsets into x, 64 bits from 4 GB on.  NSTEP: steps of 16 images the batch may have; with eight for every batch the
 // loads of dy asked for the last image again and again (29 images of 34 x 50 x 4, 13 x 13 / 2, 32 filters: 11.1 us, 8.8 with two).
 template <int NT, bool STREAM, typename OFF, int NSTEP>

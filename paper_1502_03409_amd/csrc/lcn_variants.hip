@@ -747,8 +747,11 @@ int launch_two_stage(Args a, int B, hipStream_t s, const char *where, bool *done
 // Large maps keep the two passes where those move the rows at the rate of memory and the one kernel re-walks too many: maps
 // narrower than the window ([175,62,4,128] 5 x 5: 43 and 44 us against 50 and 49), windows of 7 and 9 beyond 2 million
 // values ([25,116,107,32] 7 x 7: 63 and 75 us against 89 and 143; [20,43,97,32], 2.7 million, 40 and 42 against 23 and 20) and
-// the forward pass of 5 x 5 beyond 8 million ([78,88,83,32]: 97 us against 109; [132,38,44,48] 72 against 49).  The two passes
-// have no vectors where C is no multiple of four and are never faster there ([20,20,44,130]: 62 and 65 us against 25 and 35).
+// the forward pass of 5 x 5 beyond 8 million ([78,88,83,32]: 97 us against 109; [132,38,44,48] 72 against 49).  The number of
+// values is a coarse line, drawn where no map gets slower by much rather than where most get faster: beyond it the walk would be
+// faster on 57 of 81 maps with windows of 7 and 9, by up to 2 times, and slower on 20, down to 0.54; an estimate of the two
+// passes beside that of the walk would tell them apart.  The two passes have no vectors where C is no multiple of four and
+// are never faster there ([20,20,44,130]: 62 and 65 us against 25 and 35).
 template <bool GRAD>
 int launch_both_stages(const Args &a, int B, hipStream_t s, const char *where, bool *done) {
     *done = false;

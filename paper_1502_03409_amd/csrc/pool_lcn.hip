@@ -433,9 +433,9 @@ __device__ __forceinline__ float tap_norm(const GaussTaps &t, int p, int n, int 
 // Bound by latency on small maps (a round of loads, a reduction and two window passes, one after the other) and by the reads
 // of tile, halo and tile again on large ones.  Before, the two-stage form took two kernels each way that moved the mean, dv and its
 // channel sums through memory, window sums took KS*KS steps, a group of lanes had one pixel in flight, and channels that are no
-// multiple of four came one by one.  Over 250 maps (10 thousand to 20 million values, windows of 3 to 9): two stages 1.6 times
-// as fast forward and backward, 2.0 and 2.2 with odd channels; one stage 1.1 and 1.1, 1.7 and 1.7 with odd channels; the
-// slowest 0.92 ([5,26,60,48] forward 6.5 -> 7.1 us: one barrier more).
+// multiple of four came one by one.  Over 300 maps (10 thousand to 20 million values, windows of 3 to 15) out of the caches and in
+// them: two stages 1.55 and 1.73 times as fast forward, 1.79 and 2.01 backward; one stage 1.22 and 1.28, 1.22 and 1.33 (1.07 to
+// 1.10 with windows up to 9 and channels in fours); the slowest 0.95 ([224,76,7,72], 13 x 13, gradient 42.3 -> 43.6 us in them).
 constexpr int kLcnThreads = 1024;   // at most
 typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 template <int VEC, int OP, int NF, bool RAG, bool DIVX>
@@ -1153,7 +1153,9 @@ int lcn_threads(int pixels, int cv, int arrays, long long workgroups) {
 }
 
 // Tile of the tile kernel: at most 16 x 16 pixels, the image split evenly; halved, the longer side first, until there are two
-// workgroups per compute unit, as long as a tile with its halo is at most four times the tile.  On maps of eight such tiles
+// workgroups per compute unit, as long as a tile with a halo of one radius is at most four times the tile; with the two radii
+// of the two-stage form that is up to nine times, which is still the better side (the bound on two radii: 120 maps 0.97 times as
+// fast, 0.56 to 1.27; [1,96,16,384], 9 x 9, gradient 31 -> 53 us).  On maps of eight such tiles
 // per compute unit and more 16 columns where the last tile's missing ones are few (tiles then start on whole lines at few
 // channels: [64,224,104,4] 26 us against 29 in tiles of 15).
 void lcn_tile(int B, int H, int W, int r, int *th, int *tw) {
