@@ -64,6 +64,21 @@ def test_against_fp64(t, want):
     assert torch.all((y.double() - (0.5 * ref + bias.double())).abs() <= bound)
 
 
+def test_blocks_of_filters_in_the_second_dimension():
+    """2^24 workgroups and more: fields of four values, 65 blocks of 16 filters, against fp64 some field rows at a time."""
+    t = (17, 258200, 1, 4, 1, 1, 1040)
+    print(f"case strip grid.y {t}", flush=True)
+    dims, x, w, bias = _case(t)
+    g = lc.geom(*t)
+    assert lc.plan_query(g, Bd.LC_OP_FORWARD, lc.LC_BF16)[0]["grid"] == (t[1], 65, 1)
+    y = torch.full((t[0], t[1], 1, t[6]), float("nan"), device="cuda")
+    lc.lc_forward(g, x, w, bias, 0.5, y, lc.LC_BF16)
+    for i in range(0, t[1], 1 << 14):
+        p, q, c = x[:, i:i + (1 << 14), 0].double().transpose(0, 1).contiguous(), w[i:i + (1 << 14), 0].double(), bias[i:i + (1 << 14)].double()
+        ref, mag = 0.5 * torch.bmm(p, q) + c, 0.5 * torch.bmm(p.abs(), q.abs()) + c.abs()
+        assert torch.all((y[:, i:i + (1 << 14), 0].transpose(0, 1).double() - ref).abs() <= 6 * 2.0 ** -24 * mag)
+
+
 def test_pixels_outside_every_field_stay_out():
     """The last field of a row ends in a partly filled block whose lanes reach past it; the last strip has idle waves."""
     t = (64, 80, 64, 4, 3, 2, 32)                     # 31 fields end at pixel 63 of 64
