@@ -19,7 +19,7 @@
 // 4 kk + jj, filters NT n .." is 128 NT contiguous bytes.  128 images of 200 x 200 x 3, 20 x 20 at stride 4, 32 filters:
 // 183 -> 107 us with operands out of the caches, 109 -> 72 with what fits them, against weights from global memory by the lane
 // that multiplies them.  120 layers drawn from 17 to 256 images and 16 to 192 filters, half of them with 48 or 80 filters or at
-// most 32 images: 1.58 times out of the caches (geometric mean, 1.05 to 2.6), 1.63 in them (1.10 to 2.6).  Blocks of filters of
+// most 32 images: 1.54 times out of the caches (geometric mean, 1.02 to 2.5), 1.55 in them (1.06 to 2.4).  Blocks of filters of
 // one strip follow each other: at the far ends of the launch 80 filters on 26 images of 79 x 90 x 8, 19 x 19 / 3 took 145 us in
 // the caches (131 before the staged weights), side by side 67.
 #include "lc_common.hpp"
@@ -196,8 +196,8 @@ __global__ __launch_bounds__(256, OCC) void lc_forward_bf16_staged_kernel(Geom g
 // 32-bit byte offsets inside a batch tile of x
 bool strip_offsets_fit(const Geom &g, int BT) { return (long long)BT * g.H * g.W * g.C < (1LL << 31); }
 
-// Host check of a lc_forward_bf16_staged_kernel launch.  tparam = {MT, NT, NB, NS, waves per SIMD, 64-bit offsets}; arg = {CQ, sq4, RS (bf16
-// values), batch tiles, strips per field row, slots}.
+// Host check of a lc_forward_bf16_staged_kernel launch.  tparam = {MT, NT, NB, NS, waves per SIMD, 64-bit offsets}; arg = {CQ,
+// sq4, RS (bf16 values), batch tiles, strips per field row, slots}.
 int check_forward_bf16_staged(const Geom &g, const LaunchPlan &p) {
     const int MT = p.tparam[0], NT = p.tparam[1], NB = p.tparam[2], NS = p.tparam[3];
     const int CQ = p.arg[0], sq4 = p.arg[1], RS = p.arg[2], nbt = p.arg[3], strips = p.arg[4], nslots = p.arg[5];
@@ -606,8 +606,8 @@ int wstrip_row_stride(const Geom &g, int sqc) {
     return ((need - 8 + 63) / 64) * 64 + 8;
 }
 
-// Host check of a lc_bwd_weights_bf16_strip_kernel launch.  tparam = {NT, streamed stores, 64-bit offsets, steps of 16 images}; arg = {strips per field row, sq4, RS
-// (bf16 values), patch rows per workgroup}.
+// Host check of a lc_bwd_weights_bf16_strip_kernel launch.  tparam = {NT, streamed stores, 64-bit offsets, steps of 16 images};
+// arg = {strips per field row, sq4, RS (bf16 values), patch rows per workgroup}.
 int check_backward_weights_bf16_strip(const Geom &g, const LaunchPlan &p) {
     const int NT = p.tparam[0];
     const int strips = p.arg[0], sq4 = p.arg[1], RS = p.arg[2], rows_per_wg = p.arg[3];

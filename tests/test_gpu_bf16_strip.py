@@ -25,6 +25,7 @@ LAYERS = [
     ((32, 65, 66, 24, 9, 3, 96), (2, 2, 7, 12)),      # rows of 216 in chunks of 108
     ((99, 29, 80, 12, 7, 3, 96), (4, 2, 6, 12)),      # rows of 84 and rows of 496 in 124s with 32 filters in the LDS of two workgroups
     ((65, 43, 70, 16, 31, 1, 32), (4, 2, 8, 12)),
+    ((65, 40, 70, 12, 9, 2, 64), (4, 4, 3, 12)),      # rows of 108 in thirds with 64 filters
     ((65, 2900, 2900, 4, 4, 14, 16), (4, 1, 1, 12)),  # offsets beyond 4 GB inside a batch tile
 ]
 
