@@ -188,7 +188,10 @@ __global__ __launch_bounds__(64 * kBackDataWaves) void lc_bwd_data_general_kerne
         const int nvec = max(vend - vbeg, 0), ng = (nvec + 3) >> 2, nfull = nvec >> 2;
         if (ng > 0 && active) {
 #pragma unroll
-            for (int s = 0; s < PF; ++s) load(s);
+            for (int s = 0; s < PF; ++s) {
+                load(s);
+                __builtin_amdgcn_sched_barrier(0);
+            }
             int done = 0;
             for (; done + PF <= nfull; done += PF) {
 #pragma unroll

@@ -125,7 +125,10 @@ __global__ __launch_bounds__(256, 2) void lc_bwd_weights_general_kernel(
             }
         };
 #pragma unroll
-        for (int s = 0; s < PF; ++s) load(s, s);
+        for (int s = 0; s < PF; ++s) {
+            load(s, s);
+            __builtin_amdgcn_sched_barrier(0);
+        }
         int st = 0;
         for (; st + PF <= full; st += PF) {
 #pragma unroll

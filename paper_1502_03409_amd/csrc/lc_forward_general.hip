@@ -120,7 +120,10 @@ __global__ __launch_bounds__(64 * kForwardWaves(MT, NT)) void lc_forward_general
     const int nvec = max(vend - vbeg, 0), ng = (nvec + 3) >> 2, nfull = nvec >> 2;
     if (ng > 0 && active) {
 #pragma unroll
-        for (int s = 0; s < PF; ++s) load(s);
+        for (int s = 0; s < PF; ++s) {
+            load(s);
+            __builtin_amdgcn_sched_barrier(0);                // (the loop's waits count on this order)
+        }
         int done = 0;
         for (; done + PF <= nfull; done += PF) {
 #pragma unroll
@@ -157,8 +160,6 @@ __global__ __launch_bounds__(64 * kForwardWaves(MT, NT)) void lc_forward_general
 }
 
 namespace {
-
-struct ForwardTile { int mt, nt, nfw, tasks, ks; };
 
 // Host check of a lc_forward_general_kernel launch.  tparam = {MT, NT, filter blocks per workgroup, bytes per operand
 // element, RAG, slices of the contraction, tasks per workgroup}; arg = {vectors per patch row, vectors per patch, vectors
@@ -250,6 +251,7 @@ int launch_general(const Geom &g, const T *x, const T *w, const float *bias, flo
                    hipStream_t s) {
     static thread_local TileMemo<ForwardTile> memo;
     const ForwardTile t = memo.get(g, sizeof(T), pick_tile);
+    if (forward_turned_takes(g)) return launch_forward_turned(g, x, w, bias, alpha, alpha_dev, y, t, s);
 #define LC_TILE(M, N) if (t.mt == M && t.nt == N) return launch_tile<M, N>(g, x, w, bias, alpha, alpha_dev, y, t, s)
     LC_TILE(1, 1); LC_TILE(2, 1); LC_TILE(3, 1); LC_TILE(4, 1);
     LC_TILE(1, 2); LC_TILE(2, 2); LC_TILE(3, 2); LC_TILE(4, 2);

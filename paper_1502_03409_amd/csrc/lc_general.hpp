@@ -13,6 +13,30 @@ constexpr long long kMostTasks = 1LL << 30;   // tasks are numbered in 32 bits, 
 
 typedef const __attribute__((address_space(1))) char *gbytes;
 
+// Division of 0 <= n < 2^31 by a constant of the launch: a product and a shift, scalar where n is (the compiler's own division
+// by a variable is some thirty vector instructions, and a kernel's task takes half a dozen of them in a row).
+struct Divisor {
+    unsigned m, sh, d;
+    __host__ __device__ __forceinline__ int over(int n) const { return (int)(((unsigned long long)(unsigned)n * m) >> sh); }
+};
+inline Divisor divisor(int d) {
+    unsigned s = 0;
+    while ((1u << s) < (unsigned)d) ++s;
+    // m d = 2^(31+s) + e with 0 < e <= d <= 2^s, so that n e < 2^(31+s)
+    return {(unsigned)((1ull << (31 + s)) / (unsigned)d + 1), 31 + s, (unsigned)d};
+}
+
+// a wave's base address the compiler takes as it is
+__device__ __forceinline__ gbytes opaque(gbytes p) {
+    asm("" : "+s"(p));
+    return p;
+}
+// a lane's offset likewise (the variable itself, so that no copy is made)
+__device__ __forceinline__ unsigned opaque(unsigned &v) {
+    asm("" : "+v"(v));
+    return v;
+}
+
 // four consecutive elements at any element-aligned address (unaligned vector loads are one instruction on this chip)
 template <typename T> struct Quad;
 template <> struct Quad<float> { typedef f32x4 V; };
@@ -33,6 +57,7 @@ struct Run {
         v = *(const GV *)(base + off);
     }
     __device__ __forceinline__ float get(int i) const { return raw_get<T, N>(v, i); }
+    __device__ __forceinline__ void blank(bool z) { v = z ? typename RawVec<T, N>::V{} : v; }
 };
 template <>
 struct Run<float, 3> {
@@ -43,6 +68,7 @@ struct Run<float, 3> {
         a = p->a; b = p->b; c = p->c;
     }
     __device__ __forceinline__ float get(int i) const { return i == 0 ? a : i == 1 ? b : c; }
+    __device__ __forceinline__ void blank(bool z) { a = z ? 0.f : a; b = z ? 0.f : b; c = z ? 0.f : c; }
 };
 
 // the low / high halves of two packed pairs as one pair (a in the low half)
@@ -70,6 +96,9 @@ __device__ __forceinline__ void clear_below(unsigned (&v)[N], int skip) {
 #pragma unroll
     for (int q = 0; q < N; ++q) v[q] &= skip >= 2 * q + 2 ? 0u : skip == 2 * q + 1 ? 0xffff0000u : 0xffffffffu;
 }
+__device__ __forceinline__ f32x4 clear_below(f32x4 v, int skip) {
+    return (f32x4){skip > 0 ? 0.f : v[0], skip > 1 ? 0.f : v[1], skip > 2 ? 0.f : v[2], skip > 3 ? 0.f : v[3]};
+}
 __device__ __forceinline__ u32x2 clear_below(u32x2 v, int skip) {
     unsigned d[2] = {v[0], v[1]};
     clear_below<2>(d, skip);
@@ -86,6 +115,66 @@ __device__ __forceinline__ u32x4 clear_below(u32x4 v, int skip) {
     unsigned d[4] = {v[0], v[1], v[2], v[3]};
     clear_below<4>(d, skip);
     return (u32x4){d[0], d[1], d[2], d[3]};
+}
+
+// fp32 products on the bf16 matrix units.  An fp32 MFMA holds the vector ALU's own multipliers, 33 clocks for 2048 flop
+// and nothing beside it (a wave of 12 of them and 24 vector instructions takes 450 clocks of a SIMD, 390 without; the bf16
+// MFMA runs beside them).  A value is the exact sum of three bf16 (8 of its 24 bits each, rounded to nearest: the parts
+// fall by 2^9), and the product of two values is the six partial products down to 2^-16 of it; the three left out add up
+// to at most 2^-25.  All six add up in the fp32 accumulator, smallest first: 96 clocks for what takes 264 in fp32
+// MFMAs, and two roundings of the sum per 32 products and partial product instead of eight to 32 of it.
+// An infinite, NaN or overflowing operand makes every sum it meets non-finite: the kernels form such tiles again in fp32.
+struct Parts { u32x4 p[3]; };
+__device__ __forceinline__ unsigned cvt_pk_bf16(float a, float b) {
+    typedef float f32x2 __attribute__((ext_vector_type(2)));
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(unsigned, __builtin_convertvector(((f32x2){a, b}), bf16x2));
+}
+// eight consecutive contraction indices of a row or column
+__device__ __forceinline__ Parts split8(const float (&x)[8]) {
+    Parts s;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        float a = x[2 * q], b = x[2 * q + 1];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const unsigned v = cvt_pk_bf16(a, b);
+            s.p[i][q] = v;
+            if (i < 2) {
+                a -= bf16_lo(v);
+                b -= bf16_hi(v);
+            }
+        }
+    }
+    return s;
+}
+// acc[m][n] += the products of 32 contraction indices.  The partial products, smallest first, add up from zero and meet the
+// sum in one addition: a matrix instruction that adds to the sum itself rounds it each time, and not to nearest (layers of
+// 2000 products: 4.1e-7 of the result against 2.4e-7 in fp32 MFMAs; 1.1e-7 this way).
+template <int M, int N>
+__device__ __forceinline__ void mfma_split(const Parts (&a)[M], const Parts (&b)[N], f32x4 (&acc)[M][N]) {
+    constexpr int order[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
+#pragma unroll
+    for (int m = 0; m < M; ++m) {
+        f32x4 t[N];
+#pragma unroll
+        for (int o = 0; o < 6; ++o)
+#pragma unroll
+            for (int n = 0; n < N; ++n)
+                t[n] = mfma32_bf16(a[m].p[order[o][0]], b[n].p[order[o][1]], o == 0 ? (f32x4){0.f, 0.f, 0.f, 0.f} : t[n]);
+#pragma unroll
+        for (int n = 0; n < N; ++n) acc[m][n] += t[n];
+    }
+}
+// whether every value is finite
+template <int N>
+__device__ __forceinline__ bool all_finite(const f32x4 *v) {
+    float s = 0.f;
+#pragma unroll
+    for (int q = 0; q < N; ++q)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) s += v[q][r] * 0.f;
+    return s == 0.f;
 }
 
 // Sum of a tile over the `ks` waves (a power of two) that split its contraction: wave 0 of them ends up with it.  Pairs
@@ -108,6 +197,17 @@ __device__ __forceinline__ void add_slices(f32x4 *acc, f32x4 *buf, int group, in
         __syncthreads();
     }
 }
+
+// A forward pass's tile: image and filter blocks of a wave, then waves of a workgroup (blocks of filters, tasks, slices)
+struct ForwardTile { int mt, nt, nfw, tasks, ks; };
+
+// lc_forward_turned.hip: whether it takes a layer the general forward kernel supports, and its launches; `direct` is the
+// direct form's tile
+bool forward_turned_takes(const Geom &g);
+int launch_forward_turned(const Geom &g, const float *x, const float *w, const float *bias, float alpha, const float *alpha_dev,
+                          float *y, const ForwardTile &direct, hipStream_t s);
+int launch_forward_turned(const Geom &g, const bf16_t *x, const bf16_t *w, const float *bias, float alpha,
+                          const float *alpha_dev, float *y, const ForwardTile &direct, hipStream_t s);
 
 // The tile picked for a geometry, remembered per thread: picking is a pure function of the sizes that weighs up some
 // hundred candidates, a few microseconds that a launch-bound caller would pay on every call.  64 entries, each replaced
