@@ -137,7 +137,7 @@ __global__ __launch_bounds__(64 * kBackDataWaves) void lc_bwd_data_general_kerne
             for (int nt = 0; nt < NT; ++nt) {
                 unsigned off = boff + kn[nt];
                 if (MASK) {
-                    const bool ok = (unsigned)(rr[nt] - fa * g.S) < (unsigned)g.R && (unsigned)(cc[nt] - fp * g.S) < (unsigned)g.R;
+                    const bool ok = ((unsigned)(rr[nt] - fa * g.S) < (unsigned)g.R) & ((unsigned)(cc[nt] - fp * g.S) < (unsigned)g.R);
                     if (!ok) { off = 0; bad[s] |= 1u << nt; }
                 }
                 b[s][nt].load(wp, off);
@@ -297,8 +297,6 @@ __global__ __launch_bounds__(64 * kBackDataWaves) void lc_bwd_data_general_kerne
 
 namespace {
 
-struct DataTile { int mt, nt, tasks, ks, qr, qc; };
-
 // Filters per vector.  Eight fetch a row's cache line at once where four come back for it (bf16: and halve the loads per
 // MFMA: 128 images of 50 x 73 x 64, 12 x 12 fields at stride 8, 128 filters 163 -> 97 us; fp32 within 5 % either way);
 // four where eight pad the filters by more than a quarter (9 filters, bf16: 22 -> 18 us).
@@ -408,6 +406,8 @@ template <int VW, typename T>
 int launch_width(const Geom &g, const T *dy, const T *w, float *dx, hipStream_t s) {
     static thread_local TileMemo<DataTile> memo;
     const DataTile t = memo.get(g, sizeof(T), pick_tile);
+    if (backward_data_turned_takes(g, sizeof(T)))
+        return launch_backward_data_turned(g, dy, w, dx, t, VW, s);
 #define LC_TILE(M, N) if (t.mt == M && t.nt == N) return launch_tile<M, N, VW>(g, dy, w, dx, t, s)
     LC_TILE(1, 1); LC_TILE(2, 1); LC_TILE(3, 1); LC_TILE(4, 1);
     LC_TILE(1, 2); LC_TILE(2, 2); LC_TILE(3, 2); LC_TILE(4, 2);

@@ -259,16 +259,15 @@ __global__ __launch_bounds__(64 * kTurnedWaves(MT, NT)) void lc_forward_turned_k
                     for (int u = 0; u < NT; ++u) acc[mt][u] = mfma16_bf16(o.a[mt], b[u], acc[mt][u]);
             }
         };
-        auto split_multiply = [&](const Step &s) {
+        auto split_multiply = [&](const Operands &o0, const Operands &o1) {
             if constexpr (SPLIT) {
-                const Operands o0 = turned(s, 0), o1 = turned(s, GP - 1);
                 Parts pa[MT], pb[NT];
-    #pragma unroll
+#pragma unroll
                 for (int mt = 0; mt < MT; ++mt) {
                     const float e[8] = {o0.a[mt][0], o0.a[mt][1], o0.a[mt][2], o0.a[mt][3], o1.a[mt][0], o1.a[mt][1], o1.a[mt][2], o1.a[mt][3]};
                     pa[mt] = split8(e);
                 }
-    #pragma unroll
+#pragma unroll
                 for (int u = 0; u < NT; ++u) {
                     const float e[8] = {o0.b[0].get(u), o0.b[1].get(u), o0.b[2].get(u), o0.b[3].get(u),
                                         o1.b[0].get(u), o1.b[1].get(u), o1.b[2].get(u), o1.b[3].get(u)};
@@ -292,10 +291,25 @@ __global__ __launch_bounds__(64 * kTurnedWaves(MT, NT)) void lc_forward_turned_k
 #pragma unroll
         for (int s = 0; s < PF; ++s) load_step(step[s]);
         if constexpr (SPLIT) {
-            for (int st = 0; st < nst; ++st) {
-                masked(step[0], st);
-                split_multiply(step[0]);
+            auto contract = [&](auto multiply) {
+                for (int st = 0; st < nst; ++st) {
+                    masked(step[0], st);
+                    const Operands o0 = turned(step[0], 0), o1 = turned(step[0], 1);
+                    multiply(o0, o1);
+                    load_step(step[0]);
+                }
+            };
+            contract(split_multiply);
+            // an operand that is not finite, or a part that overflowed: once more in fp32
+            if (__any(!all_finite<MT * NT>(&acc[0][0]))) {
+                clear();
+                start();
+                ends = vbeg - dNV.over(vbeg) * NV;
                 load_step(step[0]);
+                contract([&](const Operands &o0, const Operands &o1) {
+                    plain(o0);
+                    plain(o1);
+                });
             }
         } else {
             // A step is turned while the one before it is multiplied: a lone wave of a SIMD would wait for LDS otherwise.
@@ -321,20 +335,6 @@ __global__ __launch_bounds__(64 * kTurnedWaves(MT, NT)) void lc_forward_turned_k
                     }
                     plain(o[s & 1]);
                 }
-        }
-        if constexpr (SPLIT) {
-            if (__any(!all_finite<MT * NT>(&acc[0][0]))) {
-                clear();
-                start();
-                ends = vbeg - dNV.over(vbeg) * NV;
-                for (int q = 0; q < ng; ++q) {
-                    Step one;
-                    load(one, 0);
-                    blank(one, 0, q);
-                    next_ends();
-                    plain(turned(one, 0));
-                }
-            }
         }
     }
     add_slices<MT * NT>(&acc[0][0], slices, grp, slice, ks);
@@ -462,7 +462,8 @@ double turned_clocks(const Geom &g, int es, const ForwardTile &t) {
     return turned_clocks(g, es, t.mt, t.nt, t.ks, t.tasks * t.nfw * t.ks, wgs);
 }
 
-// The fastest tile by the estimate; the direct form's where it is within a tenth of that.  Sums on the matrix units
+// The fastest tile by the estimate; the direct form's where it is within a tenth of that (a fifth in bf16,
+// where the estimate is further off).  Sums on the matrix units
 // are rounded towards zero once per instruction, so that a contraction in fewer slices ends less precise: tiles that add to
 // the sum that way take at least as many slices as the direct form's.
 ForwardTile pick_turned(const Geom &g, int es, const ForwardTile &direct) {
@@ -487,7 +488,7 @@ ForwardTile pick_turned(const Geom &g, int es, const ForwardTile &direct) {
             }
         }
     }
-    if (own < 1.1 * best_t) best = direct;
+    if (own < (es == 4 ? 1.1 : 1.2) * best_t) best = direct;
     best.ks = min(best.ks, kTurnedWaves(best.mt, best.nt));   // (millions of filters: no candidate with as many slices)
     arrange(g, &best);
     return best;

@@ -209,6 +209,17 @@ int launch_forward_turned(const Geom &g, const float *x, const float *w, const f
 int launch_forward_turned(const Geom &g, const bf16_t *x, const bf16_t *w, const float *bias, float alpha,
                           const float *alpha_dev, float *y, const ForwardTile &direct, hipStream_t s);
 
+// Backward data's: image and value blocks of a wave, tasks and slices of a workgroup, strides of a pixel block each way
+struct DataTile { int mt, nt, tasks, ks, qr, qc; };
+
+// lc_backward_data_turned.hip: whether it takes a layer the general backward-data kernel supports, and its launches; `direct`
+// and VW are the direct form's tile and vector width
+bool backward_data_turned_takes(const Geom &g, int es);
+int launch_backward_data_turned(const Geom &g, const float *dy, const float *w, float *dx, const DataTile &direct, int VW,
+                                hipStream_t s);
+int launch_backward_data_turned(const Geom &g, const bf16_t *dy, const bf16_t *w, float *dx, const DataTile &direct, int VW,
+                                hipStream_t s);
+
 // The tile picked for a geometry, remembered per thread: picking is a pure function of the sizes that weighs up some
 // hundred candidates, a few microseconds that a launch-bound caller would pay on every call.  64 entries, each replaced
 // by the next geometry that falls on it.

@@ -24,13 +24,14 @@ F32 = {(1, 1, 1): (1, 3, 6, 8, 2, 5, 24), (1, 1, 2): (65, 37, 34, 4, 11, 1, 8), 
        (4, 1, 1): (97, 32, 36, 8, 4, 1, 8), (4, 1, 2): (97, 40, 39, 4, 10, 1, 8), (4, 2, 1): (49, 30, 19, 16, 8, 3, 150),
        (4, 2, 2): (49, 12, 43, 5, 11, 1, 150), (4, 3, 1): (49, 26, 35, 8, 2, 2, 163), (4, 3, 2): (49, 27, 13, 7, 11, 1, 129),
        (4, 4, 1): (49, 27, 23, 8, 2, 1, 104), (4, 4, 2): (49, 29, 32, 7, 7, 2, 104)}
-BF16 = {(1, 1, 1): (1, 6, 7, 8, 2, 4, 8), (1, 2, 1): (1, 3, 6, 8, 2, 5, 24), (1, 2, 2): (33, 29, 46, 3, 11, 1, 24),
-        (1, 4, 1): (1, 26, 6, 8, 2, 1, 163), (1, 4, 2): (17, 35, 46, 5, 9, 2, 104), (2, 1, 1): (17, 20, 26, 8, 2, 1, 8),
-        (2, 2, 1): (17, 32, 37, 8, 2, 2, 40), (2, 2, 2): (17, 35, 51, 2, 11, 1, 40), (2, 4, 1): (17, 12, 37, 8, 2, 1, 163),
-        (2, 4, 2): (17, 15, 48, 7, 11, 1, 72), (3, 1, 1): (33, 32, 9, 8, 2, 1, 8), (3, 1, 2): (65, 37, 34, 4, 11, 1, 8),
-        (3, 2, 1): (33, 22, 34, 8, 2, 1, 40), (3, 2, 2): (33, 25, 43, 5, 10, 1, 24), (3, 4, 1): (33, 28, 29, 8, 2, 2, 136),
-        (4, 1, 1): (97, 7, 39, 8, 2, 1, 8), (4, 1, 2): (49, 25, 44, 7, 10, 1, 8), (4, 2, 1): (97, 21, 28, 8, 2, 1, 40),
-        (4, 4, 1): (97, 30, 12, 8, 2, 2, 129), (4, 4, 2): (49, 27, 13, 7, 11, 1, 129)}
+BF16 = {(1, 1, 1): (1, 5, 15, 4, 4, 5, 8), (1, 2, 1): (1, 3, 29, 8, 2, 5, 24), (1, 2, 2): (33, 29, 46, 3, 11, 1, 24),
+        (1, 4, 1): (1, 26, 6, 8, 2, 1, 163), (1, 4, 2): (17, 23, 26, 5, 9, 1, 104), (2, 1, 1): (97, 27, 32, 8, 2, 3, 8),
+        (2, 1, 2): (17, 42, 51, 7, 12, 1, 16), (2, 2, 1): (49, 23, 7, 8, 2, 1, 40), (2, 2, 2): (17, 36, 42, 5, 10, 1, 24),
+        (2, 4, 1): (49, 27, 17, 8, 2, 1, 104), (2, 4, 2): (17, 24, 41, 7, 11, 2, 131), (3, 1, 1): (33, 32, 33, 8, 2, 2, 8),
+        (3, 1, 2): (33, 30, 51, 7, 11, 1, 8), (3, 2, 1): (33, 23, 25, 4, 4, 1, 40), (3, 2, 2): (33, 21, 38, 7, 11, 1, 32),
+        (3, 4, 1): (33, 16, 41, 8, 2, 1, 129), (3, 4, 2): (33, 30, 36, 7, 12, 3, 129), (4, 1, 1): (97, 7, 39, 8, 2, 1, 8),
+        (4, 1, 2): (97, 32, 34, 4, 11, 1, 8), (4, 2, 1): (97, 21, 28, 8, 2, 1, 40), (4, 2, 2): (49, 13, 44, 7, 11, 1, 72),
+        (4, 4, 1): (63, 15, 37, 8, 2, 1, 72), (4, 4, 2): (49, 27, 13, 7, 11, 1, 129)}
 # contractions in slices: number, form
 SLICES = {(2, 1): (1, 15, 39, 8, 8, 4, 40), (8, 1): (1, 19, 8, 4, 8, 5, 8), (16, 1): (1, 15, 8, 8, 8, 5, 8), (2, 2): (49, 23, 47, 7, 11, 1, 8)}
 
