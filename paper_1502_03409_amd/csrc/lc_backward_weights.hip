@@ -7,7 +7,7 @@
 // elements and NT tiles of 16 filters, loops over the batch four images at a time and writes its
 // MTW x NT output tiles once.
 #include <type_traits>
-#include "lc_common.hpp"
+#include "lc_general.hpp"
 
 namespace lc {
 
@@ -140,13 +140,30 @@ __device__ __forceinline__ float vget(const typename VecT<N>::T &v, int i) {
     if constexpr (N == 1) return v; else return v[i];
 }
 
+// Tiles whose fp32 products are split into bf16 parts (mfma_split): 16 blocks over sides of four to eight, which share an
+// operand's parts often enough (K = 128, 64 filters, 256 images of 64 x 64 x 32: 886 -> 782 us; K = 1296, 100 images, 64
+// filters: 98 -> 69).  What is taken apart is vector work that the bf16 products run beside; fp32 ones would not.  Over 8 and
+// 24 blocks the parts cost what the products save (24: the registers spill, 215 -> 330).  The sums are 3 to 4 times nearer to
+// the exact ones.
+template <typename T>
+constexpr bool kWeightsSplit(int G, int VA, int NT) { return sizeof(T) == 4 && G * VA * NT == 16; }
+
+// Which launches of such a tile are split: 64 images and more, as what is left over of 32 runs without a pipeline (40 images
+// of 75 x 70 x 4, 11 x 11 at stride 2, 64 filters: 37.6 us against 42.7 split), but not a single wave per SIMD with 16 images
+// in flight at one group, which is bound by its loads and stores (128 images of 30 x 60 x 6, 8 x 8 at stride 5, 128 filters:
+// 13 against 14).
+bool weights_split(const Geom &g, int G, int PF, long long workgroups) {
+    return g.B >= 64 && !(G == 1 && PF == 4 && workgroups <= 256);
+}
+
 // SSQ: also leave, per location, block of patch elements and filter, the sum of squares of the values stored (a
 // code path of its own: the plain weight gradient carries none of it).
-template <int G, int VA, int NT, int PF, typename T = float, bool SSQ = false>
+template <int G, int VA, int NT, int PF, typename T = float, bool SSQ = false, bool SPLIT = false>
 // More waves per SIMD than the registers give by themselves do not pay: with 32 filters and blocks of 128 patch
 // elements, bounds of three and four waves per SIMD took 242 and 248-290 us against 221 us at two (the loads of
 // more waves in flight evict each other's lines from the vector cache).
-__global__ __launch_bounds__(256, G == 3 ? 2 : 1) void lc_bwd_weights_fast_kernel(Geom g, const T *__restrict__ x1,
+// The split form holds eight steps of four images and needs the bound of two: 512 registers would leave one wave.
+__global__ __launch_bounds__(256, G == 3 || SPLIT ? 2 : 1) void lc_bwd_weights_fast_kernel(Geom g, const T *__restrict__ x1,
                                                                   const T *__restrict__ dy1,
                                                                   const T *__restrict__ x2,
                                                                   const T *__restrict__ dy2, float beta,
@@ -263,22 +280,109 @@ __global__ __launch_bounds__(256, G == 3 ? 2 : 1) void lc_bwd_weights_fast_kerne
                             acc[gg][t][u] = mfma16(raw_get<T, VA>(a[ss][gg], t), raw_get<T, NT>(bv[ss], u), acc[gg][t][u]);
         }
     };
+    // The same with fp32 products split into bf16 parts (mfma_split), 32 images a step: lane kk has images kk, kk + 4, .. kk + 28
+    // of it.  What is left of the batch takes fp32 MFMAs.
+    auto contract_split = [&](auto ga_tag) {
+        constexpr int GA = decltype(ga_tag)::value;
+        for (int p = 0; p < 2; ++p) {
+            const T *x = p ? x2 : x1;
+            const T *dy = p ? dy2 : dy1;
+            if (!x) break;
+            gfloat_ptr xa[GA];
+#pragma unroll
+            for (int gg = 0; gg < GA; ++gg) xa[gg] = (gfloat_ptr)x + ((size_t)kk * img + off[gg]);
+            gfloat_ptr da = (gfloat_ptr)dy + (((size_t)kk * g.L + loc) * g.F + f0 + NT * m);
+            AV a[8][GA];
+            BR bv[8];
+            const int chunks = nsteps >> 3, left = nsteps & 7;
+            // (every group of patch elements is loaded again as soon as it is split: more would not fit the registers)
+            auto load_group = [&](int gg) {
+#pragma unroll
+                for (int ss = 0; ss < 8; ++ss) { a[ss][gg] = *(const GAV *)xa[gg]; xa[gg] += xstep; }
+            };
+            auto load_dy = [&] {
+#pragma unroll
+                for (int ss = 0; ss < 8; ++ss) { bv[ss] = *(const GBV *)da; da += dstep; }
+            };
+            load_dy();
+#pragma unroll
+            for (int gg = 0; gg < GA; ++gg) load_group(gg);
+            __builtin_amdgcn_sched_barrier(0);                // the loads of a step stay ahead of the MFMAs behind them
+            for (int c = 0; c < chunks; ++c) {
+                Parts pb[NT];
+#pragma unroll
+                for (int u = 0; u < NT; ++u) {
+                    float e[8];
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) e[q] = raw_get<T, NT>(bv[q], u);
+                    pb[u] = split8(e);
+                }
+                if (c + 1 < chunks) load_dy();
+#pragma unroll
+                for (int gg = 0; gg < GA; ++gg) {
+                    Parts pa[VA];
+#pragma unroll
+                    for (int t = 0; t < VA; ++t) {
+                        float e[8];
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) e[q] = raw_get<T, VA>(a[q][gg], t);
+                        pa[t] = split8(e);
+                    }
+                    if (c + 1 < chunks) load_group(gg);
+                    __builtin_amdgcn_sched_barrier(0);
+                    mfma_split(pa, pb, acc[gg]);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            }
+            for (int st = 0; st < left; ++st) {
+                AV al[GA];
+#pragma unroll
+                for (int gg = 0; gg < GA; ++gg) {
+                    al[gg] = *(const GAV *)xa[gg];
+                    xa[gg] += xstep;
+                }
+                const BR bl = *(const GBV *)da;
+                da += dstep;
+#pragma unroll
+                for (int gg = 0; gg < GA; ++gg)
+#pragma unroll
+                    for (int t = 0; t < VA; ++t)
+#pragma unroll
+                        for (int u = 0; u < NT; ++u)
+                            acc[gg][t][u] = mfma16(raw_get<T, VA>(al[gg], t), raw_get<T, NT>(bl, u), acc[gg][t][u]);
+            }
+        }
+    };
+    auto run = [&](auto ga_tag) {
+        if constexpr (SPLIT) {
+            contract_split(ga_tag);
+            if (!__any(!all_finite<G * VA * NT>(&acc[0][0][0]))) return;
+            // an operand that is not finite, or a part that overflowed: once more in fp32
+#pragma unroll
+            for (int gg = 0; gg < G; ++gg)
+#pragma unroll
+                for (int t = 0; t < VA; ++t)
+#pragma unroll
+                    for (int u = 0; u < NT; ++u) acc[gg][t][u] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        }
+        contract(ga_tag);
+    };
     const int ga = min(G, (g.K - k0 + VA * 16 - 1) / (VA * 16));
     if constexpr (G == 1) {
-        contract(std::integral_constant<int, 1>{});
+        run(std::integral_constant<int, 1>{});
     } else if constexpr (G == 2) {
-        if (ga == 2) contract(std::integral_constant<int, 2>{});
-        else contract(std::integral_constant<int, 1>{});
+        if (ga == 2) run(std::integral_constant<int, 2>{});
+        else run(std::integral_constant<int, 1>{});
     } else if constexpr (G == 3) {
-        if (ga == 3) contract(std::integral_constant<int, 3>{});
-        else if (ga == 2) contract(std::integral_constant<int, 2>{});
-        else contract(std::integral_constant<int, 1>{});
+        if (ga == 3) run(std::integral_constant<int, 3>{});
+        else if (ga == 2) run(std::integral_constant<int, 2>{});
+        else run(std::integral_constant<int, 1>{});
     } else {
         static_assert(G == 4, "groups per block");
-        if (ga == 4) contract(std::integral_constant<int, 4>{});
-        else if (ga == 3) contract(std::integral_constant<int, 3>{});
-        else if (ga == 2) contract(std::integral_constant<int, 2>{});
-        else contract(std::integral_constant<int, 1>{});
+        if (ga == 4) run(std::integral_constant<int, 4>{});
+        else if (ga == 3) run(std::integral_constant<int, 3>{});
+        else if (ga == 2) run(std::integral_constant<int, 2>{});
+        else run(std::integral_constant<int, 1>{});
     }
 
     float *ol = out + (size_t)loc * g.K * g.F + f0 + NT * m;
@@ -640,13 +744,18 @@ int launch_fast(const Geom &g, const T *x1, const T *dy1, const T *x2, const T *
     const LaunchPlan plan = make_plan("lc_bwd_weights_fast", {G, VA, NT, PF, (int)sizeof(T)}, {kblocks, (int)ntasks}, grid, 256, 0);
     if (int rc = check_backward_weights_fast(g, plan)) return rc;
     if (kblocks_out) *kblocks_out = kblocks;
-    if (ssq)
-        LC_LAUNCH(plan, "lc_backward_weights launch", (lc_bwd_weights_fast_kernel<G, VA, NT, PF, T, true>), s, g, x1, dy1,
-                  x2, dy2, beta, gamma, out, ssq, kblocks, (int)ntasks);
-    else
-        LC_LAUNCH(plan, "lc_backward_weights launch", (lc_bwd_weights_fast_kernel<G, VA, NT, PF, T, false>), s, g, x1, dy1,
-                  x2, dy2, beta, gamma, out, ssq, kblocks, (int)ntasks);
-    return LC_OK;
+    auto launch = [&](auto split) -> int {
+        if (ssq)
+            LC_LAUNCH(plan, "lc_backward_weights launch", (lc_bwd_weights_fast_kernel<G, VA, NT, PF, T, true, split()>), s, g,
+                      x1, dy1, x2, dy2, beta, gamma, out, ssq, kblocks, (int)ntasks);
+        else
+            LC_LAUNCH(plan, "lc_backward_weights launch", (lc_bwd_weights_fast_kernel<G, VA, NT, PF, T, false, split()>), s, g,
+                      x1, dy1, x2, dy2, beta, gamma, out, ssq, kblocks, (int)ntasks);
+        return LC_OK;
+    };
+    if constexpr (kWeightsSplit<T>(G, VA, NT))
+        if (weights_split(g, G, PF, (long long)grid.x * grid.y)) return launch(std::true_type{});
+    return launch(std::false_type{});
 }
 
 // Host check of a lc_bwd_weights_strip_kernel launch.  tparam = {MTR, NB, NSLOT, RV, NLOC}; arg = {strips per field row,
