@@ -1,15 +1,13 @@
 // lc_forward for layers of few fields and long patches (F a multiple of 128, patch rows that split into chunks of 32 or
 // 16 values): Eq. 1's encoder term with a workgroup tile of one field x 128 filters x 32*MT images.
 //
-// The four waves form a 2 x 2 grid (16*MT images x 64 filters each).  The field's patch rows reach the waves
-// through LDS in chunks of 32 contraction indices (128 contiguous bytes per image, two buffers, one barrier per
-// chunk); both image halves of a filter half load the same weights at the same time, so the CU's vector cache
-// serves the second.  A chunk is two groups of 16 indices: lane (m, kk) reads indices 4kk..4kk+3 of a group as
-// one 16-byte LDS read and uses component t in MFMA step t, and lane (n, kk) loads the weight rows 4kk+t at
-// filters 4n..4n+3 (16 lanes cover 256 contiguous bytes), which makes column n of filter tile u filter 4n+u.
+// Each of the four waves has 32 of the filters and all of the images.  fp32 products are split into bf16 parts (mfma_split), in
+// steps of 32 contraction indices: 96 MFMA cycles per 16 x 16 tile against 264 of fp32 MFMAs, which moreover keep the vector
+// unit idle.  What is left to bound the kernel is taking values apart, 22 vector instructions for four: an image's values are
+// taken apart once per workgroup, on their way into LDS, and a filter's once, by the only wave that has it.
 #include <algorithm>
 
-#include "lc_common.hpp"
+#include "lc_general.hpp"
 
 namespace lc {
 
@@ -17,12 +15,17 @@ namespace {
 
 typedef const __attribute__((address_space(1))) f32x4 *g4_ptr;
 typedef const __attribute__((address_space(1))) float *gf_ptr;
+typedef FVec<2>::T f32x2;
+typedef const __attribute__((address_space(1))) f32x2 *g2_ptr;
 
-// KCH = contraction indices per LDS chunk (32, or 16 for patch rows that are only a multiple of 16): KCH*4
-// contiguous bytes per image, rows padded by 16 bytes so that eight rows' 16-byte reads cover all banks.
+// KCH = contraction indices per chunk (32, or 16 for patch rows that are only a multiple of 16): KCH*4 contiguous bytes
+// per image.  A step is one chunk of 32 or two of 16; the second of the last step may be missing (zeros then).
+//
+// LDS: 1 KB per part of 16 images and 32 indices, two buffers, one barrier per step.  Indices 8 kk .. 8 kk + 7 of image m lie
+// at slot 4 m + (kk ^ m/4) of 16 bytes: stores (eight lanes a row) and reads (lane (m, kk)) meet no bank conflict.
 //
 // A layer with few fields (the dense last layer of Sec. 3.1 is a single one) gives too few workgroups; its
-// contraction is then cut into `nslices` ranges of chunks, each range a workgroup of its own that writes a partial
+// contraction is then cut into `nslices` ranges of steps, each range a workgroup of its own that writes a partial
 // result into the caller's workspace, and a second kernel adds the slices in a fixed order and applies alpha and
 // the bias.
 template <int MT, int PD, int KCH>
@@ -32,15 +35,11 @@ __global__ __launch_bounds__(256, 2) void lc_forward_wide_kernel(Geom g, const f
                                                                  const float *__restrict__ alpha_dev,
                                                                  float *__restrict__ y, float *__restrict__ partial,
                                                                  int fblocks, int btiles, int nslices) {
-    static_assert(PD == 1 || PD == 2, "one or two chunks of lookahead");
-    constexpr int ROWF = KCH + 4, SEGS = KCH / 4, SR = 256 / SEGS, GPC = KCH / 16;
-    constexpr int BT = 32 * MT, NS = BT / SR;     // NS: 16-byte staging slots per thread and chunk
-    constexpr int BUF = BT * ROWF;
-    static_assert(NS >= 1, "batch tile too small for the staging map");
+    static_assert(PD == 2, "two steps of lookahead");
+    constexpr int BT = 32 * MT, NT = 2 * MT, BUF = NT * 3 * 256;       // BUF: floats of a buffer, NT tiles of 16 images
     extern __shared__ __attribute__((aligned(16))) float xs[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, kk = lane >> 4;
-    const int wm = wave >> 1, wn = wave & 1;
     // batch tiles of one (field, filter block) are neighbours in dispatch order: they share the filters in L2
     int t_id = remap_xcd(blockIdx.x, gridDim.x);
     const int bt = t_id % btiles;
@@ -49,106 +48,167 @@ __global__ __launch_bounds__(256, 2) void lc_forward_wide_kernel(Geom g, const f
     t_id /= fblocks;
     const int loc = t_id % g.L, slice = t_id / g.L;
     const int i = loc / g.LW, j = loc - i * g.LW;
-    const int b0 = bt * BT, f0 = fb * 128 + wn * 64;
+    const int b0 = bt * BT, f0 = fb * 128 + wave * 32;
     const int WC = g.W * g.C;
-    const int cpr = g.RC / KCH, nchunks_all = g.R * cpr;
-    // this workgroup's range of chunks
-    const int c_lo = (int)((long long)nchunks_all * slice / nslices);
-    const int c_hi = (int)((long long)nchunks_all * (slice + 1) / nslices);
-    const int nchunks = c_hi - c_lo;
+    const int cpr = g.RC / KCH, nchunks = g.R * cpr, nsteps_all = (nchunks * KCH + 31) / 32;
+    // this workgroup's range of steps
+    const int s_lo = (int)((long long)nsteps_all * slice / nslices);
+    const int nsteps = (int)((long long)nsteps_all * (slice + 1) / nslices) - s_lo;
 
-    f32x4 acc[MT][4];
+    f32x4 acc[NT][2];
+    auto clear = [&] {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc[mt][u] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < NT; ++t) acc[t][0] = acc[t][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    };
 
-    // staging: slot s moves 16 bytes (segment tid % SEGS) of image tid / SEGS + SR s; images beyond the batch
-    // repeat image B-1 and their results are never stored
-    const int seg = tid % SEGS, brow = tid / SEGS;
-    int xoff[NS];
+    // staging: slot s moves 16 bytes (values 4 seg ..) of image tid / 8 + 32 s; images beyond the batch repeat image B-1 and
+    // their results are never stored
+    const int seg = tid & 7, brow = tid >> 3;
+    int xoff[MT];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) {
-        const int b = min(b0 + brow + SR * s, g.B - 1);
-        xoff[s] = (b * g.H + i * g.S) * WC + j * g.S * g.C + seg * 4;
+    for (int s = 0; s < MT; ++s) {
+        const int b = min(b0 + brow + 32 * s, g.B - 1);
+        xoff[s] = (b * g.H + i * g.S) * WC + j * g.S * g.C + (KCH == 32 ? seg : seg & 3) * 4;
     }
-    auto stage_load = [&](int c, f32x4 (&st)[NS]) {          // c: chunk index relative to c_lo
-        const int ca = c_lo + min(c, nchunks - 1), kh = ca / cpr;
-        const int o = kh * WC + (ca - kh * cpr) * KCH;
-#pragma unroll
-        for (int s = 0; s < NS; ++s) st[s] = *(g4_ptr)((gf_ptr)x + xoff[s] + o);
-    };
-    auto stage_store = [&](int buf, const f32x4 (&st)[NS]) {
-#pragma unroll
-        for (int s = 0; s < NS; ++s) *(f32x4 *)(xs + buf * BUF + (brow + SR * s) * ROWF + seg * 4) = st[s];
-    };
-    // filters: the chunks tile k contiguously; group q covers rows 16q .. 16q+15 of the field's K x F matrix
-    gf_ptr wl = (gf_ptr)w + (size_t)loc * g.K * g.F + f0 + 4 * n + (size_t)(4 * kk) * g.F;
-    const int q_lo = c_lo * GPC, ngroups = nchunks * GPC;
-    auto wload = [&](int q, f32x4 (&r)[4]) {                // q: group index relative to q_lo
-        gf_ptr p = wl + (size_t)(16 * (q_lo + min(q, ngroups - 1))) * g.F;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) r[t] = *(g4_ptr)(p + t * g.F);
-    };
+    // its slot in a tile of 16 images (tile brow / 16 + 2 s), in floats, and the half of it
+    const int sslot = (brow >> 4) * (3 * 256) + 4 * (4 * (brow & 15) + ((seg >> 1) ^ ((brow >> 2) & 3))), shalf = seg & 1;
+    const int aslot = 4 * (4 * n + (kk ^ (n >> 2)));
+    // the field's filters: lane (n, kk) has rows 8 kk .. 8 kk + 7 of a step at filters 2 n, 2 n + 1 of the wave's
+    const gbytes wl = (gbytes)(w + (size_t)loc * g.K * g.F + f0);
+    unsigned woff = (unsigned)((8 * kk * g.F + 2 * n) * 4);
+    // a last step of one chunk of 16: rows beyond the patch are read 16 rows earlier (times zeros)
+    unsigned woff_half = (unsigned)((8 * (kk & 1) * g.F + 2 * n) * 4);
 
-    if (nchunks > 0) {
-        f32x4 st[PD][NS];
-        f32x4 wr[GPC * PD][4];
+    auto pass = [&](auto split_tag) {
+        constexpr bool SPLIT = decltype(split_tag)::value;
+        // the chunk to be staged next (it stays on the last one)
+        int c = KCH == 32 ? s_lo : 2 * s_lo, kh = c / cpr, cc = c - kh * cpr;
+        auto next_chunk = [&] {
+            const int o = kh * WC + cc * KCH;
+            if (c < nchunks - 1) {
+                ++c;
+                if (++cc == cpr) { cc = 0; ++kh; }
+            }
+            return o;
+        };
+        auto stage_load = [&](f32x4 (&st)[MT]) {
+            int o = next_chunk();
+            if constexpr (KCH == 16) {
+                const int o1 = next_chunk();
+                o = seg < 4 ? o : o1;
+            }
 #pragma unroll
-        for (int q = 0; q < GPC * PD; ++q) wload(q, wr[q]);
-        stage_load(0, st[0]);
+            for (int s = 0; s < MT; ++s) st[s] = *(g4_ptr)((gf_ptr)x + xoff[s] + o);
+        };
+        auto stage_store = [&](int step, f32x4 (&st)[MT]) {
+            float *buf = xs + (step & 1) * BUF + sslot;
+            if constexpr (KCH == 16) {
+                if (2 * (s_lo + step) + 1 == nchunks && seg >= 4) {
+#pragma unroll
+                    for (int s = 0; s < MT; ++s) st[s] = (f32x4){0.f, 0.f, 0.f, 0.f};
+                }
+            }
+#pragma unroll
+            for (int s = 0; s < MT; ++s) {
+                if constexpr (SPLIT) {
+                    float e[4] = {st[s][0], st[s][1], st[s][2], st[s][3]};
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) {
+                        const u32x2 v = {cvt_pk_bf16(e[0], e[1]), cvt_pk_bf16(e[2], e[3])};
+                        *(u32x2 *)(buf + (s * 2 * 3 + q) * 256 + 2 * shalf) = v;
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) e[r] -= r & 1 ? bf16_hi(v[r >> 1]) : bf16_lo(v[r >> 1]);
+                    }
+                } else {
+                    *(f32x4 *)(buf + (s * 2 * 3 + shalf) * 256) = st[s];
+                }
+            }
+        };
+        auto wload = [&](int step, f32x2 (&r)[8]) {
+            const int sa = s_lo + min(step, nsteps - 1);
+            gbytes p = wl + (size_t)(32 * sa) * (size_t)(4 * g.F);
+            const bool half = KCH == 16 && 2 * sa + 1 == nchunks;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                r[q] = *(g2_ptr)(opaque(p) + (half ? woff_half : woff));
+                p += 4 * g.F;
+            }
+        };
+        f32x4 st[PD][MT];
+        f32x2 wr[PD][8];
+#pragma unroll
+        for (int p = 0; p < PD; ++p) wload(p, wr[p]);
+        stage_load(st[0]);
         stage_store(0, st[0]);
 #pragma unroll
-        for (int p = 0; p < PD; ++p) stage_load(p + 1, st[p]);      // set p: chunk p+1
+        for (int p = 0; p < PD; ++p) stage_load(st[p]);             // set p: step p + 1
         __syncthreads();
-        const int arow = (wm * 16 * MT + n) * ROWF + 4 * kk;
-        for (int c0 = 0; c0 < nchunks; c0 += 2) {
+        for (int c0 = 0; c0 < nsteps; c0 += 2) {
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
-                const int c = c0 + p;               // chunk c lives in buffer p (c0 is even)
-                const int sp = p % PD;              // register set that holds chunk c+1
-                if (c < nchunks) {
-                    const float *ab = xs + p * BUF + arow;
+                const int step = c0 + p;            // it lies in buffer p, and the set p holds the next one's images
+                if (step < nsteps) {
+                    const float *ab = xs + p * BUF + aslot;
+                    float e[2][8];
 #pragma unroll
-                    for (int h = 0; h < GPC; ++h) {
-                        f32x4 bo[4];
+                    for (int u = 0; u < 2; ++u)
 #pragma unroll
-                        for (int t = 0; t < 4; ++t) bo[t] = wr[GPC * sp + h][t];
-                        wload(GPC * c + h + GPC * PD, wr[GPC * sp + h]);
+                        for (int q = 0; q < 8; ++q) e[u][q] = wr[p][q][u];
+                    if constexpr (SPLIT) {
+                        const Parts pb[2] = {split8(e[0]), split8(e[1])};
+                        wload(step + PD, wr[p]);
 #pragma unroll
-                        for (int mt = 0; mt < MT; ++mt) {
-                            const f32x4 a = *(const f32x4 *)(ab + mt * 16 * ROWF + 16 * h);
+                        for (int t = 0; t < NT; ++t) {
+                            Parts pa;
 #pragma unroll
-                            for (int t = 0; t < 4; ++t)
-#pragma unroll
-                                for (int u = 0; u < 4; ++u) acc[mt][u] = mfma16(a[t], bo[t][u], acc[mt][u]);
+                            for (int q = 0; q < 3; ++q) pa.p[q] = *(const u32x4 *)(ab + (t * 3 + q) * 256);
+                            mfma_split(pa, pb, acc[t]);
                         }
+                    } else {
+                        wload(step + PD, wr[p]);
+#pragma unroll
+                        for (int t = 0; t < NT; ++t)
+#pragma unroll
+                            for (int h = 0; h < 2; ++h) {
+                                const f32x4 a = *(const f32x4 *)(ab + (t * 3 + h) * 256);
+#pragma unroll
+                                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                                    for (int u = 0; u < 2; ++u) acc[t][u] = mfma16(a[q], e[u][4 * h + q], acc[t][u]);
+                            }
                     }
-                    // the other buffer was last read in chunk c-1, which every wave left at the previous barrier
-                    if (c + 1 < nchunks) stage_store(p ^ 1, st[sp]);
-                    if (c + 1 + PD < nchunks) stage_load(c + 1 + PD, st[sp]);
+                    // the other buffer was last read in the step before, which every wave left at the barrier
+                    if (step + 1 < nsteps) stage_store(step + 1, st[p]);
+                    if (step + 1 + PD < nsteps) stage_load(st[p]);
                 }
                 __syncthreads();
             }
+        }
+    };
+    clear();
+    if (nsteps > 0) {
+        pass(std::true_type{});
+        // an operand that is not finite, or a part that overflowed: once more in fp32
+        if (__syncthreads_or(!all_finite<2 * NT>(&acc[0][0]))) {
+            clear();
+            pass(std::false_type{});
         }
     }
 
     const bool whole = nslices == 1;
     if (whole && alpha_dev) alpha = *alpha_dev;
-    f32x4 bv = (f32x4){0.f, 0.f, 0.f, 0.f};
-    if (whole && bias) bv = *(const f32x4 *)(bias + (size_t)loc * g.F + f0 + 4 * n);
+    f32x2 bv = (f32x2){0.f, 0.f};
+    if (whole && bias) bv = *(const f32x2 *)(bias + (size_t)loc * g.F + f0 + 2 * n);
     float *yo = whole ? y : partial + (size_t)slice * g.B * g.L * g.F;
     const float sc = whole ? alpha : 1.f;
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+    for (int t = 0; t < NT; ++t)
 #pragma unroll
         for (int rr = 0; rr < 4; ++rr) {
-            const int b = b0 + wm * 16 * MT + mt * 16 + 4 * kk + rr;
+            const int b = b0 + 16 * t + 4 * kk + rr;
             if (b >= g.B) continue;
-            f32x4 o;
-#pragma unroll
-            for (int u = 0; u < 4; ++u) o[u] = sc * acc[mt][u][rr] + bv[u];
-            *(f32x4 *)(yo + ((size_t)b * g.L + loc) * g.F + f0 + 4 * n) = o;
+            const f32x2 o = {sc * acc[t][0][rr] + bv[0], sc * acc[t][1][rr] + bv[1]};
+            *(f32x2 *)(yo + ((size_t)b * g.L + loc) * g.F + f0 + 2 * n) = o;
         }
 }
 
@@ -184,13 +244,11 @@ int wide_slices(const Geom &g) {
 int check_forward_wide(const Geom &g, const LaunchPlan &p) {
     const int MT = p.tparam[0], KCH = p.tparam[2];
     const int fblocks = p.arg[0], btiles = p.arg[1], nslices = p.arg[2];
-    const int BT = 32 * MT, SEGS = KCH / 4, SR = 256 / SEGS;
+    const int BT = 32 * MT;
     LC_PLAN_REQUIRE(p, p.block == 256 && (KCH == 32 || KCH == 16));
     // 128 filters per workgroup; patch rows in whole chunks whose starts are 16-byte aligned in every image row
     LC_PLAN_REQUIRE(p, g.F % 128 == 0 && fblocks == g.F / 128);
     LC_PLAN_REQUIRE(p, g.RC % KCH == 0 && (g.S * g.C) % 4 == 0 && (g.W * g.C) % 4 == 0);
-    // the staging map: 256 threads move SR image rows per slot, BT / SR whole slots
-    LC_PLAN_REQUIRE(p, BT % SR == 0 && BT / SR >= 1);
     LC_PLAN_REQUIRE(p, btiles == ceil_div(g.B, BT));
     // 32-bit element offsets of x
     LC_PLAN_REQUIRE(p, (long long)g.B * g.H * g.W * g.C < (1LL << 31));
@@ -198,7 +256,8 @@ int check_forward_wide(const Geom &g, const LaunchPlan &p) {
     LC_PLAN_REQUIRE(p, nslices >= 1 && nslices <= nchunks);
     LC_PLAN_REQUIRE(p, (long long)p.grid[0] == (long long)g.L * fblocks * btiles * nslices && p.grid[1] == 1 &&
                            p.grid[2] == 1);
-    LC_PLAN_REQUIRE(p, p.lds_bytes >= (size_t)2 * BT * (KCH + 4) * sizeof(float));
+    // two buffers of three parts of bf16, or of fp32 values where a result is not finite; 32-bit offsets inside a step's filters
+    LC_PLAN_REQUIRE(p, p.lds_bytes >= (size_t)2 * BT * 32 * 6 && (long long)g.F * 32 * 4 < (1LL << 31));
     return LC_OK;
 }
 
@@ -206,7 +265,7 @@ template <int KCH, int MT = 4>
 int launch_wide(const Geom &g, const float *x, const float *w, const float *bias, float alpha, const float *alpha_dev,
                 float *y, float *partial, int nslices, hipStream_t s) {
     constexpr int PD = 2, BT = 32 * MT;
-    const size_t lds = (size_t)2 * BT * (KCH + 4) * sizeof(float);
+    const size_t lds = (size_t)2 * BT * 32 * 6;
     auto kern = lc_forward_wide_kernel<MT, PD, KCH>;
     const int fblocks = g.F / 128, btiles = (g.B + BT - 1) / BT;
     const LaunchPlan plan = make_plan("lc_forward_wide", {MT, PD, KCH}, {fblocks, btiles, nslices},
@@ -252,15 +311,15 @@ int launch_forward_wide_f32(const Geom &g, const float *x, const float *w, const
     int ns = wide_slices(g);
     if (ns > 1 && (!ws || ws_bytes < forward_wide_workspace_bytes(g))) ns = 1;   // no workspace: one slice
     // batch tile of 128, 96 or 64 images: the one that pads the batch least, the larger one on a tie (B = 192: two
-    // tiles of 128 waste a quarter of the MFMAs); 16-value chunks stage two rows per thread, which rules 96 out
-    const bool k32 = chunk_floats(g) == 32;
-    const int mt = batch_tile_mt(g.B, k32);
-    if (k32) {
+    // tiles of 128 waste a quarter of the MFMAs)
+    const int mt = batch_tile_mt(g.B, true);
+    if (chunk_floats(g) == 32) {
         if (mt == 2) return launch_wide<32, 2>(g, x, w, bias, alpha, alpha_dev, y, (float *)ws, ns, s);
         if (mt == 3) return launch_wide<32, 3>(g, x, w, bias, alpha, alpha_dev, y, (float *)ws, ns, s);
         return launch_wide<32>(g, x, w, bias, alpha, alpha_dev, y, (float *)ws, ns, s);
     }
     if (mt == 2) return launch_wide<16, 2>(g, x, w, bias, alpha, alpha_dev, y, (float *)ws, ns, s);
+    if (mt == 3) return launch_wide<16, 3>(g, x, w, bias, alpha, alpha_dev, y, (float *)ws, ns, s);
     return launch_wide<16>(g, x, w, bias, alpha, alpha_dev, y, (float *)ws, ns, s);
 }
 

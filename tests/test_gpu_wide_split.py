@@ -1,0 +1,70 @@
+"""The workgroup-tiled kernels (few fields and long patches forwards, cells of 128 values and dense layers backwards), whose fp32
+products are split into bf16 parts, against the fp64 oracle: every batch tile, patch rows in chunks of 32 and of 16 values with a
+last step of one chunk, with and without the workspace that slices the contraction.  Tolerance as for the general kernels: four
+times sqrt(n) roundings of 2^-24."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_1502_03409_amd as lc
+import workloads as wl
+from conftest import rel_fro
+
+pytestmark = pytest.mark.gpu
+
+# (units of 32 images per workgroup, chunk): layers
+FORWARD = {(2, 32): [(300, 8, 8, 64, 8, 1, 128), (310, 17, 16, 16, 16, 1, 128)], (3, 32): [(70, 17, 16, 32, 16, 1, 128)],
+           (4, 32): [(128, 8, 8, 64, 8, 1, 128), (97, 18, 16, 18, 16, 2, 128)],
+           (2, 16): [(300, 17, 17, 16, 17, 1, 128)], (3, 16): [(70, 17, 18, 16, 17, 1, 128), (96, 20, 22, 12, 20, 2, 128)],
+           (4, 16): [(100, 17, 17, 16, 17, 1, 128), (256, 20, 20, 12, 20, 1, 128)]}
+
+
+def bar(n):
+    return 4.0 * max(n, 16) ** 0.5 * 2.0 ** -24
+
+
+def forward(shape, x, w, b, alpha, sliced):
+    G = lc.geom(*shape)
+    y = torch.full((shape[0], *b.shape), float("nan"), device="cuda")
+    n = lc.workspace_bytes(G, lc.LC_OP_FORWARD, lc.LC_F32)
+    ws = torch.full((n // 4,), float("nan"), device="cuda").view(torch.uint8) if sliced and n else None
+    lc.lc_forward(G, torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), torch.from_numpy(b).cuda(), alpha, y, lc.LC_F32, ws)
+    return y
+
+
+@pytest.mark.parametrize("tile,shape", [(k, s) for k, v in FORWARD.items() for s in v], ids=str)
+@pytest.mark.parametrize("sliced", [True, False])
+def test_forward(tile, shape, sliced):
+    print(f"case wide forward {tile} {shape} {sliced}", flush=True)
+    g = wl.LCGeom(*shape)
+    p = lc.plan_query(lc.geom(*shape), lc.LC_OP_FORWARD, lc.LC_F32)[0]
+    assert (p["kernel"], p["tparam"][0], p["tparam"][2]) == ("lc_forward_wide", *tile)
+    x, w, _ = wl.lc_inputs(g, "gaussian", seed=3)
+    b = np.random.default_rng(2).standard_normal((g.LH, g.LW, g.F)).astype(np.float32)
+    y = forward(shape, x, w, b, 0.75, sliced)
+    assert rel_fro(y.cpu().numpy(), oracle.lc_forward(shape, x, w, b, 0.75)) <= bar(g.R * g.R * g.C)
+    assert torch.equal(y, forward(shape, x, w, b, 0.75, sliced))
+
+
+@pytest.mark.parametrize("shape", [FORWARD[2, 32][0], FORWARD[3, 16][0], FORWARD[4, 16][0]], ids=str)
+@pytest.mark.parametrize("scale", [1.0, 1e-30, 2e38], ids=str)
+def test_forward_infinities_and_ends_of_the_range(shape, scale):
+    """Infinities and NaNs stay in the outputs that they reach; small and large values keep their precision (parts that overflow
+    where fp32 does not: formed again in fp32)."""
+    print(f"case wide forward range {shape} {scale}", flush=True)
+    g = wl.LCGeom(*shape)
+    x, w, _ = wl.lc_inputs(g, "gaussian", seed=4)
+    x = (x / np.abs(x).max() * scale).astype(np.float32)
+    w = (w / np.abs(w).max() / (g.R * g.R * g.C)).astype(np.float32)
+    if scale == 1.0:
+        x[0, 0, 0, 0] = np.inf
+        x[g.B - 1, g.H - 1, g.W - 1, g.C - 1] = -np.inf
+        w[0, 0, -1, g.F // 2] = np.nan
+    else:
+        x[0, 0, 0, 0] = 1.69 * scale
+    b = np.zeros((g.LH, g.LW, g.F), dtype=np.float32)
+    ref, out = oracle.lc_forward(shape, x, w, b, 1.0), forward(shape, x, w, b, 1.0, True).cpu().numpy()
+    assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.array_equal(out[np.isinf(ref)], ref[np.isinf(ref)])
+    m = np.isfinite(ref)
+    assert m.any() and rel_fro(out[m].astype(np.float64) / scale, ref[m] / scale) <= bar(g.R * g.R * g.C)
