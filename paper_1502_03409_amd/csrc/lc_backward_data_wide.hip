@@ -1,14 +1,15 @@
 // lc_backward_data for layers whose S x S x C cells hold a multiple of 128 values (Eq. 1's decoder term):
 // the workgroup tiling of the wide forward kernel with the operands' roles changed.
 //
-// A workgroup owns one cell of the input (128 of its values) and a batch tile of 32*MT images; its four waves
-// form a 2 x 2 grid (16*MT images x 64 cell values).  The contraction runs over the fields that cover the cell
-// and over their filters.  A chunk is 32 filters of one field: 128 contiguous bytes of dy per image, staged
-// through LDS (two buffers, one barrier per chunk).  The filters are contiguous in memory along the contraction
-// index: lane (n, kk) loads filters 16h + 4kk .. +3 of the weight row that cell value n has in the field, and
-// lane (m, kk) reads the same four filters of image m from LDS, component t of both being MFMA step t.  Fields
-// outside the grid are not in the chunk list; a cell no field covers gets zeros.
-#include "lc_common.hpp"
+// A workgroup owns one cell of the input (128 of its values) and a batch tile of 32*MT images; each of its four waves has 32
+// of the values and all of the images.  The contraction runs over the fields that cover the cell and over their filters, in
+// chunks of 32 filters of one field.  Fields outside the grid are not in the chunk list; a cell no field covers gets zeros.
+//
+// fp32 products are split into bf16 parts (mfma_split): 96 MFMA cycles per 16 x 16 tile and chunk against 264 of fp32 MFMAs,
+// which moreover keep the vector unit idle.  dy is taken apart once per workgroup, on its way into LDS (two buffers, one barrier
+// per chunk).  The filters of a cell value are 128 contiguous bytes of a chunk: eight lanes load them, so that neighbouring lanes
+// meet in a cache line (16 lanes with 16 rows take the cache four times as long), and the wave turns them in its own LDS.
+#include "lc_general.hpp"
 
 namespace lc {
 
@@ -18,7 +19,6 @@ typedef const __attribute__((address_space(1))) f32x4 *g4_ptr;
 typedef const __attribute__((address_space(1))) float *gf_ptr;
 
 constexpr int kChunk = 32;          // filters per LDS chunk
-constexpr int kRowFloats = 36;      // 32 floats of a chunk + 4: eight rows' 16-byte reads cover all banks
 
 // DENSE: a layer of one field that covers its whole input (R = H = W, the dense last layer of Sec. 3.1).  Every
 // input value then has the same single covering field, so a "cell" is any block of 128 consecutive values k and
@@ -28,13 +28,13 @@ __global__ __launch_bounds__(256, 2) void lc_bwd_data_wide_kernel(Geom g, const 
                                                                   const float *__restrict__ w,
                                                                   float *__restrict__ dx, int CW, int nblk,
                                                                   int btiles) {
-    static_assert(PD == 1 || PD == 2, "one or two chunks of lookahead");
-    constexpr int BT = 32 * MT, NS = MT;
-    constexpr int BUF = BT * kRowFloats;
+    static_assert(PD == 2, "two chunks of lookahead");
+    // floats of a buffer: NT tiles of 16 images in three parts of 1 KB.  Filters 8 kk .. 8 kk + 7 of row m lie at slot
+    // 4 m + (kk ^ m/4) of 16 bytes: no bank conflicts in stores (four or eight lanes a row) and reads (lane (m, kk)).
+    constexpr int BT = 32 * MT, NT = 2 * MT, BUF = NT * 3 * 256;
     extern __shared__ __attribute__((aligned(16))) float xs[];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int n = lane & 15, kk = lane >> 4;
-    const int wm = wave >> 1, wn = wave & 1;
     int t_id = remap_xcd(blockIdx.x, gridDim.x);
     const int bt = t_id % btiles;
     t_id /= btiles;
@@ -48,11 +48,11 @@ __global__ __launch_bounds__(256, 2) void lc_bwd_data_wide_kernel(Geom g, const 
     const int cpf = g.F / kChunk;
     const int nchunks = (a_hi >= a_lo && p_hi >= p_lo) ? (a_hi - a_lo + 1) * (p_hi - p_lo + 1) * cpf : 0;
 
-    f32x4 acc[MT][4];
+    f32x4 acc[NT][2];
+    auto clear = [&] {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc[mt][u] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        for (int t = 0; t < NT; ++t) acc[t][0] = acc[t][1] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    };
 
     // a cursor walks the chunk list in order and stays on the last chunk once it gets there
     struct Cursor { int a, ap, hf; };
@@ -66,102 +66,149 @@ __global__ __launch_bounds__(256, 2) void lc_bwd_data_wide_kernel(Geom g, const 
 
     const int seg = tid & 7, brow = tid >> 3;
     const int LF = g.L * g.F;
-    int doff[NS];
+    int doff[MT];
 #pragma unroll
-    for (int s = 0; s < NS; ++s) doff[s] = min(b0 + brow + 32 * s, g.B - 1) * LF + seg * 4;
-    Cursor sq = {a_lo, p_lo, 0};
-    auto stage_load = [&](f32x4 (&st)[NS]) {
-        const int o = ((ri - sq.a) * g.LW + (wi - sq.ap)) * g.F + sq.hf * kChunk;
+    for (int s = 0; s < MT; ++s) doff[s] = min(b0 + brow + 32 * s, g.B - 1) * LF + seg * 4;
+    // this thread's slot in a tile of 16 images (tile brow / 16 + 2 s), in floats, and the half of it
+    const int sslot = (brow >> 4) * (3 * 256) + 4 * (4 * (brow & 15) + ((seg >> 1) ^ ((brow >> 2) & 3))), shalf = seg & 1;
+    const int aslot = 4 * (4 * n + (kk ^ (n >> 2)));
+    // the wave's own 4 KB behind the buffers: two tiles of 16 weight rows, two halves of a slot each
+    float *wx = xs + 2 * BUF + wave * 1024;
+    // lane 4 r + q loads filters 8 k .. 8 k + 7, k = q ^ r/4, of row r of either tile, relative to the cell's corner in a field:
+    // that is the slot 4 r + q, its own number
+    const int value0 = (DENSE ? cell * 128 : nb * 128) + wave * 32;
+    int kn[2];
 #pragma unroll
-        for (int s = 0; s < NS; ++s) st[s] = *(g4_ptr)((gf_ptr)dy + doff[s] + o);
-        advance(sq);
-    };
-    auto stage_store = [&](int buf, const f32x4 (&st)[NS]) {
-#pragma unroll
-        for (int s = 0; s < NS; ++s) *(f32x4 *)(xs + buf * BUF + (brow + 32 * s) * kRowFloats + seg * 4) = st[s];
-    };
-    // weight row of this lane's cell value in tile nt, relative to the cell's corner in a field
-    int kn[4];
-#pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-        const int nn = nb * 128 + wn * 64 + nt * 16 + n;
-        const int dr = nn / SC;
-        kn[nt] = (dr * g.RC + (nn - dr * SC)) * g.F + 4 * kk;
-        // dense: row k of the only K x F matrix (rows beyond K repeat the last one and are not stored)
-        if (DENSE) kn[nt] = min(cell * 128 + wn * 64 + nt * 16 + n, g.K - 1) * g.F + 4 * kk;
+    for (int u = 0; u < 2; ++u) {
+        const int r = lane >> 2, nn = value0 + u * 16 + r, dr = nn / SC;
+        const int row = DENSE ? min(nn, g.K - 1) : dr * g.RC + (nn - dr * SC);      // (dense: rows beyond K are not stored)
+        kn[u] = row * g.F + 8 * ((lane & 3) ^ (r >> 2));
     }
-    Cursor wq = {a_lo, p_lo, 0};
-    int wh = 0;
-    auto wload = [&](f32x4 (&r)[4]) {
-        const size_t loc = (size_t)((ri - wq.a) * g.LW + (wi - wq.ap));
-        gf_ptr p = (gf_ptr)w + (loc * g.K + (size_t)g.S * wq.a * g.RC + g.S * wq.ap * g.C) * g.F + wq.hf * kChunk +
-                   16 * wh;
-#pragma unroll
-        for (int nt = 0; nt < 4; ++nt) r[nt] = *(g4_ptr)(p + kn[nt]);
-        if (wh == 1) advance(wq);
-        wh ^= 1;
-    };
 
-    if (nchunks > 0) {
-        f32x4 st[PD][NS];
-        f32x4 wr[2 * PD][4];
+    auto pass = [&](auto split_tag) {
+        constexpr bool SPLIT = decltype(split_tag)::value;
+        Cursor sq = {a_lo, p_lo, 0};
+        auto stage_load = [&](f32x4 (&st)[MT]) {
+            const int o = ((ri - sq.a) * g.LW + (wi - sq.ap)) * g.F + sq.hf * kChunk;
 #pragma unroll
-        for (int q = 0; q < 2 * PD; ++q) wload(wr[q]);
+            for (int s = 0; s < MT; ++s) st[s] = *(g4_ptr)((gf_ptr)dy + doff[s] + o);
+            advance(sq);
+        };
+        auto stage_store = [&](int p, const f32x4 (&st)[MT]) {
+            float *buf = xs + p * BUF + sslot;
+#pragma unroll
+            for (int s = 0; s < MT; ++s) {
+                if constexpr (SPLIT) {
+                    float e[4] = {st[s][0], st[s][1], st[s][2], st[s][3]};
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) {
+                        const u32x2 v = {cvt_pk_bf16(e[0], e[1]), cvt_pk_bf16(e[2], e[3])};
+                        *(u32x2 *)(buf + (s * 2 * 3 + q) * 256 + 2 * shalf) = v;
+#pragma unroll
+                        for (int r = 0; r < 4; ++r) e[r] -= r & 1 ? bf16_hi(v[r >> 1]) : bf16_lo(v[r >> 1]);
+                    }
+                } else {
+                    *(f32x4 *)(buf + (s * 2 * 3 + shalf) * 256) = st[s];
+                }
+            }
+        };
+        Cursor wq = {a_lo, p_lo, 0};
+        auto wload = [&](f32x4 (&r)[2][2]) {
+            const size_t loc = (size_t)((ri - wq.a) * g.LW + (wi - wq.ap));
+            gf_ptr p = (gf_ptr)w + (loc * g.K + (size_t)g.S * wq.a * g.RC + g.S * wq.ap * g.C) * g.F + wq.hf * kChunk;
+#pragma unroll
+            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) r[u][h] = *(g4_ptr)(p + kn[u] + 4 * h);
+            advance(wq);
+        };
+        f32x4 st[PD][MT], wr[PD][2][2];
+#pragma unroll
+        for (int p = 0; p < PD; ++p) wload(wr[p]);
         stage_load(st[0]);
         stage_store(0, st[0]);
 #pragma unroll
         for (int p = 0; p < PD; ++p) stage_load(st[p]);          // set p: chunk p+1
         __syncthreads();
-        const int arow = (wm * 16 * MT + n) * kRowFloats + 4 * kk;
         for (int c0 = 0; c0 < nchunks; c0 += 2) {
 #pragma unroll
             for (int p = 0; p < 2; ++p) {
-                const int c = c0 + p;               // chunk c lives in buffer p (c0 is even)
-                const int sp = p % PD;              // register set that holds chunk c+1
+                const int c = c0 + p;               // chunk c lies in buffer p, and the set p holds the next one's images
                 if (c < nchunks) {
-                    const float *ab = xs + p * BUF + arow;
+                    const float *ab = xs + p * BUF + aslot;
+                    // (a wave's LDS operations keep their order; nobody else has this part)
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        f32x4 bo[4];
+                    for (int u = 0; u < 2; ++u)
 #pragma unroll
-                        for (int nt = 0; nt < 4; ++nt) bo[nt] = wr[2 * sp + h][nt];
-                        wload(wr[2 * sp + h]);
+                        for (int h = 0; h < 2; ++h) *(f32x4 *)(wx + (2 * u + h) * 256 + 4 * lane) = wr[p][u][h];
+                    wload(wr[p]);
+                    __builtin_amdgcn_wave_barrier();
+                    float e[2][8];
 #pragma unroll
-                        for (int mt = 0; mt < MT; ++mt) {
-                            const f32x4 a = *(const f32x4 *)(ab + mt * 16 * kRowFloats + 16 * h);
+                    for (int u = 0; u < 2; ++u)
 #pragma unroll
-                            for (int t = 0; t < 4; ++t)
+                        for (int h = 0; h < 2; ++h) {
+                            const f32x4 v = *(const f32x4 *)(wx + (2 * u + h) * 256 + aslot);
 #pragma unroll
-                                for (int nt = 0; nt < 4; ++nt) acc[mt][nt] = mfma16(a[t], bo[nt][t], acc[mt][nt]);
+                            for (int q = 0; q < 4; ++q) e[u][4 * h + q] = v[q];
                         }
+                    __builtin_amdgcn_wave_barrier();
+                    if constexpr (SPLIT) {
+                        const Parts pb[2] = {split8(e[0]), split8(e[1])};
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) {
+                            Parts pa;
+#pragma unroll
+                            for (int q = 0; q < 3; ++q) pa.p[q] = *(const u32x4 *)(ab + (t * 3 + q) * 256);
+                            mfma_split(pa, pb, acc[t]);
+                        }
+                    } else {
+#pragma unroll
+                        for (int t = 0; t < NT; ++t)
+#pragma unroll
+                            for (int h = 0; h < 2; ++h) {
+                                const f32x4 a = *(const f32x4 *)(ab + (t * 3 + h) * 256);
+#pragma unroll
+                                for (int q = 0; q < 4; ++q)
+#pragma unroll
+                                    for (int u = 0; u < 2; ++u) acc[t][u] = mfma16(a[q], e[u][4 * h + q], acc[t][u]);
+                            }
                     }
-                    if (c + 1 < nchunks) stage_store(p ^ 1, st[sp]);
-                    if (c + 1 + PD < nchunks) stage_load(st[sp]);
+                    if (c + 1 < nchunks) stage_store(p ^ 1, st[p]);
+                    if (c + 1 + PD < nchunks) stage_load(st[p]);
                 }
                 __syncthreads();
             }
         }
+    };
+    clear();
+    if (nchunks > 0) {
+        pass(std::true_type{});
+        // an operand that is not finite, or a part that overflowed: once more in fp32
+        if (__syncthreads_or(!all_finite<2 * NT>(&acc[0][0]))) {
+            clear();
+            pass(std::false_type{});
+        }
     }
 
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-        const int nn = nb * 128 + wn * 64 + nt * 16 + n;
-        const int dr = nn / SC, rem = nn - dr * SC;
-        const int row = ri * g.S + dr, col = wi * g.S + rem / g.C;
-        size_t pix = ((size_t)row * g.W + wi * g.S) * g.C + rem;
+    for (int u = 0; u < 2; ++u) {
+        const int nn = value0 + u * 16 + n;
+        size_t pix = (size_t)nn;                     // dense, R = H = W: the patch index is the pixel index
         if (DENSE) {
-            const int k = cell * 128 + wn * 64 + nt * 16 + n;
-            if (k >= g.K) continue;
-            pix = (size_t)k;                     // R = H = W: the patch index is the pixel index
-        } else if (row >= g.H || col >= g.W) {
-            continue;
+            if (nn >= g.K) continue;
+        } else {
+            const int dr = nn / SC, rem = nn - dr * SC;
+            const int row = ri * g.S + dr, col = wi * g.S + rem / g.C;
+            pix = ((size_t)row * g.W + wi * g.S) * g.C + rem;
+            if (row >= g.H || col >= g.W) continue;
         }
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt)
+        for (int t = 0; t < NT; ++t)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const int b = b0 + wm * 16 * MT + mt * 16 + 4 * kk + r;
-                if (b < g.B) dx[(size_t)b * g.H * g.W * g.C + pix] = acc[mt][nt][r];
+                const int b = b0 + 16 * t + 4 * kk + r;
+                if (b < g.B) dx[(size_t)b * g.H * g.W * g.C + pix] = acc[t][u][r];
             }
     }
 }
@@ -186,14 +233,14 @@ int check_backward_data_wide(const Geom &g, const LaunchPlan &p) {
         cells = (long long)ceil_div(g.H, g.S) * CW;
     }
     LC_PLAN_REQUIRE(p, (long long)p.grid[0] == cells * nblk * btiles && p.grid[1] == 1 && p.grid[2] == 1);
-    LC_PLAN_REQUIRE(p, p.lds_bytes >= (size_t)2 * BT * kRowFloats * sizeof(float));
+    LC_PLAN_REQUIRE(p, p.lds_bytes >= (size_t)2 * BT * 32 * 6 + 4 * 4096);
     return LC_OK;
 }
 
 template <int MT, int PD, bool DENSE>
 int launch_wide(const Geom &g, const float *dy, const float *w, float *dx, hipStream_t s) {
     constexpr int BT = 32 * MT;
-    const size_t lds = (size_t)2 * BT * kRowFloats * sizeof(float);
+    const size_t lds = (size_t)2 * BT * 32 * 6 + 4 * 4096;
     auto kern = lc_bwd_data_wide_kernel<MT, PD, DENSE>;
     const int CH = (g.H + g.S - 1) / g.S, CW = (g.W + g.S - 1) / g.S;
     const int nblk = DENSE ? 1 : g.S * g.S * g.C / 128, btiles = (g.B + BT - 1) / BT;

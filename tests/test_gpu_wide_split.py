@@ -68,3 +68,51 @@ def test_forward_infinities_and_ends_of_the_range(shape, scale):
     assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.array_equal(out[np.isinf(ref)], ref[np.isinf(ref)])
     m = np.isfinite(ref)
     assert m.any() and rel_fro(out[m].astype(np.float64) / scale, ref[m] / scale) <= bar(g.R * g.R * g.C)
+
+
+# (units of 32 images, dense): layers
+BACKWARD = {(2, 0): [(300, 11, 13, 32, 4, 2, 32), (128, 14, 15, 32, 6, 2, 64)], (3, 0): [(80, 11, 13, 64, 4, 2, 64), (96, 21, 26, 8, 8, 4, 96)],
+            (4, 0): [(128, 33, 36, 32, 4, 2, 32), (256, 16, 18, 128, 3, 1, 32)],
+            (2, 1): [(300, 9, 9, 3, 9, 1, 64), (100, 12, 12, 5, 12, 1, 160)], (3, 1): [(70, 15, 15, 3, 15, 1, 96), (96, 7, 7, 2, 7, 1, 32)],
+            (4, 1): [(128, 58, 58, 10, 58, 1, 32)]}
+
+
+def backward(shape, dy, w):
+    B, H, W, C = shape[:4]
+    dx = torch.full((B, H, W, C), float("nan"), device="cuda")
+    lc.lc_backward_data(lc.geom(*shape), torch.from_numpy(dy).cuda(), torch.from_numpy(w).cuda(), dx)
+    return dx
+
+
+@pytest.mark.parametrize("tile,shape", [(k, s) for k, v in BACKWARD.items() for s in v], ids=str)
+def test_backward_data(tile, shape):
+    print(f"case wide backward data {tile} {shape}", flush=True)
+    g = wl.LCGeom(*shape)
+    (p,) = lc.plan_query(lc.geom(*shape), lc.LC_OP_BACKWARD_DATA, lc.LC_F32)
+    assert (p["kernel"], p["tparam"][0], p["tparam"][2]) == ("lc_bwd_data_wide", *tile)
+    _, w, dy = wl.lc_inputs(g, "gaussian", seed=3)
+    dx, ref = backward(shape, dy, w), oracle.lc_backward_data(shape, dy, w)
+    out = dx.cpu().numpy()
+    assert rel_fro(out, ref) <= bar(g.F * (-(-g.R // g.S)) ** 2)
+    assert np.all(out[ref == 0.0] == 0.0)
+    assert torch.equal(dx, backward(shape, dy, w))
+
+
+@pytest.mark.parametrize("shape", [BACKWARD[2, 0][1], BACKWARD[3, 0][0], BACKWARD[3, 1][0], BACKWARD[2, 1][1]], ids=str)
+@pytest.mark.parametrize("scale", [1.0, 1e-30, 2e38], ids=str)
+def test_backward_data_infinities_and_ends_of_the_range(shape, scale):
+    print(f"case wide backward data range {shape} {scale}", flush=True)
+    g = wl.LCGeom(*shape)
+    _, w, dy = wl.lc_inputs(g, "gaussian", seed=4)
+    dy = (dy / np.abs(dy).max() * scale).astype(np.float32)
+    w = (w / np.abs(w).max() / 1024).astype(np.float32)
+    if scale == 1.0:
+        dy[0, 0, 0, g.F - 1] = np.inf
+        dy[g.B - 1, g.LH - 1, g.LW - 1, 0] = -np.inf
+        w[g.LH - 1, g.LW - 1, -1, g.F // 2] = np.nan
+    else:
+        dy[0, 0, 0, 0] = 1.69 * scale
+    ref, out = oracle.lc_backward_data(shape, dy, w), backward(shape, dy, w).cpu().numpy()
+    assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.array_equal(out[np.isinf(ref)], ref[np.isinf(ref)])
+    m = np.isfinite(ref)
+    assert m.any() and rel_fro(out[m].astype(np.float64) / scale, ref[m] / scale) <= bar(g.F * (-(-g.R // g.S)) ** 2)
