@@ -937,14 +937,17 @@ bool takes_general(const Geom &g, int es) {
     return forward_general_supported(g, es) && ((size_t)16 * lds_row_stride(g.RC) + 8) * sizeof(float) <= 160 * 1024;
 }
 
-// The workgroup-tiled kernel of lc_forward_wide.hip keeps layers of fewer than kWideFields fields and at least kWidePatch
-// elements per patch: its slices across workgroups reach further than the general kernel's sixteen waves at most (96
-// images of 18 x 20 x 16, 16 x 16 at stride 1, 128 filters: 26.7 us against 40.6; 80 of 26 x 26 x 8, 24 x 24 at stride
-// 1, 256 filters: 41 against 47).  With more fields or shorter patches the general kernel is faster (the same 24 x 24
-// fields on 28 x 28 pixels: 72 -> 49 us; 128 images of 8 x 8 x 32, 8 x 8, 1024 filters: 27 -> 19; 256 of 64 x 64 x 32,
-// 8 x 8 at stride 2, 128 filters: 995 -> 870; 128 of 40 x 40 x 64, 4 x 4 at stride 2: 150 -> 105; 96 images, 256
-// filters, 8 x 8 at stride 2: 730 -> 721).
-constexpr int kWideFields = 16, kWidePatch = 4096;
+// The workgroup-tiled kernel of lc_forward_wide.hip takes layers of fewer than kWideFields fields and at least kWidePatch
+// elements per patch, where its slices across workgroups reach further than the general kernel's sixteen waves at most (96
+// images of 18 x 20 x 16, 16 x 16 at stride 1, 128 filters: 25.5 us against 40.6; 80 of 26 x 26 x 8, 24 x 24 at stride
+// 1, 256 filters: 31 against 47), and patches of kWideLong elements that give a workgroup to every compute unit without
+// slices: sharing images and filters in LDS then saves more than the barriers and a batch in tiles of 64 and more cost, on
+// all of 19 layers timed (256 images of 64 x 64 x 32, 8 x 8 at stride 2, 128 filters: 714 -> 635; 80 of 23 x 22 x 32, 7 x 7,
+// 512 filters: 375 -> 280; 128 of 51 x 99 x 32, 7 x 7 at stride 4, 256 filters: 224 -> 220).  With shorter patches the
+// general kernel is faster (130 of 38 x 28 x 32, 6 x 6 at stride 2, 384 filters: 192 against 210; 128 of 40 x 40 x 64, 4 x 4
+// at stride 2, 128 filters: both 89), or with slices, which want a workspace besides (192 of 22 x 7 x 32, 7 x 7 at stride 3,
+// 128 filters: 12 against 21).
+constexpr int kWideFields = 16, kWidePatch = 4096, kWideLong = 1200;
 
 // Where the register-staged kernel (mt, nt: the tile it would take) keeps a layer the general kernel could take: fields
 // that overlap four times or more and few MFMAs per staged value, so that sharing the staged strip is worth its barriers.
@@ -1106,7 +1109,9 @@ int launch_forward_generic(const Geom &g, const T *x, const T *w, const float *b
 }  // namespace
 
 bool forward_takes_wide(const Geom &g) {
-    return forward_wide_supported(g) && ((g.L < kWideFields && g.K >= kWidePatch) || !takes_general(g, 4));
+    const long long workgroups = (long long)g.L * (g.F / 128) * ((g.B + 127) / 128);
+    return forward_wide_supported(g) && ((g.L < kWideFields && g.K >= kWidePatch) || (workgroups >= kComputeUnits && g.K >= kWideLong) ||
+                                         !takes_general(g, 4));
 }
 
 int launch_forward_f32(const Geom &g, const float *x, const float *w, const float *bias, float alpha,

@@ -14,7 +14,7 @@ from conftest import rel_fro
 pytestmark = pytest.mark.gpu
 
 # (units of 32 images per workgroup, chunk): layers
-FORWARD = {(2, 32): [(300, 8, 8, 64, 8, 1, 128), (310, 17, 16, 16, 16, 1, 128)], (3, 32): [(70, 17, 16, 32, 16, 1, 128)],
+FORWARD = {(2, 32): [(300, 8, 8, 64, 8, 1, 128), (310, 17, 16, 16, 16, 1, 128)], (3, 32): [(70, 17, 16, 32, 16, 1, 128), (70, 23, 24, 20, 8, 1, 128)],
            (4, 32): [(128, 8, 8, 64, 8, 1, 128), (97, 18, 16, 18, 16, 2, 128)],
            (2, 16): [(300, 17, 17, 16, 17, 1, 128)], (3, 16): [(70, 17, 18, 16, 17, 1, 128), (96, 20, 22, 12, 20, 2, 128)],
            (4, 16): [(100, 17, 17, 16, 17, 1, 128), (256, 20, 20, 12, 20, 1, 128)]}

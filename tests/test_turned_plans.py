@@ -169,3 +169,13 @@ def test_backward_data(seed):
                         got = {key: int(n[v]) for key, n in formed.items() if n[v]}
                         assert set(got) == cover and all(n == 1 for n in got.values()), (geo, p, row, col)
     assert turned > 60
+
+
+@pytest.mark.parametrize("shape,wide", [((70, 23, 24, 20, 8, 1, 128), True), ((70, 23, 22, 20, 8, 1, 128), False),
+                                        ((128, 40, 40, 64, 4, 2, 128), False), ((64, 23, 24, 20, 8, 1, 128), False),
+                                        ((70, 23, 24, 19, 8, 4, 128), False), ((70, 23, 24, 20, 8, 1, 64), False)], ids=str)
+def test_long_patches_take_the_workgroup_tiles(shape, wide):
+    """Patches of 1200 elements and a workgroup for every compute unit without slices: no workspace either way."""
+    g = lc.geom(*shape)
+    assert (lc.plan_query(g, lc.LC_OP_FORWARD, lc.LC_F32)[0]["kernel"] == "lc_forward_wide") == wide
+    assert lc.workspace_bytes(g, lc.LC_OP_FORWARD, lc.LC_F32) == 0
