@@ -156,11 +156,13 @@ __global__ __launch_bounds__(256, 2) void lc_bwd_data_wide_kernel(Geom g, const 
                     if constexpr (SPLIT) {
                         const Parts pb[2] = {split8(e[0]), split8(e[1])};
 #pragma unroll
-                        for (int t = 0; t < NT; ++t) {
-                            Parts pa;
+                        for (int t = 0; t < NT; t += 2) {
+                            Parts pa[2];
 #pragma unroll
-                            for (int q = 0; q < 3; ++q) pa.p[q] = *(const u32x4 *)(ab + (t * 3 + q) * 256);
-                            mfma_split(pa, pb, acc[t]);
+                            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                                for (int q = 0; q < 3; ++q) pa[m].p[q] = *(const u32x4 *)(ab + ((t + m) * 3 + q) * 256);
+                            mfma_split_rows(pa, pb, acc + t);
                         }
                     } else {
 #pragma unroll

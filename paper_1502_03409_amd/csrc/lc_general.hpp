@@ -148,20 +148,30 @@ __device__ __forceinline__ Parts split8(const float (&x)[8]) {
     }
     return s;
 }
-// acc[n] += the products of 32 contraction indices of a row and N columns.  The partial products, smallest first, add up from zero and meet the
-// sum in one addition: a matrix instruction that adds to the sum itself rounds it each time, and not to nearest (layers of
-// 2000 products: 4.1e-7 of the result against 2.4e-7 in fp32 MFMAs; 1.1e-7 this way).
-template <int N>
-__device__ __forceinline__ void mfma_split(const Parts &a, const Parts (&b)[N], f32x4 (&acc)[N]) {
+// acc[m][n] += the products of 32 contraction indices of M rows and N columns.  The partial products, smallest first, add up
+// from zero and meet the sum in one addition: a matrix instruction that adds to the sum itself rounds it each time, and not to
+// nearest (layers of 2000 products: 4.1e-7 of the result against 2.4e-7 in fp32 MFMAs; 1.1e-7 this way).  The M N chains of
+// six run side by side: with two a wave waits for its own results (four instead of two in the workgroup-tiled kernels: one
+// field of 62 x 62 x 24, 192 images, 4096 filters backwards 940 -> 918 us).
+template <int M, int N>
+__device__ __forceinline__ void mfma_split_rows(const Parts (&a)[M], const Parts (&b)[N], f32x4 (*acc)[N]) {
     constexpr int order[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
-    f32x4 t[N];
+    f32x4 t[M][N];
 #pragma unroll
     for (int o = 0; o < 6; ++o)
 #pragma unroll
-        for (int n = 0; n < N; ++n)
-            t[n] = mfma32_bf16(a.p[order[o][0]], b[n].p[order[o][1]], o == 0 ? (f32x4){0.f, 0.f, 0.f, 0.f} : t[n]);
+        for (int m = 0; m < M; ++m)
 #pragma unroll
-    for (int n = 0; n < N; ++n) acc[n] += t[n];
+            for (int n = 0; n < N; ++n)
+                t[m][n] = mfma32_bf16(a[m].p[order[o][0]], b[n].p[order[o][1]], o == 0 ? (f32x4){0.f, 0.f, 0.f, 0.f} : t[m][n]);
+#pragma unroll
+    for (int m = 0; m < M; ++m)
+#pragma unroll
+        for (int n = 0; n < N; ++n) acc[m][n] += t[m][n];
+}
+template <int N>
+__device__ __forceinline__ void mfma_split(const Parts &a, const Parts (&b)[N], f32x4 (&acc)[N]) {
+    mfma_split_rows(reinterpret_cast<const Parts(&)[1]>(a), b, &acc);
 }
 template <int M, int N>
 __device__ __forceinline__ void mfma_split(const Parts (&a)[M], const Parts (&b)[N], f32x4 (&acc)[M][N]) {
