@@ -85,6 +85,7 @@ __global__ __launch_bounds__(256, 2) void lc_bwd_data_wide_kernel(Geom g, const 
         kn[u] = row * g.F + 8 * ((lane & 3) ^ (r >> 2));
     }
 
+    bool nans = false;                  // (the same in all threads)
     auto pass = [&](auto split_tag) {
         constexpr bool SPLIT = decltype(split_tag)::value;
         Cursor sq = {a_lo, p_lo, 0};
@@ -179,7 +180,35 @@ __global__ __launch_bounds__(256, 2) void lc_bwd_data_wide_kernel(Geom g, const 
                     if (c + 1 < nchunks) stage_store(p ^ 1, st[p]);
                     if (c + 1 + PD < nchunks) stage_load(st[p]);
                 }
-                __syncthreads();
+                // Operands of a diverged layer show in the first two chunks: the fp32 pass starts there and then, unless
+                // every value has a NaN among its first weights, so that no sum is anything else.
+                if (SPLIT && p == 1 && c0 == 0) {
+                    if (__syncthreads_or(!all_finite<2 * NT>(&acc[0][0]))) {
+                        f32x4 first[2][2];
+                        wq = {a_lo, p_lo, 0};
+                        wload(first);
+                        bool every = true;
+#pragma unroll
+                        for (int u = 0; u < 2; ++u) {
+                            bool a = false;
+#pragma unroll
+                            for (int h = 0; h < 2; ++h)
+#pragma unroll
+                                for (int q = 0; q < 4; ++q) a |= first[u][h][q] != first[u][h][q];
+                            unsigned long long m = __ballot(a);         // lanes 4 r .. 4 r + 3: row r
+                            m |= m >> 1;
+                            m |= m >> 2;
+                            every = every && (m & 0x1111111111111111ull) == 0x1111111111111111ull;
+                        }
+                        nans = !__syncthreads_or(!every);
+                        if (!nans) return;
+                        // where the loads ahead were: chunk min(2 + PD, last)
+                        wq = {a_lo, p_lo, 0};
+                        for (int k = 0; k < 2 + PD; ++k) advance(wq);
+                    }
+                } else {
+                    __syncthreads();
+                }
             }
         }
     };
@@ -187,7 +216,7 @@ __global__ __launch_bounds__(256, 2) void lc_bwd_data_wide_kernel(Geom g, const 
     if (nchunks > 0) {
         pass(std::true_type{});
         // an operand that is not finite, or a part that overflowed: once more in fp32
-        if (__syncthreads_or(!all_finite<2 * NT>(&acc[0][0]))) {
+        if (!nans && __syncthreads_or(!all_finite<2 * NT>(&acc[0][0]))) {
             clear();
             pass(std::false_type{});
         }

@@ -79,6 +79,7 @@ __global__ __launch_bounds__(256, 2) void lc_forward_wide_kernel(Geom g, const f
     // a last step of one chunk of 16: rows beyond the patch are read 16 rows earlier (times zeros)
     unsigned woff_half = (unsigned)((8 * (kk & 1) * g.F + 2 * n) * 4);
 
+    bool nans = false;                  // (the same in all threads)
     auto pass = [&](auto split_tag) {
         constexpr bool SPLIT = decltype(split_tag)::value;
         // the chunk to be staged next (it stays on the last one)
@@ -183,7 +184,25 @@ __global__ __launch_bounds__(256, 2) void lc_forward_wide_kernel(Geom g, const f
                     if (step + 1 < nsteps) stage_store(step + 1, st[p]);
                     if (step + 1 + PD < nsteps) stage_load(st[p]);
                 }
-                __syncthreads();
+                // Operands of a diverged layer show in the first two steps: the fp32 pass starts there and then, unless
+                // every filter has a NaN among its first weights, so that no sum is anything else.
+                if (SPLIT && p == 1 && c0 == 0) {
+                    if (__syncthreads_or(!all_finite<2 * NT>(&acc[0][0]))) {
+                        f32x2 first[8];
+                        wload(0, first);
+                        bool a = false, b = false;
+#pragma unroll
+                        for (int q = 0; q < 8; ++q) {
+                            a |= first[q][0] != first[q][0];
+                            b |= first[q][1] != first[q][1];
+                        }
+                        const unsigned long long ma = __ballot(a), mb = __ballot(b);
+                        nans = !__syncthreads_or(!every_column(ma) || !every_column(mb));
+                        if (!nans) return;
+                    }
+                } else {
+                    __syncthreads();
+                }
             }
         }
     };
@@ -191,7 +210,7 @@ __global__ __launch_bounds__(256, 2) void lc_forward_wide_kernel(Geom g, const f
     if (nsteps > 0) {
         pass(std::true_type{});
         // an operand that is not finite, or a part that overflowed: once more in fp32
-        if (__syncthreads_or(!all_finite<2 * NT>(&acc[0][0]))) {
+        if (!nans && __syncthreads_or(!all_finite<2 * NT>(&acc[0][0]))) {
             clear();
             pass(std::false_type{});
         }

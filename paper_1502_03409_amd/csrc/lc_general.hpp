@@ -189,6 +189,13 @@ __device__ __forceinline__ bool all_finite(const f32x4 *v) {
     return s == 0.f;
 }
 
+// whether every column n (lanes n, n + 16, n + 32, n + 48) has a lane set
+__device__ __forceinline__ bool every_column(unsigned long long m) {
+    m |= m >> 32;
+    m |= m >> 16;
+    return (m & 0xffffull) == 0xffffull;
+}
+
 // Sum of a tile over the `ks` waves (a power of two) that split its contraction: wave 0 of them ends up with it.  Pairs
 // are added in a fixed order, so the result does not depend on timing.  buf: one slot of NACC*64 vectors per group of
 // waves and per half of them.  Every wave of the workgroup calls it.

@@ -87,3 +87,19 @@ def test_two_terms_and_row_norms(shape):
     out = wd.cpu().numpy().astype(np.float64)
     np.testing.assert_allclose(np.linalg.norm(out, axis=2), 1.0, rtol=1e-6)
     assert rel_fro(out, wo) <= 1e-6
+
+
+@pytest.mark.parametrize("step", [1, 2])
+@pytest.mark.parametrize("shape", [SHAPES[1, 4, 4, 1][1], SHAPES[2, 2, 4, 4][0], SHAPES[4, 2, 2, 1][1]], ids=str)
+def test_not_a_number_in_the_first_gradients(shape, step):
+    """A diverged layer: NaN in every filter's first gradients (the sums are all NaN), or in every second one's."""
+    print(f"case split weight gradient NaN {shape} {step}", flush=True)
+    g = wl.LCGeom(*shape)
+    x, w, dy = wl.lc_inputs(g, "gaussian", seed=5)
+    dy[2, :, :, ::step] = np.nan
+    dw = torch.zeros(w.shape, device="cuda")
+    lc.lc_backward_weights(lc.geom(*shape), torch.from_numpy(x).cuda(), torch.from_numpy(dy).cuda(), 0.0, dw)
+    ref, out = oracle.lc_backward_weights(shape, x, dy), dw.cpu().numpy()
+    assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.isnan(ref).all() == (step == 1)
+    m = np.isfinite(ref)
+    assert step == 1 or rel_fro(out[m], ref[m]) <= bar(g.B)

@@ -116,3 +116,27 @@ def test_backward_data_infinities_and_ends_of_the_range(shape, scale):
     assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.array_equal(out[np.isinf(ref)], ref[np.isinf(ref)])
     m = np.isfinite(ref)
     assert m.any() and rel_fro(out[m].astype(np.float64) / scale, ref[m] / scale) <= bar(g.F * (-(-g.R // g.S)) ** 2)
+
+
+@pytest.mark.parametrize("columns", ["all", "some"])
+def test_not_a_number_in_the_first_weights(columns):
+    """A diverged layer: NaN in every filter's first weights (the sums are all NaN), or in every second one's (the others are not)."""
+    print(f"case wide NaN {columns}", flush=True)
+    step = 1 if columns == "all" else 2
+    shape = FORWARD[3, 16][0]
+    g = wl.LCGeom(*shape)
+    x, w, _ = wl.lc_inputs(g, "gaussian", seed=5)
+    w[:, :, 3, ::step] = np.nan
+    b = np.zeros((g.LH, g.LW, g.F), dtype=np.float32)
+    ref, out = oracle.lc_forward(shape, x, w, b, 1.0), forward(shape, x, w, b, 1.0, True).cpu().numpy()
+    assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.isnan(ref).all() == (step == 1)
+    m = np.isfinite(ref)
+    assert step == 1 or rel_fro(out[m], ref[m]) <= bar(g.R * g.R * g.C)
+    for shape in (BACKWARD[3, 1][0], BACKWARD[2, 0][1]):
+        g = wl.LCGeom(*shape)
+        _, w, dy = wl.lc_inputs(g, "gaussian", seed=5)
+        w[:, :, ::step, 1] = np.nan
+        ref, out = oracle.lc_backward_data(shape, dy, w), backward(shape, dy, w).cpu().numpy()
+        assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.isnan(ref[0, 0, 0]).all() == (step == 1)
+        m = np.isfinite(ref)       # (pixels that no field covers among them)
+        assert step == 1 or rel_fro(out[m], ref[m]) <= bar(g.F * (-(-g.R // g.S)) ** 2)
