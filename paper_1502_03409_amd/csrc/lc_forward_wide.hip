@@ -76,7 +76,7 @@ __global__ __launch_bounds__(256, 2) void lc_forward_wide_kernel(Geom g, const f
     // the field's filters: lane (n, kk) has rows 8 kk .. 8 kk + 7 of a step at filters 2 n, 2 n + 1 of the wave's
     const gbytes wl = (gbytes)(w + (size_t)loc * g.K * g.F + f0);
     unsigned woff = (unsigned)((8 * kk * g.F + 2 * n) * 4);
-    // a last step of one chunk of 16: rows beyond the patch are read 16 rows earlier (times zeros)
+    // a last step of one chunk of 16: rows beyond the patch are read 16 rows earlier and count as zero
     unsigned woff_half = (unsigned)((8 * (kk & 1) * g.F + 2 * n) * 4);
 
     bool nans = false;                  // (the same in all threads)
@@ -155,6 +155,15 @@ __global__ __launch_bounds__(256, 2) void lc_forward_wide_kernel(Geom g, const f
                     for (int u = 0; u < 2; ++u)
 #pragma unroll
                         for (int q = 0; q < 8; ++q) e[u][q] = wr[p][q][u];
+                    if constexpr (KCH == 16) {
+                        // (an infinite weight times the zero of an image is a NaN)
+                        if (2 * (s_lo + step) + 1 == nchunks && kk >= 2) {
+#pragma unroll
+                            for (int u = 0; u < 2; ++u)
+#pragma unroll
+                                for (int q = 0; q < 8; ++q) e[u][q] = 0.f;
+                        }
+                    }
                     if constexpr (SPLIT) {
                         const Parts pb[2] = {split8(e[0]), split8(e[1])};
                         wload(step + PD, wr[p]);

@@ -81,6 +81,7 @@ def test_infinities_and_ends_of_the_range(shape, scale):
         dy[0, 0, 0, g.F - 1] = np.inf
         dy[g.B - 1, g.LH - 1, g.LW - 1, 0] = -np.inf
         dy[g.B // 2, g.LH // 2, g.LW // 2, g.F // 2] = np.nan
+        w[0, 0, 0, 0], w[g.LH - 1, g.LW - 1, -1, g.F - 1] = np.inf, -np.inf
     else:
         dy[0, 0, 0, 0] = 1.69 * scale
     dx = torch.full((g.B, g.H, g.W, g.C), float("nan"), device="cuda")

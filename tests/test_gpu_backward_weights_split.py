@@ -62,6 +62,7 @@ def test_infinities_and_ends_of_the_range(shape, scale):
         x[0, 0, 0, 0] = np.inf
         x[g.B - 1, g.H - 1, g.W - 1, g.C - 1] = -np.inf
         dy[g.B // 2, g.LH // 2, g.LW // 2, g.F // 2] = np.nan
+        dy[0, 0, 0, 0], dy[g.B - 1, 0, 0, g.F - 1] = np.inf, -np.inf
     else:
         x[0, 0, 0, 0] = 1.69 * scale
     dw = torch.full(w.shape, float("nan"), device="cuda")

@@ -70,6 +70,25 @@ def test_forward_infinities_and_ends_of_the_range(shape, scale):
     assert m.any() and rel_fro(out[m].astype(np.float64) / scale, ref[m] / scale) <= bar(g.R * g.R * g.C)
 
 
+@pytest.mark.parametrize("sliced", [True, False])
+@pytest.mark.parametrize("row", [3, -5], ids=["first", "last"])
+@pytest.mark.parametrize("shape", [FORWARD[2, 32][0], FORWARD[2, 16][0], FORWARD[3, 16][0], FORWARD[3, 16][1], FORWARD[4, 16][0]], ids=str)
+def test_forward_infinite_weights(shape, row, sliced):
+    """An infinite weight among the first or last 16 of a patch makes its filter's outputs infinite (chunks of 16 and an odd number
+    of them: the last step has 16 elements and no others), and no others anything but finite."""
+    print(f"case wide forward infinite weights {shape} {row} {sliced}", flush=True)
+    g = wl.LCGeom(*shape)
+    x, w, _ = wl.lc_inputs(g, "gaussian", seed=6)
+    w[0, 0, row, g.F // 2] = np.inf
+    w[-1, -1, row, 0] = -np.inf
+    b = np.zeros((g.LH, g.LW, g.F), dtype=np.float32)
+    ref, out = oracle.lc_forward(shape, x, w, b, 1.0), forward(shape, x, w, b, 1.0, sliced).cpu().numpy()
+    assert np.isinf(ref).sum() == 2 * g.B and not np.isnan(ref).any()
+    assert not np.isnan(out).any() and np.array_equal(out[np.isinf(ref)], ref[np.isinf(ref)])
+    m = np.isfinite(ref)
+    assert rel_fro(out[m], ref[m]) <= bar(g.R * g.R * g.C)
+
+
 # (units of 32 images, dense): layers
 BACKWARD = {(2, 0): [(300, 11, 13, 32, 4, 2, 32), (128, 14, 15, 32, 6, 2, 64)], (3, 0): [(80, 11, 13, 64, 4, 2, 64), (96, 21, 26, 8, 8, 4, 96)],
             (4, 0): [(128, 33, 36, 32, 4, 2, 32), (256, 16, 18, 128, 3, 1, 32)],
@@ -110,6 +129,7 @@ def test_backward_data_infinities_and_ends_of_the_range(shape, scale):
         dy[0, 0, 0, g.F - 1] = np.inf
         dy[g.B - 1, g.LH - 1, g.LW - 1, 0] = -np.inf
         w[g.LH - 1, g.LW - 1, -1, g.F // 2] = np.nan
+        w[0, 0, 1, 0], w[0, 0, g.K - 2, g.F - 1] = np.inf, -np.inf
     else:
         dy[0, 0, 0, 0] = 1.69 * scale
     ref, out = oracle.lc_backward_data(shape, dy, w), backward(shape, dy, w).cpu().numpy()
