@@ -28,6 +28,12 @@
  *    (forward, weight gradient), fewer than four filters (backward data), tensors beyond
  *    32-bit offsets, layers of few filters whose fields do not overlap (backward data), and
  *    most weight gradients of fewer than 32 images.
+ *    fp32 operands count with all of their bits over the whole range, subnormal ones included.  Many kernels
+ *    form fp32 products on the bf16 matrix unit from three bf16 parts of each operand: a sum of many products is
+ *    nearer to the exact one than with the fp32 matrix instruction (0.2 to 0.4 of its error), a sum with a single
+ *    product that is not zero may be off by 2^-22 of it instead of 2^-24.  Tiles that meet an operand that is not
+ *    finite or has bits below 2^-133, or whose sums overflow on the way, are formed again with the fp32
+ *    instruction, at the cost of both.
  *  - `hip_stream` is a hipStream_t passed as void* (NULL = the default stream).  Calls
  *    only enqueue work; none synchronises.  Arguments are validated on the host before
  *    anything is launched, so every error except LC_EHIP is returned without touching

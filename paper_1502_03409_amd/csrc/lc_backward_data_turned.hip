@@ -213,6 +213,7 @@ __global__ __launch_bounds__(64 * kTurnedDataWaves) void lc_bwd_data_turned_kern
 #pragma unroll
         for (int s = 0; s < PF; ++s) load_step(step[s]);
         if constexpr (SPLIT) {
+            unsigned low = 0;
             auto contract = [&](auto multiply) {
                 for (int q = 0; q < ng; q += 2) {
                     const Operands o0 = turned(step[0], 0);
@@ -227,22 +228,22 @@ __global__ __launch_bounds__(64 * kTurnedDataWaves) void lc_bwd_data_turned_kern
                 }
             };
             contract([&](const Operands &o0, const Operands &o1) {
+                load_step(step[0]);                           // (ahead of the split, which runs beside the products then)
                 Parts pa[MT], pb[NT];
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) {
                     const float e[8] = {o0.a[mt][0], o0.a[mt][1], o0.a[mt][2], o0.a[mt][3], o1.a[mt][0], o1.a[mt][1], o1.a[mt][2], o1.a[mt][3]};
-                    pa[mt] = split8(e);
+                    pa[mt] = split8(e, low);
                 }
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) {
                     const float e[8] = {o0.b[nt][0], o0.b[nt][1], o0.b[nt][2], o0.b[nt][3], o1.b[nt][0], o1.b[nt][1], o1.b[nt][2], o1.b[nt][3]};
-                    pb[nt] = split8(e);
+                    pb[nt] = split8(e, low);
                 }
-                load_step(step[0]);
                 mfma_split(pa, pb, acc);
             });
-            // an operand that is not finite, or a part that overflowed: once more in fp32
-            if (__any(!all_finite<MT * NT>(&acc[0][0]))) {
+            // an operand that is not finite or too small, or a part that overflowed: once more in fp32
+            if (__any(!all_finite<MT * NT>(&acc[0][0]) || inexact(low))) {
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt)
 #pragma unroll

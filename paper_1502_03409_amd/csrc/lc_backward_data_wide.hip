@@ -15,9 +15,6 @@ namespace lc {
 
 namespace {
 
-typedef const __attribute__((address_space(1))) f32x4 *g4_ptr;
-typedef const __attribute__((address_space(1))) float *gf_ptr;
-
 constexpr int kChunk = 32;          // filters per LDS chunk
 
 // DENSE: a layer of one field that covers its whole input (R = H = W, the dense last layer of Sec. 3.1).  Every
@@ -66,9 +63,16 @@ __global__ __launch_bounds__(256, 2) void lc_bwd_data_wide_kernel(Geom g, const 
 
     const int seg = tid & 7, brow = tid >> 3;
     const int LF = g.L * g.F;
-    int doff[MT];
+    // 32 images' first one is the wave's, the rest of a place 32 bits of bytes: a whole address a lane would cost eight registers
+    // more than there are
+    gbytes dyp[MT];
+    unsigned doff[MT];
 #pragma unroll
-    for (int s = 0; s < MT; ++s) doff[s] = min(b0 + brow + 32 * s, g.B - 1) * LF + seg * 4;
+    for (int s = 0; s < MT; ++s) {
+        const int first = min(b0 + 32 * s, g.B - 1);
+        dyp[s] = (gbytes)(dy + (size_t)first * LF);
+        doff[s] = ((unsigned)min(brow, g.B - 1 - first) * (unsigned)LF + seg * 4) * 4u;
+    }
     // this thread's slot in a tile of 16 images (tile brow / 16 + 2 s), in floats, and the half of it
     const int sslot = (brow >> 4) * (3 * 256) + 4 * (4 * (brow & 15) + ((seg >> 1) ^ ((brow >> 2) & 3))), shalf = seg & 1;
     const int aslot = 4 * (4 * n + (kk ^ (n >> 2)));
@@ -77,22 +81,23 @@ __global__ __launch_bounds__(256, 2) void lc_bwd_data_wide_kernel(Geom g, const 
     // lane 4 r + q loads filters 8 k .. 8 k + 7, k = q ^ r/4, of row r of either tile, relative to the cell's corner in a field:
     // that is the slot 4 r + q, its own number
     const int value0 = (DENSE ? cell * 128 : nb * 128) + wave * 32;
-    int kn[2];
+    unsigned kn[2];
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         const int r = lane >> 2, nn = value0 + u * 16 + r, dr = nn / SC;
         const int row = DENSE ? min(nn, g.K - 1) : dr * g.RC + (nn - dr * SC);      // (dense: rows beyond K are not stored)
-        kn[u] = row * g.F + 8 * ((lane & 3) ^ (r >> 2));
+        kn[u] = ((unsigned)row * (unsigned)g.F + 8 * ((lane & 3) ^ (r >> 2))) * 4u;
     }
 
     bool nans = false;                  // (the same in all threads)
+    unsigned low = 0;
     auto pass = [&](auto split_tag) {
         constexpr bool SPLIT = decltype(split_tag)::value;
         Cursor sq = {a_lo, p_lo, 0};
         auto stage_load = [&](f32x4 (&st)[MT]) {
             const int o = ((ri - sq.a) * g.LW + (wi - sq.ap)) * g.F + sq.hf * kChunk;
 #pragma unroll
-            for (int s = 0; s < MT; ++s) st[s] = *(g4_ptr)((gf_ptr)dy + doff[s] + o);
+            for (int s = 0; s < MT; ++s) st[s] = load_quad<float>(opaque(dyp[s] + (size_t)o * 4), doff[s]);
             advance(sq);
         };
         auto stage_store = [&](int p, const f32x4 (&st)[MT]) {
@@ -104,6 +109,10 @@ __global__ __launch_bounds__(256, 2) void lc_bwd_data_wide_kernel(Geom g, const 
 #pragma unroll
                     for (int q = 0; q < 3; ++q) {
                         const u32x2 v = {cvt_pk_bf16(e[0], e[1]), cvt_pk_bf16(e[2], e[3])};
+                        if (q == 2) {
+                            gather_low(low, e[0], e[1]);
+                            gather_low(low, e[2], e[3]);
+                        }
                         *(u32x2 *)(buf + (s * 2 * 3 + q) * 256 + 2 * shalf) = v;
 #pragma unroll
                         for (int r = 0; r < 4; ++r) e[r] -= r & 1 ? bf16_hi(v[r >> 1]) : bf16_lo(v[r >> 1]);
@@ -116,11 +125,11 @@ __global__ __launch_bounds__(256, 2) void lc_bwd_data_wide_kernel(Geom g, const 
         Cursor wq = {a_lo, p_lo, 0};
         auto wload = [&](f32x4 (&r)[2][2]) {
             const size_t loc = (size_t)((ri - wq.a) * g.LW + (wi - wq.ap));
-            gf_ptr p = (gf_ptr)w + (loc * g.K + (size_t)g.S * wq.a * g.RC + g.S * wq.ap * g.C) * g.F + wq.hf * kChunk;
+            const gbytes p = opaque((gbytes)(w + (loc * g.K + (size_t)g.S * wq.a * g.RC + g.S * wq.ap * g.C) * g.F + wq.hf * kChunk));
 #pragma unroll
             for (int u = 0; u < 2; ++u)
 #pragma unroll
-                for (int h = 0; h < 2; ++h) r[u][h] = *(g4_ptr)(p + kn[u] + 4 * h);
+                for (int h = 0; h < 2; ++h) r[u][h] = load_quad<float>(p, kn[u] + 16 * h);
             advance(wq);
         };
         f32x4 st[PD][MT], wr[PD][2][2];
@@ -155,7 +164,7 @@ __global__ __launch_bounds__(256, 2) void lc_bwd_data_wide_kernel(Geom g, const 
                         }
                     __builtin_amdgcn_wave_barrier();
                     if constexpr (SPLIT) {
-                        const Parts pb[2] = {split8(e[0]), split8(e[1])};
+                        const Parts pb[2] = {split8(e[0], low), split8(e[1], low)};
 #pragma unroll
                         for (int t = 0; t < NT; t += 2) {
                             Parts pa[2];
@@ -164,6 +173,8 @@ __global__ __launch_bounds__(256, 2) void lc_bwd_data_wide_kernel(Geom g, const 
 #pragma unroll
                                 for (int q = 0; q < 3; ++q) pa[m].p[q] = *(const u32x4 *)(ab + ((t + m) * 3 + q) * 256);
                             mfma_split_rows(pa, pb, acc + t);
+                            // (or the compiler reads all tiles ahead, and spills what the next chunk's loads need: 690 -> 747 us)
+                            if (t + 2 == NT / 2) __builtin_amdgcn_sched_barrier(0);
                         }
                     } else {
 #pragma unroll
@@ -183,7 +194,7 @@ __global__ __launch_bounds__(256, 2) void lc_bwd_data_wide_kernel(Geom g, const 
                 // Operands of a diverged layer show in the first two chunks: the fp32 pass starts there and then, unless
                 // every value has a NaN among its first weights, so that no sum is anything else.
                 if (SPLIT && p == 1 && c0 == 0) {
-                    if (__syncthreads_or(!all_finite<2 * NT>(&acc[0][0]))) {
+                    if (__syncthreads_or(!all_finite<2 * NT>(&acc[0][0]) || inexact(low))) {
                         f32x4 first[2][2];
                         wq = {a_lo, p_lo, 0};
                         wload(first);
@@ -215,8 +226,8 @@ __global__ __launch_bounds__(256, 2) void lc_bwd_data_wide_kernel(Geom g, const 
     clear();
     if (nchunks > 0) {
         pass(std::true_type{});
-        // an operand that is not finite, or a part that overflowed: once more in fp32
-        if (!nans && __syncthreads_or(!all_finite<2 * NT>(&acc[0][0]))) {
+        // an operand that is not finite or too small, or a part that overflowed: once more in fp32
+        if (!nans && __syncthreads_or(!all_finite<2 * NT>(&acc[0][0]) || inexact(low))) {
             clear();
             pass(std::false_type{});
         }
@@ -252,8 +263,8 @@ int check_backward_data_wide(const Geom &g, const LaunchPlan &p) {
     const int BT = 32 * MT;
     LC_PLAN_REQUIRE(p, p.block == 256);
     LC_PLAN_REQUIRE(p, g.F % kChunk == 0 && btiles == ceil_div(g.B, BT));
-    // 32-bit element offsets of dy and inside a field's K x F matrix
-    LC_PLAN_REQUIRE(p, (long long)g.B * g.L * g.F < (1LL << 31) && (long long)g.K * g.F < (1LL << 31));
+    // 32-bit byte offsets into 32 images' dy and inside a field's K x F matrix
+    LC_PLAN_REQUIRE(p, (long long)32 * g.L * g.F * 4 < (1LL << 32) && (long long)g.K * g.F * 4 <= (1LL << 32));
     long long cells;
     if (DENSE) {
         LC_PLAN_REQUIRE(p, g.L == 1 && g.R == g.H && g.R == g.W && nblk == 1);

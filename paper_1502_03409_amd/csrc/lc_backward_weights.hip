@@ -282,6 +282,7 @@ __global__ __launch_bounds__(256, G == 3 || SPLIT ? 2 : 1) void lc_bwd_weights_f
     };
     // The same with fp32 products split into bf16 parts (mfma_split), 32 images a step: lane kk has images kk, kk + 4, .. kk + 28
     // of it.  What is left of the batch takes fp32 MFMAs.
+    unsigned low = 0;
     auto contract_split = [&](auto ga_tag) {
         constexpr int GA = decltype(ga_tag)::value;
         for (int p = 0; p < 2; ++p) {
@@ -295,7 +296,7 @@ __global__ __launch_bounds__(256, G == 3 || SPLIT ? 2 : 1) void lc_bwd_weights_f
             AV a[8][GA];
             BR bv[8];
             const int chunks = nsteps >> 3, left = nsteps & 7;
-            // (every group of patch elements is loaded again as soon as it is split: more would not fit the registers)
+            // (every group of patch elements is loaded again where it is split: more would not fit the registers)
             auto load_group = [&](int gg) {
 #pragma unroll
                 for (int ss = 0; ss < 8; ++ss) { a[ss][gg] = *(const GAV *)xa[gg]; xa[gg] += xstep; }
@@ -309,27 +310,40 @@ __global__ __launch_bounds__(256, G == 3 || SPLIT ? 2 : 1) void lc_bwd_weights_f
             for (int gg = 0; gg < GA; ++gg) load_group(gg);
             __builtin_amdgcn_sched_barrier(0);                // the loads of a step stay ahead of the MFMAs behind them
             for (int c = 0; c < chunks; ++c) {
+                const bool more = c + 1 < chunks;
                 Parts pb[NT];
 #pragma unroll
-                for (int u = 0; u < NT; ++u) {
-                    float e[8];
-#pragma unroll
-                    for (int q = 0; q < 8; ++q) e[q] = raw_get<T, NT>(bv[q], u);
-                    pb[u] = split8(e);
-                }
-                if (c + 1 < chunks) load_dy();
-#pragma unroll
                 for (int gg = 0; gg < GA; ++gg) {
+                    // the next step's loads go ahead of the split, which runs beside the products then
+                    AV ag[8];
+                    BR bg[8];
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) {
+                        ag[q] = a[q][gg];
+                        if (gg == 0) bg[q] = bv[q];
+                    }
+                    if (more) {
+                        if (gg == 0) load_dy();
+                        load_group(gg);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (gg == 0) {
+#pragma unroll
+                        for (int u = 0; u < NT; ++u) {
+                            float e[8];
+#pragma unroll
+                            for (int q = 0; q < 8; ++q) e[q] = raw_get<T, NT>(bg[q], u);
+                            pb[u] = split8(e, low);
+                        }
+                    }
                     Parts pa[VA];
 #pragma unroll
                     for (int t = 0; t < VA; ++t) {
                         float e[8];
 #pragma unroll
-                        for (int q = 0; q < 8; ++q) e[q] = raw_get<T, VA>(a[q][gg], t);
-                        pa[t] = split8(e);
+                        for (int q = 0; q < 8; ++q) e[q] = raw_get<T, VA>(ag[q], t);
+                        pa[t] = split8(e, low);
                     }
-                    if (c + 1 < chunks) load_group(gg);
-                    __builtin_amdgcn_sched_barrier(0);
                     mfma_split(pa, pb, acc[gg]);
                     __builtin_amdgcn_sched_barrier(0);
                 }
@@ -356,8 +370,8 @@ __global__ __launch_bounds__(256, G == 3 || SPLIT ? 2 : 1) void lc_bwd_weights_f
     auto run = [&](auto ga_tag) {
         if constexpr (SPLIT) {
             contract_split(ga_tag);
-            if (!__any(!all_finite<G * VA * NT>(&acc[0][0][0]))) return;
-            // An operand that is not finite, or a part that overflowed: once more in fp32.  (A look after the first step, to begin
+            if (!__any(!all_finite<G * VA * NT>(&acc[0][0][0]) || inexact(low))) return;
+            // An operand that is not finite or too small, or a part that overflowed: once more in fp32.  (A look after the first step, to begin
             // at once, costs finite layers more than it saves: 203 -> 226 us at K = 1200, 32 filters, batch 128.)
 #pragma unroll
             for (int gg = 0; gg < G; ++gg)

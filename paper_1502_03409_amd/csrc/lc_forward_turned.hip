@@ -20,6 +20,12 @@ constexpr int kTurnedWaves(int mt, int nt) { return mt * nt <= 2 ? 16 : 8; }
 template <typename T>
 constexpr bool kTurnedSplit(int mt, int nt) { return sizeof(T) == 4 && mt * nt >= 6; }
 
+// Waves per SIMD that the registers leave room for: a workgroup's, and one more for split tiles of 12 blocks and fewer, which are
+// within a few registers of it (100 images of 60 x 61 x 8, 8 x 8 at stride 2, 96 filters, 4 x 3 blocks: 70 us, and 74 with 173
+// registers).
+template <typename T>
+constexpr int kTurnedResident(int mt, int nt) { return kTurnedSplit<T>(mt, nt) && mt * nt <= 12 ? 3 : kTurnedWaves(mt, nt) / 4; }
+
 // Where a wave's vectors are.  kWhole: four lanes' vectors are always 16 neighbouring elements of one patch row (rows of whole
 // 16-element blocks), so the place is the wave's.  kTable: the workgroup writes every vector's place into LDS first.
 enum { kWhole = 1, kTable = 2 };
@@ -32,7 +38,7 @@ template <typename T>
 constexpr int turn_bytes(int mt, int nt, bool bl) { return (mt * 256 + (bl ? nt * 320 : 0)) * (int)sizeof(T); }
 
 template <int MT, int NT, typename T, int WALK, bool BL>
-__global__ __launch_bounds__(64 * kTurnedWaves(MT, NT)) void lc_forward_turned_kernel(
+__global__ __launch_bounds__(64 * kTurnedWaves(MT, NT), kTurnedResident<T>(MT, NT)) void lc_forward_turned_kernel(
     Geom g, const T *__restrict__ x, const T *__restrict__ w, const float *__restrict__ bias, float alpha,
     const float *__restrict__ alpha_dev, float *__restrict__ y, Divisor dNV, int nvt, int per_slice, Divisor dnbt, Divisor dLW,
     int lnfw, int lks, int ntask) {
@@ -259,19 +265,20 @@ __global__ __launch_bounds__(64 * kTurnedWaves(MT, NT)) void lc_forward_turned_k
                     for (int u = 0; u < NT; ++u) acc[mt][u] = mfma16_bf16(o.a[mt], b[u], acc[mt][u]);
             }
         };
+        unsigned low = 0;
         auto split_multiply = [&](const Operands &o0, const Operands &o1) {
             if constexpr (SPLIT) {
                 Parts pa[MT], pb[NT];
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt) {
                     const float e[8] = {o0.a[mt][0], o0.a[mt][1], o0.a[mt][2], o0.a[mt][3], o1.a[mt][0], o1.a[mt][1], o1.a[mt][2], o1.a[mt][3]};
-                    pa[mt] = split8(e);
+                    pa[mt] = split8(e, low);
                 }
 #pragma unroll
                 for (int u = 0; u < NT; ++u) {
                     const float e[8] = {o0.b[0].get(u), o0.b[1].get(u), o0.b[2].get(u), o0.b[3].get(u),
                                         o1.b[0].get(u), o1.b[1].get(u), o1.b[2].get(u), o1.b[3].get(u)};
-                    pb[u] = split8(e);
+                    pb[u] = split8(e, low);
                 }
                 mfma_split(pa, pb, acc);
             }
@@ -300,8 +307,8 @@ __global__ __launch_bounds__(64 * kTurnedWaves(MT, NT)) void lc_forward_turned_k
                 }
             };
             contract(split_multiply);
-            // an operand that is not finite, or a part that overflowed: once more in fp32
-            if (__any(!all_finite<MT * NT>(&acc[0][0]))) {
+            // an operand that is not finite or too small, or a part that overflowed: once more in fp32
+            if (__any(!all_finite<MT * NT>(&acc[0][0]) || inexact(low))) {
                 clear();
                 start();
                 ends = vbeg - dNV.over(vbeg) * NV;

@@ -13,8 +13,6 @@ namespace lc {
 
 namespace {
 
-typedef const __attribute__((address_space(1))) f32x4 *g4_ptr;
-typedef const __attribute__((address_space(1))) float *gf_ptr;
 typedef FVec<2>::T f32x2;
 typedef const __attribute__((address_space(1))) f32x2 *g2_ptr;
 
@@ -64,11 +62,15 @@ __global__ __launch_bounds__(256, 2) void lc_forward_wide_kernel(Geom g, const f
     // staging: slot s moves 16 bytes (values 4 seg ..) of image tid / 8 + 32 s; images beyond the batch repeat image B-1 and
     // their results are never stored
     const int seg = tid & 7, brow = tid >> 3;
-    int xoff[MT];
+    // (32 images' first one is the wave's, the rest of a place 32 bits of bytes: a whole address a lane would cost eight registers
+    // more than there are)
+    gbytes xp[MT];
+    unsigned xoff[MT];
 #pragma unroll
     for (int s = 0; s < MT; ++s) {
-        const int b = min(b0 + brow + 32 * s, g.B - 1);
-        xoff[s] = (b * g.H + i * g.S) * WC + j * g.S * g.C + (KCH == 32 ? seg : seg & 3) * 4;
+        const int first = min(b0 + 32 * s, g.B - 1);
+        xp[s] = (gbytes)(x + ((size_t)first * g.H + i * g.S) * WC + j * g.S * g.C);
+        xoff[s] = ((unsigned)min(brow, g.B - 1 - first) * (unsigned)(g.H * WC) + (KCH == 32 ? seg : seg & 3) * 4) * 4u;
     }
     // its slot in a tile of 16 images (tile brow / 16 + 2 s), in floats, and the half of it
     const int sslot = (brow >> 4) * (3 * 256) + 4 * (4 * (brow & 15) + ((seg >> 1) ^ ((brow >> 2) & 3))), shalf = seg & 1;
@@ -80,6 +82,7 @@ __global__ __launch_bounds__(256, 2) void lc_forward_wide_kernel(Geom g, const f
     unsigned woff_half = (unsigned)((8 * (kk & 1) * g.F + 2 * n) * 4);
 
     bool nans = false;                  // (the same in all threads)
+    unsigned low = 0;
     auto pass = [&](auto split_tag) {
         constexpr bool SPLIT = decltype(split_tag)::value;
         // the chunk to be staged next (it stays on the last one)
@@ -93,13 +96,16 @@ __global__ __launch_bounds__(256, 2) void lc_forward_wide_kernel(Geom g, const f
             return o;
         };
         auto stage_load = [&](f32x4 (&st)[MT]) {
-            int o = next_chunk();
+            const int o = next_chunk();
             if constexpr (KCH == 16) {
                 const int o1 = next_chunk();
-                o = seg < 4 ? o : o1;
-            }
+                const unsigned oh = (unsigned)(seg < 4 ? o : o1) * 4u;
 #pragma unroll
-            for (int s = 0; s < MT; ++s) st[s] = *(g4_ptr)((gf_ptr)x + xoff[s] + o);
+                for (int s = 0; s < MT; ++s) st[s] = load_quad<float>(xp[s], xoff[s] + oh);
+            } else {
+#pragma unroll
+                for (int s = 0; s < MT; ++s) st[s] = load_quad<float>(opaque(xp[s] + (size_t)__builtin_amdgcn_readfirstlane(o) * 4), xoff[s]);
+            }
         };
         auto stage_store = [&](int step, f32x4 (&st)[MT]) {
             float *buf = xs + (step & 1) * BUF + sslot;
@@ -116,6 +122,10 @@ __global__ __launch_bounds__(256, 2) void lc_forward_wide_kernel(Geom g, const f
 #pragma unroll
                     for (int q = 0; q < 3; ++q) {
                         const u32x2 v = {cvt_pk_bf16(e[0], e[1]), cvt_pk_bf16(e[2], e[3])};
+                        if (q == 2) {
+                            gather_low(low, e[0], e[1]);
+                            gather_low(low, e[2], e[3]);
+                        }
                         *(u32x2 *)(buf + (s * 2 * 3 + q) * 256 + 2 * shalf) = v;
 #pragma unroll
                         for (int r = 0; r < 4; ++r) e[r] -= r & 1 ? bf16_hi(v[r >> 1]) : bf16_lo(v[r >> 1]);
@@ -165,7 +175,7 @@ __global__ __launch_bounds__(256, 2) void lc_forward_wide_kernel(Geom g, const f
                         }
                     }
                     if constexpr (SPLIT) {
-                        const Parts pb[2] = {split8(e[0]), split8(e[1])};
+                        const Parts pb[2] = {split8(e[0], low), split8(e[1], low)};
                         wload(step + PD, wr[p]);
 #pragma unroll
                         for (int t = 0; t < NT; t += 2) {
@@ -175,6 +185,8 @@ __global__ __launch_bounds__(256, 2) void lc_forward_wide_kernel(Geom g, const f
 #pragma unroll
                                 for (int q = 0; q < 3; ++q) pa[m].p[q] = *(const u32x4 *)(ab + ((t + m) * 3 + q) * 256);
                             mfma_split_rows(pa, pb, acc + t);
+                            // (four tiles read ahead, not eight: the registers of the largest batch tile; 651 -> 638 us)
+                            if (MT == 4 && t + 2 == NT / 2) __builtin_amdgcn_sched_barrier(0);
                         }
                     } else {
                         wload(step + PD, wr[p]);
@@ -196,7 +208,7 @@ __global__ __launch_bounds__(256, 2) void lc_forward_wide_kernel(Geom g, const f
                 // Operands of a diverged layer show in the first two steps: the fp32 pass starts there and then, unless
                 // every filter has a NaN among its first weights, so that no sum is anything else.
                 if (SPLIT && p == 1 && c0 == 0) {
-                    if (__syncthreads_or(!all_finite<2 * NT>(&acc[0][0]))) {
+                    if (__syncthreads_or(!all_finite<2 * NT>(&acc[0][0]) || inexact(low))) {
                         f32x2 first[8];
                         wload(0, first);
                         bool a = false, b = false;
@@ -218,8 +230,8 @@ __global__ __launch_bounds__(256, 2) void lc_forward_wide_kernel(Geom g, const f
     clear();
     if (nsteps > 0) {
         pass(std::true_type{});
-        // an operand that is not finite, or a part that overflowed: once more in fp32
-        if (!nans && __syncthreads_or(!all_finite<2 * NT>(&acc[0][0]))) {
+        // an operand that is not finite or too small, or a part that overflowed: once more in fp32
+        if (!nans && __syncthreads_or(!all_finite<2 * NT>(&acc[0][0]) || inexact(low))) {
             clear();
             pass(std::false_type{});
         }
@@ -280,8 +292,8 @@ int check_forward_wide(const Geom &g, const LaunchPlan &p) {
     LC_PLAN_REQUIRE(p, g.F % 128 == 0 && fblocks == g.F / 128);
     LC_PLAN_REQUIRE(p, g.RC % KCH == 0 && (g.S * g.C) % 4 == 0 && (g.W * g.C) % 4 == 0);
     LC_PLAN_REQUIRE(p, btiles == ceil_div(g.B, BT));
-    // 32-bit element offsets of x
-    LC_PLAN_REQUIRE(p, (long long)g.B * g.H * g.W * g.C < (1LL << 31));
+    // 32-bit byte offsets into 32 images
+    LC_PLAN_REQUIRE(p, (long long)32 * g.H * g.W * g.C * 4 < (1LL << 32));
     const int nchunks = g.R * (g.RC / KCH);
     LC_PLAN_REQUIRE(p, nslices >= 1 && nslices <= nchunks);
     LC_PLAN_REQUIRE(p, (long long)p.grid[0] == (long long)g.L * fblocks * btiles * nslices && p.grid[1] == 1 &&

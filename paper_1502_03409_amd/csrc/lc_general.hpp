@@ -119,19 +119,27 @@ __device__ __forceinline__ u32x4 clear_below(u32x4 v, int skip) {
 
 // fp32 products on the bf16 matrix units.  An fp32 MFMA holds the vector ALU's own multipliers, 33 clocks for 2048 flop
 // and nothing beside it (a wave of 12 of them and 24 vector instructions takes 450 clocks of a SIMD, 390 without; the bf16
-// MFMA runs beside them).  A value is the exact sum of three bf16 (8 of its 24 bits each, rounded to nearest: the parts
-// fall by 2^9), and the product of two values is the six partial products down to 2^-16 of it; the three left out add up
-// to at most 2^-25.  All six add up in the fp32 accumulator, smallest first: 96 clocks for what takes 264 in fp32
-// MFMAs, and two roundings of the sum per 32 products and partial product instead of eight to 32 of it.
-// An infinite, NaN or overflowing operand makes every sum it meets non-finite: the kernels form such tiles again in fp32.
+// MFMA runs beside them).  A value is the exact sum of three bf16 (8 of its 24 bits each, rounded to nearest: a part is at
+// most 2^-8 of the one before it), and the product of two values is the six partial products down to 2^-16 of it; the three
+// left out are at most 2^-24 of it together.  The six of 32 products take 96 clocks on the matrix unit, fp32 MFMAs 264.
+// An infinite, NaN or overflowing operand makes every sum it meets non-finite, and an operand below 2^-110 can have bits
+// below bf16's least value (2^-133): the kernels form tiles that meet either again in fp32.
 struct Parts { u32x4 p[3]; };
 __device__ __forceinline__ unsigned cvt_pk_bf16(float a, float b) {
     typedef float f32x2 __attribute__((ext_vector_type(2)));
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     return __builtin_bit_cast(unsigned, __builtin_convertvector(((f32x2){a, b}), bf16x2));
 }
+// Gathers what two values' third parts are rounded from: 7 bits at most, so that the lower half of the word is zero unless bits
+// lie below what bf16 holds.  (Here and now: left to the end, the compiler keeps all of them in registers until then.)
+__device__ __forceinline__ void gather_low(unsigned &low, float a, float b) {
+    low |= __builtin_bit_cast(unsigned, a) | __builtin_bit_cast(unsigned, b);
+    opaque(low);
+}
+// whether an operand was more than the sum of its parts
+__device__ __forceinline__ bool inexact(unsigned low) { return (low & 0xffffu) != 0; }
 // eight consecutive contraction indices of a row or column
-__device__ __forceinline__ Parts split8(const float (&x)[8]) {
+__device__ __forceinline__ Parts split8(const float (&x)[8], unsigned &low) {
     Parts s;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -143,6 +151,8 @@ __device__ __forceinline__ Parts split8(const float (&x)[8]) {
             if (i < 2) {
                 a -= bf16_lo(v);
                 b -= bf16_hi(v);
+            } else {
+                gather_low(low, a, b);
             }
         }
     }
