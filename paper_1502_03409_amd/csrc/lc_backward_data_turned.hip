@@ -436,7 +436,9 @@ void fields_across(const Geom &g, int q, int n, int most, double *sum, int *larg
 
 // The fastest tile by the estimate, where that is a tenth less than the direct form's takes here; grids of fewer than seven
 // fields one way, whose blocks are mostly borders, keep the direct form's, whose estimate is of such (161 layers: 1.12 times
-// as fast as the direct form in fp32 and 1.13 in bf16, 1.08 and 1.11 on its tiles).
+// as fast as the direct form in fp32 and 1.13 in bf16, 1.08 and 1.11 on its tiles).  Tiles that are not split take at least as
+// many slices as the direct form's: a running sum is rounded once per matrix instruction, and fewer slices end less precise (45
+// layers 1.28 times the direct form's error, 0.97 with as many; 1.10 times the time).
 DataTile pick_turned(const Geom &g, int es, const DataTile &direct) {
     if (g.LH < 7 || g.LW < 7) return direct;
     const int FG = ceil_div(g.F, 64 / es);
@@ -464,7 +466,8 @@ DataTile pick_turned(const Geom &g, int es, const DataTile &direct) {
             for (int nt = 1; nt <= 4; ++nt) {
                 if (nt > 1 && 16 * (nt - 1) >= N) break;
                 if ((N + 16 * nt - 1) / (16 * nt) > 65535) continue;
-                for (int ks = 1; ks <= kTurnedDataWaves && (ks == 1 || 2 * ks <= mr * mc * FG); ks *= 2) {
+                const int least = es == 4 && mt * nt >= 3 ? 1 : direct.ks;
+                for (int ks = least; ks <= kTurnedDataWaves && (ks == least || 2 * ks <= mr * mc * FG); ks *= 2) {
                     const DataTile t = {mt, nt, ks >= 4 ? 1 : 4 / ks, ks, q[0], q[1]};
                     const double c = turned_clocks(g, es, t, fr * fc * FG, mr * mc * FG);
                     if (c < best_t) {

@@ -470,9 +470,9 @@ double turned_clocks(const Geom &g, int es, const ForwardTile &t) {
 }
 
 // The fastest tile by the estimate; the direct form's where it is within a tenth of that (a fifth in bf16,
-// where the estimate is further off).  Sums on the matrix units
-// are rounded towards zero once per instruction, so that a contraction in fewer slices ends less precise: tiles that add to
-// the sum that way take at least as many slices as the direct form's.
+// where the estimate is further off).  The matrix
+// unit rounds a running sum once per instruction (by half a unit in the last place on average), so that a contraction in fewer
+// slices ends less precise: tiles that add to the sum that way take at least as many slices as the direct form's.
 ForwardTile pick_turned(const Geom &g, int es, const ForwardTile &direct) {
     ForwardTile best = direct;
     const int groups = ceil_div(g.R * ceil_div(g.RC, 4), 4);

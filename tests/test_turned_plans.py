@@ -171,6 +171,18 @@ def test_backward_data(seed):
     assert turned > 60
 
 
+# layers whose direct form adds a pixel's sum in this many slices, and whose tiles here are not split into bf16 parts
+@pytest.mark.parametrize("dtype,shape,slices", [(0, (3, 174, 21, 24, 4, 1, 64), 4), (0, (23, 34, 105, 16, 14, 1, 32), 8), (0, (20, 59, 36, 24, 5, 1, 16), 2),
+                                                (0, (16, 25, 83, 32, 11, 1, 32), 8), (1, (16, 25, 83, 32, 11, 1, 32), 8), (1, (98, 73, 85, 3, 13, 8, 80), 2),
+                                                (1, (128, 21, 81, 16, 4, 1, 64), 4), (1, (169, 45, 94, 3, 18, 3, 64), 8), (1, (64, 59, 63, 1, 9, 8, 128), 8)],
+                         ids=str)
+def test_backward_data_slices(dtype, shape, slices):
+    """A sum that is formed in fewer slices than the direct form's is rounded more often in a row."""
+    p = lc.plan_query(lc.geom(*shape), lc.LC_OP_BACKWARD_DATA, dtype)[0]
+    assert (p["kernel"], p["tparam"][7]) == ("lc_bwd_data_general", 1)
+    assert (dtype == 0 and p["tparam"][0] * p["tparam"][1] >= 3) or p["tparam"][4] >= slices
+
+
 @pytest.mark.parametrize("shape,wide", [((70, 23, 24, 20, 8, 1, 128), True), ((70, 23, 22, 20, 8, 1, 128), False),
                                         ((128, 40, 40, 64, 4, 2, 128), False), ((64, 23, 24, 20, 8, 1, 128), False),
                                         ((70, 23, 24, 19, 8, 4, 128), False), ((70, 23, 24, 20, 8, 1, 64), False)], ids=str)
