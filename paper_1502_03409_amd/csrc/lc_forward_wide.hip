@@ -77,9 +77,9 @@ __global__ __launch_bounds__(256, 2) void lc_forward_wide_kernel(Geom g, const f
     const int aslot = 4 * (4 * n + (kk ^ (n >> 2)));
     // the field's filters: lane (n, kk) has rows 8 kk .. 8 kk + 7 of a step at filters 2 n, 2 n + 1 of the wave's
     const gbytes wl = (gbytes)(w + (size_t)loc * g.K * g.F + f0);
-    unsigned woff = (unsigned)((8 * kk * g.F + 2 * n) * 4);
+    unsigned woff = (8u * kk * (unsigned)g.F + 2 * n) * 4u;
     // a last step of one chunk of 16: rows beyond the patch are read 16 rows earlier and count as zero
-    unsigned woff_half = (unsigned)((8 * (kk & 1) * g.F + 2 * n) * 4);
+    unsigned woff_half = (8u * (kk & 1) * (unsigned)g.F + 2 * n) * 4u;
 
     bool nans = false;                  // (the same in all threads)
     unsigned low = 0;
@@ -298,8 +298,9 @@ int check_forward_wide(const Geom &g, const LaunchPlan &p) {
     LC_PLAN_REQUIRE(p, nslices >= 1 && nslices <= nchunks);
     LC_PLAN_REQUIRE(p, (long long)p.grid[0] == (long long)g.L * fblocks * btiles * nslices && p.grid[1] == 1 &&
                            p.grid[2] == 1);
-    // two buffers of three parts of bf16, or of fp32 values where a result is not finite; 32-bit offsets inside a step's filters
-    LC_PLAN_REQUIRE(p, p.lds_bytes >= (size_t)2 * BT * 32 * 6 && (long long)g.F * 32 * 4 < (1LL << 31));
+    // two buffers of three parts of bf16, or of fp32 values where a result is not finite; a lane's 32-bit byte offset into a
+    // step's filters: row 24 at most, eight rows on from the wave's (33 million filters, a field's most, are 3.2e9)
+    LC_PLAN_REQUIRE(p, p.lds_bytes >= (size_t)2 * BT * 32 * 6 && (24LL * g.F + 32) * 4 <= (1LL << 32));
     return LC_OK;
 }
 

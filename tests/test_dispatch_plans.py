@@ -639,3 +639,12 @@ def test_fused_pool_lcn_plans_cover_every_pooled_pixel_once():
         fused += 1
     assert fused > 500
     assert lc.l2pool_lcn_plan_query((4, 20, 20, 16), 2, 2, 5) is None      # other pooling windows: the two kernels
+
+
+@pytest.mark.parametrize("t", [(66, 1, 1, 32, 1, 1, 2 ** 24 + 128), (65, 1, 1, 32, 1, 1, 2 ** 25), (128, 4, 2, 32, 1, 2, 20550016),
+                               (129, 4, 1, 32, 1, 1, 30275456)])
+def test_fields_of_many_million_filters(t):
+    """More filters than blocks of 64 fit a grid's second dimension: the workgroup-tiled kernel, up to a field's 2^30 weights."""
+    plans = lc.plan_query(lc.geom(*t), B.LC_OP_FORWARD)
+    assert [p["kernel"] for p in plans] == ["lc_forward_wide"]
+    check_plans(wl.LCGeom(*t), B.LC_OP_FORWARD, B.LC_F32, plans, replay=False)

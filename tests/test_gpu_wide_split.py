@@ -89,6 +89,22 @@ def test_forward_infinite_weights(shape, row, sliced):
     assert rel_fro(out[m], ref[m]) <= bar(g.R * g.R * g.C)
 
 
+def test_forward_millions_of_filters():
+    """Rows of filters 64 MB apart: offsets of more than 31 bits from a step's first row to a lane's last."""
+    shape = (66, 1, 1, 32, 1, 1, 2 ** 24 + 128)
+    print(f"case wide forward {shape}", flush=True)
+    B, F = shape[0], shape[-1]
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    x = torch.randn((B, 1, 1, 32), generator=gen, device="cuda")
+    w = torch.randn((1, 1, 32, F), generator=gen, device="cuda")
+    y = torch.full((B, 1, 1, F), float("nan"), device="cuda")
+    lc.lc_forward(lc.geom(*shape), x, w, None, 1.0, y, lc.LC_F32, None)
+    for f in (0, 2 ** 23 - 64, F - 256):
+        ref = x.view(B, 32).double() @ w.view(32, F)[:, f:f + 256].double()
+        assert rel_fro(y.view(B, F)[:, f:f + 256].cpu().numpy(), ref.cpu().numpy()) <= bar(32)
+    assert not torch.isnan(y).any()
+
+
 # (units of 32 images, dense): layers
 BACKWARD = {(2, 0): [(300, 11, 13, 32, 4, 2, 32), (128, 14, 15, 32, 6, 2, 64)], (3, 0): [(80, 11, 13, 64, 4, 2, 64), (96, 21, 26, 8, 8, 4, 96)],
             (4, 0): [(128, 33, 36, 32, 4, 2, 32), (256, 16, 18, 128, 3, 1, 32)],
