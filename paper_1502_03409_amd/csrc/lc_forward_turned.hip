@@ -352,6 +352,9 @@ __global__ __launch_bounds__(64 * kTurnedWaves(MT, NT), kTurnedResident<T>(MT, N
 #pragma unroll
     for (int u = 0; u < NT; ++u) bv[u] = bias ? bias[(size_t)loc * g.F + fl + u] : 0.f;
     struct __attribute__((packed, aligned(4))) Out { float v[NT]; };
+    // A run that would cross the last filter shares filters with the lane before it, or with the block before: those are stored
+    // there, as another wave may have formed its tile in other products.
+    const int shared = f0 + NT * n - fl;
 #pragma unroll
     for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
@@ -361,7 +364,14 @@ __global__ __launch_bounds__(64 * kTurnedWaves(MT, NT), kTurnedResident<T>(MT, N
             Out o;
 #pragma unroll
             for (int u = 0; u < NT; ++u) o.v[u] = alpha * acc[mt][u][r] + bv[u];
-            *(Out *)(y + ((size_t)b * g.L + loc) * g.F + fl) = o;
+            float *p = y + ((size_t)b * g.L + loc) * g.F + fl;
+            if (shared == 0) {
+                *(Out *)p = o;
+            } else {
+#pragma unroll
+                for (int u = 1; u < NT; ++u)
+                    if (u >= shared) p[u] = o.v[u];
+            }
         }
 }
 

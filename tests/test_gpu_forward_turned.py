@@ -96,3 +96,28 @@ def test_infinities_and_ends_of_the_range(shape, scale):
     assert np.array_equal(np.isnan(y), np.isnan(ref)) and np.array_equal(y[np.isinf(ref)], ref[np.isinf(ref)])
     m = np.isfinite(ref)
     assert m.mean() > 0.3 and rel_fro(y[m].astype(np.float64) / scale, ref[m] / scale) <= bar(g.K)
+
+
+@pytest.mark.parametrize("shape", [(49, 27, 23, 8, 2, 1, 145), (49, 27, 23, 8, 2, 1, 193), (64, 30, 30, 16, 4, 2, 193)], ids=str)
+def test_one_writer_for_every_filter(shape):
+    """A last block of one filter: its wave also forms the two or three before it, which belong to the block before.  Formed again in
+    fp32 for an infinite weight, it leaves those as they are, bit by bit; and so does the block before with the last one."""
+    print(f"case turned forward last filters {shape}", flush=True)
+    g, G = wl.LCGeom(*shape), lc.geom(*shape)
+    (p,) = lc.plan_query(G, lc.LC_OP_FORWARD, lc.LC_F32)
+    MT, NT = p["tparam"][:2]
+    assert p["tparam"][7] and MT * NT >= 6 and g.F % (16 * NT) == 1
+    x, w, _ = wl.lc_inputs(g, "gaussian", seed=7)
+    xd = torch.from_numpy(x).cuda()
+
+    def forward(weights):
+        y = torch.full((g.B, g.LH, g.LW, g.F), float("nan"), device="cuda")
+        lc.lc_forward(G, xd, torch.from_numpy(weights).cuda(), None, 1.0, y)
+        return y
+
+    y = forward(w)
+    assert rel_fro(y.cpu().numpy(), oracle.lc_forward(shape, x, w)) <= bar(g.K)
+    last, before = w.copy(), w.copy()
+    last[:, :, 1, g.F - 1], before[:, :, 1, g.F - 1 - 8 * NT] = np.inf, np.inf
+    assert torch.equal(forward(last)[..., :-1], y[..., :-1])
+    assert torch.equal(forward(before)[..., -1], y[..., -1])
