@@ -352,27 +352,32 @@ __global__ __launch_bounds__(64 * kTurnedWaves(MT, NT), kTurnedResident<T>(MT, N
 #pragma unroll
     for (int u = 0; u < NT; ++u) bv[u] = bias ? bias[(size_t)loc * g.F + fl + u] : 0.f;
     struct __attribute__((packed, aligned(4))) Out { float v[NT]; };
-    // A run that would cross the last filter shares filters with the lane before it, or with the block before: those are stored
-    // there, as another wave may have formed its tile in other products.
-    const int shared = f0 + NT * n - fl;
+    // Runs that would cross the last filter start earlier, inside the wave's filters as a rule, where the same sums are stored
+    // twice.  A last block of fewer filters than a run reaches into the block before: in split tiles those are stored there only, as
+    // either wave may have formed its tile in fp32.
+    const int first = SPLIT ? max(f0 - (g.F - NT), 0) : 0;
+    auto store = [&](auto whole) {
 #pragma unroll
-    for (int mt = 0; mt < MT; ++mt)
+        for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int b = b0 + mt * 16 + 4 * kk + r;
-            if (b >= g.B) continue;
-            Out o;
+            for (int r = 0; r < 4; ++r) {
+                const int b = b0 + mt * 16 + 4 * kk + r;
+                if (b >= g.B) continue;
+                Out o;
 #pragma unroll
-            for (int u = 0; u < NT; ++u) o.v[u] = alpha * acc[mt][u][r] + bv[u];
-            float *p = y + ((size_t)b * g.L + loc) * g.F + fl;
-            if (shared == 0) {
-                *(Out *)p = o;
-            } else {
+                for (int u = 0; u < NT; ++u) o.v[u] = alpha * acc[mt][u][r] + bv[u];
+                float *p = y + ((size_t)b * g.L + loc) * g.F + fl;
+                if constexpr (whole()) {
+                    *(Out *)p = o;
+                } else {
 #pragma unroll
-                for (int u = 1; u < NT; ++u)
-                    if (u >= shared) p[u] = o.v[u];
+                    for (int u = 1; u < NT; ++u)
+                        if (u >= first) p[u] = o.v[u];
+                }
             }
-        }
+    };
+    if (first == 0) store(std::true_type{});
+    else store(std::false_type{});
 }
 
 namespace {
