@@ -251,6 +251,8 @@ int allow_dynamic_lds(const void *kernel, size_t bytes, const char *where);
         }                                                \
     } while (0)
 
+constexpr int kComputeUnits = 256;
+
 // Batch tile of the workgroup-tiled kernels in units of 32 images: 4, 3 (if allowed) or 2, whichever pads the
 // batch least; the larger tile on a tie.
 inline int batch_tile_mt(int B, bool allow3) {

@@ -755,7 +755,7 @@ int launch_direct(const Geom &g, const float *x, const float *w, const float *bi
 // compute unit, so a grid that is not a multiple of 2 x 256 ends in a round that leaves most of the
 // chip idle.  The strips of that last partial round are therefore issued as a second launch whose
 // workgroups take a quarter of the batch tile each: four times as many, a quarter as long.
-constexpr int kComputeUnits = 256, kBigTilesPerCu = 2;
+constexpr int kBigTilesPerCu = 2;
 
 template <int MT, int NT, int NLOC, int UNR, typename T>
 int launch_fast_tiered(const Geom &g, const T *x, const T *w, const float *bias, float alpha,

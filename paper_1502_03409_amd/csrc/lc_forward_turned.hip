@@ -435,6 +435,11 @@ int launch_tile(const Geom &g, const T *x, const T *w, const float *bias, float 
     return LC_EINTERNAL;
 }
 
+// 16 images x 16 filters x 16 patch elements, what a layer is measured in below
+double blocks_of(const Geom &g) {
+    return (double)g.L * ceil_div(g.B, 16) * ceil_div(g.F, 16) * ceil_div(g.R * ceil_div(g.RC, 4), 4);
+}
+
 // Which layers: filters in whole 32-byte vectors of fp32, or more than 128 of them, where the tile is picked for this form (below;
 // on the direct form's tiles it gains a third of that, and bf16 rows at odd addresses lose: 4 images of 194 x 52 x 2, 19
 // filters 1.6 times the time).  Rows of whole 16-element blocks at any size: 106 layers of 6000 to 14 million blocks of 16
@@ -445,8 +450,7 @@ int turned_form(const Geom &g) {
     if (g.F % 8 != 0 && g.F <= 128) return 0;
     if (g.RC % 16 == 0) return kWhole;
     const int nvt = g.R * ceil_div(g.RC, 4);
-    const double blocks = (double)g.L * ceil_div(g.B, 16) * ceil_div(g.F, 16) * ceil_div(nvt, 4);
-    return blocks >= 100000 && nvt >= 64 && nvt <= kMostPlaces ? kTable : 0;
+    return blocks_of(g) >= 100000 && nvt >= 64 && nvt <= kMostPlaces ? kTable : 0;
 }
 
 // Estimated clocks of a launch.  A group of 16 elements costs a wave its MFMAs (132 clocks a 16 x 16 tile in fp32, 48 where
@@ -454,14 +458,16 @@ int turned_form(const Geom &g) {
 // cache its loads; the waves share SIMDs, caches and L2, and none ends before its own chain.  The constants are a fit to 211
 // layers timed with every tile and number of slices, in the caches and out of them; what is picked is on average 6 % (fp32)
 // and 10 % (bf16) slower than the fastest.
-double turned_clocks(const Geom &g, int es, int mt, int nt, int ks, int waves_wg, double wgs) {
+// fullest: every compute unit has as many workgroups as the one with most.
+double turned_clocks(const Geom &g, int es, int mt, int nt, int ks, int waves_wg, double wgs,
+                    bool fullest) {
     const bool split = es == 4 && mt * nt >= 6, f32 = es == 4;
     const double mm = (split ? 48.0 : f32 ? 132.0 : 17.0) * mt * nt;
     const double form = g.RC % 16 == 0 ? 0.2 : g.RC % 4 != 0 ? 2.0 : 1.0;
     const double issue = mm + (split ? 20.6 : f32 ? 0.0 : 10.3) * 4 * (mt + nt) + (f32 ? 45.6 : 21.2) * form;
     const double per = ceil_div(ceil_div(g.R * ceil_div(g.RC, 4), 4), ks);
     const double add = (ks > 1 ? (f32 ? 308.0 : 270.0) * mt * nt + (f32 ? 176.0 : 91.0) * __builtin_ctz(ks) : 0) + (f32 ? 589.0 : 1085.0);
-    const double waves = wgs * waves_wg;
+    const double waves = (fullest ? ceil(wgs / kComputeUnits) * kComputeUnits : wgs) * waves_wg;
     const double busy = waves * (per * issue + add) / 1024, loads = waves * per * (f32 ? 45.5 : 33.2) * mt / 256;
     const double alone = per * (issue + (f32 ? 46.0 : 90.5)) + add;
     const double lines = waves * per * (mt + nt) * 256 * es / ((f32 ? 78.1 : 49.3) * 256);
@@ -478,30 +484,36 @@ void arrange(const Geom &g, ForwardTile *t) {
     while (t->tasks * t->nfw * t->ks < 4) t->tasks *= 2;
 }
 
-double turned_clocks(const Geom &g, int es, const ForwardTile &t) {
+double turned_clocks(const Geom &g, int es, const ForwardTile &t, bool fullest) {
     const double ntask = (double)g.L * ceil_div(g.B, 16 * t.mt);
     const double wgs = ceil((ntask + t.tasks - 1) / t.tasks) * ceil_div(g.F, t.nfw * t.nt * 16);
-    return turned_clocks(g, es, t.mt, t.nt, t.ks, t.tasks * t.nfw * t.ks, wgs);
+    return turned_clocks(g, es, t.mt, t.nt, t.ks, t.tasks * t.nfw * t.ks, wgs, fullest);
 }
+
+bool turned_splits(int es, int mt, int nt) { return es == 4 && mt * nt >= 6; }
 
 // The fastest tile by the estimate; the direct form's where it is within a tenth of that (a fifth in bf16,
 // where the estimate is further off).  The matrix
 // unit rounds a running sum once per instruction (by half a unit in the last place on average), so that a contraction in fewer
 // slices ends less precise: tiles that add to the sum that way take at least as many slices as the direct form's.
-ForwardTile pick_turned(const Geom &g, int es, const ForwardTile &direct) {
-    ForwardTile best = direct;
+// first (nullable): a tile to be no less precise than either, in slices and in split products.
+ForwardTile fastest_turned(const Geom &g, int es, const ForwardTile &direct, const ForwardTile *first) {
+    ForwardTile best = first ? *first : direct;
     const int groups = ceil_div(g.R * ceil_div(g.RC, 4), 4);
+    const bool first_splits = first && turned_splits(es, first->mt, first->nt);
     double own = 1e300, best_t = 1e300;
     for (int mt = 1; mt <= 4; ++mt) {
         if (mt > 1 && 16 * (mt - 1) >= g.B) break;
         if ((long long)g.L * ceil_div(g.B, 16 * mt) > kMostTasks) continue;
         for (int nt = 1; nt <= 4; ++nt) {
             if (nt > g.F || (nt > 1 && 16 * (nt - 1) >= g.F) || (es == 2 && nt == 3) || ceil_div(g.F, 16 * nt) > 65535) continue;
-            const int least = es == 4 && mt * nt >= 6 ? 1 : direct.ks;
+            const bool split = turned_splits(es, mt, nt);
+            if (first_splits && !split) continue;
+            const int least = max(split ? 1 : direct.ks, first && split == first_splits ? first->ks : 1);
             for (int ks = least; ks <= kTurnedWaves(mt, nt) && (ks == least || 2 * ks <= groups); ks *= 2) {
                 ForwardTile t = {mt, nt, 1, 1, ks};
                 arrange(g, &t);
-                const double c = turned_clocks(g, es, t);
+                const double c = turned_clocks(g, es, t, first != nullptr);
                 if (mt == direct.mt && nt == direct.nt && ks == direct.ks) own = c;
                 if (c < best_t) {
                     best_t = c;
@@ -514,6 +526,20 @@ ForwardTile pick_turned(const Geom &g, int es, const ForwardTile &direct) {
     best.ks = min(best.ks, kTurnedWaves(best.mt, best.nt));   // (millions of filters: no candidate with as many slices)
     arrange(g, &best);
     return best;
+}
+
+// Layers of kFullest blocks and more are as slow as the compute unit with most workgroups: the largest tiles run one or two of
+// them a unit, and 265 of those take the time of 512.  Where that makes a tile no less precise 1.15 times as fast, they take it: 80 of
+// 371 layers timed in fp32 (1.17 times as fast) and 92 of 336 in bf16 (1.18; 64 images of 28 x 142 x 5, 20 x 20 at stride 8, 223
+// filters: 160 workgroups of 86 KB 37 and 25 us, now 256 of 53 KB 22 and 18; 88 x 28 x 5, 16 x 16 at stride 5, 382 filters: 51 -> 40).
+// More than a tenth slower than the direct form were 27 and 6 of them, are 15 and 1.  Smaller layers are what the constants
+// were fitted to.
+constexpr double kFullest = 131072;
+ForwardTile pick_turned(const Geom &g, int es, const ForwardTile &direct) {
+    const ForwardTile t = fastest_turned(g, es, direct, nullptr);
+    if (blocks_of(g) < kFullest) return t;
+    const ForwardTile u = fastest_turned(g, es, direct, &t);
+    return turned_clocks(g, es, t, true) > 1.15 * turned_clocks(g, es, u, true) ? u : t;
 }
 
 template <typename T>

@@ -191,3 +191,13 @@ def test_long_patches_take_the_workgroup_tiles(shape, wide):
     g = lc.geom(*shape)
     assert (lc.plan_query(g, lc.LC_OP_FORWARD, lc.LC_F32)[0]["kernel"] == "lc_forward_wide") == wide
     assert lc.workspace_bytes(g, lc.LC_OP_FORWARD, lc.LC_F32) == 0
+
+
+@pytest.mark.parametrize("geo,dtype", [((64, 28, 142, 5, 20, 8, 223), 0), ((64, 28, 142, 5, 20, 8, 223), 1),
+                                       ((64, 88, 28, 5, 16, 5, 382), 0)])
+def test_large_layers_fill_the_compute_units(geo, dtype):
+    """Layers of 131072 blocks and more: no tile whose workgroups leave a round of compute units more than a fifth empty where a
+    smaller one does not (these had 160, 128 and 270 workgroups that a compute unit runs one by one)."""
+    p = lc.plan_query(lc.geom(*geo), B.LC_OP_FORWARD, dtype)[0]
+    n = p["grid"][0] * p["grid"][1]
+    assert p["tparam"][7] and n / (256 * cdiv(n, 256)) >= 0.8, p
