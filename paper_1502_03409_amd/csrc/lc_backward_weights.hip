@@ -348,22 +348,27 @@ __global__ __launch_bounds__(256, G == 3 || SPLIT ? 2 : 1) void lc_bwd_weights_f
                     __builtin_amdgcn_sched_barrier(0);
                 }
             }
-            for (int st = 0; st < left; ++st) {
-                AV al[GA];
+            // what is left of 32 images, its loads together
+            if (left > 0) {
 #pragma unroll
-                for (int gg = 0; gg < GA; ++gg) {
-                    al[gg] = *(const GAV *)xa[gg];
-                    xa[gg] += xstep;
-                }
-                const BR bl = *(const GBV *)da;
-                da += dstep;
+                for (int q = 0; q < 7; ++q)
+                    if (q < left) {
 #pragma unroll
-                for (int gg = 0; gg < GA; ++gg)
+                        for (int gg = 0; gg < GA; ++gg) { a[q][gg] = *(const GAV *)xa[gg]; xa[gg] += xstep; }
+                        bv[q] = *(const GBV *)da;
+                        da += dstep;
+                    }
 #pragma unroll
-                    for (int t = 0; t < VA; ++t)
+                for (int q = 0; q < 7; ++q)
+                    if (q < left) {
 #pragma unroll
-                        for (int u = 0; u < NT; ++u)
-                            acc[gg][t][u] = mfma16(raw_get<T, VA>(al[gg], t), raw_get<T, NT>(bl, u), acc[gg][t][u]);
+                        for (int gg = 0; gg < GA; ++gg)
+#pragma unroll
+                            for (int t = 0; t < VA; ++t)
+#pragma unroll
+                                for (int u = 0; u < NT; ++u)
+                                    acc[gg][t][u] = mfma16(raw_get<T, VA>(a[q][gg], t), raw_get<T, NT>(bv[q], u), acc[gg][t][u]);
+                    }
             }
         }
     };
