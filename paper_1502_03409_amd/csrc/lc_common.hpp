@@ -309,6 +309,7 @@ int launch_backward_data_bf16(const Geom &g, const void *dy, const void *w, floa
 // any geometry (patch rows of at least four values): both operands straight from global memory, contraction split over
 // waves where the layer has few tiles
 bool forward_general_supported(const Geom &g, int es);   // es: bytes per operand element
+double forward_general_clocks(const Geom &g);            // estimate for fp32 rows of whole 16-element blocks, 8 n filters
 int launch_forward_general_f32(const Geom &g, const float *x, const float *w, const float *bias, float alpha,
                                const float *alpha_dev, float *y, hipStream_t s);
 int launch_forward_general_bf16(const Geom &g, const void *x, const void *w, const float *bias, float alpha, float *y,

@@ -8,6 +8,8 @@
 // of it.  A wave holds the whole batch tile for its location: each weight is fetched from global
 // memory exactly once per batch tile, straight into the MFMA B operand (lanes run along f, the
 // contiguous axis of w), and reused for MT MFMAs.
+#include <math.h>
+
 #include "lc_common.hpp"
 
 namespace lc {
@@ -941,12 +943,10 @@ bool takes_general(const Geom &g, int es) {
 // elements per patch, where its slices across workgroups reach further than the general kernel's sixteen waves at most (96
 // images of 18 x 20 x 16, 16 x 16 at stride 1, 128 filters: 25.5 us against 40.6; 80 of 26 x 26 x 8, 24 x 24 at stride
 // 1, 256 filters: 31 against 47), and patches of kWideLong elements that give a workgroup to every compute unit without
-// slices: sharing images and filters in LDS then saves more than the barriers and a batch in tiles of 64 and more cost, on
-// all of 19 layers timed (256 images of 64 x 64 x 32, 8 x 8 at stride 2, 128 filters: 714 -> 635; 80 of 23 x 22 x 32, 7 x 7,
-// 512 filters: 375 -> 280; 128 of 51 x 99 x 32, 7 x 7 at stride 4, 256 filters: 224 -> 220).  With shorter patches the
-// general kernel is faster (130 of 38 x 28 x 32, 6 x 6 at stride 2, 384 filters: 192 against 210; 128 of 40 x 40 x 64, 4 x 4
-// at stride 2, 128 filters: both 89), or with slices, which want a workspace besides (192 of 22 x 7 x 32, 7 x 7 at stride 3,
-// 128 filters: 12 against 21).
+// slices: sharing images and filters in LDS then saves more than the barriers cost, where the batch fills its tiles of 64 to 128
+// images and the workgroups their rounds (long_patches_gain).  With shorter patches the general kernel is faster (130 of 38 x 28 x 32,
+// 6 x 6 at stride 2, 384 filters: 192 against 210; 128 of 40 x 40 x 64, 4 x 4 at stride 2, 128 filters: both 89), or with slices,
+// which want a workspace besides (192 of 22 x 7 x 32, 7 x 7 at stride 3, 128 filters: 12 against 21).
 constexpr int kWideFields = 16, kWidePatch = 4096, kWideLong = 1200;
 
 // Where the register-staged kernel (mt, nt: the tile it would take) keeps a layer the general kernel could take: fields
@@ -1108,10 +1108,24 @@ int launch_forward_generic(const Geom &g, const T *x, const T *w, const float *b
 
 }  // namespace
 
+// Whether the workgroup-tiled kernel is faster on a layer of long patches that gives every compute unit a workgroup.  Its time is a
+// fit to 150 such layers, 4 % off: half of it is that of the compute unit with most workgroups, and both halves are those of the
+// padded batch.  The general kernel's estimate is 6 % off, and 1.16 times too long on average.  Of the 150 layers 99 stay
+// (1.13 times as fast as the general kernel, warm and out of the caches; 256 images of 64 x 64 x 32, 8 x 8 at stride 2, 128
+// filters: 714 -> 635 us), 5 of them slower by 5 to 10 %; without the estimates 42 were slower, down to 0.74 just above a batch tile or
+// a round (130 of 22 x 69 x 32, 14 x 14 at stride 2, 128 filters: 254 -> 351 us).
+bool long_patches_gain(const Geom &g) {
+    const int mt = batch_tile_mt(g.B, true);
+    const double rounds = (double)g.L * (g.F / 128) * ceil_div(g.B, 32 * mt) / kComputeUnits;
+    const double wide = 9.7 * (mt + 1) * g.K * (ceil(rounds) + rounds) + (double)g.L * g.K * g.F / 2690 + 41600;
+    return forward_general_clocks(g) >= 1.15 * wide;
+}
+
 bool forward_takes_wide(const Geom &g) {
+    if (!forward_wide_supported(g)) return false;
+    if ((g.L < kWideFields && g.K >= kWidePatch) || !takes_general(g, 4)) return true;
     const long long workgroups = (long long)g.L * (g.F / 128) * ((g.B + 127) / 128);
-    return forward_wide_supported(g) && ((g.L < kWideFields && g.K >= kWidePatch) || (workgroups >= kComputeUnits && g.K >= kWideLong) ||
-                                         !takes_general(g, 4));
+    return workgroups >= kComputeUnits && g.K >= kWideLong && long_patches_gain(g);
 }
 
 int launch_forward_f32(const Geom &g, const float *x, const float *w, const float *bias, float alpha,

@@ -246,11 +246,15 @@ ForwardTile pick_tile(const Geom &g, int es) {
     return best;
 }
 
+ForwardTile direct_tile(const Geom &g, int es) {
+    static thread_local TileMemo<ForwardTile> memo;
+    return memo.get(g, es, pick_tile);
+}
+
 template <typename T>
 int launch_general(const Geom &g, const T *x, const T *w, const float *bias, float alpha, const float *alpha_dev, float *y,
                    hipStream_t s) {
-    static thread_local TileMemo<ForwardTile> memo;
-    const ForwardTile t = memo.get(g, sizeof(T), pick_tile);
+    const ForwardTile t = direct_tile(g, sizeof(T));
     if (forward_turned_takes(g)) return launch_forward_turned(g, x, w, bias, alpha, alpha_dev, y, t, s);
 #define LC_TILE(M, N) if (t.mt == M && t.nt == N) return launch_tile<M, N>(g, x, w, bias, alpha, alpha_dev, y, t, s)
     LC_TILE(1, 1); LC_TILE(2, 1); LC_TILE(3, 1); LC_TILE(4, 1);
@@ -268,6 +272,8 @@ bool forward_general_supported(const Geom &g, int es) {
     // fields leave to the masked kernel
     return g.RC >= 4 && g.F <= 64 * kMostBlocks && (long long)g.L * ceil_div(g.B, 64) <= kMostTasks && (long long)64 * g.H * g.W * g.C * es < (1LL << 32) && (long long)g.K * g.F * es < (1LL << 32);
 }
+
+double forward_general_clocks(const Geom &g) { return forward_turned_clocks(g, direct_tile(g, 4)); }
 
 int launch_forward_general_f32(const Geom &g, const float *x, const float *w, const float *bias, float alpha,
                                const float *alpha_dev, float *y, hipStream_t s) {

@@ -542,12 +542,16 @@ ForwardTile pick_turned(const Geom &g, int es, const ForwardTile &direct) {
     return turned_clocks(g, es, t, true) > 1.15 * turned_clocks(g, es, u, true) ? u : t;
 }
 
+ForwardTile turned_tile(const Geom &g, int es, const ForwardTile &direct) {
+    static thread_local TileMemo<ForwardTile> memo;
+    return memo.get(g, es, [&](const Geom &, int) { return pick_turned(g, es, direct); });
+}
+
 template <typename T>
 int launch(const Geom &g, const T *x, const T *w, const float *bias, float alpha, const float *alpha_dev, float *y,
            const ForwardTile &direct, hipStream_t s) {
     const int form = turned_form(g);
-    static thread_local TileMemo<ForwardTile> memo;
-    const ForwardTile t = memo.get(g, sizeof(T), [&](const Geom &, int es) { return pick_turned(g, es, direct); });
+    const ForwardTile t = turned_tile(g, sizeof(T), direct);
 #define LC_TILE(M, N) if (t.mt == M && t.nt == N) return launch_tile<M, N>(g, x, w, bias, alpha, alpha_dev, y, t, form, s)
     LC_TILE(1, 1); LC_TILE(2, 1); LC_TILE(3, 1); LC_TILE(4, 1);
     LC_TILE(1, 2); LC_TILE(2, 2); LC_TILE(3, 2); LC_TILE(4, 2);
@@ -560,6 +564,10 @@ int launch(const Geom &g, const T *x, const T *w, const float *bias, float alpha
 }  // namespace
 
 bool forward_turned_takes(const Geom &g) { return turned_form(g) != 0; }
+
+double forward_turned_clocks(const Geom &g, const ForwardTile &direct) {
+    return turned_clocks(g, 4, turned_tile(g, 4, direct), true);
+}
 
 int launch_forward_turned(const Geom &g, const float *x, const float *w, const float *bias, float alpha, const float *alpha_dev,
                           float *y, const ForwardTile &direct, hipStream_t s) {

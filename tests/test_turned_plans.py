@@ -201,3 +201,11 @@ def test_large_layers_fill_the_compute_units(geo, dtype):
     p = lc.plan_query(lc.geom(*geo), B.LC_OP_FORWARD, dtype)[0]
     n = p["grid"][0] * p["grid"][1]
     assert p["tparam"][7] and n / (256 * cdiv(n, 256)) >= 0.8, p
+
+
+@pytest.mark.parametrize("geo,wide", [((130, 22, 69, 32, 14, 2, 128), False), ((133, 60, 52, 16, 12, 4, 128), False), ((200, 64, 31, 64, 6, 5, 256), False),
+                                      ((160, 53, 59, 32, 10, 4, 128), False), ((256, 64, 64, 32, 8, 2, 128), True), ((80, 23, 22, 32, 7, 1, 512), True)])
+def test_long_patches_in_padded_batches_and_rounds(geo, wide):
+    """The workgroup-tiled kernel where its tiles of the batch and its rounds of workgroups are filled: just above either the general
+    kernel is up to 1.4 times as fast."""
+    assert (lc.plan_query(lc.geom(*geo), B.LC_OP_FORWARD, B.LC_F32)[0]["kernel"] == "lc_forward_wide") == wide
