@@ -402,7 +402,8 @@ int check_forward_turned(const Geom &g, const LaunchPlan &p, bool bl) {
     // slices, the waves' turning space, places up to the last one read
     const size_t sums = ks > 1 ? (size_t)(waves / 2) * MT * NT * 1024 : 0;
     const size_t turns = (size_t)waves * (ES == 4 ? turn_bytes<float>(MT, NT, bl) : turn_bytes<bf16_t>(MT, NT, bl));
-    const int groups = ceil_div(nvt, 4) + 1 + (ES == 4 && MT * NT >= 6 ? 2 : 5);
+    // (split: an even number of groups, a step of two ahead and the next one's place; otherwise four steps ahead and the next)
+    const int groups = ceil_div(nvt, 4) + 1 + (ES == 4 && MT * NT >= 6 ? 3 : 5);
     LC_PLAN_REQUIRE(p, p.lds_bytes >= sums + turns + (form == kTable ? (size_t)4 * groups * 8 : 0));
     LC_PLAN_REQUIRE(p, form != kTable || 4 * groups <= nvt + kPlacesBeyond);
     // 32-bit byte offsets: into a batch tile's images, into a field's K x F matrix
@@ -416,7 +417,7 @@ int launch_tile(const Geom &g, const T *x, const T *w, const float *bias, float 
     const int NV = ceil_div(g.RC, 4), nvt = g.R * NV, per = ceil_div(ceil_div(nvt, 4), t.ks) * 4;
     const int nbt = ceil_div(g.B, 16 * MT), waves = t.ks * t.nfw * t.tasks;
     const long long ntask = (long long)g.L * nbt;
-    const bool bl = NT <= 2 && g.F >= 4;
+    const bool bl = NT <= 2;                                  // (turned_form: eight filters at least)
     const size_t lds = (t.ks > 1 ? (size_t)(waves / 2) * MT * NT * 1024 : 0) + (size_t)waves * turn_bytes<T>(MT, NT, bl) +
                        (form == kTable ? (size_t)(nvt + kPlacesBeyond) * 8 : 0);
     dim3 grid((unsigned)((ntask + t.tasks - 1) / t.tasks), ceil_div(g.F, t.nfw * NT * 16));
@@ -430,7 +431,7 @@ int launch_tile(const Geom &g, const T *x, const T *w, const float *bias, float 
         return LC_OK;                                                                                                     \
     }
     if constexpr (NT <= 2) { LC_FORM(kWhole, true) LC_FORM(kTable, true) }
-    if constexpr (NT != 2) { LC_FORM(kWhole, false) LC_FORM(kTable, false) }
+    if constexpr (NT > 2) { LC_FORM(kWhole, false) LC_FORM(kTable, false) }
 #undef LC_FORM
     return LC_EINTERNAL;
 }
