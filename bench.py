@@ -315,6 +315,14 @@ def bench_sae(lc, wl, np, torch, dev, steps, warmup):
 
 
 BF16_MFMA_PEAK_TFLOPS = 2500.0   # MI355X dense bf16 matrix peak
+SPLIT_MFMA_PEAK_TFLOPS = BF16_MFMA_PEAK_TFLOPS / 6   # fp32 products as six products of bf16 parts, which many kernels use
+
+
+def mfma_fractions(tf, dt):
+    """Shares of the matrix peaks.  An fp32 pass may run on either unit: the fp32 one's share exceeds 1 where products are split."""
+    if dt == "bf16":
+        return {"frac_mfma_peak": round(tf / BF16_MFMA_PEAK_TFLOPS, 4)}
+    return {"frac_fp32_mfma_peak": round(tf / FP32_MFMA_PEAK_TFLOPS, 4), "frac_split_mfma_peak": round(tf / SPLIT_MFMA_PEAK_TFLOPS, 4)}
 
 
 def timed_ms(torch, stream, f, iters, warm_ms=60.0):
@@ -364,22 +372,20 @@ def bench_others(lc, wl, torch, iters):
         min_bytes = {"lc_forward": esz * (w.numel() + x.numel()) + 4 * y.numel(),
                      "lc_backward_data": esz * (w.numel() + dy.numel()) + 4 * dx.numel(),
                      "lc_backward_weights": esz * (x.numel() + dy.numel()) + 4 * dw.numel()}
-        peak = BF16_MFMA_PEAK_TFLOPS if dt == "bf16" else FP32_MFMA_PEAK_TFLOPS
         entry, total = {}, 0.0
         for kn, f in fns.items():
             ms = timed_ms(torch, stream, f, iters)
             total += ms
             tf = g.flop_per_pass / (ms * 1e-3) / 1e12
-            entry[kn] = {"ms": round(ms, 4), "TFLOP/s": round(tf, 1), "frac_mfma_peak": round(tf / peak, 4),
+            entry[kn] = {"ms": round(ms, 4), "TFLOP/s": round(tf, 1), **mfma_fractions(tf, dt),
                          "frac_hbm_roof": round(min_bytes[kn] / (HBM_PEAK_GBS * 1e9) / (ms * 1e-3), 4)}
         tf = 3 * g.flop_per_pass / (total * 1e-3) / 1e12
-        entry["fwd_bwd"] = {"ms": round(total, 4), "TFLOP/s": round(tf, 1), "frac_mfma_peak": round(tf / peak, 4)}
+        entry["fwd_bwd"] = {"ms": round(total, 4), "TFLOP/s": round(tf, 1), **mfma_fractions(tf, dt)}
         # the three passes back to back, as a training step runs them: a kernel timed alone in a loop finds operands
         # that fit the 256 MB Infinity Cache still there from its own previous call, behind the other passes it does not
         seq = timed_ms(torch, stream, lambda: [f() for f in fns.values()], max(iters // 2, 5))
         tf = 3 * g.flop_per_pass / (seq * 1e-3) / 1e12
-        entry["fwd_bwd_in_sequence"] = {"ms": round(seq, 4), "TFLOP/s": round(tf, 1),
-                                        "frac_mfma_peak": round(tf / peak, 4)}
+        entry["fwd_bwd_in_sequence"] = {"ms": round(seq, 4), "TFLOP/s": round(tf, 1), **mfma_fractions(tf, dt)}
         entry["shape"] = dict(zip("BHWCRSF", g.as_tuple()))
         res[f"{name}_{dt}"] = entry
         del x, w, dy, y, dx, dw
@@ -398,7 +404,7 @@ def bench_others(lc, wl, torch, iters):
     ms = timed_ms(torch, stream, f, iters)
     tf = 5 * g.flop_per_pass / (ms * 1e-3) / 1e12
     res["paper_layer1_sae_step"] = {"ms": round(ms, 3), "images_per_s": round(g.B / (ms * 1e-3), 1),
-                                    "TFLOP/s": round(tf, 1), "frac_mfma_peak": round(tf / FP32_MFMA_PEAK_TFLOPS, 4),
+                                    "TFLOP/s": round(tf, 1), **mfma_fractions(tf, "f32"),
                                     "shape": dict(zip("BHWCRSF", g.as_tuple()))}
     del x, w, b, h, ws
     torch.cuda.empty_cache()
@@ -418,7 +424,7 @@ def bench_others(lc, wl, torch, iters):
         ms = timed_ms(torch, stream, f, iters)
         tf = 5 * g.flop_per_pass / (ms * 1e-3) / 1e12
         res[name] = {"ms": round(ms, 3), "images_per_s": round(g.B / (ms * 1e-3), 1), "TFLOP/s": round(tf, 1),
-                     "frac_mfma_peak": round(tf / FP32_MFMA_PEAK_TFLOPS, 4), "lambda": lam, "flags": 3,
+                     **mfma_fractions(tf, "f32"), "lambda": lam, "flags": 3,
                      "shape": dict(zip("BHWCRSF", g.as_tuple()))}
         del x, w, b, h, ws
         torch.cuda.empty_cache()

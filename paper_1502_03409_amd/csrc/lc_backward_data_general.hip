@@ -308,19 +308,6 @@ namespace {
 // four where eight pad the filters by more than a quarter (9 filters, bf16: 22 -> 18 us).
 int vector_width(const Geom &g) { return g.F >= 8 && ceil_div(g.F, 8) * 8 <= 5 * ceil_div(g.F, 4) ? 8 : 4; }
 
-// Fields that touch a block of q strides, summed over the blocks along an image side of n pixels with most fields, and
-// their largest number.
-void fields_across(const Geom &g, int q, int n, int most, double *sum, int *largest) {
-    *sum = 0;
-    *largest = 0;
-    for (int r0 = 0; r0 < n; r0 += q * g.S) {
-        const int lo = r0 < g.R ? 0 : (r0 - g.R + g.S) / g.S, hi = (r0 + q * g.S - 1) / g.S;
-        const int c = (hi < most ? hi : most - 1) - lo + 1;
-        if (c > 0) *sum += c;
-        if (c > *largest) *largest = c;
-    }
-}
-
 // Host check of a lc_bwd_data_general_kernel launch.  tparam = {MT, NT, bytes per operand element, MASK, slices of the
 // contraction, tasks per workgroup, VW}; arg = {PR, PC, pixel blocks per row, vectors per field's filters, batch tiles,
 // tasks}.

@@ -421,19 +421,6 @@ double turned_clocks(const Geom &g, int es, const DataTile &t, double G, int mos
     return cbrt(sum * sum) + (double)g.L * g.K * g.F * es * ceil_div(g.B, 16 * t.mt) / 3200 + 11000;
 }
 
-// Fields that touch a block of q strides, summed over the blocks along an image side of n pixels with most fields, and
-// their largest number.
-void fields_across(const Geom &g, int q, int n, int most, double *sum, int *largest) {
-    *sum = 0;
-    *largest = 0;
-    for (int r0 = 0; r0 < n; r0 += q * g.S) {
-        const int lo = r0 < g.R ? 0 : (r0 - g.R + g.S) / g.S, hi = (r0 + q * g.S - 1) / g.S;
-        const int c = (hi < most ? hi : most - 1) - lo + 1;
-        if (c > 0) *sum += c;
-        if (c > *largest) *largest = c;
-    }
-}
-
 // The fastest tile by the estimate, where that is a tenth less than the direct form's takes here; grids of fewer than seven
 // fields one way, whose blocks are mostly borders, keep the direct form's, whose estimate is of such (161 layers: 1.12 times
 // as fast as the direct form in fp32 and 1.13 in bf16, 1.08 and 1.11 on its tiles).  Tiles that are not split take at least as

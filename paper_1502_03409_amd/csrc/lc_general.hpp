@@ -159,8 +159,8 @@ __device__ __forceinline__ Parts split8(const float (&x)[8], unsigned &low) {
     return s;
 }
 // acc[m][n] += the products of 32 contraction indices of M rows and N columns.  The partial products, smallest first, add up
-// from zero and meet the sum in one addition: a matrix instruction that adds to the sum itself rounds it each time, and not to
-// nearest (layers of 2000 products: 4.1e-7 of the result against 2.4e-7 in fp32 MFMAs; 1.1e-7 this way).  The M N chains of
+// from zero and meet the sum in one addition: a matrix instruction that adds to the sum itself rounds it each time (layers of
+// 2000 products: 4.1e-7 of the result against 2.4e-7 in fp32 MFMAs; 1.1e-7 this way).  The M N chains of
 // six run side by side: with two a wave waits for its own results (four instead of two in the workgroup-tiled kernels: one
 // field of 62 x 62 x 24, 192 images, 4096 filters backwards 940 -> 918 us).
 template <int M, int N>
@@ -241,6 +241,19 @@ int launch_forward_turned(const Geom &g, const bf16_t *x, const bf16_t *w, const
 
 // Backward data's: image and value blocks of a wave, tasks and slices of a workgroup, strides of a pixel block each way
 struct DataTile { int mt, nt, tasks, ks, qr, qc; };
+
+// Fields that touch a block of q strides, summed over the blocks along an image side of n pixels with most fields, and
+// their largest number.
+inline void fields_across(const Geom &g, int q, int n, int most, double *sum, int *largest) {
+    *sum = 0;
+    *largest = 0;
+    for (int r0 = 0; r0 < n; r0 += q * g.S) {
+        const int lo = r0 < g.R ? 0 : (r0 - g.R + g.S) / g.S, hi = (r0 + q * g.S - 1) / g.S;
+        const int c = (hi < most ? hi : most - 1) - lo + 1;
+        if (c > 0) *sum += c;
+        if (c > *largest) *largest = c;
+    }
+}
 
 // lc_backward_data_turned.hip: whether it takes a layer the general backward-data kernel supports, and its launches; `direct`
 // and VW are the direct form's tile and vector width
