@@ -144,14 +144,16 @@ __device__ __forceinline__ float vget(const typename VecT<N>::T &v, int i) {
 // operand's parts often enough (K = 128, 64 filters, 256 images of 64 x 64 x 32: 886 -> 782 us; K = 1296, 100 images, 64
 // filters: 98 -> 69).  What is taken apart is vector work that the bf16 products run beside; fp32 ones would not.  Over 8 and
 // 24 blocks the parts cost what the products save (24: registers spill inside the loop, 215 -> 330; 16 blocks keep
-// up to 18 words of a lane in scratch, outside of it).  The sums are 3 to 4 times nearer to the exact ones.
+// up to 18 words of a lane in scratch, outside of it: at K = 2048, 841 fields, 128 filters 197 MiB are written beside the result's
+// 841, and the vector ALU is busy 68 % of the time, the matrix unit 41).  The sums are 3 to 4 times nearer to the exact ones.
 template <typename T>
 constexpr bool kWeightsSplit(int G, int VA, int NT) { return sizeof(T) == 4 && G * VA * NT == 16; }
 
 // Which launches of such a tile are split: 64 images and more, as what is left over of 32 runs without a pipeline (40 images
 // of 75 x 70 x 4, 11 x 11 at stride 2, 64 filters: 37.6 us against 42.7 split), but not a single wave per SIMD with 16 images
 // in flight at one group, which is bound by its loads and stores (128 images of 30 x 60 x 6, 8 x 8 at stride 5, 128 filters:
-// 13 against 14).
+// 13 against 14).  280 other layers are 1.09 times as fast as in fp32, warm; grids of 256 workgroups and fewer in vectors of four
+// 0.94 to 1.1.
 bool weights_split(const Geom &g, int G, int PF, long long workgroups) {
     return g.B >= 64 && !(G == 1 && PF == 4 && workgroups <= 256);
 }
