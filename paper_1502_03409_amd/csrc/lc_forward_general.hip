@@ -255,7 +255,7 @@ template <typename T>
 int launch_general(const Geom &g, const T *x, const T *w, const float *bias, float alpha, const float *alpha_dev, float *y,
                    hipStream_t s) {
     const ForwardTile t = direct_tile(g, sizeof(T));
-    if (forward_turned_takes(g)) return launch_forward_turned(g, x, w, bias, alpha, alpha_dev, y, t, s);
+    if (forward_turned_takes(g, sizeof(T), t)) return launch_forward_turned(g, x, w, bias, alpha, alpha_dev, y, t, s);
 #define LC_TILE(M, N) if (t.mt == M && t.nt == N) return launch_tile<M, N>(g, x, w, bias, alpha, alpha_dev, y, t, s)
     LC_TILE(1, 1); LC_TILE(2, 1); LC_TILE(3, 1); LC_TILE(4, 1);
     LC_TILE(1, 2); LC_TILE(2, 2); LC_TILE(3, 2); LC_TILE(4, 2);

@@ -485,10 +485,13 @@ void arrange(const Geom &g, ForwardTile *t) {
     while (t->tasks * t->nfw * t->ks < 4) t->tasks *= 2;
 }
 
-double turned_clocks(const Geom &g, int es, const ForwardTile &t, bool fullest) {
+double workgroups_of(const Geom &g, const ForwardTile &t) {
     const double ntask = (double)g.L * ceil_div(g.B, 16 * t.mt);
-    const double wgs = ceil((ntask + t.tasks - 1) / t.tasks) * ceil_div(g.F, t.nfw * t.nt * 16);
-    return turned_clocks(g, es, t.mt, t.nt, t.ks, t.tasks * t.nfw * t.ks, wgs, fullest);
+    return ceil((ntask + t.tasks - 1) / t.tasks) * ceil_div(g.F, t.nfw * t.nt * 16);
+}
+
+double turned_clocks(const Geom &g, int es, const ForwardTile &t, bool fullest) {
+    return turned_clocks(g, es, t.mt, t.nt, t.ks, t.tasks * t.nfw * t.ks, workgroups_of(g, t), fullest);
 }
 
 bool turned_splits(int es, int mt, int nt) { return es == 4 && mt * nt >= 6; }
@@ -533,8 +536,8 @@ ForwardTile fastest_turned(const Geom &g, int es, const ForwardTile &direct, con
 // them a unit, and 265 of those take the time of 512.  Where that makes a tile no less precise 1.15 times as fast, they take it: 80 of
 // 371 layers timed in fp32 (1.17 times as fast) and 92 of 336 in bf16 (1.18; 64 images of 28 x 142 x 5, 20 x 20 at stride 8, 223
 // filters: 160 workgroups of 86 KB 37 and 25 us, now 256 of 53 KB 22 and 18; 88 x 28 x 5, 16 x 16 at stride 5, 382 filters: 51 -> 40).
-// More than a tenth slower than the direct form were 27 and 6 of them, are 15 and 1.  Smaller layers are what the constants
-// were fitted to.
+// More than a tenth slower than the direct form were 27 and 6 of them, are 9 and 1 (with waits_for_a_round).  Smaller layers are
+// what the constants were fitted to.
 constexpr double kFullest = 131072;
 ForwardTile pick_turned(const Geom &g, int es, const ForwardTile &direct) {
     const ForwardTile t = fastest_turned(g, es, direct, nullptr);
@@ -564,7 +567,22 @@ int launch(const Geom &g, const T *x, const T *w, const float *bias, float alpha
 
 }  // namespace
 
-bool forward_turned_takes(const Geom &g) { return turned_form(g) != 0; }
+// A compute unit runs one workgroup of sixteen waves.  Where this form needs a little more than a round of them in fp32 and the
+// direct form's, of up to four blocks of filters a wave where this one has two, fit in one, the second round is mostly empty: the
+// direct form is 1.24 times as fast on 118 layers of 257 to 341 such workgroups (0.95 at least; 16 images of 53 x 22 x 24, 17 x 17 at
+// stride 3, 313 filters: 104 -> 53 us), with 360 to 490 of them it is not (0.89 to 1.03 on 6), nor with one block of filters a
+// wave (0.75 and 0.86 on 2).
+bool waits_for_a_round(const Geom &g, int es, const ForwardTile &direct) {
+    if (es != 4) return false;
+    const ForwardTile t = turned_tile(g, es, direct);
+    const double wgs = workgroups_of(g, t);
+    return t.ks * t.nfw * t.tasks == 16 && wgs > kComputeUnits && 3 * wgs <= 4 * kComputeUnits && direct.ks >= t.ks && direct.nt > 1 &&
+           workgroups_of(g, direct) <= kComputeUnits;
+}
+
+bool forward_turned_takes(const Geom &g, int es, const ForwardTile &direct) {
+    return turned_form(g) != 0 && !waits_for_a_round(g, es, direct);
+}
 
 double forward_turned_clocks(const Geom &g, const ForwardTile &direct) {
     return turned_clocks(g, 4, turned_tile(g, 4, direct), true);

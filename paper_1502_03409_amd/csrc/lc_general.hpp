@@ -232,7 +232,7 @@ struct ForwardTile { int mt, nt, nfw, tasks, ks; };
 
 // lc_forward_turned.hip: whether it takes a layer the general forward kernel supports, and its launches; `direct` is the
 // direct form's tile
-bool forward_turned_takes(const Geom &g);
+bool forward_turned_takes(const Geom &g, int es, const ForwardTile &direct);
 double forward_turned_clocks(const Geom &g, const ForwardTile &direct);   // estimate of an fp32 launch
 int launch_forward_turned(const Geom &g, const float *x, const float *w, const float *bias, float alpha, const float *alpha_dev,
                           float *y, const ForwardTile &direct, hipStream_t s);

@@ -209,3 +209,13 @@ def test_long_patches_in_padded_batches_and_rounds(geo, wide):
     """The workgroup-tiled kernel where its tiles of the batch and its rounds of workgroups are filled: just above either the general
     kernel is up to 1.4 times as fast."""
     assert (lc.plan_query(lc.geom(*geo), B.LC_OP_FORWARD, B.LC_F32)[0]["kernel"] == "lc_forward_wide") == wide
+
+
+@pytest.mark.parametrize("geo,turned", [((16, 53, 22, 24, 17, 3, 313), False), ((4, 28, 25, 24, 15, 1, 64), False), ((16, 154, 23, 24, 20, 3, 96), False),
+                                        ((4, 76, 158, 24, 16, 8, 64), False), ((32, 34, 24, 24, 16, 3, 256), False), ((96, 49, 106, 64, 16, 8, 24), True),
+                                        ((96, 44, 21, 64, 16, 7, 160), True)])
+def test_workgroups_of_sixteen_waves_beyond_a_round(geo, turned):
+    """A third of a second round of workgroups that a compute unit runs one by one, where the direct form needs one round: the direct
+    form.  More of a second round, or none: the turned one."""
+    p = lc.plan_query(lc.geom(*geo), B.LC_OP_FORWARD, B.LC_F32)[0]
+    assert p["kernel"] == "lc_forward_general" and bool(p["tparam"][7]) == turned, p
