@@ -227,7 +227,17 @@ __global__ __launch_bounds__(64 * kTurnedDataWaves) void lc_bwd_data_turned_kern
                     multiply(o0, o1);
                 }
             };
-            contract([&](const Operands &o0, const Operands &o1) {
+            // a layer that has diverged shows in the first group's operands
+            float first = 0.f;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) first += step[0].a[0][mt][r] * 0.f;
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) first += step[0].b[0][nt][r] * 0.f;
+            }
+            const bool finite = !__any(first != 0.f);
+            if (finite) contract([&](const Operands &o0, const Operands &o1) {
                 load_step(step[0]);                           // (ahead of the split, which runs beside the products then)
                 Parts pa[MT], pb[NT];
 #pragma unroll
@@ -243,7 +253,7 @@ __global__ __launch_bounds__(64 * kTurnedDataWaves) void lc_bwd_data_turned_kern
                 mfma_split(pa, pb, acc);
             });
             // an operand that is not finite or too small, or a part that overflowed: once more in fp32
-            if (__any(!all_finite<MT * NT>(&acc[0][0]) || inexact(low))) {
+            if (!finite || __any(!all_finite<MT * NT>(&acc[0][0]) || inexact(low))) {
 #pragma unroll
                 for (int mt = 0; mt < MT; ++mt)
 #pragma unroll

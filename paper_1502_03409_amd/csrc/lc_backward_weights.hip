@@ -311,6 +311,11 @@ __global__ __launch_bounds__(256, G == 3 || SPLIT ? 2 : 1) void lc_bwd_weights_f
 #pragma unroll
             for (int gg = 0; gg < GA; ++gg) load_group(gg);
             __builtin_amdgcn_sched_barrier(0);                // the loads of a step stay ahead of the MFMAs behind them
+            // A layer that has diverged shows in the gradients of its first images.
+            float first = 0.f;
+#pragma unroll
+            for (int u = 0; u < NT; ++u) first += raw_get<T, NT>(bv[0], u) * 0.f;
+            if (__any(first != 0.f)) return false;
             for (int c = 0; c < chunks; ++c) {
                 const bool more = c + 1 < chunks;
                 Parts pb[NT];
@@ -373,13 +378,13 @@ __global__ __launch_bounds__(256, G == 3 || SPLIT ? 2 : 1) void lc_bwd_weights_f
                     }
             }
         }
+        return true;
     };
     auto run = [&](auto ga_tag) {
         if constexpr (SPLIT) {
-            contract_split(ga_tag);
-            if (!__any(!all_finite<G * VA * NT>(&acc[0][0][0]) || inexact(low))) return;
-            // An operand that is not finite or too small, or a part that overflowed: once more in fp32.  (A look after the first step, to begin
-            // at once, costs finite layers more than it saves: 203 -> 226 us at K = 1200, 32 filters, batch 128.)
+            if (contract_split(ga_tag) && !__any(!all_finite<G * VA * NT>(&acc[0][0][0]) || inexact(low))) return;
+            // An operand that is not finite or too small, or a part that overflowed: once more in fp32.  (A look at the sums after the
+            // first step, to begin at once, costs finite layers more than it saves: 203 -> 226 us at K = 1200, 32 filters, batch 128.)
 #pragma unroll
             for (int gg = 0; gg < G; ++gg)
 #pragma unroll

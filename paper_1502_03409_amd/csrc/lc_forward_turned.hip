@@ -306,9 +306,23 @@ __global__ __launch_bounds__(64 * kTurnedWaves(MT, NT), kTurnedResident<T>(MT, N
                     load_step(step[0]);
                 }
             };
-            contract(split_multiply);
+            // a layer that has diverged shows in the first step's operands
+            float first = 0.f;
+#pragma unroll
+            for (int mt = 0; mt < MT; ++mt)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) first += step[0].a[0][mt][r] * 0.f;
+#pragma unroll
+            for (int t = 0; t < NB; ++t)
+#pragma unroll
+                for (int u = 0; u < (BL ? 4 : NT); ++u) {
+                    if constexpr (BL) first += step[0].b[0][t][u] * 0.f;
+                    else first += step[0].b[0][t].get(u) * 0.f;
+                }
+            const bool finite = !__any(first != 0.f);
+            if (finite) contract(split_multiply);
             // an operand that is not finite or too small, or a part that overflowed: once more in fp32
-            if (__any(!all_finite<MT * NT>(&acc[0][0]) || inexact(low))) {
+            if (!finite || __any(!all_finite<MT * NT>(&acc[0][0]) || inexact(low))) {
                 clear();
                 start();
                 ends = vbeg - dNV.over(vbeg) * NV;

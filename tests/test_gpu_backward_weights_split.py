@@ -104,3 +104,19 @@ def test_not_a_number_in_the_first_gradients(shape, step):
     assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.isnan(ref).all() == (step == 1)
     m = np.isfinite(ref)
     assert step == 1 or rel_fro(out[m], ref[m]) <= bar(g.B)
+
+
+@pytest.mark.parametrize("image", [1, -1], ids=["first", "last"])
+@pytest.mark.parametrize("shape", [SHAPES[1, 4, 4, 4][1], SHAPES[2, 4, 2, 1][0], SHAPES[2, 2, 4, 4][0], SHAPES[4, 2, 2, 1][0]], ids=str)
+def test_not_a_number_in_one_filter(shape, image):
+    """Among the first images a NaN sends a tile to the fp32 form at once, among the last ones after its split products: the filter's
+    gradient is NaN, all others are what they are."""
+    print(f"case split weight gradient NaN {shape} {image}", flush=True)
+    g = wl.LCGeom(*shape)
+    x, w, dy = wl.lc_inputs(g, "gaussian", seed=6)
+    dy[image, :, :, 0] = np.nan
+    dw = torch.full(w.shape, float("nan"), device="cuda")
+    lc.lc_backward_weights(lc.geom(*shape), torch.from_numpy(x).cuda(), torch.from_numpy(dy).cuda(), 0.0, dw)
+    ref, out = oracle.lc_backward_weights(shape, x, dy), dw.cpu().numpy()
+    assert np.isnan(out[..., 0]).all() and np.isnan(ref[..., 0]).all()
+    assert rel_fro(out[..., 1:], ref[..., 1:]) <= bar(g.B)

@@ -121,3 +121,20 @@ def test_one_writer_for_every_filter(shape):
     last[:, :, 1, g.F - 1], before[:, :, 1, g.F - 1 - 8 * NT] = np.inf, np.inf
     assert torch.equal(forward(last)[..., :-1], y[..., :-1])
     assert torch.equal(forward(before)[..., -1], y[..., -1])
+
+
+@pytest.mark.parametrize("row", [1, -2], ids=["first", "last"])
+@pytest.mark.parametrize("shape", [F32[2, 3, 1], F32[4, 4, 1], F32[2, 3, 2], F32[4, 2, 2]], ids=str)
+def test_not_a_number_in_one_filter(shape, row):
+    """Among the first weights a NaN sends a tile to the fp32 form at once, among the last ones after its split products: the filter's
+    outputs are NaN, all others are what they are."""
+    print(f"case turned forward NaN {shape} {row}", flush=True)
+    g = wl.LCGeom(*shape)
+    x, w, _ = wl.lc_inputs(g, "gaussian", seed=8)
+    w[:, :, row, 3] = np.nan
+    y = torch.full((g.B, g.LH, g.LW, g.F), float("nan"), device="cuda")
+    lc.lc_forward(lc.geom(*shape), torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), None, 1.0, y)
+    ref, out = oracle.lc_forward(shape, x, w), y.cpu().numpy()
+    assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.isnan(ref[..., 3]).all()
+    m = np.isfinite(ref)
+    assert rel_fro(out[m], ref[m]) <= bar(g.K)
