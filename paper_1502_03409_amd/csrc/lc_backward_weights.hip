@@ -180,8 +180,9 @@ __global__ __launch_bounds__(256, G == 3 || SPLIT ? 2 : 1) void lc_bwd_weights_f
     typedef __attribute__((address_space(1))) BR GBV;
     typedef const __attribute__((address_space(1))) T *gfloat_ptr;
     constexpr int KB = G * VA * 16;  // patch elements per task
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int m = lane & 15, kk = lane >> 4;
+    // (the split form has no registers for what is the same in a whole wave)
+    const int wave = SPLIT ? __builtin_amdgcn_readfirstlane(threadIdx.x >> 6) : threadIdx.x >> 6;
+    int m = threadIdx.x & 15, kk = (threadIdx.x >> 4) & 3;
     const int task = remap_xcd(blockIdx.x, gridDim.x) * 4 + wave;
     if (task >= ntasks) return;
     // Where a wave loads more of x than of dy per batch step (G * VA > NT), tasks are ordered field row by field row,
@@ -211,13 +212,16 @@ __global__ __launch_bounds__(256, G == 3 || SPLIT ? 2 : 1) void lc_bwd_weights_f
     // Rows of the A tiles that fall beyond K are loaded from a valid address (element 0 of the patch)
     // and never masked: row m of A only reaches row m of D, and those rows are not stored.
     int off[G];
+    auto find_rows = [&] {
 #pragma unroll
-    for (int gg = 0; gg < G; ++gg) {
-        const int k = k0 + gg * VA * 16 + VA * m;
-        const int kc = k < g.K ? k : 0;
-        const int kh = kc / g.RC, rem = kc - kh * g.RC;
-        off[gg] = ((i * g.S + kh) * g.W + j * g.S) * g.C + rem;
-    }
+        for (int gg = 0; gg < G; ++gg) {
+            const int k = k0 + gg * VA * 16 + VA * m;
+            const int kc = k < g.K ? k : 0;
+            const int kh = kc / g.RC, rem = kc - kh * g.RC;
+            off[gg] = ((i * g.S + kh) * g.W + j * g.S) * g.C + rem;
+        }
+    };
+    find_rows();
 
     f32x4 acc[G][VA][NT];
 #pragma unroll
@@ -382,7 +386,15 @@ __global__ __launch_bounds__(256, G == 3 || SPLIT ? 2 : 1) void lc_bwd_weights_f
     };
     auto run = [&](auto ga_tag) {
         if constexpr (SPLIT) {
-            if (contract_split(ga_tag) && !__any(!all_finite<G * VA * NT>(&acc[0][0][0]) || inexact(low))) return;
+            const bool whole = contract_split(ga_tag) && !__any(!all_finite<G * VA * NT>(&acc[0][0][0]) || inexact(low));
+            // The lane's numbers anew, for what follows: kept, they and what is formed of them go to scratch over the split loop.
+            unsigned none = 0;
+            asm volatile("" : "+s"(none));
+            const int lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, none));
+            m = lane & 15;
+            kk = lane >> 4;
+            if (whole) return;
+            find_rows();
             // An operand that is not finite or too small, or a part that overflowed: once more in fp32.  (A look at the sums after the
             // first step, to begin at once, costs finite layers more than it saves: 203 -> 226 us at K = 1200, 32 filters, batch 128.)
 #pragma unroll
