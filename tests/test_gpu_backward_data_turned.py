@@ -81,7 +81,6 @@ def test_infinities_and_ends_of_the_range(shape, scale):
         dy[0, 0, 0, g.F - 1] = np.inf
         dy[g.B - 1, g.LH - 1, g.LW - 1, 0] = -np.inf
         dy[g.B // 2, g.LH // 2, g.LW // 2, g.F // 2] = np.nan
-        w[0, 0, 0, 0], w[g.LH - 1, g.LW - 1, -1, g.F - 1] = np.inf, -np.inf
     else:
         dy[0, 0, 0, 0] = 1.69 * scale
     dx = torch.full((g.B, g.H, g.W, g.C), float("nan"), device="cuda")
@@ -91,3 +90,18 @@ def test_infinities_and_ends_of_the_range(shape, scale):
     m = np.isfinite(ref)
     if m.any():
         assert rel_fro(out[m].astype(np.float64) / scale, ref[m] / scale) <= bar(g.F * (-(-g.R // g.S)) ** 2)
+
+
+@pytest.mark.parametrize("shape", [F32[1, 1, 1], F32[1, 2, 1], F32[1, 4, 0], F32[1, 4, 1], F32[2, 2, 1], F32[3, 2, 1]], ids=str)
+def test_infinite_weights(shape):
+    """An infinite weight stays in the pixel that it reaches."""
+    print(f"case turned backward data infinite weights {shape}", flush=True)
+    g = wl.LCGeom(*shape)
+    _, w, dy = wl.lc_inputs(g, "gaussian", seed=9)
+    w[0, 0, 0, 0], w[g.LH - 1, g.LW - 1, -1, g.F - 1] = np.inf, -np.inf
+    dx = torch.full((g.B, g.H, g.W, g.C), float("nan"), device="cuda")
+    lc.lc_backward_data(lc.geom(*shape), torch.from_numpy(dy).cuda(), torch.from_numpy(w).cuda(), dx)
+    ref, out = oracle.lc_backward_data(shape, dy, w), dx.cpu().numpy()
+    assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.array_equal(out[np.isinf(ref)], ref[np.isinf(ref)])
+    m = np.isfinite(ref)
+    assert np.isinf(ref).any() and rel_fro(out[m], ref[m]) <= bar(g.F * (-(-g.R // g.S)) ** 2)

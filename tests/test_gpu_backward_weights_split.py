@@ -62,7 +62,6 @@ def test_infinities_and_ends_of_the_range(shape, scale):
         x[0, 0, 0, 0] = np.inf
         x[g.B - 1, g.H - 1, g.W - 1, g.C - 1] = -np.inf
         dy[g.B // 2, g.LH // 2, g.LW // 2, g.F // 2] = np.nan
-        dy[0, 0, 0, 0], dy[g.B - 1, 0, 0, g.F - 1] = np.inf, -np.inf
     else:
         x[0, 0, 0, 0] = 1.69 * scale
     dw = torch.full(w.shape, float("nan"), device="cuda")
@@ -120,3 +119,18 @@ def test_not_a_number_in_one_filter(shape, image):
     ref, out = oracle.lc_backward_weights(shape, x, dy), dw.cpu().numpy()
     assert np.isnan(out[..., 0]).all() and np.isnan(ref[..., 0]).all()
     assert rel_fro(out[..., 1:], ref[..., 1:]) <= bar(g.B)
+
+
+@pytest.mark.parametrize("shape", [SHAPES[1, 4, 4, 1][1], SHAPES[2, 4, 2, 1][0], SHAPES[2, 2, 4, 2][0], SHAPES[4, 2, 2, 1][2]], ids=str)
+def test_infinite_gradients(shape):
+    """An infinite gradient among the first or last images stays in its filter's weights."""
+    print(f"case split weight gradient infinite gradients {shape}", flush=True)
+    g = wl.LCGeom(*shape)
+    x, w, dy = wl.lc_inputs(g, "gaussian", seed=9)
+    dy[0, 0, 0, 0], dy[g.B - 1, 0, 0, g.F - 1] = np.inf, -np.inf
+    dw = torch.full(w.shape, float("nan"), device="cuda")
+    lc.lc_backward_weights(lc.geom(*shape), torch.from_numpy(x).cuda(), torch.from_numpy(dy).cuda(), 0.0, dw)
+    ref, out = oracle.lc_backward_weights(shape, x, dy), dw.cpu().numpy()
+    assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.array_equal(out[np.isinf(ref)], ref[np.isinf(ref)])
+    m = np.isfinite(ref)
+    assert np.isinf(ref).any() and m.any() and rel_fro(out[m], ref[m]) <= bar(g.B)

@@ -77,7 +77,7 @@ def test_slices(slices, shape):
 @pytest.mark.parametrize("shape", [F32[1, 2, 1], F32[2, 3, 1], F32[4, 4, 1], F32[2, 3, 2], F32[1, 3, 2]], ids=str)
 @pytest.mark.parametrize("scale", [1.0, 1e-30, 2e38], ids=str)
 def test_infinities_and_ends_of_the_range(shape, scale):
-    """Infinite pixels and weights make the outputs of their fields infinite or NaN as the sums of fp32 products are, nothing else; small
+    """Infinite pixels make the outputs of their fields infinite or NaN as the sums of fp32 products are, nothing else; small
     and large values keep their precision (products split into bf16 parts overflow where fp32 does not: formed again)."""
     print(f"case turned forward range {shape} {scale}", flush=True)
     g = wl.LCGeom(*shape)
@@ -87,7 +87,6 @@ def test_infinities_and_ends_of_the_range(shape, scale):
     if scale == 1.0:
         x[0, 1, 2, 0] = np.inf
         x[g.B - 1, g.H // 2, g.W // 2, g.C - 1] = -np.inf
-        w[0, 0, -1, g.F - 1], w[g.LH - 1, g.LW - 1, 0, 0] = np.inf, -np.inf
     else:
         x[0, 0, 0, 0] = 1.69 * scale
     y = torch.full((g.B, g.LH, g.LW, g.F), float("nan"), device="cuda")
@@ -138,3 +137,18 @@ def test_not_a_number_in_one_filter(shape, row):
     assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.isnan(ref[..., 3]).all()
     m = np.isfinite(ref)
     assert rel_fro(out[m], ref[m]) <= bar(g.K)
+
+
+@pytest.mark.parametrize("shape", [F32[1, 2, 1], F32[2, 3, 1], F32[4, 4, 1], F32[2, 3, 2], F32[1, 3, 2]], ids=str)
+def test_infinite_weights(shape):
+    """An infinite weight, the first or last of a patch, makes its filter's outputs infinite and no others."""
+    print(f"case turned forward infinite weights {shape}", flush=True)
+    g = wl.LCGeom(*shape)
+    x, w, _ = wl.lc_inputs(g, "gaussian", seed=9)
+    w[0, 0, -1, g.F - 1], w[g.LH - 1, g.LW - 1, 0, 0] = np.inf, -np.inf
+    y = torch.full((g.B, g.LH, g.LW, g.F), float("nan"), device="cuda")
+    lc.lc_forward(lc.geom(*shape), torch.from_numpy(x).cuda(), torch.from_numpy(w).cuda(), None, 1.0, y)
+    ref, out = oracle.lc_forward(shape, x, w), y.cpu().numpy()
+    assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.array_equal(out[np.isinf(ref)], ref[np.isinf(ref)])
+    m = np.isfinite(ref)
+    assert np.isinf(ref).any() and rel_fro(out[m], ref[m]) <= bar(g.K)

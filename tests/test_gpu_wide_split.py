@@ -145,7 +145,6 @@ def test_backward_data_infinities_and_ends_of_the_range(shape, scale):
         dy[0, 0, 0, g.F - 1] = np.inf
         dy[g.B - 1, g.LH - 1, g.LW - 1, 0] = -np.inf
         w[g.LH - 1, g.LW - 1, -1, g.F // 2] = np.nan
-        w[0, 0, 1, 0], w[0, 0, g.K - 2, g.F - 1] = np.inf, -np.inf
     else:
         dy[0, 0, 0, 0] = 1.69 * scale
     ref, out = oracle.lc_backward_data(shape, dy, w), backward(shape, dy, w).cpu().numpy()
@@ -176,3 +175,16 @@ def test_not_a_number_in_the_first_weights(columns):
         assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.isnan(ref[0, 0, 0]).all() == (step == 1)
         m = np.isfinite(ref)       # (pixels that no field covers among them)
         assert step == 1 or rel_fro(out[m], ref[m]) <= bar(g.F * (-(-g.R // g.S)) ** 2)
+
+
+@pytest.mark.parametrize("shape", [BACKWARD[2, 0][1], BACKWARD[3, 0][0], BACKWARD[3, 1][0], BACKWARD[2, 1][1]], ids=str)
+def test_backward_data_infinite_weights(shape):
+    """An infinite weight of the first or last filter stays in the pixel that it reaches."""
+    print(f"case wide backward data infinite weights {shape}", flush=True)
+    g = wl.LCGeom(*shape)
+    _, w, dy = wl.lc_inputs(g, "gaussian", seed=9)
+    w[0, 0, 1, 0], w[0, 0, g.K - 2, g.F - 1] = np.inf, -np.inf
+    ref, out = oracle.lc_backward_data(shape, dy, w), backward(shape, dy, w).cpu().numpy()
+    assert np.array_equal(np.isnan(out), np.isnan(ref)) and np.array_equal(out[np.isinf(ref)], ref[np.isinf(ref)])
+    m = np.isfinite(ref)
+    assert np.isinf(ref).any() and rel_fro(out[m], ref[m]) <= bar(g.F * (-(-g.R // g.S)) ** 2)
