@@ -141,11 +141,11 @@ __device__ __forceinline__ float vget(const typename VecT<N>::T &v, int i) {
 }
 
 // Tiles whose fp32 products are split into bf16 parts (mfma_split): 16 blocks over sides of four to eight, which share an
-// operand's parts often enough (K = 128, 64 filters, 256 images of 64 x 64 x 32: 886 -> 782 us; K = 1296, 100 images, 64
+// operand's parts often enough (K = 2048, 841 fields, 128 filters, 256 images: 886 -> 766 us; K = 1296, 100 images, 64
 // filters: 98 -> 69).  What is taken apart is vector work that the bf16 products run beside; fp32 ones would not.  Over 8 and
-// 24 blocks the parts cost what the products save (24: registers spill inside the loop, 215 -> 330; 16 blocks keep
-// up to 18 words of a lane in scratch, outside of it: at K = 2048, 841 fields, 128 filters 197 MiB are written beside the result's
-// 841, and the vector ALU is busy 68 % of the time, the matrix unit 41).  The sums are 3 to 4 times nearer to the exact ones.
+// 24 blocks the parts cost what the products save (24: registers spill inside the loop, 215 -> 330; 16 blocks keep at most
+// nine words of a lane in scratch, outside of it: in the first of these layers 26 MiB are written beside the result's 841, and
+// the vector ALU is busy 68 % of the time, the matrix unit 41).  The sums are 3 to 4 times nearer to the exact ones.
 template <typename T>
 constexpr bool kWeightsSplit(int G, int VA, int NT) { return sizeof(T) == 4 && G * VA * NT == 16; }
 
